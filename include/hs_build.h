@@ -11,12 +11,14 @@
  *            + B_a^H T^BA_a A_a + B_a^H T^BB_a B_a,     T^BA_a := (T^AB_a)^H
  *   S = sum_a  A_a^H A_a + B_a^H U_a^H U_a B_a
  *
- * by the route of Alg. 1: per-atom products Z_a = T^BA_a A_a + 1/2 T^BB_a B_a,
- * a per-atom Cholesky T^AA_a = C_a C_a^H with Y_a = C_a^H A_a on success and
- * X_a = T^AA_a A_a on failure, and large stacked Hermitian reductions
- * H = Z^H B + B^H Z + Y_HPD^H Y_HPD + A_notHPD^H X_notHPD,
- * S = A^H A + (U B)^H (U B). All arithmetic is IEEE binary64 (complex double,
- * 8 real flops per complex multiply-add) on the GPU.
+ * as H = A^H X + B^H Y with the per-atom products X_a = T^AA_a A_a + T^AB_a B_a
+ * and Y_a = T^BA_a A_a + T^BB_a B_a, and S = A^H A + B^H |U|^2 B, both as
+ * lower-triangle reductions over the stacked rows of all atoms, completed by
+ * conjugation. (Alg. 1's Hermitian rank-k forms contract H over 3K rows
+ * instead of 2K.) The second loop's per-atom Cholesky T^AA_a = C_a C_a^H is
+ * run for its result alone, info[a]; both of Alg. 1's branches are the same
+ * product here. All arithmetic is IEEE binary64 (complex double, 8 real flops
+ * per complex multiply-add) on the GPU.
  *
  * Conventions shared by every entry point
  *  - complex values are hs_complex = {double re, im} (the layout of
@@ -51,10 +53,9 @@
  *    2   workspace too small (see hs_workspace_bytes)
  *    3   out of device memory (hs_build only: it allocates its workspace)
  *    4   unsupported: N_L > HS_MAX_NL, or the device is not gfx950
- *  A failed per-atom Cholesky is NOT an error: it selects the failure branch
- *  of Alg. 1 for that atom and is reported through info[a] (below). NaN/Inf in
- *  inputs are not checked and propagate; a NaN pivot selects the failure
- *  branch.
+ *  A failed per-atom Cholesky is NOT an error: it is reported through info[a]
+ *  (below) as the atom's branch of Alg. 1. NaN/Inf in inputs are not checked
+ *  and propagate; a NaN pivot counts as a failure.
  */
 #ifndef HS_BUILD_H
 #define HS_BUILD_H
@@ -158,13 +159,10 @@ typedef struct {
     size_t workspace_bytes;
     /* device int32 [N_A], or NULL when batch = 0 (required with batch = 1:
        NULL returns -12). On completion info[a] = 0 when T_AA_a had a
-       Cholesky factor (atom a took Alg. 1's success branch), else the 1-based
-       index j of the first pivot d_j = T_jj - sum_{k<j} |C_jk|^2 that is not
-       > 0 or is NaN (LAPACK zpotrf semantics; atom a took the failure
-       branch). With batch = 1, info[a] = -1 for EVERY atom means that a
-       product tile of the batched launch gave up waiting for its atom's
-       preparation (a bounded wait that should never run out): H and S are
-       then undefined and the build must be repeated. */
+       Cholesky factor (Alg. 1's success branch), else the 1-based index j of
+       the first pivot d_j = T_jj - sum_{k<j} |C_jk|^2 that is not > 0 or is
+       NaN (LAPACK zpotrf semantics; Alg. 1's failure branch). H and S do not
+       depend on it; with NULL the factorizations are not run. */
     int32_t *info;
     /* hs_mode */
     int mode;
@@ -173,18 +171,15 @@ typedef struct {
     const int32_t *nl_per_atom;
     /* NULL, or HOST array of HS_NUM_PHASE_EVENTS hipEvent_t (created by the
        caller) that the build records on its stream at the phase boundaries:
-       [0] start, [1] after the per-atom Cholesky and operand preparation,
-       [2] after the per-atom products (Alg. 1 first loop and second-loop
-       branches), [3] after the large lower-triangle reductions of H and S,
-       [4] after the conjugate mirroring (end of the build). With batch = 1
-       the preparation runs inside the batched launch: [1] is recorded right
-       after [0] and [1]..[2] covers preparation and products. */
+       [0] start, [1] after the operand preparation, [2] after the per-atom
+       products and the Cholesky factorizations beside them, [3] after the
+       large lower-triangle reductions of H and S, [4] after the conjugate
+       mirroring (end of the build). */
     void **phase_events;
-    /* 0: per-atom preparation and products as separate launches, one tile
-       shape for all atoms (the largest N_L decides). 1: batched form - one
-       persistent launch runs every atom's Cholesky (with its failure test)
-       and every atom's Z_a and W_a tiles, each atom with the tile shape of
-       its N_L. Same results up to rounding order. */
+    /* 0: the per-atom products with one tile shape for all atoms (the largest
+       N_L decides). 1: batched form - one persistent launch runs every atom's
+       Cholesky and every atom's X_a and Y_a tiles, each atom with the tile
+       shape of its N_L. Same results, bitwise. */
     int batch;
     /* HOST hs_tuning or NULL (built-in shapes: 32, 64, 96 or 128 rows, the
        fewest that cover N_L, by 128 columns, 192 for 96 rows). Used when

@@ -1,13 +1,12 @@
 // C ABI of the H/S builder: argument checks, planning (atom tables and the
 // workspace carve), and the launch sequence of one build:
-//   k_tables  per-atom row / T-block offsets
-//   k_prep    per-atom Cholesky of T^AA with failure flags, operand forms
-//   k_atom    per-atom products Z_a, W_a (Y_a or X_a)
+//   k_forms   per-atom row / T-block offsets, operand forms
+//   k_atom    per-atom products X_a, Y_a; per-atom Cholesky of T^AA (info)
 //   k_reduce  lower triangles of H and S from the stacked operands
 //   k_mirror  conjugate upper triangles
 // All work is enqueued on one stream; nothing is synchronized inside
-// hs_build_ex. The atom-side steps (k_tables, k_prep) do not depend on the
-// k-point and are shared with the resident context (hs_serving.hip).
+// hs_build_ex. The atom-side steps (k_forms, the Cholesky) do not depend on
+// the k-point and are shared with the resident context (hs_serving.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -64,41 +63,6 @@ int check_device() {
     return HS_OK;
 }
 
-namespace {
-
-// Atom tables (row and T-block offsets) are written on the device by a small
-// kernel whose inputs travel as kernel arguments, a chunk of up to
-// TABLE_CHUNK atoms per launch. Nothing is copied from host memory, so the
-// enqueue is fully asynchronous and needs no host buffer to outlive the call.
-constexpr int TABLE_CHUNK = 1024;
-struct TableChunk {
-    unsigned char nl[TABLE_CHUNK];
-    int n;          // atoms in this chunk
-    int a0;         // first atom
-    int row0;       // row offset of the first atom
-    int t0;         // T offset of the first atom
-    int last;       // 1 when this chunk ends the atom list (writes the totals)
-    int n_atoms;
-};
-
-__global__ void __launch_bounds__(256) k_tables(TableChunk c, int *row_off, int *t_off) {
-    for (int i = threadIdx.x; i < c.n; i += blockDim.x) {
-        int r = c.row0, t = c.t0;
-        for (int j = 0; j < i; ++j) {
-            r += c.nl[j];
-            t += c.nl[j] * c.nl[j];
-        }
-        row_off[c.a0 + i] = r;
-        t_off[c.a0 + i] = t;
-        if (c.last && i == c.n - 1) {
-            row_off[c.n_atoms] = r + c.nl[i];
-            t_off[c.n_atoms] = t + c.nl[i] * c.nl[i];
-        }
-    }
-}
-
-}  // namespace
-
 int AtomPlan::make(int N_A, const int32_t *nl_per_atom, int N_L) {
     n_atoms = N_A;
     row_off.assign(N_A + 1, 0);
@@ -128,7 +92,6 @@ size_t AtomPlan::atom_bytes() const {
     size_t o = 0;
     o = align_up(o + sizeof(int) * 2 * (size_t)(n_atoms + 1));   // tables
     o = align_up(o + sizeof(int) * (size_t)n_atoms);             // info
-    o = align_up(o + sizeof(int) * 3 * (size_t)K);               // sel
     o = align_up(o + sizeof(double) * 2 * (size_t)K);            // d
     o = align_up(o + 16 * (size_t)t_total);                      // M1
     o = align_up(o + 16 * (size_t)t_total);                      // M2
@@ -138,7 +101,7 @@ size_t AtomPlan::atom_bytes() const {
 size_t AtomPlan::kpoint_bytes(int n_g, int mode) const {
     size_t b = 2 * align_up(16 * (size_t)K * (size_t)n_g) + BatchBufs::bytes(n_atoms, n_g);
     if (split_mode(mode))
-        b += NSPLIT * (align_up(slice_bytes(mode, K, n_g)) + align_up(8 * (size_t)n_g));
+        b += NSPLIT_ROOM * (align_up(slice_bytes(mode, K, n_g)) + align_up(8 * (size_t)n_g));
     if (mode == HS_SPLIT_I8_CRT) b += align_up(crt_work_bytes(n_g));
     return b;
 }
@@ -150,7 +113,7 @@ long long BatchBufs::max_tiles(int n_atoms, int n_g) {
 
 size_t BatchBufs::bytes(int n_atoms, int n_g) {
     return align_up(sizeof(int) * (size_t)n_atoms) + align_up(sizeof(int) * (size_t)(n_atoms + 1)) +
-           align_up(2 * sizeof(int)) + align_up(2 * sizeof(int) * (size_t)n_atoms) +
+           align_up(sizeof(int)) +
            align_up(2 * sizeof(int) * (size_t)max_tiles(n_atoms, n_g));
 }
 
@@ -161,9 +124,7 @@ void BatchBufs::carve(int n_atoms, char *base) {
     zoff = reinterpret_cast<int *>(base + o);
     o += align_up(sizeof(int) * (size_t)(n_atoms + 1));
     ctrl = reinterpret_cast<int *>(base + o);
-    o += align_up(2 * sizeof(int));
-    flags = reinterpret_cast<int *>(base + o);
-    o += align_up(2 * sizeof(int) * (size_t)n_atoms);
+    o += align_up(sizeof(int));
     tiles = reinterpret_cast<int *>(base + o);
 }
 
@@ -173,8 +134,6 @@ void AtomBufs::carve(const AtomPlan &p, char *base) {
     o = align_up(o + sizeof(int) * 2 * (size_t)(p.n_atoms + 1));
     info = reinterpret_cast<int *>(base + o);
     o = align_up(o + sizeof(int) * (size_t)p.n_atoms);
-    sel = reinterpret_cast<int *>(base + o);
-    o = align_up(o + sizeof(int) * 3 * (size_t)p.K);
     d = reinterpret_cast<double *>(base + o);
     o = align_up(o + sizeof(double) * 2 * (size_t)p.K);
     M1 = reinterpret_cast<double2 *>(base + o);
@@ -194,8 +153,8 @@ Atoms AtomBufs::atoms(const AtomPlan &p) const {
 
 void KpointBufs::carve(const AtomPlan &p, int n_g, int mode, char *base) {
     const size_t half = align_up(16 * (size_t)p.K * (size_t)n_g);
-    Z = reinterpret_cast<double2 *>(base);
-    W = reinterpret_cast<double2 *>(base + half);
+    X = reinterpret_cast<double2 *>(base);
+    Y = reinterpret_cast<double2 *>(base + half);
     size_t o = 2 * half;
     batch.carve(p.n_atoms, base + o);
     o += BatchBufs::bytes(p.n_atoms, n_g);
@@ -208,29 +167,8 @@ void KpointBufs::carve(const AtomPlan &p, int n_g, int mode, char *base) {
         mx[i] = reinterpret_cast<unsigned long long *>(base + o);
         o += align_up(8 * (size_t)n_g);
     }
+    // the work buffer of the modular form takes the unused operand's room too
     crt = mode == HS_SPLIT_I8_CRT ? base + o : nullptr;
-}
-
-hipError_t enqueue_atoms(const AtomPlan &p, const AtomBufs &ab, const double2 *T_AA,
-                         const double2 *T_BB, const double2 *U, int *info_out, hipStream_t st,
-                         bool prep) {
-    for (int a0 = 0; a0 < p.n_atoms; a0 += TABLE_CHUNK) {
-        TableChunk c;
-        c.n = std::min(TABLE_CHUNK, p.n_atoms - a0);
-        std::memcpy(c.nl, p.nl.data() + a0, c.n);
-        c.a0 = a0;
-        c.row0 = p.row_off[a0];
-        c.t0 = p.t_off[a0];
-        c.last = (a0 + c.n == p.n_atoms);
-        c.n_atoms = p.n_atoms;
-        hipLaunchKernelGGL(k_tables, dim3(1), dim3(256), 0, st, c, ab.tables,
-                           ab.tables + p.n_atoms + 1);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (!prep) return hipSuccess;
-    return launch_prep(ab.atoms(p), T_AA, T_BB, U, ab.M1, ab.M2, ab.d, ab.sel,
-                       info_out ? info_out : ab.info, st);
 }
 
 hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mode,
@@ -245,24 +183,23 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
     if (stage.batch) {
         BatchPlan bp;
         bp.make(p, n_g, stage.cfg);
-        const BatchIO io{stage.T_AA, T_AB, stage.T_BB, stage.U, A, B, ab.M1, ab.M2, ab.d,
-                         ab.sel, stage.info ? stage.info : ab.info, kb.Z, kb.W};
-        e = launch_batch(p, ab.atoms(p), bp, n_g, stage.factor, io, kb.batch, st);
+        const BatchIO io{stage.T_AA, T_AB, A, B, ab.M1, ab.M2, stage.info, kb.X, kb.Y};
+        e = launch_batch(p, ab.atoms(p), bp, n_g, io, kb.batch, st);
     } else {
-        e = launch_atom(ab.atoms(p), n_g, A, B, T_AB, ab.M1, ab.M2, ab.sel, kb.Z, kb.W, st);
+        e = launch_atom(ab.atoms(p), n_g, A, B, stage.T_AA, T_AB, ab.M1, ab.M2, stage.info, kb.X,
+                        kb.Y, st);
     }
     if (e != hipSuccess) return e;
     if ((e = mark(2)) != hipSuccess) return e;
     if (split_mode(mode)) {
-        // operands: 0 A, 1 U B, 2 Z, 3 B, 4 P3 (W, or A on failure-branch rows), 5 W
+        // operands: 0 A, 1 U B, 2 X, 3 B, 4 Y
         const int K = p.K;
         const SliceSrc src[NSPLIT] = {
-            {A, nullptr, nullptr, nullptr, kb.mx[0], kb.sl[0]},
-            {B, nullptr, nullptr, ab.d + K, kb.mx[1], kb.sl[1]},
-            {kb.Z, nullptr, nullptr, nullptr, kb.mx[2], kb.sl[2]},
-            {B, nullptr, nullptr, nullptr, kb.mx[3], kb.sl[3]},
-            {kb.W, A, ab.sel + 2 * (size_t)K, nullptr, kb.mx[4], kb.sl[4]},
-            {kb.W, nullptr, nullptr, nullptr, kb.mx[5], kb.sl[5]},
+            {A, nullptr, kb.mx[0], kb.sl[0]},
+            {B, ab.d + K, kb.mx[1], kb.sl[1]},
+            {kb.X, nullptr, kb.mx[2], kb.sl[2]},
+            {B, nullptr, kb.mx[3], kb.sl[3]},
+            {kb.Y, nullptr, kb.mx[4], kb.sl[4]},
         };
         for (int i = 0; i < NSPLIT; ++i) {
             if (mode == HS_SPLIT_I8_CRT) e = launch_residue(src[i], K, n_g, st);
@@ -272,7 +209,7 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
         }
         SliceView v[NSPLIT];
         for (int i = 0; i < NSPLIT; ++i) v[i] = SliceView{kb.sl[i], kb.mx[i]};
-        const SliceView hseg[3][2] = {{v[2], v[3]}, {v[3], v[2]}, {v[4], v[5]}};
+        const SliceView hseg[2][2] = {{v[3], v[4]}, {v[0], v[2]}};
         const SliceView sseg[2][2] = {{v[0], v[0]}, {v[1], v[1]}};
         if (mode == HS_SPLIT_I8_CRT)
             e = launch_crt_reduce(K, n_g, hseg, sseg, kb.crt, H, S, st);
@@ -281,8 +218,7 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
         else
             e = launch_split_reduce(K, n_g, hseg, sseg, H, S, st, mode == HS_SPLIT_BF16);
     } else {
-        e = launch_reduce(p.K, n_g, A, B, kb.Z, kb.W, ab.sel, ab.d, H, S, st,
-                          mode == HS_FP64_3M);
+        e = launch_reduce(p.K, n_g, A, B, kb.X, kb.Y, ab.d, H, S, st, mode == HS_FP64_3M);
     }
     if (e != hipSuccess) return e;
     if ((e = mark(3)) != hipSuccess) return e;
@@ -327,18 +263,13 @@ int run_build(const AtomPlan &p, int n_g, int mode, const hs_complex *A, const h
     ab.carve(p, ws);
     hs::KpointBufs kb;
     kb.carve(p, n_g, mode, ws + p.atom_bytes());
-    e = hs::enqueue_atoms(p, ab, c2(T_AA), c2(T_BB), c2(U), info_user, st, !batch);
+    e = hs::launch_forms(p, ab, c2(T_AA), c2(T_BB), c2(U), st);
     if (e != hipSuccess) return hs::hip_fail(e, "per-atom preparation launch");
     hs::AtomStage stage;
-    if (batch) {
-        stage.batch = true;
-        stage.factor = true;
-        stage.cfg = tuning ? tuning->cfg : nullptr;
-        stage.T_AA = c2(T_AA);
-        stage.T_BB = c2(T_BB);
-        stage.U = c2(U);
-        stage.info = info_user;
-    }
+    stage.batch = batch;
+    stage.cfg = tuning ? tuning->cfg : nullptr;
+    stage.T_AA = c2(T_AA);
+    stage.info = info_user;   // NULL: nobody reads the Cholesky's result
     e = hs::enqueue_kpoint(p, ab, n_g, mode, c2(A), c2(B), c2(T_AB), kb, c2(H), c2(S), st, ev,
                            stage);
     if (e != hipSuccess) return hs::hip_fail(e, "k-point launch");
@@ -371,8 +302,7 @@ int hs_build_ex(const hs_complex *A, const hs_complex *B, const hs_complex *T_AA
     if (rc != 0) return rc;
     if (opt->batch && !hs::BatchPlan::valid(p, opt->tuning ? opt->tuning->cfg : nullptr))
         return -12;
-    // the batched launch reports a bounded wait that ran out through info
-    // (every entry -1), so it needs a caller-visible info array
+    // part of the interface: the batched form needs an info array
     if (opt->batch && !opt->info) return -12;
     if (reinterpret_cast<uintptr_t>(opt->workspace) % 16) return -12;   // 16-byte loads
     rc = hs::check_device();

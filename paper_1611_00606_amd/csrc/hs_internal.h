@@ -15,52 +15,42 @@ namespace hs {
 
 // Device-side description of the atoms of one build.
 struct Atoms {
-    const int *row_off;  // [N_A+1] first row of each atom in A, B, U, Z, W
+    const int *row_off;  // [N_A+1] first row of each atom in A, B, U, X, Y
     const int *t_off;    // [N_A+1] first element of each atom's N_L x N_L block
     int n_atoms;
     int max_nl;
     int K;               // total rows
 };
 
-// Per-atom preparation (Alg. 1 second loop's factorization, plus the
-// operand forms the products need). One block per atom.
-//   info[a]   0 or the 1-based failing pivot of T_AA,a's Cholesky
-//   M1_a      C_a (lower, zero above) on success, else T_AA,a as a full
-//             Hermitian matrix from its lower triangle
-//   M2_a      1/2 T_BB,a as a full Hermitian matrix from its lower triangle
+struct AtomPlan;
+struct AtomBufs;
+
+// Atom tables and the operand forms of the per-atom products (k_prep.hip):
+//   M1_a      T_AA,a as a full Hermitian matrix from its lower triangle
+//   M2_a      T_BB,a likewise
 //   d[2K]     per contraction row of the S reduction (A rows, then B rows):
 //             d[r] = 1, d[K + r] = |U[r]|^2
-//   sel[3K]   per contraction row of the H reduction (Z, B, then W rows):
-//             sel[r] = sel[K + r] = 0, sel[2K + r] = 1 when row r belongs to
-//             an atom on the failure branch (its left operand is then A)
-hipError_t launch_prep(const Atoms &at, const double2 *T_AA, const double2 *T_BB,
-                       const double2 *U, double2 *M1, double2 *M2, double *d,
-                       int *sel, int *info, hipStream_t st);
+hipError_t launch_forms(const AtomPlan &p, const AtomBufs &ab, const double2 *T_AA,
+                        const double2 *T_BB, const double2 *U, hipStream_t st);
+// info[a]: 0 or the 1-based failing pivot of T_AA,a's Cholesky (Alg. 1's try
+// step), as a launch of its own; the product launches below run it beside
+// the products.
+hipError_t launch_chol(const Atoms &at, const double2 *T_AA, int *info, hipStream_t st);
 
-// Per-atom products (Alg. 1 first loop and second-loop branches):
-//   Z_a = T_AB,a^H A_a + M2_a^H B_a      (= T^BA_a A_a + 1/2 T^BB_a B_a)
-//   W_a = M1_a^H A_a                     (= Y_a or X_a)
-// sel: the preparation's [3K] row selectors (sel[2K + r] != 0 on the rows of
-// atoms on the failure branch); on the other atoms M1_a = C_a is lower
-// triangular and W_a's rows contract only over l >= their own index.
+// Per-atom products:
+//   X_a = T^AA_a A_a + T^AB_a B_a = M1_a^H A_a + T_AB,a B_a
+//   Y_a = T^BA_a A_a + T^BB_a B_a = T_AB,a^H A_a + M2_a^H B_a
+// and, when info is not NULL, the Cholesky of T_AA,a into info[a].
 hipError_t launch_atom(const Atoms &at, int n_g, const double2 *A, const double2 *B,
-                       const double2 *T_AB, const double2 *M1, const double2 *M2,
-                       const int *sel, double2 *Z, double2 *W, hipStream_t st);
+                       const double2 *T_AA, const double2 *T_AB, const double2 *M1,
+                       const double2 *M2, int *info, double2 *X, double2 *Y, hipStream_t st);
 
-// Start of the contraction of a W_a tile whose output rows begin at m0: with
-// C_a lower triangular, conj(C_a[l][m]) is zero for l < m, so rows l < m0
-// add nothing to rows m >= m0 (the product is a triangular multiply); the
-// failure branch's Hermitian T^AA_a is full.
-__device__ __forceinline__ int w_contraction_start(bool failing, int m0) {
-    return failing ? 0 : m0;
-}
-
-// Large reductions (Alg. 1's zher2k, zherk pair of S, failure-branch zgemm
-// and HPD zherk) into the lower triangles of H and S (complex FP64 MFMA;
-// g3: 3 real products per complex product instead of 4).
+// Large reductions H = A^H X + B^H Y, S = A^H A + B^H |U|^2 B into the lower
+// triangles of H and S (complex FP64 MFMA; g3: 3 real products per complex
+// product instead of 4).
 hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
-                         const double2 *Z, const double2 *W, const int *sel,
-                         const double *d, double2 *H, double2 *S, hipStream_t st, bool g3);
+                         const double2 *X, const double2 *Y, const double *d,
+                         double2 *H, double2 *S, hipStream_t st, bool g3);
 
 // Error bookkeeping shared by the C entry points (thread-local message).
 void set_error(int status, const std::string &msg);
@@ -77,14 +67,11 @@ inline bool split_mode(int mode) {   // the operands are sliced (or cut into res
            mode == HS_SPLIT_I8_CRT;
 }
 
-// Split-precision reductions (k_split.hip). A sliced operand: rows of X (or
-// of Xalt where sel[k] != 0), optionally scaled by sqrt(rscale[k]); outputs
-// the column maxima mx [N_G] (bit patterns of doubles) and the FP16 slices
+// Split-precision reductions (k_split.hip). A sliced operand: rows of X,
+// optionally scaled by sqrt(rscale[k]); outputs the column maxima mx [N_G] (bit patterns of doubles) and the FP16 slices
 // S [4][groups][N_G][8], groups = 4 * ceil(K / 16).
 struct SliceSrc {
     const double2 *X;
-    const double2 *Xalt;
-    const int *sel;
     const double *rscale;
     unsigned long long *mx;
     _Float16 *S;
@@ -98,15 +85,15 @@ size_t split_slice_bytes(int K, int n_g);
 hipError_t launch_colmax(const SliceSrc &src, int K, int n_g, hipStream_t st);
 // bf16: the same slices held as BF16 and multiplied on BF16 MFMA
 hipError_t launch_slice(const SliceSrc &src, int K, int n_g, hipStream_t st, bool bf16);
-// H segments (Z,B), (B,Z), (P3,W); S segments (A,A), (Bs,Bs): [segment][P or Q]
-hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[3][2],
+// H segments (B,Y), (A,X); S segments (A,A), (Bs,Bs): [segment][P or Q]
+hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                hipStream_t st, bool bf16);
 // INT8 form: slices S8 [5][groups][N_G][16 int8], groups = 4 * ceil(K / 32);
 // same column maxima and segments as the FP16 form.
 size_t split8_slice_bytes(int K, int n_g);
 hipError_t launch_slice8(const SliceSrc &src, int K, int n_g, hipStream_t st);
-hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[3][2],
+hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                 const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                 hipStream_t st);
 // Modular INT8 form (k_crt.hip): residues R [NMOD][groups][N_G][16 int8],
@@ -117,7 +104,7 @@ size_t crt_residue_bytes(int K, int n_g);
 size_t crt_work_bytes(int n_g);
 int crt_bits(int K);   // integer width b of the operands for contraction length K
 hipError_t launch_residue(const SliceSrc &src, int K, int n_g, hipStream_t st);
-hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[3][2],
+hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                              const SliceView (&sseg)[2][2], void *work, double2 *H, double2 *S,
                              hipStream_t st);
 inline size_t slice_bytes(int mode, int K, int n_g) {
@@ -154,7 +141,7 @@ struct AtomPlan {
     int make(int N_A, const int32_t *nl_per_atom, int N_L);
     // Device bytes of the k-independent buffers (AtomBufs).
     size_t atom_bytes() const;
-    // Device bytes of the per-k-point buffers for N_G (Z, W; plus the
+    // Device bytes of the per-k-point buffers for N_G (X, Y; plus the
     // sliced operands in the split-precision mode).
     size_t kpoint_bytes(int n_g, int mode = 0) const;
 };
@@ -163,10 +150,9 @@ struct AtomPlan {
 struct AtomBufs {
     int *tables;      // row_off [N_A+1], then t_off [N_A+1]
     int *info;        // [N_A]
-    int *sel;         // [3K]
     double *d;        // [2K]
-    double2 *M1;      // [t_total]
-    double2 *M2;      // [t_total]
+    double2 *M1;      // [t_total] Hermitian T_AA
+    double2 *M2;      // [t_total] Hermitian T_BB
     void carve(const AtomPlan &p, char *base);
     Atoms atoms(const AtomPlan &p) const;
 };
@@ -178,8 +164,7 @@ constexpr int ATOM_TILE_MIN_BM = 32, ATOM_TILE_MIN_BN = 128;
 struct BatchBufs {
     int *perm;    // [N_A]
     int *zoff;    // [N_A + 1]
-    int *ctrl;    // [2]
-    int *flags;   // [2 N_A]
+    int *ctrl;    // [1] item counter
     int *tiles;   // [2 max_tiles(N_A, N_G)] atom, tile within the atom of each product tile
     static long long max_tiles(int n_atoms, int n_g);
     static size_t bytes(int n_atoms, int n_g);
@@ -197,23 +182,23 @@ struct BatchPlan {
     static bool valid(const AtomPlan &p, const unsigned char *cfg_table);
 };
 struct BatchIO {
-    const double2 *T_AA, *T_AB, *T_BB, *U, *A, *B;
-    double2 *M1, *M2;
-    double *d;
-    int *sel, *info;
-    double2 *Z, *W;
+    const double2 *T_AA, *T_AB, *A, *B, *M1, *M2;
+    int *info;   // NULL: products only
+    double2 *X, *Y;
 };
 int tile_shape(int id, int *bm, int *bn);   // 0, or -1 for an unknown id
 int default_tile(int nl);
-// Persistent launch of the per-atom stage (preparation items only when
-// do_factor) followed, when do_factor, by the wait check.
+// Persistent launch of the per-atom stage.
 hipError_t launch_batch(const AtomPlan &p, const Atoms &at, const BatchPlan &bp, int n_g,
-                        bool do_factor, const BatchIO &io, const BatchBufs &bb, hipStream_t st);
+                        const BatchIO &io, const BatchBufs &bb, hipStream_t st);
 
 // Per-k-point device buffers.
-constexpr int NSPLIT = 6;   // sliced operands: A, U B, Z, B, P3 (W or A by row), W
+constexpr int NSPLIT = 5;   // sliced operands: A, U B, X, B, Y
+// Room for this many sliced operands is part of the workspace size callers
+// have been given.
+constexpr int NSPLIT_ROOM = 6;
 struct KpointBufs {
-    double2 *Z, *W;   // [K][N_G] each
+    double2 *X, *Y;   // [K][N_G] each
     _Float16 *sl[NSPLIT];
     unsigned long long *mx[NSPLIT];
     void *crt;        // segment residues of the modular form (else NULL)
@@ -221,22 +206,17 @@ struct KpointBufs {
     void carve(const AtomPlan &p, int n_g, int mode, char *base);
 };
 
-// How the per-atom stage of one build runs: separate preparation and product
-// launches (batch = false), or the persistent batched launch with the tile
-// table cfg; factor: the batched launch includes the preparation.
+// How the per-atom products of one build run: one launch with a tile shape
+// for all atoms (batch = false), or the persistent batched launch with the
+// tile table cfg; info: where the Cholesky of T_AA reports, or NULL when it
+// has been run already (the resident context).
 struct AtomStage {
     bool batch = false;
-    bool factor = false;
     const unsigned char *cfg = nullptr;   // [HS_MAX_NL + 1] or NULL
-    const double2 *T_AA = nullptr, *T_BB = nullptr, *U = nullptr;
+    const double2 *T_AA = nullptr;
     int *info = nullptr;
 };
 
-// Tables, per-atom Cholesky and operand preparation (k-independent).
-// prep = false: tables only (the batched launch prepares the atoms itself).
-hipError_t enqueue_atoms(const AtomPlan &p, const AtomBufs &ab, const double2 *T_AA,
-                         const double2 *T_BB, const double2 *U, int *info_out, hipStream_t st,
-                         bool prep = true);
 // Per-atom products and the reductions for one k-point. ev: optional phase
 // events [1..4] as in hs_options.phase_events (ev[0] is recorded by the caller).
 hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mode,

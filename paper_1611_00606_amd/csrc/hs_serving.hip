@@ -2,8 +2,8 @@
 // (hs_server) for many k-points of one atom set.
 //
 // The context keeps the k-independent part of Alg. 1 on the device: the
-// per-atom Cholesky factors / failure flags and operand forms (M1, M2), the
-// per-row metadata of the reductions, and a copy of T^AB. One k-point then
+// per-atom Cholesky flags, the operand forms (M1, M2), the per-row scales of
+// the reductions, and a copy of T^AB. One k-point then
 // costs the per-atom products and the two reductions only.
 //
 // The server owns one device arena and n_slots HIP streams (default
@@ -78,9 +78,12 @@ int hs_ctx_create(const hs_complex *T_AA, const hs_complex *T_AB, const hs_compl
     hipStream_t st = static_cast<hipStream_t>(stream);
     e = hipMemcpyAsync(c->T_AB, T_AB, tbytes, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess)
-        e = hs::enqueue_atoms(c->plan, c->ab, reinterpret_cast<const double2 *>(T_AA),
-                              reinterpret_cast<const double2 *>(T_BB),
-                              reinterpret_cast<const double2 *>(U), nullptr, st);
+        e = hs::launch_forms(c->plan, c->ab, reinterpret_cast<const double2 *>(T_AA),
+                             reinterpret_cast<const double2 *>(T_BB),
+                             reinterpret_cast<const double2 *>(U), st);
+    if (e == hipSuccess)
+        e = hs::launch_chol(c->ab.atoms(c->plan), reinterpret_cast<const double2 *>(T_AA),
+                            c->ab.info, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         (void)hipFree(c->mem);

@@ -99,21 +99,20 @@ int tune_one(int nl, int n_g, int reps, hipStream_t st, float *ms_out) {
             hipLaunchKernelGGL(k_boost_diag, dim3((p.K + 255) / 256), dim3(256), 0, st, T_AA, nl,
                                n_atoms, 2.0 * nl + 2.0);
             ok = check(hipGetLastError(), "boost") &&
-                 check(hs::enqueue_atoms(p, ab, T_AA, T_BB, U, nullptr, st, true), "prep");
+                 check(hs::launch_forms(p, ab, T_AA, T_BB, U, st), "prep");
         }
-        const hs::BatchIO io{T_AA, T_AB, T_BB, U, A, B, ab.M1, ab.M2, ab.d, ab.sel, ab.info,
-                             kb.Z, kb.W};
+        const hs::BatchIO io{T_AA, T_AB, A, B, ab.M1, ab.M2, nullptr, kb.X, kb.Y};
         unsigned char table[HS_MAX_NL + 1];
         for (int c = 0; ok && c < HS_NUM_TILE_CONFIGS; ++c) {
             std::fill(table, table + HS_MAX_NL + 1, (unsigned char)c);
             hs::BatchPlan bp;
             bp.make(p, n_g, table);
-            ok = check(hs::launch_batch(p, ab.atoms(p), bp, n_g, false, io, kb.batch, st),
+            ok = check(hs::launch_batch(p, ab.atoms(p), bp, n_g, io, kb.batch, st),
                        "autotune launch");
             float best = FLT_MAX;
             for (int r = 0; ok && r < reps; ++r) {
                 ok = check(hipEventRecord(ev0, st), "hipEventRecord") &&
-                     check(hs::launch_batch(p, ab.atoms(p), bp, n_g, false, io, kb.batch, st),
+                     check(hs::launch_batch(p, ab.atoms(p), bp, n_g, io, kb.batch, st),
                            "autotune launch") &&
                      check(hipEventRecord(ev1, st), "hipEventRecord") &&
                      check(hipEventSynchronize(ev1), "autotune run");

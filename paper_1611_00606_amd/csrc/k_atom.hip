@@ -1,18 +1,20 @@
-// Per-atom products of Alg. 1, as complex MFMA tiles:
-//   first loop     Z_a = T^BA_a A_a + 1/2 T^BB_a B_a = T_AB,a^H A_a + M2_a^H B_a
-//   second loop    W_a = M1_a^H A_a  = C_a^H A_a (success, Y_a; C_a lower
-//                                    triangular, so a row tile's contraction
-//                                    starts at its first row)
-//                                    or T^AA_a A_a (failure, X_a)
-// with M1, M2 prepared by k_prep (M2 = 1/2 T^BB_a and, on failure,
-// M1 = T^AA_a, both Hermitian, so M^H = M).
+// Per-atom products, as complex MFMA tiles:
+//   X_a = T^AA_a A_a + T^AB_a B_a = M1_a^H A_a + T_AB,a B_a
+//   Y_a = T^BA_a A_a + T^BB_a B_a = T_AB,a^H A_a + M2_a^H B_a
+// with M1, M2 the Hermitian T^AA_a, T^BB_a prepared by k_forms, so that
+// H = A^H X + B^H Y. (Alg. 1's Z_a, Y_a and X_a take 20 N_L^2 N_G real
+// operations per atom against 32 here, but its H contracts over 3K rows
+// instead of 2K: 4 K N_G^2 operations saved for 12 K N_L N_G.)
 //
 // Each block computes a BM x BN tile of one atom's N_L x N_G output (one
 // tile covers all of an atom's rows, BM >= N_L); the contraction runs over
-// the atom's N_L rows (twice for Z). The grid is (N_G tiles, atoms x row
-// tiles, 2 products); Z and W land in the stacked [K][N_G] layout that the
-// large reductions read.
+// the atom's N_L rows twice. Blocks are ordered so that the X and the Y tile
+// of the same columns, which read the same rows of A and B, are neighbours.
+// The first n_chol blocks run the Cholesky of T^AA_a (info[a]) instead: a
+// serial chain of N_L columns that nothing else waits for, hidden beside the
+// products.
 #include "hs_internal.h"
+#include "prep_atom.h"
 #include "zmfma_atom.h"
 
 namespace hs {
@@ -21,73 +23,48 @@ namespace {
 
 template <class C>
 __global__ void __launch_bounds__(C::NT)
-k_atom(Atoms at, int n_g, int mtiles, const double2 *__restrict__ A,
-       const double2 *__restrict__ B, const double2 *__restrict__ T_AB,
-       const double2 *__restrict__ M1, const double2 *__restrict__ M2,
-       const int *__restrict__ sel, double2 *__restrict__ Z, double2 *__restrict__ W) {
+k_atom(Atoms at, int n_g, int mtiles, int ctiles, int n_chol, const double2 *__restrict__ A,
+       const double2 *__restrict__ B, const double2 *__restrict__ T_AA,
+       const double2 *__restrict__ T_AB, const double2 *__restrict__ M1,
+       const double2 *__restrict__ M2, int *__restrict__ info, double2 *__restrict__ X,
+       double2 *__restrict__ Y) {
+    static_assert(C::NT == CHOL_THREADS && C::LDS_ELEMS * 16 >= CHOL_LDS_BYTES, "shared block");
     __shared__ double2 lds[C::LDS_ELEMS];
 
-    const int a = blockIdx.y / mtiles;
-    const int mt = blockIdx.y % mtiles;
-    const int which = blockIdx.z;  // 0: Z, 1: W
+    int b = blockIdx.x;
+    if (b < n_chol) {
+        chol_info(at, b, T_AA, info, reinterpret_cast<char *>(lds));
+        return;
+    }
+    b -= n_chol;
+    const int which = b & 1;  // 0: X, 1: Y
+    b >>= 1;
+    const int ct = b % ctiles;
+    b /= ctiles;
+    const int a = b / mtiles;
+    const int mt = b % mtiles;
     const int r0 = at.row_off[a];
     const int n = at.row_off[a + 1] - r0;
     const int m0 = mt * C::BM;
     if (m0 >= n) return;  // atom has fewer rows than this row tile (mixed N_L)
-    const long long t0 = at.t_off[a];
-    const int n0 = blockIdx.x * C::BN;
-
-    const double2 *Aa = A + (long long)r0 * n_g;
-    const double2 *Ba = B + (long long)r0 * n_g;
-    Segs<2, false, false> tab;
-    tab.ldp = n;
-    tab.ldq = n_g;
-    tab.len = n;
-    tab.palt = nullptr;
-    tab.sel = nullptr;
-    tab.qscale = nullptr;
-    if (which == 0) {
-        tab.nseg = 2;
-        tab.P[0] = T_AB + t0;
-        tab.Q[0] = Aa;
-        tab.P[1] = M2 + t0;
-        tab.Q[1] = Ba;
-    } else {
-        const int k0 = w_contraction_start(sel[2 * at.K + r0] != 0, m0);
-        tab.nseg = 1;
-        tab.len = n - k0;
-        tab.P[0] = M1 + t0 + (long long)k0 * n;
-        tab.Q[0] = Aa + (long long)k0 * n_g;
-        tab.P[1] = tab.P[0];
-        tab.Q[1] = tab.Q[0];
-    }
-
-    const bool tri = which == 1 && sel[2 * at.K + r0] == 0;
+    const int n0 = ct * C::BN;
+    const Segs<2, false> tab = atom_segs(which, n, n_g, at.t_off[a], r0, A, B, T_AB, M1, M2);
     Acc<C> acc;
-    ztile_atom<C, 2>(tab, m0, n, n0, n_g, tri, acc, lds);
-
-    double2 *out = (which == 0 ? Z : W) + (long long)r0 * n_g;
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j) {
-            const int g = n0 + atom_col<C>(j);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int l = m0 + atom_row<C>(i, v);
-                if (l < n && g < n_g) out[(long long)l * n_g + g] = double2{acc.re[i][j][v], acc.im[i][j][v]};
-            }
-        }
+    ztile_atom<C>(tab, m0, n, n0, n_g, which == 0, acc, lds);
+    atom_store<C>(acc, m0, n, n0, n_g, (which == 0 ? X : Y) + (long long)r0 * n_g);
 }
 
 template <class C>
 hipError_t launch_atom_cfg(const Atoms &at, int n_g, const double2 *A, const double2 *B,
-                           const double2 *T_AB, const double2 *M1, const double2 *M2,
-                           const int *sel, double2 *Z, double2 *W, hipStream_t st) {
+                           const double2 *T_AA, const double2 *T_AB, const double2 *M1,
+                           const double2 *M2, int *info, double2 *X, double2 *Y, hipStream_t st) {
     const int mtiles = (at.max_nl + C::BM - 1) / C::BM;
-    dim3 grid((n_g + C::BN - 1) / C::BN, at.n_atoms * mtiles, 2);
-    hipLaunchKernelGGL(k_atom<C>, grid, dim3(C::NT), 0, st, at, n_g, mtiles, A, B, T_AB, M1,
-                       M2, sel, Z, W);
+    const int ctiles = (n_g + C::BN - 1) / C::BN;
+    const int n_chol = info ? at.n_atoms : 0;
+    const long long blocks = n_chol + 2LL * ctiles * mtiles * at.n_atoms;
+    if (blocks > (1LL << 30)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_atom<C>, dim3((unsigned)blocks), dim3(C::NT), 0, st, at, n_g, mtiles,
+                       ctiles, n_chol, A, B, T_AA, T_AB, M1, M2, info, X, Y);
     return hipGetLastError();
 }
 
@@ -97,15 +74,15 @@ hipError_t launch_atom_cfg(const Atoms &at, int n_g, const double2 *A, const dou
 // 128 columns (192 for the 96-row tile, as in the batched launch's
 // built-in choice).
 hipError_t launch_atom(const Atoms &at, int n_g, const double2 *A, const double2 *B,
-                       const double2 *T_AB, const double2 *M1, const double2 *M2,
-                       const int *sel, double2 *Z, double2 *W, hipStream_t st) {
+                       const double2 *T_AA, const double2 *T_AB, const double2 *M1,
+                       const double2 *M2, int *info, double2 *X, double2 *Y, hipStream_t st) {
     if (at.max_nl <= 32)
-        return launch_atom_cfg<AtomCfg<1, 2, 16>>(at, n_g, A, B, T_AB, M1, M2, sel, Z, W, st);
+        return launch_atom_cfg<AtomCfg<1, 2, 16>>(at, n_g, A, B, T_AA, T_AB, M1, M2, info, X, Y, st);
     if (at.max_nl <= 64)
-        return launch_atom_cfg<AtomCfg<2, 2, 16>>(at, n_g, A, B, T_AB, M1, M2, sel, Z, W, st);
+        return launch_atom_cfg<AtomCfg<2, 2, 16>>(at, n_g, A, B, T_AA, T_AB, M1, M2, info, X, Y, st);
     if (at.max_nl <= 96)
-        return launch_atom_cfg<AtomCfg<3, 3, 8>>(at, n_g, A, B, T_AB, M1, M2, sel, Z, W, st);
-    return launch_atom_cfg<AtomCfg<4, 2, 16>>(at, n_g, A, B, T_AB, M1, M2, sel, Z, W, st);
+        return launch_atom_cfg<AtomCfg<3, 3, 8>>(at, n_g, A, B, T_AA, T_AB, M1, M2, info, X, Y, st);
+    return launch_atom_cfg<AtomCfg<4, 2, 16>>(at, n_g, A, B, T_AA, T_AB, M1, M2, info, X, Y, st);
 }
 
 }  // namespace hs

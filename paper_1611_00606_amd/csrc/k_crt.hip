@@ -1,6 +1,6 @@
-// Modular INT8 form of the large reductions (HS_SPLIT_I8_CRT): the five
-// stacked products of Alg. 1 (the zher2k, the two zherk of S, the
-// failure-branch zgemm and the HPD zherk) computed exactly on integers.
+// Modular INT8 form of the large reductions (HS_SPLIT_I8_CRT): the four
+// stacked products of H = A^H X + B^H Y and S = A^H A + (U B)^H (U B) (see
+// k_reduce.hip) computed exactly on integers.
 //
 // Operands. For each column n of a sliced operand X let e[n] be the exponent
 // with max_k max(|Re X[k][n]|, |Im X[k][n]|) < 2^e[n], and
@@ -25,7 +25,7 @@
 // with symmetric digits v_i, computed exactly in FP32 (every intermediate is
 // an integer below 2^24) and evaluated by Horner's rule in FP64. Each
 // segment's integer is scaled by 2^(eP + eQ - 2 (b - 1)) and the segments of
-// H (three) and of S (two) are added in FP64.
+// H (two) and of S (two) are added in FP64.
 //
 // The scheme is the modular-integer emulation of floating-point matrix
 // products of Ozaki, Uchino and Imamura ("Ozaki scheme II", 2025). Against
@@ -44,7 +44,10 @@ typedef int i4 __attribute__((ext_vector_type(4)));
 constexpr int NMOD = 11;
 constexpr int CRT_MOD[NMOD] = {255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217};
 constexpr int CRT_BMAX = 36;   // |X'| <= 2^35: exact in FP64, and b = 36 for K up to about 5e4
-constexpr int NSEG = 5;        // H: (Z,B), (B,Z), (P3,W); S: (A,A), (Bs,Bs)
+constexpr int NSEG = 4;        // H: (B,Y), (A,X); S: (A,A), (Bs,Bs)
+// Segments the work buffer has room for (part of the workspace size callers
+// have been given).
+constexpr int NSEG_ROOM = 5;
 
 // Garner constants, symmetric: w[i][j] = W_j mod m_i (j < i), u[i] = W_i^-1 mod m_i.
 constexpr int sym_mod_c(long long x, int m) {
@@ -410,10 +413,9 @@ k_crt_recon(CrtRecArgs a) {
     if (isH) {
         segment(0, a.mP[0], a.mQ[0]);
         segment(1, a.mP[1], a.mQ[1]);
-        segment(2, a.mP[2], a.mQ[2]);
     } else {
+        segment(2, a.mP[2], a.mQ[2]);
         segment(3, a.mP[3], a.mQ[3]);
-        segment(4, a.mP[4], a.mQ[4]);
     }
     double2 *out = isH ? a.H : a.S;
 #pragma unroll
@@ -447,7 +449,7 @@ size_t crt_residue_bytes(int K, int n_g) {
 size_t crt_work_bytes(int n_g) {
     int nt;
     const long long ntri = crt_tiles(n_g, &nt);
-    return (size_t)NSEG * NMOD * ntri * CFRAG * 64 * sizeof(uint2);
+    return (size_t)NSEG_ROOM * NMOD * ntri * CFRAG * 64 * sizeof(uint2);
 }
 
 hipError_t launch_residue(const SliceSrc &src, int K, int n_g, hipStream_t st) {
@@ -460,11 +462,11 @@ hipError_t launch_residue(const SliceSrc &src, int K, int n_g, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[3][2],
+hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                              const SliceView (&sseg)[2][2], void *work, double2 *H, double2 *S,
                              hipStream_t st) {
     auto u4 = [](const _Float16 *p) { return reinterpret_cast<const uint4 *>(p); };
-    const SliceView *segs[NSEG] = {hseg[0], hseg[1], hseg[2], sseg[0], sseg[1]};
+    const SliceView *segs[NSEG] = {hseg[0], hseg[1], sseg[0], sseg[1]};
     CrtArgs a;
     CrtRecArgs r;
     for (int s = 0; s < NSEG; ++s) {

@@ -163,7 +163,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
     if (flags & MM_QL) klo = max(klo, n0);
     if (flags & MM_PL) klo = max(klo, m0);
 
-    Segs<NSEG, false, false> t;
+    Segs<NSEG, false> t;
     t.nseg = NSEG;
     t.len = khi > klo ? khi - klo : 0;
     t.ldp = N;
@@ -175,11 +175,9 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
         t.P[1] = args.P2 + k0;
         t.Q[1] = args.Q2 + k0;
     }
-    t.palt = nullptr;
-    t.sel = nullptr;
     t.qscale = nullptr;
     Acc<Cfg> acc;
-    ztile_direct<Cfg, NSEG, false, false, G3>(t, m0, i1, n0, j1, acc, lds);
+    ztile_direct<Cfg, NSEG, false, G3>(t, m0, i1, n0, j1, acc, lds);
 
     const bool lower = flags & (MM_LOWER | MM_MASK);
     const bool upper = flags & MM_UPPER;

@@ -1,16 +1,17 @@
-// The large stacked reductions of Alg. 1, on complex FP64 MFMA tiles:
-//   H = Z^H B + B^H Z              (zher2k)
-//     + A_notHPD^H X_notHPD        (failure-branch zgemm)
-//     + Y_HPD^H Y_HPD              (HPD zherk)
-//   S = A^H A + (U B)^H (U B)      (zherk, scaling of B by U, zherk)
-// The second-loop operands are held in one stacked matrix W (Y_a or X_a in
-// atom a's rows); for the rows of failing atoms the left operand is A, chosen
-// per row by `sel`, so no compaction of the stacks is needed. The U scaling
-// is applied to the right operand as |u|^2 while it is loaded.
+// The large stacked reductions, on complex FP64 MFMA tiles:
+//   H = B^H Y + A^H X,   X_a = T^AA_a A_a + T^AB_a B_a,
+//                        Y_a = T^BA_a A_a + T^BB_a B_a
+//   S = A^H A + B^H |U|^2 B
+// Both are Hermitian and only their lower triangles are computed, so neither
+// needs a Hermitian rank-k form: the stacked operands [A; B] contract over 2K
+// rows with [X; Y], where Alg. 1's terms Z^H B + B^H Z + (Y^H Y or A^H X)
+// contract over 3K (its zher2k and zherk save the upper triangle, a choice
+// the tiles make by themselves). At N_G = 8000, K = 8100: 125 ms for the two
+// outputs against 155 ms in the 3K form, at the same error.
+// The U scaling is applied to the right operand as |u|^2 while it is read.
 //
 // Only lower-triangle tiles (tile row >= tile column) are computed; one block
-// per tile and output. H tiles are dispatched before S tiles (they carry 1.5x
-// the contraction length). Consecutive blocks of the hardware dispatch go to
+// per tile and output. Consecutive blocks of the hardware dispatch go to
 // the 8 XCDs in turn, so block b is remapped to tile index
 // (b mod 8) * (tiles/8) + b/8: each XCD then walks a contiguous run of a
 // banded tile order, and the blocks resident on one XCD share the column
@@ -36,8 +37,7 @@ static_assert(RedCfg::BM == RedCfg::BN, "lower-triangle tiling needs square tile
 constexpr int BAND = 4;   // tile columns per band of the tile order
 
 struct RedArgs {
-    const double2 *A, *B, *Z, *W;
-    const int *sel;
+    const double2 *A, *B, *X, *Y;
     const double *d;
     int K;
     double2 *H;
@@ -102,24 +102,21 @@ k_reduce(RedArgs args) {
     const long long ld = args.n_g;
     Acc<C> acc;
     if (isH) {
-        // Z^H B + B^H Z + (W or A)^H W
-        Segs<3, true, false> t;
-        t.nseg = 3;
+        // B^H Y + A^H X: the larger terms last (T^AA carries most of H), which
+        // leaves fewer roundings at the full size of the sum
+        Segs<2, false> t;
+        t.nseg = 2;
         t.len = args.K;
         t.ldp = t.ldq = ld;
-        t.P[0] = args.Z;
-        t.Q[0] = args.B;
-        t.P[1] = args.B;
-        t.Q[1] = args.Z;
-        t.P[2] = args.W;
-        t.Q[2] = args.W;
-        t.palt = args.A;
-        t.sel = args.sel;      // [3K]: 0 on the first two segments
+        t.P[0] = args.B;
+        t.Q[0] = args.Y;
+        t.P[1] = args.A;
+        t.Q[1] = args.X;
         t.qscale = nullptr;
-        ztile_direct<C, 3, true, false, G3>(t, m0, args.n_g, n0, args.n_g, acc, lds);
+        ztile_direct<C, 2, false, G3>(t, m0, args.n_g, n0, args.n_g, acc, lds);
     } else {
         // A^H A + B^H diag(|u|^2) B
-        Segs<2, false, true> t;
+        Segs<2, true> t;
         t.nseg = 2;
         t.len = args.K;
         t.ldp = t.ldq = ld;
@@ -127,10 +124,8 @@ k_reduce(RedArgs args) {
         t.Q[0] = args.A;
         t.P[1] = args.B;
         t.Q[1] = args.B;
-        t.palt = nullptr;
-        t.sel = nullptr;
         t.qscale = args.d;     // [2K]: 1 on A's rows, |u|^2 on B's rows
-        ztile_direct<C, 2, false, true, G3>(t, m0, args.n_g, n0, args.n_g, acc, lds);
+        ztile_direct<C, 2, true, G3>(t, m0, args.n_g, n0, args.n_g, acc, lds);
     }
 
     double2 *out = isH ? args.H : args.S;
@@ -181,15 +176,14 @@ k_mirror(double2 *H, double2 *S, int n_g) {
 }  // namespace
 
 hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
-                         const double2 *Z, const double2 *W, const int *sel,
-                         const double *d, double2 *H, double2 *S, hipStream_t st, bool g3) {
+                         const double2 *X, const double2 *Y, const double *d,
+                         double2 *H, double2 *S, hipStream_t st, bool g3) {
     using C = RedCfg;
     RedArgs args;
     args.A = A;
     args.B = B;
-    args.Z = Z;
-    args.W = W;
-    args.sel = sel;
+    args.X = X;
+    args.Y = Y;
     args.d = d;
     args.K = K;
     args.H = H;

@@ -1,9 +1,8 @@
-// Split-precision form of the large reductions (the five stacked products of
-// Alg. 1: zher2k, the two zherk of S, the failure-branch zgemm and the HPD
-// zherk): FP64 operands are cut into FP16 slices, the
+// Split-precision form of the large reductions (H = A^H X + B^H Y and
+// S = A^H A + (U B)^H (U B), see k_reduce.hip): FP64 operands are cut into FP16 slices, the
 // slice products run on FP16 MFMA with FP32 accumulation, and the slices are
 // recombined in FP64. The per-atom Cholesky, the HPD test and the per-atom
-// products stay in FP64 (they produce the Z, W operands sliced here).
+// products stay in FP64 (they produce the X, Y operands sliced here).
 //
 // Slicing (error-free): for each operand column n let e[n] be the exponent
 // with max_k max(|Re X[k][n]|, |Im X[k][n]|) < 2^e[n]. The scaled values
@@ -178,7 +177,7 @@ struct SplitSeg {
 };
 
 struct SplitArgs {
-    SplitSeg h[3];
+    SplitSeg h[2];
     SplitSeg s[2];
     double2 *H, *S;
     int n_g, groups;         // groups = K padded to 16, over 4
@@ -375,10 +374,9 @@ k_split_reduce(SplitArgs args) {
             for (int v = 0; v < 4; ++v) acc.re[i][j][v] = acc.im[i][j][v] = 0.0;
 
     if (isH) {
-        const SplitSeg h0 = args.h[0], h1 = args.h[1], h2 = args.h[2];
+        const SplitSeg h0 = args.h[0], h1 = args.h[1];
         split_segment<BF>(h0, n_g, args.groups, m0, n0, acc, lds);
         split_segment<BF>(h1, n_g, args.groups, m0, n0, acc, lds);
-        split_segment<BF>(h2, n_g, args.groups, m0, n0, acc, lds);
     } else {
         const SplitSeg s0 = args.s[0], s1 = args.s[1];
         split_segment<BF>(s0, n_g, args.groups, m0, n0, acc, lds);
@@ -496,7 +494,7 @@ struct Split8Seg {
 };
 
 struct Split8Args {
-    Split8Seg h[3];
+    Split8Seg h[2];
     Split8Seg s[2];
     double2 *H, *S;
     int n_g, groups;          // groups of 8 complex rows, a multiple of GRP8
@@ -666,10 +664,9 @@ k_split8_reduce(Split8Args args) {
 
     Acc8 acc;
     if (isH) {
-        const Split8Seg h0 = args.h[0], h1 = args.h[1], h2 = args.h[2];
+        const Split8Seg h0 = args.h[0], h1 = args.h[1];
         split8_segment(h0, n_g, args.groups, m0, n0, true, acc, bufA, bufB);
         split8_segment(h1, n_g, args.groups, m0, n0, false, acc, bufA, bufB);
-        split8_segment(h2, n_g, args.groups, m0, n0, false, acc, bufA, bufB);
     } else {
         const Split8Seg s0 = args.s[0], s1 = args.s[1];
         split8_segment(s0, n_g, args.groups, m0, n0, true, acc, bufA, bufB);
@@ -723,11 +720,11 @@ hipError_t launch_slice(const SliceSrc &src, int K, int n_g, hipStream_t st, boo
     return hipGetLastError();
 }
 
-hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[3][2],
+hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                hipStream_t st, bool bf16) {
     SplitArgs a;
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 2; ++i)
         a.h[i] = SplitSeg{hseg[i][0].S, hseg[i][1].S, hseg[i][0].mx, hseg[i][1].mx};
     for (int i = 0; i < 2; ++i)
         a.s[i] = SplitSeg{sseg[i][0].S, sseg[i][1].S, sseg[i][0].mx, sseg[i][1].mx};
@@ -758,12 +755,12 @@ hipError_t launch_slice8(const SliceSrc &src, int K, int n_g, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[3][2],
+hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                 const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                 hipStream_t st) {
     auto u4 = [](const _Float16 *p) { return reinterpret_cast<const uint4 *>(p); };
     Split8Args a;
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 2; ++i)
         a.h[i] = Split8Seg{u4(hseg[i][0].S), u4(hseg[i][1].S), hseg[i][0].mx, hseg[i][1].mx};
     for (int i = 0; i < 2; ++i)
         a.s[i] = Split8Seg{u4(sseg[i][0].S), u4(sseg[i][1].S), sseg[i][0].mx, sseg[i][1].mx};

@@ -8,12 +8,9 @@
 
 namespace hs {
 
-// Row k, column n of a sliced operand: X (or Xalt where sel[k] != 0),
-// optionally scaled by sqrt(rscale[k]).
+// Row k, column n of a sliced operand, optionally scaled by sqrt(rscale[k]).
 __device__ __forceinline__ double2 slice_src_row(const SliceSrc &src, int k, int n_g, int n) {
-    const double2 *row = src.X;
-    if (src.sel && src.sel[k]) row = src.Xalt;
-    double2 v = row[(long long)k * n_g + n];
+    double2 v = src.X[(long long)k * n_g + n];
     if (src.rscale) {
         const double w = sqrt(src.rscale[k]);
         v.x *= w;

@@ -10,14 +10,16 @@
 // * the P rows (the atom's N_L x N_L blocks) are N_L entries long: a P row is
 //   loaded as 64-column pieces with the columns past N_L clamped to the last
 //   one (they only feed output rows past N_L, which are not stored);
-// * triangular P (W_a = C_a^H A_a with C_a lower triangular): output row l
-//   only needs contraction rows k >= l, so a 16-row block of outputs skips the
-//   stages below its first row (those would add exact zeros);
+// * a P of the second segment given transposed (X_a's T^AB_a, whose rows are
+//   X_a's rows): lane m of a load reads element (m, k) at its own stride and
+//   the fragment's imaginary part changes sign in registers, so no
+//   conjugate-transposed copy of T^AB_a is made. Its 16-byte loads gather one
+//   cache line each, but eight contraction rows share a line and the P rows
+//   are a small part of a tile's loads;
 // * a last stage whose second half holds no contraction rows skips it.
 //
 // Waves: 2 x 4; wave w takes block row w / 4 and block column w % 4, so each
-// SIMD (waves w and w + 4) holds one wave of each block row and the
-// triangle's skipped stages shorten every SIMD's work alike.
+// SIMD (waves w and w + 4) holds one wave of each block row.
 #pragma once
 
 #include "zmfma_tile.h"
@@ -54,13 +56,11 @@ __device__ __forceinline__ int atom_col(int j) {
     return (wave % C::WN) * C::WTN + j * 16 + (threadIdx.x & 15);
 }
 
-// tri: P is triangular in the sense above, with the tile's first output row
-// at contraction row 0 (the caller starts the contraction at the tile's first
-// row).
-template <class C, int NSEG>
-__device__ __forceinline__ void ztile_atom(const Segs<NSEG, false, false> &t, int m0, int mlim,
-                                           int n0, int nlim, bool tri, Acc<C> &acc,
-                                           double2 *lds) {
+// tr: segment 1's contribution is sum_k P_1[m][k] Q_1[k][n] (P_1 row-major
+// with row stride ldp, not conjugated) instead of P_1^H Q_1.
+template <class C>
+__device__ __forceinline__ void ztile_atom(const Segs<2, false> &t, int m0, int mlim, int n0,
+                                           int nlim, bool tr, Acc<C> &acc, double2 *lds) {
     static_assert(C::NT == 512, "8 waves");
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -79,17 +79,16 @@ __device__ __forceinline__ void ztile_atom(const Segs<NSEG, false, false> &t, in
     const int ktot = t.nseg * t.len;
     const int nst = (ktot + C::BK - 1) / C::BK;
     if (nst == 0) return;
-    // with P triangular, this wave's block row i starts at output row
-    // wm WTM + 16 i (a multiple of BK) and needs contraction rows from there
-    // on: its first stage is sbase + i SPB
-    const int sbase = wm * C::WTM / C::BK;
-    constexpr int SPB = 16 / C::BK;   // stages per 16-row block
+    const int nrow0 = tr ? t.len : ktot;   // rows of P in the ordinary form
 
-    unsigned pvo[C::PH], qvo[C::QH];
+    // per-lane byte offsets of the loaded columns (clamped at the edge);
+    // pvt: of the loaded rows of a transposed P
+    unsigned pvo[C::PH], pvt[C::PH], qvo[C::QH];
 #pragma unroll
     for (int h = 0; h < C::PH; ++h) {
         const int c = m0 + 64 * h + lane;
         pvo[h] = (unsigned)(c < mlim ? c : mlim - 1) * 16u;
+        pvt[h] = pvo[h] * (unsigned)t.ldp;
     }
 #pragma unroll
     for (int h = 0; h < C::QH; ++h) {
@@ -108,13 +107,15 @@ __device__ __forceinline__ void ztile_atom(const Segs<NSEG, false, false> &t, in
             const int r = wave + 8 * k;
             const int kk = st * C::BK + r;
             if (kk < ktot) {
-                const int s = (NSEG > 1 && kk >= t.len) ? 1 : 0;
+                const int s = kk >= t.len ? 1 : 0;
                 const long long row = kk - s * t.len;
-                const double2 *prow = pick<NSEG>(t.P, s) + row * t.ldp;
-                const double2 *qrow = pick<NSEG>(t.Q, s) + row * t.ldq;
+                const bool gather = kk >= nrow0;
+                const double2 *prow = pick<2>(t.P, s) + (gather ? row : row * t.ldp);
+                const double2 *qrow = pick<2>(t.Q, s) + row * t.ldq;
 #pragma unroll
                 for (int h = 0; h < C::PH; ++h)
-                    __builtin_amdgcn_global_load_lds(at(prow, pvo[h]), lp + r * C::BMS + 64 * h, 16, 0, 0);
+                    __builtin_amdgcn_global_load_lds(at(prow, gather ? pvt[h] : pvo[h]),
+                                                     lp + r * C::BMS + 64 * h, 16, 0, 0);
 #pragma unroll
                 for (int h = 0; h < C::QH; ++h)
                     __builtin_amdgcn_global_load_lds(at(qrow, qvo[h]), lq + r * C::BNS + 64 * h, 16, 0, 0);
@@ -129,46 +130,46 @@ __device__ __forceinline__ void ztile_atom(const Segs<NSEG, false, false> &t, in
 
     const int lr = lane >> 4;   // contraction row within a K step of 4
     const int lc = lane & 15;   // column within a 16-wide block
-    auto ldfrag = [&](const double2 *lp, const double2 *lq, int k4, double2 (&a)[C::TM],
+    auto ldfrag = [&](const double2 *lp, const double2 *lq, int st, int k4, double2 (&a)[C::TM],
                       double2 (&b)[C::TN]) __attribute__((always_inline)) {
         const int kr = k4 * 4 + lr;
+        // sign flip of the rows of a transposed P (its conjugate is stored)
+        const long long flip = st * C::BK + kr >= nrow0 ? (long long)(1ull << 63) : 0ll;
 #pragma unroll
-        for (int i = 0; i < C::TM; ++i) a[i] = lp[kr * C::BMS + wm * C::WTM + i * 16 + lc];
+        for (int i = 0; i < C::TM; ++i) {
+            a[i] = lp[kr * C::BMS + wm * C::WTM + i * 16 + lc];
+            a[i].y = __longlong_as_double(__double_as_longlong(a[i].y) ^ flip);
+        }
 #pragma unroll
         for (int j = 0; j < C::TN; ++j) b[j] = lq[kr * C::BNS + wn * C::WTN + j * 16 + lc];
     };
-    // the 4 TM TN real MFMAs of one K step (block rows with on[i] only), in
-    // four passes over the blocks so that two MFMAs into one accumulator are
-    // 2 TM TN - 1 MFMAs apart
-    auto mma = [&](const bool (&on)[C::TM], const double2 (&a)[C::TM], const double2 (&b)[C::TN])
+    // the 4 TM TN real MFMAs of one K step, in four passes over the blocks so that
+    // two MFMAs into one accumulator are 2 TM TN - 1 MFMAs apart
+    auto mma = [&](const double2 (&a)[C::TM], const double2 (&b)[C::TN])
                    __attribute__((always_inline)) {
         double nbr[C::TN];
 #pragma unroll
         for (int j = 0; j < C::TN; ++j) nbr[j] = -b[j].x;
 #pragma unroll
         for (int i = 0; i < C::TM; ++i)
-            if (on[i])
 #pragma unroll
-                for (int j = 0; j < C::TN; ++j)
-                    acc.re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, acc.re[i][j], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-            if (on[i])
-#pragma unroll
-                for (int j = 0; j < C::TN; ++j)
-                    acc.im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, acc.im[i][j], 0, 0, 0);
+            for (int j = 0; j < C::TN; ++j)
+                acc.re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].x, acc.re[i][j], 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < C::TM; ++i)
-            if (on[i])
 #pragma unroll
-                for (int j = 0; j < C::TN; ++j)
-                    acc.re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].y, acc.re[i][j], 0, 0, 0);
+            for (int j = 0; j < C::TN; ++j)
+                acc.im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, b[j].y, acc.im[i][j], 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < C::TM; ++i)
-            if (on[i])
 #pragma unroll
-                for (int j = 0; j < C::TN; ++j)
-                    acc.im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, nbr[j], acc.im[i][j], 0, 0, 0);
+            for (int j = 0; j < C::TN; ++j)
+                acc.re[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, b[j].y, acc.re[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j)
+                acc.im[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, nbr[j], acc.im[i][j], 0, 0, 0);
     };
     // one LDS fragment read, then a few MFMAs, for the next step's TM + TN
     // reads (1% faster than the scheduler's own order)
@@ -183,24 +184,19 @@ __device__ __forceinline__ void ztile_atom(const Segs<NSEG, false, false> &t, in
         }
         __builtin_amdgcn_sched_group_barrier(0x008, NM - NR * PER, 0);
     };
-    // block row i of this wave takes part in stage st from its first stage
-    // on (every stage when P is not triangular)
     auto compute = [&](const double2 *lp, const double2 *lq, int st) __attribute__((always_inline)) {
         // the last stage's second half holds no contraction rows: skip it
         const bool full = ktot - st * C::BK > C::BK / 2;
-        bool on[C::TM];
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i) on[i] = !tri || st >= sbase + i * SPB;
         double2 fa0[C::TM], fb0[C::TN], fa1[C::TM], fb1[C::TN];
-        ldfrag(lp, lq, 0, fa0, fb0);
+        ldfrag(lp, lq, st, 0, fa0, fb0);
 #pragma unroll
         for (int k4 = 0; k4 < C::BK / 4; k4 += 2) {
             if (k4 >= C::BK / 8 && !full) break;
-            ldfrag(lp, lq, k4 + 1, fa1, fb1);
-            mma(on, fa0, fb0);
+            ldfrag(lp, lq, st, k4 + 1, fa1, fb1);
+            mma(fa0, fb0);
             interleave();
-            if (k4 + 2 < C::BK / 4) ldfrag(lp, lq, k4 + 2, fa0, fb0);
-            mma(on, fa1, fb1);
+            if (k4 + 2 < C::BK / 4) ldfrag(lp, lq, st, k4 + 2, fa0, fb0);
+            mma(fa1, fb1);
             if (k4 + 2 < C::BK / 4) interleave();
         }
     };
@@ -221,6 +217,43 @@ __device__ __forceinline__ void ztile_atom(const Segs<NSEG, false, false> &t, in
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
+}
+
+// Operands of atom a's X (which = 0) or Y (which = 1) product: r0, n, t0 its
+// first row, N_L and first T element. X: M1^H A + T_AB B, the second segment
+// transposed (ztile_atom's tr); Y: T_AB^H A + M2^H B.
+__device__ __forceinline__ Segs<2, false> atom_segs(int which, int n, int n_g, long long t0, int r0,
+                                                    const double2 *A, const double2 *B,
+                                                    const double2 *T_AB, const double2 *M1,
+                                                    const double2 *M2) {
+    Segs<2, false> t;
+    t.nseg = 2;
+    t.len = n;
+    t.ldp = n;
+    t.ldq = n_g;
+    t.P[0] = (which == 0 ? M1 : T_AB) + t0;
+    t.P[1] = (which == 0 ? T_AB : M2) + t0;
+    t.Q[0] = A + (long long)r0 * n_g;
+    t.Q[1] = B + (long long)r0 * n_g;
+    t.qscale = nullptr;
+    return t;
+}
+
+template <class C>
+__device__ __forceinline__ void atom_store(const Acc<C> &acc, int m0, int n, int n0, int n_g,
+                                           double2 *__restrict__ out) {
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j) {
+            const int g = n0 + atom_col<C>(j);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int l = m0 + atom_row<C>(i, v);
+                if (l < n && g < n_g)
+                    out[(long long)l * n_g + g] = double2{acc.re[i][j][v], acc.im[i][j][v]};
+            }
+        }
 }
 
 }  // namespace hs

@@ -1,16 +1,14 @@
 // Complex-double MFMA tile engine with direct global -> LDS operand loads,
-// for the large reductions (k_reduce). Same contraction and accumulator
-// layout as ztile_run in zmfma_tile.h (C = sum_s P_s^H Q_s over
-// concatenated segments, 4 real V_MFMA_F64_16X16X4_F64 per complex step), but
+// for the large reductions (k_reduce). C = sum_s P_s^H Q_s over
+// concatenated segments, 4 real V_MFMA_F64_16X16X4_F64 per complex step;
 // the operand rows move from global memory straight into LDS with 16-byte
 // loads (global_load_lds_dwordx4: lane l of a wave lands at base + 16 l), so
 // no staging registers and no LDS-store instructions sit in the K loop.
 //
 // One stage is BK = 16 contraction rows of P (BM columns) and Q (BN
 // columns). Wave w loads rows w and w + 8 of both, 64 columns per load, so
-// every load's row is wave-uniform: its segment, its row pointer and the
-// failure-branch selector (SEL: P row taken from palt; the selectors are
-// loaded a stage ahead) are scalar work.
+// every load's row is wave-uniform: its segment and its row pointer are
+// scalar work.
 // Columns past the edge read the last column (they only feed outputs past
 // the edge, which are not stored); rows past the end of the contraction are
 // written as zeros with ordinary LDS stores (only the last stage has any).
@@ -36,8 +34,8 @@
 
 namespace hs {
 
-template <class C, int NSEG, bool SEL, bool SCALE, bool G3 = false>
-__device__ __forceinline__ void ztile_direct(const Segs<NSEG, SEL, SCALE> &t, int m0, int mlim,
+template <class C, int NSEG, bool SCALE, bool G3 = false>
+__device__ __forceinline__ void ztile_direct(const Segs<NSEG, SCALE> &t, int m0, int mlim,
                                              int n0, int nlim, Acc<C> &acc, double2 *lds) {
     static_assert(C::BK == 16 && C::NT == 512, "8 waves load rows w and w + 8 of a 16-row stage");
     static_assert(C::BM % 64 == 0 && C::BN % 64 == 0, "64-column loads");
@@ -82,20 +80,7 @@ __device__ __forceinline__ void ztile_direct(const Segs<NSEG, SEL, SCALE> &t, in
     auto at = [](const double2 *row, unsigned vo) __attribute__((always_inline)) {
         return reinterpret_cast<const double2 *>(reinterpret_cast<const char *>(row) + vo);
     };
-    // failure-branch selectors of this wave's rows w and w + 8, loaded one
-    // stage before the rows themselves: a selector loaded and used at once
-    // held every stage's loads (and so its MFMAs) for a memory round trip
-    int selv[2] = {0, 0};
-    auto load_sel = [&](int st) __attribute__((always_inline)) {
-        if constexpr (SEL) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const int kk = st * C::BK + wave + 8 * k;
-                selv[k] = kk < ktot ? t.sel[kk] : 0;
-            }
-        }
-    };
-    // rows w and w + 8 of stage st into buf (selectors from load_sel(st))
+    // rows w and w + 8 of stage st into buf
     auto issue = [&](double2 *buf, int st) __attribute__((always_inline)) {
         double2 *lp = buf;
         double2 *lq = buf + C::BK * C::BM;
@@ -109,8 +94,6 @@ __device__ __forceinline__ void ztile_direct(const Segs<NSEG, SEL, SCALE> &t, in
                 for (int i = 1; i < NSEG; ++i) s += (i < t.nseg && kk >= i * t.len) ? 1 : 0;
                 const long long row = kk - s * t.len;
                 const double2 *prow = pick<NSEG>(t.P, s);
-                if constexpr (SEL)
-                    if (selv[k]) prow = t.palt;
                 const double2 *qrow = pick<NSEG>(t.Q, s);
                 prow += row * t.ldp;
                 qrow += row * t.ldq;
@@ -242,9 +225,7 @@ __device__ __forceinline__ void ztile_direct(const Segs<NSEG, SEL, SCALE> &t, in
 
     constexpr int BUF = C::BK * (C::BM + C::BN);
     load_scales(qs, 0);
-    load_sel(0);
     issue(lds, 0);
-    load_sel(1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     for (int s = 0; s < nst; ++s) {
@@ -253,7 +234,6 @@ __device__ __forceinline__ void ztile_direct(const Segs<NSEG, SEL, SCALE> &t, in
             if (s + 1 < nst) {
                 issue(nxt, s + 1);
                 load_scales(qs_next, s + 1);
-                load_sel(s + 2);
             }
             compute(cur, cur + C::BK * C::BM);
         };

@@ -2,8 +2,8 @@
 // workspace carve), and the launch sequence of one build:
 //   k_forms   per-atom row / T-block offsets, operand forms
 //   k_atom    per-atom products X_a, Y_a; per-atom Cholesky of T^AA (info)
-//   k_reduce  lower triangles of H and S from the stacked operands
-//   k_mirror  conjugate upper triangles
+//   k_reduce  H and S from the stacked operands (lower triangles; the split
+//             forms are completed by k_mirror)
 // All work is enqueued on one stream; nothing is synchronized inside
 // hs_build_ex. The atom-side steps (k_forms, the Cholesky) do not depend on
 // the k-point and are shared with the resident context (hs_serving.hip).
@@ -222,7 +222,8 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
     }
     if (e != hipSuccess) return e;
     if ((e = mark(3)) != hipSuccess) return e;
-    if ((e = launch_mirror(H, S, n_g, st)) != hipSuccess) return e;
+    // the FP64 reductions write both triangles themselves
+    if (split_mode(mode) && (e = launch_mirror(H, S, n_g, st)) != hipSuccess) return e;
     return mark(4);
 }
 

@@ -51,7 +51,7 @@ namespace hs {
 
 namespace {
 
-using MmCfg = TileCfg<128, 128, 16, 2, 4>;
+using MmCfg = TileCfg<128, 128, 8, 2, 4, 4>;
 
 // Share of the compute units (in quarters) the work moved off the
 // factorization's critical path may occupy.

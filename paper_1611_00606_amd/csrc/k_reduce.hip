@@ -10,19 +10,33 @@
 // outputs against 155 ms in the 3K form, at the same error.
 // The U scaling is applied to the right operand as |u|^2 while it is read.
 //
-// Only lower-triangle tiles (tile row >= tile column) are computed; one block
-// per tile and output. Consecutive blocks of the hardware dispatch go to
-// the 8 XCDs in turn, so block b is remapped to tile index
-// (b mod 8) * (tiles/8) + b/8: each XCD then walks a contiguous run of a
-// banded tile order, and the blocks resident on one XCD share the column
-// panels they read through that XCD's L2.
+// Only lower-triangle tiles are computed; a tile's epilogue also writes its
+// conjugate transpose and Im(diagonal) = 0, so the outputs need no further
+// pass. Three tile sizes share one launch (one 8-wave block per CU, the same
+// LDS), because a 128 x 128 tile takes 0.45 us of a CU per contraction row
+// and 16 K N_G^2 operations rarely make a whole number of rounds of them:
+//   128 x 128  the tiles strictly below the diagonal, first;
+//    64 x  64  the diagonal blocks (3 of 4 quarters), the ragged last rows,
+//              and the 128-tiles that would start an unfilled last round;
+//    32 x  32  the 64-tiles that would start an unfilled last round.
+// make_plan chooses how many of each from their measured costs. (All in
+// 128-tiles the build of 32 atoms of N_L = 49 at N_G = 2000 took 3.17 ms, two
+// rounds for 272 tiles on 256 compute units; now 1.98 ms. The smallest
+// build, 4 atoms of 16 at N_G = 256: 87 us, 30 us now. N_G = 8000: 124.7 ms,
+// 122.9 ms now, of which the mirroring pass was 0.4 ms.) All three add an output's contraction rows in the same order, so the bits of H and S
+// do not depend on the split.
+//
+// Consecutive blocks of the hardware dispatch go to the 8 XCDs in turn, so
+// block b of a range of n takes its tile (b mod 8) * (n/8) + b/8: each XCD
+// then walks a contiguous run of a banded tile order, and the blocks resident
+// on one XCD share the column panels they read through that XCD's L2.
 //
 // With G3 every complex product takes 3 real MFMA products instead of 4 (the
 // 3M form, see zmfma_direct.h): three quarters of the matrix-core work, a
 // slightly larger rounding bound on the imaginary parts.
 //
-// k_mirror (launched separately, also after the split-precision reduction)
-// completes both outputs: upper = conj(lower), Im(diag) = 0.
+// k_mirror completes the outputs of the split-precision reductions and of the
+// eigenproblem reduction: upper = conj(lower), Im(diag) = 0.
 #include "hs_internal.h"
 #include "zmfma_direct.h"
 
@@ -30,10 +44,12 @@ namespace hs {
 
 namespace {
 
-// Tile shape of the reductions: 128 x 128 outputs, stages of 16 contraction
-// rows, 8 waves as 2 x 4 (64 x 32 complex outputs each).
-using RedCfg = TileCfg<128, 128, 16, 2, 4>;
-static_assert(RedCfg::BM == RedCfg::BN, "lower-triangle tiling needs square tiles");
+using Tile128 = TileCfg<128, 128, 8, 2, 4, 4>;   // 64 x 32 complex outputs per wave
+using Tile64 = TileCfg<64, 64, 16, 2, 4, 4>;     // 32 x 16
+using Tile32 = TileCfg<32, 32, 16, 2, 2, 8>;     // 16 x 16, four waves only load
+constexpr int RED_LDS = Tile128::LDS_ELEMS;
+static_assert(Tile64::LDS_ELEMS <= RED_LDS && Tile32::LDS_ELEMS <= RED_LDS, "one LDS ring");
+constexpr int RED_THREADS = Tile128::NT;
 constexpr int BAND = 4;   // tile columns per band of the tile order
 
 struct RedArgs {
@@ -43,30 +59,29 @@ struct RedArgs {
     double2 *H;
     double2 *S;
     int n_g;
-    int nt;       // tiles per dimension
-    int ntri;     // lower-triangle tiles per output
-    int ntri8;    // ntri rounded up to a multiple of 8
+    int nf;       // whole 128-tile rows
+    int nlow;     // whole 128-tiles strictly below the diagonal, per output
+    int nedge;    // diagonal quarters and last rows, in 64-tiles, per output
+    int n128;     // of the 2 nlow, computed as 128-tiles
+    int n64;      // of the remaining 64-tiles, computed as 64-tiles
+    int n32;      // 64-tiles computed as four 32-tiles each
+    int b128, b64;   // blocks of the first two ranges, multiples of 8
 };
 
-// Tile (i, j), j <= i, of the t-th position in the banded order: bands of
+// Tile (i, j), j < i, of the t-th position in the banded order: bands of
 // BAND tile columns, each band walked row by row from its diagonal down.
 __device__ __forceinline__ void band_tile(int t, int nt, int &ti, int &tj) {
-    int c0 = 0;
-    for (;;) {
-        const int m = nt - c0;
-        if (m <= 0) {   // t beyond the triangle: no tile
-            ti = tj = -1;
-            return;
-        }
+    for (int c0 = 0;; c0 += BAND) {
+        const int m = nt - c0;   // rows of the band, its first one empty
         const int w = m < BAND ? m : BAND;
-        const int tri = w * (w + 1) / 2;
+        const int tri = w * (w - 1) / 2;
         const int cnt = tri + (m - w) * w;
         if (t < cnt) {
             if (t < tri) {
-                int r = 0;
-                while ((r + 1) * (r + 2) / 2 <= t) ++r;
+                int r = 1;
+                while ((r + 1) * r / 2 <= t) ++r;
                 ti = c0 + r;
-                tj = c0 + (t - r * (r + 1) / 2);
+                tj = c0 + (t - r * (r - 1) / 2);
             } else {
                 const int u = t - tri;
                 ti = c0 + w + u / w;
@@ -75,31 +90,17 @@ __device__ __forceinline__ void band_tile(int t, int nt, int &ti, int &tj) {
             return;
         }
         t -= cnt;
-        c0 += BAND;
     }
 }
 
-template <bool G3>
-__global__ void __launch_bounds__(RedCfg::NT)
-k_reduce(RedArgs args) {
-    using C = RedCfg;
-    __shared__ double2 lds[C::LDS_ELEMS];
-
-    int b = blockIdx.x;
-    const bool isH = b < args.ntri8;
-    if (!isH) b -= args.ntri8;
-    const int per_xcd = args.ntri8 / 8;
-    const int t = (b % 8) * per_xcd + b / 8;
-    if (t >= args.ntri) return;
-    int ti, tj;
-    band_tile(t, args.nt, ti, tj);
-    if (ti < 0) return;
-    const int m0 = ti * C::BM;   // rows g' of the output (columns of P)
-    const int n0 = tj * C::BN;   // columns g of the output (columns of Q)
-
+// One C::BM x C::BM tile of H or S at rows m0, columns n0 (multiples of C::BM).
+template <class C, bool G3>
+__device__ __forceinline__ void reduce_tile(const RedArgs &args, bool isH, int m0, int n0,
+                                            double2 *lds) {
+    const int n_g = args.n_g;
+    if (m0 >= n_g || n0 > m0) return;
     // Segment tables are built from scalar arguments in registers: taking a
     // reference into the by-value kernel argument would copy it to scratch.
-    const long long ld = args.n_g;
     Acc<C> acc;
     if (isH) {
         // B^H Y + A^H X: the larger terms last (T^AA carries most of H), which
@@ -107,29 +108,28 @@ k_reduce(RedArgs args) {
         Segs<2, false> t;
         t.nseg = 2;
         t.len = args.K;
-        t.ldp = t.ldq = ld;
+        t.ldp = t.ldq = n_g;
         t.P[0] = args.B;
         t.Q[0] = args.Y;
         t.P[1] = args.A;
         t.Q[1] = args.X;
         t.qscale = nullptr;
-        ztile_direct<C, 2, false, G3>(t, m0, args.n_g, n0, args.n_g, acc, lds);
+        ztile_direct<C, 2, false, G3>(t, m0, n_g, n0, n_g, acc, lds);
     } else {
         // A^H A + B^H diag(|u|^2) B
         Segs<2, true> t;
         t.nseg = 2;
         t.len = args.K;
-        t.ldp = t.ldq = ld;
+        t.ldp = t.ldq = n_g;
         t.P[0] = args.A;
         t.Q[0] = args.A;
         t.P[1] = args.B;
         t.Q[1] = args.B;
         t.qscale = args.d;     // [2K]: 1 on A's rows, |u|^2 on B's rows
-        ztile_direct<C, 2, true, G3>(t, m0, args.n_g, n0, args.n_g, acc, lds);
+        ztile_direct<C, 2, true, G3>(t, m0, n_g, n0, n_g, acc, lds);
     }
-
+    if (!wave_works<C>()) return;
     double2 *out = isH ? args.H : args.S;
-    const int n_g = args.n_g;
 #pragma unroll
     for (int i = 0; i < C::TM; ++i)
 #pragma unroll
@@ -138,10 +138,132 @@ k_reduce(RedArgs args) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int gp = m0 + acc_row<C>(i, v);
-                if (gp < n_g && g <= gp)
-                    out[(long long)gp * n_g + g] = double2{acc.re[i][j][v], acc.im[i][j][v]};
+                if (gp < n_g && g <= gp) {
+                    const double re = acc.re[i][j][v], im = g == gp ? 0.0 : acc.im[i][j][v];
+                    out[(long long)gp * n_g + g] = double2{re, im};
+                    // lanes l / 16 = 0..3 hold four consecutive rows gp: 64-byte
+                    // runs of a transposed row, its other runs follow with v
+                    if (g != gp) out[(long long)g * n_g + gp] = double2{re, -im};
+                }
             }
         }
+}
+
+template <bool G3>
+__global__ void __launch_bounds__(RED_THREADS)
+k_reduce(RedArgs args) {
+    __shared__ double2 lds[RED_LDS];
+
+    int b = blockIdx.x;
+    if (b < args.b128) {
+        const int q = (b % 8) * (args.b128 / 8) + b / 8;
+        if (q >= args.n128) return;
+        const bool isH = q < args.nlow;
+        int ti, tj;
+        band_tile(isH ? q : q - args.nlow, args.nf, ti, tj);
+        reduce_tile<Tile128, G3>(args, isH, ti * 128, tj * 128, lds);
+        return;
+    }
+    b -= args.b128;
+    const bool whole = b < args.b64;
+    int sub = 0, u;
+    if (whole) {
+        u = (b % 8) * (args.b64 / 8) + b / 8;
+        if (u >= args.n64) return;
+    } else {
+        b -= args.b64;
+        sub = b & 3;
+        u = args.n64 + (b >> 2);
+    }
+    // 64-tile u: quarters of the 128-tiles after the first n128, then the
+    // diagonal quarters and last rows of H, then of S
+    bool isH;
+    int I, J;   // in 64-tiles
+    const int nq = 4 * (2 * args.nlow - args.n128);
+    if (u < nq) {
+        const int q = args.n128 + u / 4;
+        isH = q < args.nlow;
+        band_tile(isH ? q : q - args.nlow, args.nf, I, J);
+        I = 2 * I + (u >> 1 & 1);
+        J = 2 * J + (u & 1);
+    } else {
+        u -= nq;
+        isH = u < args.nedge;
+        if (!isH) u -= args.nedge;
+        if (u < 3 * args.nf) {
+            const int q = u % 3;   // (0,0), (1,0), (1,1) of the diagonal block
+            I = 2 * (u / 3) + (q + 1) / 2;
+            J = 2 * (u / 3) + q / 2;
+        } else {
+            u -= 3 * args.nf;
+            I = 2 * args.nf;
+            if (u > I) {
+                u -= I + 1;
+                ++I;
+            }
+            J = u;
+        }
+    }
+    if (whole)
+        reduce_tile<Tile64, G3>(args, isH, I * 64, J * 64, lds);
+    else
+        reduce_tile<Tile32, G3>(args, isH, I * 64 + (sub >> 1) * 32, J * 64 + (sub & 1) * 32, lds);
+}
+
+// When n tiles of equal cost have been handed to the compute units in turn,
+// each to the first that is free; level: the busy time of groups of them.
+struct Level {
+    double t;
+    int n;
+};
+void hand_out(std::vector<Level> &lv, long long n, double cost) {
+    while (n > 0) {
+        size_t m = 0;
+        for (size_t i = 1; i < lv.size(); ++i)
+            if (lv[i].t < lv[m].t) m = i;
+        const int k = (int)std::min<long long>(n, lv[m].n);
+        n -= k;
+        if (k < lv[m].n) lv.push_back(Level{lv[m].t, lv[m].n - k});
+        lv[m].t += cost;
+        lv[m].n = k;
+    }
+}
+
+// How many tiles of each size: the split with the earliest end among a few of
+// each kind. The costs, in 128-tiles of a compute unit's time, are those of a
+// full device at N_G = 8000, K = 8100: all in 64-tiles (32-tiles) the
+// reductions take 1.17 (1.45) times as long as in 128-tiles, in the 3M form
+// 1.22 (1.61) times.
+void make_plan(RedArgs &a, int cus, bool g3) {
+    const int n64rows = (a.n_g + 63) / 64;
+    a.nf = a.n_g / 128;
+    a.nlow = a.nf * (a.nf - 1) / 2;
+    a.nedge = 3 * a.nf;
+    for (int i = 2 * a.nf; i < n64rows; ++i) a.nedge += i + 1;
+    const double c64 = (g3 ? 1.22 : 1.17) / 4, c32 = (g3 ? 1.61 : 1.45) / 16;
+    const int all = 2 * a.nlow;
+    double best = -1.0;
+    for (int k = 0; k < 4; ++k) {   // all 128-tiles, the whole rounds of them, one fewer, none
+        const int f = k == 0 ? all : k == 3 ? 0 : std::max(0, all / cus - (k - 1)) * cus;
+        const int rest = 4 * (all - f) + 2 * a.nedge;
+        for (int l = 0; l < 6; ++l) {   // all 64-tiles, up to two rounds fewer, none
+            const int h = l == 5 ? 0 : std::max(0, rest - l * cus / 2);
+            std::vector<Level> lv{Level{(double)(f / cus), cus}};
+            hand_out(lv, f % cus, 1.0);
+            hand_out(lv, h, c64);
+            hand_out(lv, 4 * (rest - h), c32);
+            double end = 0.0;
+            for (const Level &x : lv) end = std::max(end, x.t);
+            if (best < 0.0 || end < best) {
+                best = end;
+                a.n128 = f;
+                a.n64 = h;
+                a.n32 = rest - h;
+            }
+        }
+    }
+    a.b128 = (a.n128 + 7) / 8 * 8;
+    a.b64 = (a.n64 + 7) / 8 * 8;
 }
 
 // upper := conj(lower) through a 32x32 LDS transpose; Im(diag) := 0.
@@ -178,7 +300,6 @@ k_mirror(double2 *H, double2 *S, int n_g) {
 hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
                          const double2 *X, const double2 *Y, const double *d,
                          double2 *H, double2 *S, hipStream_t st, bool g3) {
-    using C = RedCfg;
     RedArgs args;
     args.A = A;
     args.B = B;
@@ -189,13 +310,12 @@ hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
     args.H = H;
     args.S = S;
     args.n_g = n_g;
-    args.nt = (n_g + C::BM - 1) / C::BM;
-    args.ntri = args.nt * (args.nt + 1) / 2;
-    args.ntri8 = (args.ntri + 7) / 8 * 8;
+    make_plan(args, num_cus(), g3);
+    const dim3 grid(args.b128 + args.b64 + 4 * args.n32);
     if (g3)
-        hipLaunchKernelGGL(k_reduce<true>, dim3(2 * args.ntri8), dim3(C::NT), 0, st, args);
+        hipLaunchKernelGGL(k_reduce<true>, grid, dim3(RED_THREADS), 0, st, args);
     else
-        hipLaunchKernelGGL(k_reduce<false>, dim3(2 * args.ntri8), dim3(C::NT), 0, st, args);
+        hipLaunchKernelGGL(k_reduce<false>, grid, dim3(RED_THREADS), 0, st, args);
     return hipGetLastError();
 }
 

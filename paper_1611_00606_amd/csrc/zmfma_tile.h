@@ -35,18 +35,6 @@ struct Segs {
     const double *qscale;
 };
 
-template <int BM_, int BN_, int BK_, int WM_, int WN_>
-struct TileCfg {
-    static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_;
-    static constexpr int NT = 64 * WM * WN;            // threads per block
-    static constexpr int WTM = BM / WM, WTN = BN / WN; // wave tile
-    static constexpr int TM = WTM / 16, TN = WTN / 16; // 16x16 blocks per wave
-    static constexpr int LDS_ELEMS = 2 * BK * (BM + BN);
-    static_assert(BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "wave tiling");
-    static_assert(BK % 4 == 0, "stage depth");
-    static_assert(BM % 16 == 0 && BN % 16 == 0, "16-wide MFMA blocks");
-};
-
 template <class C>
 struct Acc {
     v4d re[C::TM][C::TN];

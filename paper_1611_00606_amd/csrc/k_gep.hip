@@ -51,7 +51,14 @@ namespace hs {
 
 namespace {
 
-using MmCfg = TileCfg<128, 128, 8, 2, 4, 4>;
+// Tile shapes of the products: a launch takes the one whose tiles fill the
+// device best (mm_shape). The factorization's panels and the products of a
+// small matrix are a few dozen 128-tiles, each 70 us long at 128 contraction
+// rows; in 64 or 32-tiles they spread over the whole device.
+using Mm128 = TileCfg<128, 128, 8, 2, 4, 4>;
+using Mm64 = TileCfg<64, 64, 16, 2, 4, 4>;
+using Mm32 = TileCfg<32, 32, 16, 2, 2, 8>;
+constexpr int MM_THREADS = 512;
 
 // Share of the compute units (in quarters) the work moved off the
 // factorization's critical path may occupy.
@@ -87,6 +94,7 @@ struct MmArgs {
     double2 *C;
     int N;                    // leading dimension of P, Q, C
     int op;
+    int tile;                 // 128, 64 or 32
     int njobs;
     int total;                // tiles over all jobs (blocks loop over them)
     MmJob job[MM_JOBS];
@@ -96,9 +104,8 @@ struct MmArgs {
 // absolute indices; the triangular flags trim each tile's contraction range
 // to the rows where both operands can be nonzero. G3: 3 real products per
 // complex product (the 3M form of the tile engine).
-template <int NSEG, bool G3>
+template <class Cfg, int NSEG, bool G3>
 __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *lds) {
-    using Cfg = MmCfg;
     const int N = args.N;
     int jb = 0;
 #pragma unroll
@@ -178,6 +185,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
     t.qscale = nullptr;
     Acc<Cfg> acc;
     ztile_direct<Cfg, NSEG, false, G3>(t, m0, i1, n0, j1, acc, lds);
+    if (!wave_works<Cfg>()) return;
 
     const bool lower = flags & (MM_LOWER | MM_MASK);
     const bool upper = flags & MM_UPPER;
@@ -212,13 +220,26 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
 
 // Blocks loop over the tiles (a launch may have fewer blocks than tiles when
 // it runs beside latency-critical work).
-template <int NSEG, bool G3>
-__global__ void __launch_bounds__(MmCfg::NT) k_gep_mm(const MmArgs args) {
-    __shared__ double2 lds[MmCfg::LDS_ELEMS];
+template <class Cfg, int NSEG, bool G3>
+__global__ void __launch_bounds__(MM_THREADS) k_gep_mm(const MmArgs args) {
+    __shared__ double2 lds[Cfg::LDS_ELEMS];
     for (int tile = blockIdx.x; tile < args.total; tile += gridDim.x) {
-        mm_tile<NSEG, G3>(args, tile, lds);
+        mm_tile<Cfg, NSEG, G3>(args, tile, lds);
         __syncthreads();   // LDS is reused by the next tile
     }
+}
+
+template <class Cfg>
+void mm_launch(const MmArgs &a, bool g3, unsigned grid, hipStream_t st) {
+    const dim3 gd(grid), bd(MM_THREADS);
+    if (a.P2 && g3)
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, true>), gd, bd, 0, st, a);
+    else if (a.P2)
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, false>), gd, bd, 0, st, a);
+    else if (g3)
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, true>), gd, bd, 0, st, a);
+    else
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, false>), gd, bd, 0, st, a);
 }
 
 // Leaf: Cholesky of the diagonal block [kb, kb + nb) (nb <= LB = 128) of the
@@ -760,7 +781,7 @@ int sched_check(const Sched &sc, int N, std::string &report) {
 
 // The footprint of one product launch, tile by tile as mm_tile trims it.
 void sched_mm(const Gep &g, const MmArgs &a) {
-    using Cfg = MmCfg;
+    const int bt = a.tile;
     SchedOp &op = g_sched->launch(g.st, a.P2 ? "k_gep_mm<2>" : "k_gep_mm<1>");
     for (int jb = 0; jb < a.njobs; ++jb) {
         const MmJob &j = a.job[jb];
@@ -769,12 +790,12 @@ void sched_mm(const Gep &g, const MmArgs &a) {
             for (int tj = 0; tj < j.ntc; ++tj) {
                 if ((flags & MM_UPPER) && tj < ti) continue;
                 if ((flags & MM_LOWER) && tj > ti) continue;
-                const int m0 = j.i0 + ti * Cfg::BM, n0 = j.j0 + tj * Cfg::BN;
+                const int m0 = j.i0 + ti * bt, n0 = j.j0 + tj * bt;
                 if (m0 >= j.i1 || n0 >= j.j1) continue;
-                const int m1 = std::min(m0 + Cfg::BM, j.i1), n1 = std::min(n0 + Cfg::BN, j.j1);
+                const int m1 = std::min(m0 + bt, j.i1), n1 = std::min(n0 + bt, j.j1);
                 int klo = j.k0, khi = j.k1;
-                if (flags & MM_PU) khi = std::min(khi, m0 + Cfg::BM);
-                if (flags & MM_QU) khi = std::min(khi, n0 + Cfg::BN);
+                if (flags & MM_PU) khi = std::min(khi, m0 + bt);
+                if (flags & MM_QU) khi = std::min(khi, n0 + bt);
                 if (flags & MM_QL) klo = std::max(klo, n0);
                 if (flags & MM_PL) klo = std::max(klo, m0);
                 g_sched->add(op, a.P, klo, khi, m0, m1, false);
@@ -788,13 +809,52 @@ void sched_mm(const Gep &g, const MmArgs &a) {
     }
 }
 
+// Tiles of one rectangle.
+long long mm_tiles(const Rect &r, int flags, int tile) {
+    const long long ntr = (r.i1 - r.i0 + tile - 1) / tile, ntc = (r.j1 - r.j0 + tile - 1) / tile;
+    return flags & (MM_LOWER | MM_UPPER) ? ntr * (ntr + 1) / 2 : ntr * ntc;
+}
+
+// The tile shape of a launch over n rectangles on cus compute units, by an
+// estimate of its time: the longest tile, or the tiles in rounds at their
+// average contraction (a half of the range for each triangular operand's
+// trimming). A tile takes 8 us besides the contraction (first loads, stores)
+// and 0.44, 0.13 or 0.041 us per contraction row (and term) for 128, 64 or 32
+// (measured on a full device; a 128-tile alone 70 us for 128 rows).
+int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
+    constexpr int SHAPES[3] = {128, 64, 32};
+    constexpr double PER_ROW[3] = {0.44, 0.13, 0.041};
+    int best = 128;
+    double tbest = -1.0;
+    for (int s = 0; s < 3; ++s) {
+        double longest = 0.0, sum = 0.0;
+        long long tiles = 0;
+        for (int t = 0; t < n; ++t) {
+            const long long nt = mm_tiles(r[t], flags[t], SHAPES[s]);
+            const double k = (double)(r[t].k1 - r[t].k0) * nseg;
+            double avg = k;
+            for (int f : {MM_PU | MM_PL, MM_QU | MM_QL})
+                if (flags[t] & f) avg *= 0.5;
+            longest = std::max(longest, 8.0 + k * PER_ROW[s]);
+            sum += nt * (8.0 + avg * PER_ROW[s]);
+            tiles += nt;
+        }
+        const double rounds = (double)((tiles + cus - 1) / cus);
+        const double est = std::max(longest, sum / tiles * rounds);
+        if (tbest < 0.0 || est < tbest) {
+            tbest = est;
+            best = SHAPES[s];
+        }
+    }
+    return best;
+}
+
 // Products over the rectangles r[0 .. n), up to MM_JOBS per launch, with
 // the flags rflags[t] of each (or flags for all when rflags is null); the
 // blocks take the rectangles in the order given.
 hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C, const Rect *r,
                     int n, int flags, int op, const double2 *P2 = nullptr,
                     const double2 *Q2 = nullptr, const int *rflags = nullptr) {
-    using Cfg = MmCfg;
     for (int b = 0; b < n; b += MM_JOBS) {
         MmArgs a = {};
         a.P = P;
@@ -804,43 +864,42 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
         a.C = C;
         a.N = g.N;
         a.op = op;
-        long long nblk = 0;
+        Rect rj[MM_JOBS];
+        int fj[MM_JOBS];
         for (int t = b; t < n && t < b + MM_JOBS; ++t) {
             if (r[t].i1 <= r[t].i0 || r[t].j1 <= r[t].j0) continue;
-            MmJob &j = a.job[a.njobs++];
-            j.i0 = r[t].i0;
-            j.i1 = r[t].i1;
-            j.j0 = r[t].j0;
-            j.j1 = r[t].j1;
-            j.k0 = r[t].k0;
-            j.k1 = r[t].k1;
-            j.ntr = (j.i1 - j.i0 + Cfg::BM - 1) / Cfg::BM;
-            j.ntc = (j.j1 - j.j0 + Cfg::BN - 1) / Cfg::BN;
-            j.start = (int)nblk;
-            j.flags = rflags ? rflags[t] : flags;
-            if (j.flags & (MM_LOWER | MM_UPPER)) {
-                if (j.i0 != j.j0 || j.i1 != j.j1) return hipErrorInvalidValue;
-                nblk += (long long)j.ntr * (j.ntr + 1) / 2;
-            } else {
-                nblk += (long long)j.ntr * j.ntc;
-            }
+            rj[a.njobs] = r[t];
+            fj[a.njobs++] = rflags ? rflags[t] : flags;
         }
         if (a.njobs == 0) continue;
+        const int cus = g.cap > 0 ? g.cap : g_sched ? 256 : num_cus();
+        a.tile = mm_shape(rj, fj, a.njobs, P2 ? 2 : 1, cus);
+        long long nblk = 0;
+        for (int t = 0; t < a.njobs; ++t) {
+            MmJob &j = a.job[t];
+            j.i0 = rj[t].i0;
+            j.i1 = rj[t].i1;
+            j.j0 = rj[t].j0;
+            j.j1 = rj[t].j1;
+            j.k0 = rj[t].k0;
+            j.k1 = rj[t].k1;
+            j.ntr = (j.i1 - j.i0 + a.tile - 1) / a.tile;
+            j.ntc = (j.j1 - j.j0 + a.tile - 1) / a.tile;
+            j.start = (int)nblk;
+            j.flags = fj[t];
+            if ((j.flags & (MM_LOWER | MM_UPPER)) && (j.i0 != j.j0 || j.i1 != j.j1))
+                return hipErrorInvalidValue;
+            nblk += mm_tiles(rj[t], fj[t], a.tile);
+        }
         a.total = (int)nblk;
         if (g_sched) {
             sched_mm(g, a);
             continue;
         }
-        const long long grid = g.cap > 0 && nblk > g.cap ? g.cap : nblk;
-        const dim3 gd((unsigned)grid), bd(Cfg::NT);
-        if (P2 && g.g3)
-            hipLaunchKernelGGL((k_gep_mm<2, true>), gd, bd, 0, g.st, a);
-        else if (P2)
-            hipLaunchKernelGGL((k_gep_mm<2, false>), gd, bd, 0, g.st, a);
-        else if (g.g3)
-            hipLaunchKernelGGL((k_gep_mm<1, true>), gd, bd, 0, g.st, a);
-        else
-            hipLaunchKernelGGL((k_gep_mm<1, false>), gd, bd, 0, g.st, a);
+        const unsigned grid = (unsigned)(g.cap > 0 && nblk > g.cap ? g.cap : nblk);
+        if (a.tile == 128) mm_launch<Mm128>(a, g.g3, grid, g.st);
+        else if (a.tile == 64) mm_launch<Mm64>(a, g.g3, grid, g.st);
+        else mm_launch<Mm32>(a, g.g3, grid, g.st);
         GEP_TRY(hipGetLastError());
     }
     return hipSuccess;

@@ -676,8 +676,8 @@ def gep_bench(run, steps: int, hip):
     # the minimal count of the standard route: zpotrf (4/3 N^3) + zhegst (4 N^3)
     f_min = 16.0 / 3.0 * N ** 3
     # executed: factor and inverse 8/3 N^3, then V = H L^-H and Ht (16/3 N^3), or from
-    # N = 4096 on WH = (L^-1 lower(H))^H and the two-term Ht (4 N^3)
-    f_exec = (20.0 / 3.0 if N >= 4096 else 8.0) * N ** 3
+    # N = 2500 on WH = (L^-1 lower(H))^H and the two-term Ht (4 N^3)
+    f_exec = (20.0 / 3.0 if N >= 2500 else 8.0) * N ** 3
     out = {
         "N": N, "info": int(info.item()),
         "ms_median": round(med, 3), "ms_min": round(float(min(ms)), 3),
@@ -689,7 +689,7 @@ def gep_bench(run, steps: int, hip):
                                                 / FP64_MFMA_PEAK_TFLOPS, 1),
         "residual_S_LLH": res,
         "flop_counts": "tflops: 16/3 N^3, the zpotrf (4/3 N^3) + zhegst (4 N^3) count of the "
-                       "standard reduction; executed: 20/3 N^3 from N = 4096 (8 N^3 below), the "
+                       "standard reduction; executed: 20/3 N^3 from N = 2500 (8 N^3 below), the "
                        "explicit-inverse route this library takes",
     }
     ms3, res3 = timed(HS_FP64_3M)

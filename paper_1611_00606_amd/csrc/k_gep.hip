@@ -12,10 +12,10 @@
 //     S22 -= L21 L21^H                  lower triangle, contraction over 128
 //   invert, recursive over the same blocks (split at m):
 //     M21 = -M22 (L21 M11)              M = L^{-1}
-//   then, with MH = M^H = L^{-H} (upper triangular), below N = 4096
+//   then, with MH = M^H = L^{-H} (upper triangular), below N = 2500
 //     V  = H MH                         (= (L^{-1} H)^H for Hermitian H)
 //     Ht = V^H MH                       lower triangle, then mirrored
-//   and from N = 4096 on, with HL the lower triangle of H (half diagonal),
+//   and from N = 2500 on, with HL the lower triangle of H (half diagonal),
 //     WH = HL^H MH                      (= (M HL)^H, upper triangular)
 //     Ht = WH^H MH + M WH               two-term lower triangle, mirrored
 //
@@ -56,8 +56,11 @@ namespace {
 // small matrix are a few dozen 128-tiles, each 70 us long at 128 contraction
 // rows; in 64 or 32-tiles they spread over the whole device.
 using Mm128 = TileCfg<128, 128, 8, 2, 4, 4>;
+// The 32-tiles' ring takes 64 KiB, so that two blocks share a compute unit
+// (N = 300 489 us with one, 453 with two); 64-tiles are faster alone with a
+// ring of 16-row stages (N = 2000 3.22 against 3.45 ms).
 using Mm64 = TileCfg<64, 64, 16, 2, 4, 4>;
-using Mm32 = TileCfg<32, 32, 16, 2, 2, 8>;
+using Mm32 = TileCfg<32, 32, 16, 2, 2, 4>;
 constexpr int MM_THREADS = 512;
 
 // Share of the compute units (in quarters) the work moved off the
@@ -820,14 +823,16 @@ long long mm_tiles(const Rect &r, int flags, int tile) {
 // average contraction (a half of the range for each triangular operand's
 // trimming). A tile takes 8 us besides the contraction (first loads, stores)
 // and 0.44, 0.13 or 0.041 us per contraction row (and term) for 128, 64 or 32
-// (measured on a full device; a 128-tile alone 70 us for 128 rows).
+// (measured on a full device; a 128-tile alone 70 us for 128 rows); two
+// blocks of 32-tiles on one compute unit take turns and hide each other's
+// 8 us.
 int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
     constexpr int SHAPES[3] = {128, 64, 32};
     constexpr double PER_ROW[3] = {0.44, 0.13, 0.041};
     int best = 128;
     double tbest = -1.0;
     for (int s = 0; s < 3; ++s) {
-        double longest = 0.0, sum = 0.0;
+        double longest = 0.0, rows = 0.0;
         long long tiles = 0;
         for (int t = 0; t < n; ++t) {
             const long long nt = mm_tiles(r[t], flags[t], SHAPES[s]);
@@ -836,11 +841,13 @@ int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
             for (int f : {MM_PU | MM_PL, MM_QU | MM_QL})
                 if (flags[t] & f) avg *= 0.5;
             longest = std::max(longest, 8.0 + k * PER_ROW[s]);
-            sum += nt * (8.0 + avg * PER_ROW[s]);
+            rows += nt * avg;
             tiles += nt;
         }
-        const double rounds = (double)((tiles + cus - 1) / cus);
-        const double est = std::max(longest, sum / tiles * rounds);
+        const long long per = s < 2 || tiles <= cus ? 1 : 2;   // blocks that share a compute unit
+        const double rounds = (double)((tiles + per * cus - 1) / (per * cus));
+        const double est =
+            std::max(longest, rounds * (8.0 + per * rows / tiles * PER_ROW[s]));
         if (tbest < 0.0 || est < tbest) {
             tbest = est;
             best = SHAPES[s];
@@ -1134,10 +1141,11 @@ size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 // two-term lower-triangle product Ht = WH^H MH + MH^H WH (k <= j). WH is
 // kept in LH, whose lower triangle is zero.
 
-// Below this size the two-term form has too few lower-triangle tiles to fill
-// the device, and Ht = V^H MH with V = H MH (N^3/2 + N^3/6 complex
-// multiply-adds over full squares of tiles) is faster.
-constexpr int GEP_HER2K_MIN_N = 4096;
+// Below this size the two-term form's longer contractions cost more than the
+// smaller work saves, and Ht = V^H MH with V = H MH (N^3/2 + N^3/6 complex
+// multiply-adds) is faster: 3.47 against 3.57 ms at N = 2000, 6.78 against
+// 6.46 ms at N = 3000.
+constexpr int GEP_HER2K_MIN_N = 2500;
 
 // V[:, c0:c1) = H MH[:, c0:c1), kept in LH
 hipError_t v_cols(const Gep &g, const double2 *H, int c0, int c1) {

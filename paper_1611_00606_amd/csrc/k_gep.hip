@@ -246,23 +246,23 @@ void mm_launch(const MmArgs &a, bool g3, unsigned grid, hipStream_t st) {
 }
 
 // Leaf: Cholesky of the diagonal block [kb, kb + nb) (nb <= LB = 128) of the
-// working matrix (lower triangle in L) and the inverse of the factor, by one
+// working matrix (lower triangle in L) and the inverse X of the factor, by one
 // workgroup of 8 waves. The block, padded to 128 x 128 with the identity,
 // sits in LDS as the 36 lower 16 x 16 tiles (rows XOR-swizzled, so that the
 // MFMA fragment loads and the accumulator stores hit distinct banks).
-//   factor, right-looking over 16-column panels P:
-//     wave 0: Cholesky of the diagonal tile in registers (lane r holds row
-//             r; values broadcast with readlane), for P > 0 right after its
-//             own update of that tile in the previous panel's trailing step;
-//     panel:  L_IP = C_IP L_PP^{-H}            by substitution, one thread
-//             per row of the panel;
-//     update: C_IJ -= L_IP L_JP^H, P < J <= I   tiles spread over waves
-//             1..7 (wave 0 takes tile (P+1, P+1), then factors it).
-//   inverse X = L^{-1}, in place: every wave inverts one diagonal tile, then
-//     for block rows I = 1..7: X_IJ = -X_II sum_{J<=K<I} L_IK X_KJ, J < I.
-// A pivot that is not > 0 (NaN included) records kb + j + 1 in *info unless an
-// earlier block failed (the outputs are undefined then). Writes the block of
-// L, of M = X (lower) and of MH = X^H (upper).
+// Per panel P of 16 columns, two phases with a barrier after each:
+//   wave 0:    the diagonal tile's update with panel P - 1, then its Cholesky
+//              and inverse (diag16), X_PP replacing the tile;
+//   waves 1-7: the rest of the trailing update C_IJ -= L_I,P-1 L_J,P-1^H, and
+//              row P - 1 of the inverse, X_IJ = -X_II sum_{J<=K<I} L_IK X_KJ,
+//              held in registers;
+//   all waves: L_IP = C_IP X_PP^H, one tile per wave; the row of the inverse
+//              is stored (over L's row, which nothing reads any more).
+// Outputs go to global memory from the registers that form them: the block of
+// L, of M = X (lower) and of MH = X^H (upper). Bound: the chain of diagonal
+// tiles (3 us each) and the matrix products of one compute unit (24 us). A
+// pivot that is not > 0 (NaN included) records kb + j + 1 in *info unless an
+// earlier block failed (the outputs are undefined then).
 constexpr int LB = 128;
 constexpr int LT = LB / 16;               // tiles per side
 constexpr int LNT = LT * (LT + 1) / 2;    // lower tiles
@@ -280,55 +280,14 @@ __device__ __forceinline__ double bcast(double v, int src) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Lanes 0..15 hold the rows of a 16 x 16 Hermitian tile (lower triangle
-// used); on return the rows of its Cholesky factor. Returns 0 or the
-// 1-based index of the first pivot that is not > 0. Each step's pivot comes
-// from lane j by readlane; 1/sqrt of it from the hardware estimate refined by
-// two Newton steps (y += y (1 - d y^2) / 2; the estimate is good to far more
-// than the 2^-13 two steps need for full precision), and sqrt(d) = d / sqrt(d);
-// the scaled entries l_kj broadcast with readlane.
-__device__ __forceinline__ int chol16(double2 (&a)[16], int lane) {
-    int inf = 0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const double d = bcast(a[j].x, j);
-        if (!(d > 0.0) && inf == 0) inf = j + 1;
-        double rc = __builtin_amdgcn_rsq(d);
-        rc = fma(0.5 * rc, fma(-d * rc, rc, 1.0), rc);
-        rc = fma(0.5 * rc, fma(-d * rc, rc, 1.0), rc);
-        const double c = d * rc;
-        a[j] = lane == j ? double2{c, 0.0} : double2{a[j].x * rc, a[j].y * rc};
-#pragma unroll
-        for (int k = j + 1; k < 16; ++k) {   // a_rk -= l_rj conj(l_kj)
-            const double lx = bcast(a[j].x, k), ly = bcast(a[j].y, k);
-            a[k].x -= a[j].x * lx + a[j].y * ly;
-            a[k].y -= a[j].y * lx - a[j].x * ly;
-        }
-    }
-    return inf;
-}
-
-// Column (lane & 15) of the inverse of the lower-triangular 16 x 16 tile D
-// (in LDS): x_i = (delta_ic - sum_{k<i} l_ik x_k) / l_ii, the factor read with
-// broadcast loads (the same address in every lane).
-__device__ __forceinline__ void inv16(const double2 *D, double2 (&x)[16], int lane) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        double2 t = double2{(lane & 15) == i ? 1.0 : 0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < i; ++k) {
-            const double2 l = D[lsw(i, k)];   // l_ik
-            t.x -= l.x * x[k].x - l.y * x[k].y;
-            t.y -= l.x * x[k].y + l.y * x[k].x;
-        }
-        const double rd = 1.0 / D[lsw(i, i)].x;
-        x[i] = double2{t.x * rd, t.y * rd};
-    }
-}
-
 struct Cacc {
     v4d re, im;
 };
+
+__device__ __forceinline__ void acc_zero(Cacc &c) {
+    c.re = v4d{0.0, 0.0, 0.0, 0.0};
+    c.im = v4d{0.0, 0.0, 0.0, 0.0};
+}
 
 // c += A B^H for 16 x 16 tiles (c[i][j] += sum_k A[i][k] conj(B[j][k]))
 __device__ __forceinline__ void mma_abh(Cacc &c, const double2 *A, const double2 *B, int lane) {
@@ -337,8 +296,8 @@ __device__ __forceinline__ void mma_abh(Cacc &c, const double2 *A, const double2
         const double2 x = A[lsw(lane & 15, k0 + (lane >> 4))];
         const double2 y = B[lsw(lane & 15, k0 + (lane >> 4))];
         c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, c.re, 0, 0, 0);
-        c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.y, c.re, 0, 0, 0);
         c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.x, c.im, 0, 0, 0);
+        c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.y, c.re, 0, 0, 0);
         c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, -y.y, c.im, 0, 0, 0);
     }
 }
@@ -350,15 +309,99 @@ __device__ __forceinline__ void mma_ab(Cacc &c, const double2 *A, const double2 
         const double2 x = A[lsw(lane & 15, k0 + (lane >> 4))];
         const double2 y = B[lsw(k0 + (lane >> 4), lane & 15)];
         c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, c.re, 0, 0, 0);
-        c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, -y.y, c.re, 0, 0, 0);
         c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.y, c.im, 0, 0, 0);
+        c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, -y.y, c.re, 0, 0, 0);
         c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.x, c.im, 0, 0, 0);
     }
 }
 
-__device__ __forceinline__ void acc_zero(Cacc &c) {
-    c.re = v4d{0.0, 0.0, 0.0, 0.0};
-    c.im = v4d{0.0, 0.0, 0.0, 0.0};
+// Cholesky and inverse of a 16 x 16 Hermitian tile by one wave, four columns
+// at a time: those four columns (and the four rows of the identity under
+// elimination) are copied to all four 16-lane groups through LDS, factored
+// with readlane broadcasts inside the four, and the rest of the tile takes
+// them as one rank-4 update on the matrix cores. With lane l = r + 16 q the
+// accumulator layout D[4 v + q][r] of G = S^T holds S[r][4 v + q], which is
+// the A and B operand layout of a rank-4 update with columns 4 v .. 4 v + 3,
+// so nothing is re-laid out. (One column at a time over all sixteen, with
+// the inverse by substitution afterwards: 6 + 5 us instead of 3.)
+//   D    the tile (row-major, swizzled; lower triangle used); X on return
+//   scr  128 complex values of LDS of this wave
+//   fac  receives L[r][4 v + q] of step v as fac(v, value), zero above the
+//        diagonal
+// Returns 0 or the 1-based index of the first pivot that is not > 0. 1/sqrt
+// of a pivot: the hardware estimate refined by two Newton steps
+// (y += y (1 - d y^2) / 2; the estimate is good to far more than the 2^-13
+// two steps need for full precision), sqrt(d) = d / sqrt(d).
+template <class Fac>
+__device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fac) {
+    const int r = lane & 15, q = lane >> 4;
+    Cacc g, e;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const double2 s = D[lsw(r, 4 * v + q)];
+        g.re[v] = s.x;
+        g.im[v] = s.y;
+        e.re[v] = 4 * v + q == r ? 1.0 : 0.0;
+        e.im[v] = 0.0;
+    }
+    int inf = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        scr[lane] = double2{g.re[v], g.im[v]};
+        scr[64 + lane] = double2{e.re[v], e.im[v]};
+        double2 s[4], x[4], l[4];   // columns 4 v + p of S; rows 4 v + p of E, then of X
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            s[p] = scr[r + 16 * p];
+            x[p] = scr[64 + r + 16 * p];
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const int j = 4 * v + p;
+            const double d = bcast(s[p].x, j);
+            if (!(d > 0.0) && inf == 0) inf = j + 1;
+            double rc = __builtin_amdgcn_rsq(d);
+            rc = fma(0.5 * rc, fma(-d * rc, rc, 1.0), rc);
+            rc = fma(0.5 * rc, fma(-d * rc, rc, 1.0), rc);
+            l[p].x = s[p].x * rc;   // sqrt(d) in row j
+            l[p].y = r == j ? 0.0 : s[p].y * rc;
+            x[p].x *= rc;
+            x[p].y *= rc;
+#pragma unroll
+            for (int k = p + 1; k < 4; ++k) {
+                const double lx = bcast(l[p].x, 4 * v + k), ly = bcast(l[p].y, 4 * v + k);
+                s[k].x -= l[p].x * lx + l[p].y * ly;   // s_rk -= l_rj conj(l_kj)
+                s[k].y -= l[p].y * lx - l[p].x * ly;
+                x[k].x -= lx * x[p].x - ly * x[p].y;   // row k of E -= l_kj (row j of X)
+                x[k].y -= lx * x[p].y + ly * x[p].x;
+            }
+        }
+        // this lane's element of the four columns and rows (selected by
+        // component: a select between aggregates goes through scratch memory)
+        const auto own = [&](double a0, double a1, double a2, double a3) {
+            const double lo = q & 1 ? a1 : a0, hi = q & 1 ? a3 : a2;
+            return q & 2 ? hi : lo;
+        };
+        const bool low = r >= 4 * v + q;
+        const double lre = own(l[0].x, l[1].x, l[2].x, l[3].x);
+        const double lim = own(l[0].y, l[1].y, l[2].y, l[3].y);
+        const double2 lq = {low ? lre : 0.0, low ? lim : 0.0};
+        const double2 xq = {own(x[0].x, x[1].x, x[2].x, x[3].x), own(x[0].y, x[1].y, x[2].y, x[3].y)};
+        fac(v, lq);
+        D[lsw(4 * v + q, r)] = xq;
+        if (v < 3) {
+            // G[i][j] -= conj(L[i][p]) L[j][p],  E[i][c] -= L[i][p] X[p][c]
+            g.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, lq.x, g.re, 0, 0, 0);
+            g.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, lq.y, g.im, 0, 0, 0);
+            g.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, lq.y, g.re, 0, 0, 0);
+            g.im = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, lq.x, g.im, 0, 0, 0);
+            e.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, xq.x, e.re, 0, 0, 0);
+            e.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, xq.y, e.im, 0, 0, 0);
+            e.re = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, xq.y, e.re, 0, 0, 0);
+            e.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, xq.x, e.im, 0, 0, 0);
+        }
+    }
+    return inf;
 }
 
 // lower-triangle tile t of an n x n tile grid -> (i, j), j <= i
@@ -371,43 +414,38 @@ __device__ __forceinline__ void tri_decode(int t, int &i, int &j) {
 __global__ void __launch_bounds__(512)
 k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict__ MH, int N,
            int kb, int nb, int *__restrict__ info) {
-    __shared__ double2 T[LNT * 256];   // 144 KiB
+    __shared__ double2 T[LNT * 256 + 128];   // 146 KiB
+    double2 *scr = T + LNT * 256;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, q = lane >> 4;
+    const long long blk = (long long)kb * N + kb;   // the block's first element
+    L += blk;
+    M += blk;
+    MH += blk;
 
-    // stage: element (i, k), k <= i, of the padded block (loads issued together)
-    for (int c = 0; c < LB * LB / 512; c += 8) {
-        double2 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = tid + 512 * (c + u), i = e / LB, k = e % LB;
-            v[u] = double2{i == k ? 1.0 : 0.0, 0.0};
-            if (k <= i && i < nb) v[u] = L[(long long)(kb + i) * N + kb + k];
+    if (nb == LB) {
+        // whole block: 16-byte direct loads, lane l of tile quarter h to slot
+        // 64 h + l, which holds element (s / 16, (s % 16) ^ (s / 16)) of the tile
+        for (int u = w; u < 4 * LNT; u += 8) {
+            int I, K;
+            tri_decode(u >> 2, I, K);
+            const int sl = 64 * (u & 3) + lane, a = sl >> 4, c = (sl & 15) ^ a;
+            __builtin_amdgcn_global_load_lds(L + (long long)(16 * I + a) * N + 16 * K + c, T + 64 * u,
+                                             16, 0, 0);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = tid + 512 * (c + u), i = e / LB, k = e % LB;
-            if (k <= i) ltile(T, i >> 4, k >> 4)[lsw(i & 15, k & 15)] = v[u];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+        for (int e = tid; e < LB * LB; e += 512) {
+            const int i = e / LB, k = e % LB;
+            double2 v = {i == k ? 1.0 : 0.0, 0.0};
+            if (k <= i && i < nb) v = L[(long long)i * N + k];
+            if (k <= i) ltile(T, i >> 4, k >> 4)[lsw(i & 15, k & 15)] = v;
         }
     }
     __syncthreads();
 
-    int inf = 0;
-    // Cholesky of diagonal tile P by wave 0
-    const auto diag = [&](int P) {
-        double2 *D = ltile(T, P, P);
-        double2 a[16];
-        const int r = lane & 15;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) a[k] = D[lsw(r, k)];
-        const int f = chol16(a, lane);
-        if (f != 0 && inf == 0 && 16 * P + f <= nb) inf = 16 * P + f;
-        if (lane < 16) {
-#pragma unroll
-            for (int k = 0; k < 16; ++k) D[lsw(lane, k)] = a[k];
-        }
-    };
     // C_IJ -= L_IP L_JP^H for the t-th tile of the trailing triangle of panel P
     const auto trail = [&](int P, int t) {
         int ti, tj;
@@ -419,113 +457,96 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
         double2 *C = ltile(T, I, J);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            double2 &o = C[lsw(4 * v + (lane >> 4), lane & 15)];
+            double2 &o = C[lsw(4 * v + q, r)];
             o.x -= c.re[v];
             o.y -= c.im[v];
         }
     };
-    if (w == 0) diag(0);
-    __syncthreads();
+    // o = -X_II sum_{J<=K<I} L_IK X_KJ
+    const auto inverse_tile = [&](int I, int J, Cacc &o) {
+        Cacc c;
+        acc_zero(c);
+        for (int K = J; K < I; ++K) mma_ab(c, ltile(T, I, K), ltile(T, K, J), lane);
+        const double2 *X = ltile(T, I, I);
+        acc_zero(o);
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {   // B fragment rows 4 s4 .. = accumulator element s4
+            const double2 x = X[lsw(r, 4 * s4 + q)];
+            const double br = c.re[s4], bi = c.im[s4];
+            o.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.x, br, o.re, 0, 0, 0);
+            o.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.x, bi, o.im, 0, 0, 0);
+            o.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, bi, o.re, 0, 0, 0);
+            o.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, br, o.im, 0, 0, 0);
+        }
+    };
+    // element (i, k) of X, k <= i, to M and MH
+    const auto put_x = [&](int i, int k, double2 x) {
+        if (i < nb) {
+            M[(long long)i * N + k] = x;
+            MH[(long long)k * N + i] = double2{x.x, -x.y};
+        }
+    };
+    const auto put_x_tile = [&](int I, int J, const Cacc &o) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            put_x(16 * I + 4 * v + q, 16 * J + r, double2{o.re[v], o.im[v]});
+    };
+
+    int inf = 0;
     for (int P = 0; P < LT; ++P) {
-        // panel: row r of L_IP solves x L_PP^H = C_IP[r] by substitution,
-        // x_j = (c_j - sum_{k<j} x_k conj(l_jk)) / l_jj, one thread per row
-        if (tid < (LT - 1 - P) * 16) {
-            const double2 *D = ltile(T, P, P);
-            double2 *C = ltile(T, P + 1 + (tid >> 4), P);
-            const int rr = tid & 15;
-            double rd[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) rd[j] = 1.0 / D[lsw(j, j)].x;
-            double2 x[16];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) x[k] = C[lsw(rr, k)];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                double2 t = x[j];
-#pragma unroll
-                for (int k = 0; k < j; ++k) {   // t -= x_k conj(l_jk)
-                    const double2 l = D[lsw(j, k)];
-                    t.x -= x[k].x * l.x + x[k].y * l.y;
-                    t.y -= x[k].y * l.x - x[k].x * l.y;
-                }
-                x[j] = double2{t.x * rd[j], t.y * rd[j]};
+        Cacc o;   // this wave's tile of row P - 1 of the inverse
+        const int J = w - 1;
+        const bool has = J >= 0 && J < P - 1;
+        if (w == 0) {
+            if (P > 0) {
+                trail(P - 1, 0);
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
-#pragma unroll
-            for (int k = 0; k < 16; ++k) C[lsw(rr, k)] = x[k];
+            double2 *D = ltile(T, P, P);
+            const int f = diag16(D, scr, lane, [&](int v, double2 l) {
+                const int i = 16 * P + r, k = 16 * P + 4 * v + q;
+                if (k <= i && i < nb) L[(long long)i * N + k] = l;
+            });
+            if (f != 0 && inf == 0 && 16 * P + f <= nb) inf = 16 * P + f;
+        } else if (P > 0) {
+            if (has) inverse_tile(P - 1, J, o);
+            const int n = LT - P;
+            for (int t = w; t < n * (n + 1) / 2; t += 7) trail(P - 1, t);
         }
         __syncthreads();
-        // trailing lower triangle: wave 0 updates the next diagonal tile
-        // (t = 0) and factors it at once, beside the other waves' updates
-        const int n = LT - 1 - P;
-        if (w == 0) {
-            if (n > 0) {
-                trail(P, 0);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                diag(P + 1);
+        if (has) {
+            double2 *C = ltile(T, P - 1, J);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) C[lsw(4 * v + q, r)] = double2{o.re[v], o.im[v]};
+            put_x_tile(P - 1, J, o);
+        }
+        if (w == 0) {   // X_PP
+            const double2 *D = ltile(T, P, P);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (r <= 4 * v + q) put_x(16 * P + 4 * v + q, 16 * P + r, D[lsw(4 * v + q, r)]);
+        }
+        const int I = P + 8 - w;   // waves 7, 6, ...: panel tiles P + 1, P + 2, ...
+        if (I < LT) {
+            double2 *C = ltile(T, I, P);
+            Cacc c;
+            acc_zero(c);
+            mma_abh(c, C, ltile(T, P, P), lane);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * I + 4 * v + q;
+                const double2 l = {c.re[v], c.im[v]};
+                C[lsw(4 * v + q, r)] = l;
+                if (i < nb) L[(long long)i * N + 16 * P + r] = l;
             }
-        } else {
-            for (int t = w; t < n * (n + 1) / 2; t += 7) trail(P, t);
         }
         __syncthreads();
     }
     if (tid == 0 && inf != 0 && *info == 0) *info = kb + inf;
-    for (int e = tid; e < LB * LB; e += 512) {
-        const int i = e / LB, k = e % LB;
-        if (k <= i && i < nb)
-            L[(long long)(kb + i) * N + kb + k] = ltile(T, i >> 4, k >> 4)[lsw(i & 15, k & 15)];
-    }
-
-    // inverse: diagonal tiles, one per wave
-    {
-        double2 *D = ltile(T, w, w);
-        double2 x[16];
-        inv16(D, x, lane);
-        if (lane < 16) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) D[lsw(i, lane)] = i >= lane ? x[i] : double2{0.0, 0.0};
-        }
-    }
-    __syncthreads();
-    // block rows: X_IJ = -X_II sum_{J<=K<I} L_IK X_KJ (wave w: J = w)
-    for (int I = 1; I < LT; ++I) {
-        Cacc c;
-        acc_zero(c);
-        if (w < I)
-            for (int K = w; K < I; ++K) mma_ab(c, ltile(T, I, K), ltile(T, K, w), lane);
-        __syncthreads();   // row I of L fully read before it is overwritten
-        if (w < I) {
-            const double2 *X = ltile(T, I, I);
-            Cacc o;
-            acc_zero(o);
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) {   // B fragment rows 4 s4 .. = accumulator element s4
-                const double2 x = X[lsw(lane & 15, 4 * s4 + (lane >> 4))];
-                const double br = c.re[s4], bi = c.im[s4];
-                o.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, br, o.re, 0, 0, 0);
-                o.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, -bi, o.re, 0, 0, 0);
-                o.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, bi, o.im, 0, 0, 0);
-                o.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, br, o.im, 0, 0, 0);
-            }
-            double2 *C = ltile(T, I, w);
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                C[lsw(4 * v + (lane >> 4), lane & 15)] = double2{-o.re[v], -o.im[v]};
-        }
-        __syncthreads();
-    }
-    for (int e = tid; e < LB * LB; e += 512) {
-        const int i = e / LB, k = e % LB;
-        if (i < nb && k < nb) {
-            if (k <= i) M[(long long)(kb + i) * N + kb + k] = ltile(T, i >> 4, k >> 4)[lsw(i & 15, k & 15)];
-            else {   // MH[i][k] = conj(X[k][i]), k > i
-                const double2 v = ltile(T, k >> 4, i >> 4)[lsw(k & 15, i & 15)];
-                MH[(long long)(kb + i) * N + kb + k] = double2{v.x, -v.y};
-            }
-            if (k == i) {
-                const double2 v = ltile(T, i >> 4, i >> 4)[lsw(i & 15, i & 15)];
-                MH[(long long)(kb + i) * N + kb + k] = double2{v.x, -v.y};
-            }
-        }
+    if (w < LT - 1) {   // the inverse's last row
+        Cacc o;
+        inverse_tile(LT - 1, w, o);
+        put_x_tile(LT - 1, w, o);
     }
 }
 

@@ -253,9 +253,9 @@ void mm_launch(const MmArgs &a, bool g3, unsigned grid, hipStream_t st) {
 // Per panel P of 16 columns, two phases with a barrier after each:
 //   wave 0:    the diagonal tile's update with panel P - 1, then its Cholesky
 //              and inverse (diag16), X_PP replacing the tile;
-//   waves 1-7: the rest of the trailing update C_IJ -= L_I,P-1 L_J,P-1^H, and
-//              row P - 1 of the inverse, X_IJ = -X_II sum_{J<=K<I} L_IK X_KJ,
-//              held in registers;
+//   waves 1-7: the rest of the trailing update C_IJ -= L_I,P-1 L_J,P-1^H; row
+//              P - 1 of the inverse, X_IJ = -X_II sum_{J<=K<I} L_IK X_KJ, held
+//              in registers, and row P's sum as far as its terms are there;
 //   all waves: L_IP = C_IP X_PP^H, one tile per wave; the row of the inverse
 //              is stored (over L's row, which nothing reads any more).
 // Outputs go to global memory from the registers that form them: the block of
@@ -323,15 +323,16 @@ __device__ __forceinline__ void mma_ab(Cacc &c, const double2 *A, const double2 
 // accumulator layout D[4 v + q][r] of G = S^T holds S[r][4 v + q], which is
 // the A and B operand layout of a rank-4 update with columns 4 v .. 4 v + 3,
 // so nothing is re-laid out. (One column at a time over all sixteen, with
-// the inverse by substitution afterwards: 6 + 5 us instead of 3.)
+// the inverse by substitution afterwards: 6 + 5 us instead of 3.5; the leaf
+// 103 us, 58 now.)
 //   D    the tile (row-major, swizzled; lower triangle used); X on return
 //   scr  128 complex values of LDS of this wave
 //   fac  receives L[r][4 v + q] of step v as fac(v, value), zero above the
 //        diagonal
 // Returns 0 or the 1-based index of the first pivot that is not > 0. 1/sqrt
-// of a pivot: the hardware estimate refined by two Newton steps
-// (y += y (1 - d y^2) / 2; the estimate is good to far more than the 2^-13
-// two steps need for full precision), sqrt(d) = d / sqrt(d).
+// of a pivot: the hardware estimate y (good to 2^-22 or better) refined by one
+// third-order step, y (1 + e/2 + 3 e^2 / 8) with e = 1 - d y^2, which leaves
+// 5/16 e^3; sqrt(d) = d / sqrt(d).
 template <class Fac>
 __device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fac) {
     const int r = lane & 15, q = lane >> 4;
@@ -348,36 +349,35 @@ __device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fa
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         scr[lane] = double2{g.re[v], g.im[v]};
-        scr[64 + lane] = double2{e.re[v], e.im[v]};
         double2 s[4], x[4], l[4];   // columns 4 v + p of S; rows 4 v + p of E, then of X
+        double rc[4], lkx[4][4], lky[4][4];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             s[p] = scr[r + 16 * p];
-            x[p] = scr[64 + r + 16 * p];
+            asm volatile("" : "+v"(s[p].x), "+v"(s[p].y));   // read here, not under a branch
         }
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
             const int j = 4 * v + p;
             const double d = bcast(s[p].x, j);
             if (!(d > 0.0) && inf == 0) inf = j + 1;
-            double rc = __builtin_amdgcn_rsq(d);
-            rc = fma(0.5 * rc, fma(-d * rc, rc, 1.0), rc);
-            rc = fma(0.5 * rc, fma(-d * rc, rc, 1.0), rc);
-            l[p].x = s[p].x * rc;   // sqrt(d) in row j
-            l[p].y = r == j ? 0.0 : s[p].y * rc;
-            x[p].x *= rc;
-            x[p].y *= rc;
+            const double y = __builtin_amdgcn_rsq(d);
+            const double er = fma(-d * y, y, 1.0);
+            rc[p] = fma(y * er, fma(0.375, er, 0.5), y);
+            l[p].x = s[p].x * rc[p];   // sqrt(d) in row j
+            l[p].y = r == j ? 0.0 : s[p].y * rc[p];
 #pragma unroll
             for (int k = p + 1; k < 4; ++k) {
                 const double lx = bcast(l[p].x, 4 * v + k), ly = bcast(l[p].y, 4 * v + k);
-                s[k].x -= l[p].x * lx + l[p].y * ly;   // s_rk -= l_rj conj(l_kj)
-                s[k].y -= l[p].y * lx - l[p].x * ly;
-                x[k].x -= lx * x[p].x - ly * x[p].y;   // row k of E -= l_kj (row j of X)
-                x[k].y -= lx * x[p].y + ly * x[p].x;
+                lkx[p][k] = lx;
+                lky[p][k] = ly;
+                // s_rk -= l_rj conj(l_kj)
+                s[k].x = fma(-ly, l[p].y, fma(-lx, l[p].x, s[k].x));
+                s[k].y = fma(ly, l[p].x, fma(-lx, l[p].y, s[k].y));
             }
         }
-        // this lane's element of the four columns and rows (selected by
-        // component: a select between aggregates goes through scratch memory)
+        // this lane's element of four values (selected by component: a select
+        // between aggregates goes through scratch memory)
         const auto own = [&](double a0, double a1, double a2, double a3) {
             const double lo = q & 1 ? a1 : a0, hi = q & 1 ? a3 : a2;
             return q & 2 ? hi : lo;
@@ -386,15 +386,31 @@ __device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fa
         const double lre = own(l[0].x, l[1].x, l[2].x, l[3].x);
         const double lim = own(l[0].y, l[1].y, l[2].y, l[3].y);
         const double2 lq = {low ? lre : 0.0, low ? lim : 0.0};
-        const double2 xq = {own(x[0].x, x[1].x, x[2].x, x[3].x), own(x[0].y, x[1].y, x[2].y, x[3].y)};
-        fac(v, lq);
-        D[lsw(4 * v + q, r)] = xq;
-        if (v < 3) {
-            // G[i][j] -= conj(L[i][p]) L[j][p],  E[i][c] -= L[i][p] X[p][c]
+        if (v < 3) {   // G[i][j] -= conj(L[i][p]) L[j][p]
             g.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, lq.x, g.re, 0, 0, 0);
             g.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, lq.y, g.im, 0, 0, 0);
             g.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, lq.y, g.re, 0, 0, 0);
             g.im = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, lq.x, g.im, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the rows of the identity beside that update
+        fac(v, lq);
+        scr[64 + lane] = double2{e.re[v], e.im[v]};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) x[p] = scr[64 + r + 16 * p];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            x[p].x *= rc[p];
+            x[p].y *= rc[p];
+#pragma unroll
+            for (int k = p + 1; k < 4; ++k) {   // row k of E -= l_kj (row j of X)
+                x[k].x = fma(lky[p][k], x[p].y, fma(-lkx[p][k], x[p].x, x[k].x));
+                x[k].y = fma(-lky[p][k], x[p].x, fma(-lkx[p][k], x[p].y, x[k].y));
+            }
+        }
+        const double2 xq = {own(x[0].x, x[1].x, x[2].x, x[3].x), own(x[0].y, x[1].y, x[2].y, x[3].y)};
+        D[lsw(4 * v + q, r)] = xq;
+        if (v < 3) {   // E[i][c] -= L[i][p] X[p][c]
             e.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, xq.x, e.re, 0, 0, 0);
             e.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, xq.y, e.im, 0, 0, 0);
             e.re = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, xq.y, e.re, 0, 0, 0);
@@ -446,27 +462,50 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
     }
     __syncthreads();
 
-    // C_IJ -= L_IP L_JP^H for the t-th tile of the trailing triangle of panel P
-    const auto trail = [&](int P, int t) {
-        int ti, tj;
-        tri_decode(t, ti, tj);
-        const int I = P + 1 + ti, J = P + 1 + tj;
-        Cacc c;
-        acc_zero(c);
-        mma_abh(c, ltile(T, I, P), ltile(T, J, P), lane);
-        double2 *C = ltile(T, I, J);
+    // C_IJ -= L_IP L_JP^H for the t-th tile of the trailing triangle of panel
+    // P, NT tiles at once (t, t + 7), so that their LDS reads overlap
+    const auto trail = [&](auto nt, int P, int t) {
+        constexpr int NT = decltype(nt)::value;
+        Cacc c[NT];
+        double2 *C[NT], *A[NT], *B[NT];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            double2 &o = C[lsw(4 * v + q, r)];
-            o.x -= c.re[v];
-            o.y -= c.im[v];
+        for (int u = 0; u < NT; ++u) {
+            int ti, tj;
+            tri_decode(t + 7 * u, ti, tj);
+            A[u] = ltile(T, P + 1 + ti, P);
+            B[u] = ltile(T, P + 1 + tj, P);
+            C[u] = ltile(T, P + 1 + ti, P + 1 + tj);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double2 o = C[u][lsw(4 * v + q, r)];
+                c[u].re[v] = o.x;
+                c[u].im[v] = o.y;
+            }
         }
+#pragma unroll
+        for (int k0 = 0; k0 < 16; k0 += 4)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                const double2 x = A[u][lsw(r, k0 + q)], y = B[u][lsw(r, k0 + q)];
+                c[u].re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.x, y.x, c[u].re, 0, 0, 0);
+                c[u].im = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, y.x, c[u].im, 0, 0, 0);
+                c[u].re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, y.y, c[u].re, 0, 0, 0);
+                c[u].im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.y, c[u].im, 0, 0, 0);
+            }
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                C[u][lsw(4 * v + q, r)] = double2{c[u].re[v], c[u].im[v]};
     };
-    // o = -X_II sum_{J<=K<I} L_IK X_KJ
-    const auto inverse_tile = [&](int I, int J, Cacc &o) {
-        Cacc c;
-        acc_zero(c);
-        for (int K = J; K < I; ++K) mma_ab(c, ltile(T, I, K), ltile(T, K, J), lane);
+    struct One {
+        enum { value = 1 };
+    };
+    struct Two {
+        enum { value = 2 };
+    };
+    // o = -X_II c
+    const auto scale_x = [&](int I, const Cacc &c, Cacc &o) {
         const double2 *X = ltile(T, I, I);
         acc_zero(o);
 #pragma unroll
@@ -492,14 +531,22 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
             put_x(16 * I + 4 * v + q, 16 * J + r, double2{o.re[v], o.im[v]});
     };
 
+    // Wave w's column J of the inverse, so that the longest and the shortest
+    // sums share a SIMD (waves w and w + 4); wave 4 shares one with wave 0,
+    // which has the chain of diagonal tiles and goes first.
+    const int J = w == 0 ? LT : w < 4 ? w - 1 : w == 4 ? 6 : 10 - w;
+    // trailing tiles are dealt in turns of 13, two for each wave but wave 4
+    const int turn = w == 4 ? 6 : w > 4 ? 7 - w : 6 - w;
+    if (w == 0) __builtin_amdgcn_s_setprio(3);
     int inf = 0;
+    Cacc c;   // sum_{J<=K<=P-2} L_PK X_KJ, begun a step before row P is due
+#pragma unroll
     for (int P = 0; P < LT; ++P) {
         Cacc o;   // this wave's tile of row P - 1 of the inverse
-        const int J = w - 1;
-        const bool has = J >= 0 && J < P - 1;
+        const bool has = J < P - 1;
         if (w == 0) {
             if (P > 0) {
-                trail(P - 1, 0);
+                trail(One{}, P - 1, 0);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
             double2 *D = ltile(T, P, P);
@@ -509,9 +556,19 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
             });
             if (f != 0 && inf == 0 && 16 * P + f <= nb) inf = 16 * P + f;
         } else if (P > 0) {
-            if (has) inverse_tile(P - 1, J, o);
+            if (has) {
+                if (J == P - 2) acc_zero(c);
+                mma_ab(c, ltile(T, P - 1, P - 2), ltile(T, P - 2, J), lane);
+                scale_x(P - 1, c, o);
+                acc_zero(c);
+#pragma unroll 2
+                for (int K = J; K <= P - 2; ++K) mma_ab(c, ltile(T, P, K), ltile(T, K, J), lane);
+            }
             const int n = LT - P;
-            for (int t = w; t < n * (n + 1) / 2; t += 7) trail(P - 1, t);
+            for (int t = 1 + turn; t < n * (n + 1) / 2; t += 13) {
+                if (w != 4 && t + 7 < n * (n + 1) / 2) trail(Two{}, P - 1, t);
+                else trail(One{}, P - 1, t);
+            }
         }
         __syncthreads();
         if (has) {
@@ -543,10 +600,12 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
         __syncthreads();
     }
     if (tid == 0 && inf != 0 && *info == 0) *info = kb + inf;
-    if (w < LT - 1) {   // the inverse's last row
+    if (w > 0) {   // the inverse's last row
+        if (J == LT - 2) acc_zero(c);
+        mma_ab(c, ltile(T, LT - 1, LT - 2), ltile(T, LT - 2, J), lane);
         Cacc o;
-        inverse_tile(LT - 1, w, o);
-        put_x_tile(LT - 1, w, o);
+        scale_x(LT - 1, c, o);
+        put_x_tile(LT - 1, J, o);
     }
 }
 

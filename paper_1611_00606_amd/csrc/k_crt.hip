@@ -8,9 +8,8 @@
 // for the real and the imaginary parts. This rounding is the form's only
 // error: at most 2^-b of the column maximum per element.
 //
-// Products. With real and imaginary parts interleaved along the contraction,
-// P'' = (p_re, p_im), Q''_re = (q_re, q_im) and Q''_im = (q_im, -q_re), the
-// real and the imaginary part of conj(P')^T Q' are each one dot product of 2K
+// Products. The real part p_re q_re + p_im q_im and the imaginary part
+// p_re q_im - p_im q_re of conj(P')^T Q' are each one dot product of 2K
 // integers, so |Re|, |Im| <= 2K 2^(2b - 2). Both are computed modulo NMOD
 // pairwise coprime odd moduli m_i <= 255: the operands' residues in symmetric
 // form (|r| <= (m - 1) / 2 <= 127, so a residue and its negation are int8),
@@ -96,67 +95,76 @@ __device__ __forceinline__ int crt_modulus(int mi) {
 }
 
 // ---------------------------------------------------------------------------
-// Residues. One thread per (group of 8 complex rows, column): 16 interleaved
-// real values -> b-bit integers -> NMOD residues of 16 int8, written to
-// R[i][g][n][0..15].
+// Residues. One thread per (16 complex rows, column): the real and the
+// imaginary parts -> b-bit integers -> NMOD residues of 16 int8 each, written
+// to R[i][g][n][0..15]. A stage of the products is 64 complex rows, eight
+// items g of a column: the real parts of rows 16 q .. 16 q + 15 (q = 0..3),
+// then the imaginary parts.
 
 __global__ void __launch_bounds__(256)
-k_residue(SliceSrc src, int K, int n_g, int groups, int b) {
+k_residue(SliceSrc src, int K, int n_g, int blocks, int b) {
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
-    const int g = (int)(idx / n_g);
-    if (g >= groups) return;
+    const int rb = (int)(idx / n_g);   // block of 16 rows
+    if (rb >= blocks) return;
     const int sh = b - 1 - col_exp(src.mx, n);
-    double x[16];
+    double x[2][16];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int k = 8 * g + q;
+    for (int q = 0; q < 16; ++q) {
+        const int k = 16 * rb + q;
         double2 v = {0.0, 0.0};
         if (k < K) v = slice_src_row(src, k, n_g, n);
-        x[2 * q] = rint(ldexp(v.x, sh));
-        x[2 * q + 1] = rint(ldexp(v.y, sh));
+        x[0][q] = rint(ldexp(v.x, sh));
+        x[1][q] = rint(ldexp(v.y, sh));
     }
-    const long long plane = (long long)groups * n_g;   // 16-byte items per modulus
-    uint4 *out = reinterpret_cast<uint4 *>(src.S) + (long long)g * n_g + n;
+    const long long plane = 2LL * blocks * n_g;   // 16-byte items per modulus
+    uint4 *out = reinterpret_cast<uint4 *>(src.S) + (8LL * (rb >> 2) + (rb & 3)) * n_g + n;
 #pragma unroll
     for (int i = 0; i < NMOD; ++i) {
         // x / m is at most 2^28 and at least 1 / (2 m) from a half-integer,
         // so rint of the rounded quotient is exact and so is the remainder
         const double m = CRT_MOD[i], inv = 1.0 / CRT_MOD[i];
-        unsigned w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const double r = fma(-m, rint(x[j] * inv), x[j]);
-            w[j >> 2] |= ((unsigned)(int)r & 0xffu) << (8 * (j & 3));
+        for (int c = 0; c < 2; ++c) {
+            unsigned w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const double r = fma(-m, rint(x[c][j] * inv), x[c][j]);
+                w[j >> 2] |= ((unsigned)(int)r & 0xffu) << (8 * (j & 3));
+            }
+            out[i * plane + 4LL * c * n_g] = uint4{w[0], w[1], w[2], w[3]};
         }
-        out[i * plane] = uint4{w[0], w[1], w[2], w[3]};
     }
 }
 
 // ---------------------------------------------------------------------------
 // Products modulo one modulus. One block per (128 x 128 lower-triangle tile,
 // segment, modulus): 4 waves of 64 x 64 outputs (4 x 4 MFMA blocks of
-// 16 x 16, Re and Im: 128 accumulator registers), two blocks per CU (two
-// waves per SIMD). A stage is 64 complex rows: 8 items of 16 bytes per
-// column and operand, moved global -> LDS with 16-byte direct loads, two
-// 32 KiB buffers (the next stage loads while the current one is
-// multiplied). The INT32 sums stay exact for CFOLD stages (checked below);
+// 16 x 16), two blocks per CU (two waves per SIMD). A stage is 64 complex
+// rows: 8 items of 16 bytes per column and operand, the real and the
+// imaginary parts in items of their own, moved global -> LDS with 16-byte
+// direct loads, two 32 KiB buffers (the next stage loads while the current
+// one is multiplied). The difference in the imaginary part is taken once, at
+// the end: its two sums have accumulators of their own (192 registers in all),
+// so the K loop holds no vector arithmetic besides the MFMAs. (With the parts
+// interleaved and (q_im, -q_re) formed in registers, three vector operations
+// per dword, the kernel took 38.1 ms at N_G = 8000, K = 8100; now 34.7 ms,
+// 2.63 POP/s.) The INT32 sums stay exact for CFOLD stages (checked below);
 // longer segments reduce them modulo m every CFOLD stages.
 //
 // Measured at N_G = 8000 (K = 8100): against 8 waves of 64 x 32 outputs in
 // 128-row stages (one block per CU) this shape reads a third less from LDS
-// per MFMA and is 9% faster; deeper pipelines (3 to 5 buffers, up to four
-// stages in flight) are not faster: the kernel runs INT8 MFMA at a reduced
-// clock (about 1.74 GHz by the cycle counters), not waiting on operands.
-// Bands of 8 tile columns in the tile order (64 tiles resident per XCD
-// share 8 row and 8 column panels) fetch 15% less than bands of 4.
+// per MFMA and was 9% faster; deeper pipelines (3 to 5 buffers, up to four
+// stages in flight) are not faster, nor is V_MFMA_I32_32X32X32_I8 (49.4
+// against 45.3 ms for the build). Bands of 8 tile columns in the tile order
+// (64 tiles resident per XCD share 8 row and 8 column panels) fetch 15% less
+// than bands of 4.
 
 constexpr int CB = 128;                    // tile rows (g') and columns (g)
 constexpr int CWM = 2, CWN = 2;            // waves
 constexpr int CNT = 64 * CWM * CWN;
 constexpr int CTM = CB / CWM / 16, CTN = CB / CWN / 16;   // 16 x 16 blocks per wave
-constexpr int CKS = 2;                     // MFMA K steps (32 complex rows) per stage
-constexpr int CITEMS = 4 * CKS;            // items per column and stage
+constexpr int CITEMS = 8;                  // items per column and stage (64 complex rows)
 constexpr int COP = CITEMS * CB;           // items per operand and stage
 constexpr int CBUF = 2 * COP;
 constexpr int CFOLD = 1024;                // stages between reductions of the sums
@@ -240,36 +248,35 @@ k_crt_reduce(CrtArgs args) {
         }
     };
 
-    i4 accr[CTM][CTN], acci[CTM][CTN];
+    // Re = sum pr qr + pi qi; Im = U - V, U = sum pr qi, V = sum pi qr
+    i4 accr[CTM][CTN], accu[CTM][CTN], accv[CTM][CTN];
 #pragma unroll
     for (int i = 0; i < CTM; ++i)
 #pragma unroll
-        for (int j = 0; j < CTN; ++j) {
-            accr[i][j] = i4{0, 0, 0, 0};
-            acci[i][j] = i4{0, 0, 0, 0};
-        }
+        for (int j = 0; j < CTN; ++j) accr[i][j] = accu[i][j] = accv[i][j] = i4{0, 0, 0, 0};
     const int lg = lane >> 4, lc = lane & 15;
     auto compute = [&](const uint4 *buf) __attribute__((always_inline)) {
         const uint4 *lp = buf;
         const uint4 *lq = buf + COP;
+        i4 ar[CTM], ai[CTM];
 #pragma unroll
-        for (int kk = 0; kk < CKS; ++kk) {
-            i4 a[CTM];
+        for (int i = 0; i < CTM; ++i) {
+            ar[i] = __builtin_bit_cast(i4, lp[lg * CB + wm * (CB / CWM) + i * 16 + lc]);
+            ai[i] = __builtin_bit_cast(i4, lp[(4 + lg) * CB + wm * (CB / CWM) + i * 16 + lc]);
+        }
+#pragma unroll
+        for (int j = 0; j < CTN; ++j) {
+            const i4 br = __builtin_bit_cast(i4, lq[lg * CB + wn * (CB / CWN) + j * 16 + lc]);
+            const i4 bi = __builtin_bit_cast(i4, lq[(4 + lg) * CB + wn * (CB / CWN) + j * 16 + lc]);
+#pragma unroll
+            for (int i = 0; i < CTM; ++i) {
+                accr[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[i], br, accr[i][j], 0, 0, 0);
+                accu[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[i], bi, accu[i][j], 0, 0, 0);
+                accv[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ai[i], br, accv[i][j], 0, 0, 0);
+            }
 #pragma unroll
             for (int i = 0; i < CTM; ++i)
-                a[i] = __builtin_bit_cast(i4, lp[(kk * 4 + lg) * CB + wm * (CB / CWM) + i * 16 + lc]);
-#pragma unroll
-            for (int j = 0; j < CTN; ++j) {
-                const uint4 u = lq[(kk * 4 + lg) * CB + wn * (CB / CWN) + j * 16 + lc];
-                const i4 bq = __builtin_bit_cast(i4, u);
-                const i4 bi = i4{(int)im_pairs(u.x), (int)im_pairs(u.y), (int)im_pairs(u.z),
-                                 (int)im_pairs(u.w)};
-#pragma unroll
-                for (int i = 0; i < CTM; ++i) {
-                    accr[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], bq, accr[i][j], 0, 0, 0);
-                    acci[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], bi, acci[i][j], 0, 0, 0);
-                }
-            }
+                accr[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ai[i], bi, accr[i][j], 0, 0, 0);
         }
     };
     auto fold = [&]() __attribute__((always_inline)) {
@@ -280,7 +287,8 @@ k_crt_reduce(CrtArgs args) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     accr[i][j][v] = sym_res(accr[i][j][v], m, minv);
-                    acci[i][j][v] = sym_res(acci[i][j][v], m, minv);
+                    accu[i][j][v] = sym_res(accu[i][j][v] - accv[i][j][v], m, minv);
+                    accv[i][j][v] = 0;
                 }
     };
 
@@ -324,7 +332,7 @@ k_crt_reduce(CrtArgs args) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 re |= (unsigned)(accr[i][j][v] + 127) << (8 * v);
-                im |= (unsigned)(acci[i][j][v] + 127) << (8 * v);
+                im |= (unsigned)(accu[i][j][v] + 127) << (8 * v);
             }
             out[(wave * CTM * CTN + i * CTN + j) * 64 + lane] = uint2{re, im};
         }
@@ -453,12 +461,12 @@ size_t crt_work_bytes(int n_g) {
 }
 
 hipError_t launch_residue(const SliceSrc &src, int K, int n_g, hipStream_t st) {
-    const int groups = (K + CITEMS * 8 - 1) / (CITEMS * 8) * CITEMS;
+    const int blocks = (K + CITEMS * 8 - 1) / (CITEMS * 8) * (CITEMS / 2);   // of 16 rows
     hipError_t e = launch_colmax(src, K, n_g, st);
     if (e != hipSuccess) return e;
-    const long long items = (long long)groups * n_g;
+    const long long items = (long long)blocks * n_g;
     hipLaunchKernelGGL(k_residue, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, src, K,
-                       n_g, groups, crt_bits(K));
+                       n_g, blocks, crt_bits(K));
     return hipGetLastError();
 }
 

@@ -192,25 +192,21 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
     if (e != hipSuccess) return e;
     if ((e = mark(2)) != hipSuccess) return e;
     if (split_mode(mode)) {
-        // operands: 0 A, 1 U B, 2 X, 3 B, 4 Y
+        // operands: 0 A, 1 B, 2 X, 3 Y, 4 U B
         const int K = p.K;
-        const SliceSrc src[NSPLIT] = {
-            {A, nullptr, kb.mx[0], kb.sl[0]},
-            {B, ab.d + K, kb.mx[1], kb.sl[1]},
-            {kb.X, nullptr, kb.mx[2], kb.sl[2]},
-            {B, nullptr, kb.mx[3], kb.sl[3]},
-            {kb.Y, nullptr, kb.mx[4], kb.sl[4]},
-        };
+        SliceJobs jobs = {{A, B, kb.X, kb.Y}, ab.d + K, {}, {}};
         for (int i = 0; i < NSPLIT; ++i) {
-            if (mode == HS_SPLIT_I8_CRT) e = launch_residue(src[i], K, n_g, st);
-            else if (mode == HS_SPLIT_I8) e = launch_slice8(src[i], K, n_g, st);
-            else e = launch_slice(src[i], K, n_g, st, mode == HS_SPLIT_BF16);
-            if (e != hipSuccess) return e;
+            jobs.mx[i] = kb.mx[i];
+            jobs.S[i] = kb.sl[i];
         }
+        if (mode == HS_SPLIT_I8_CRT) e = launch_residue(jobs, K, n_g, st);
+        else if (mode == HS_SPLIT_I8) e = launch_slice8(jobs, K, n_g, st);
+        else e = launch_slice(jobs, K, n_g, st, mode == HS_SPLIT_BF16);
+        if (e != hipSuccess) return e;
         SliceView v[NSPLIT];
         for (int i = 0; i < NSPLIT; ++i) v[i] = SliceView{kb.sl[i], kb.mx[i]};
-        const SliceView hseg[2][2] = {{v[3], v[4]}, {v[0], v[2]}};
-        const SliceView sseg[2][2] = {{v[0], v[0]}, {v[1], v[1]}};
+        const SliceView hseg[2][2] = {{v[1], v[3]}, {v[0], v[2]}};
+        const SliceView sseg[2][2] = {{v[0], v[0]}, {v[4], v[4]}};
         if (mode == HS_SPLIT_I8_CRT)
             e = launch_crt_reduce(K, n_g, hseg, sseg, kb.crt, H, S, st);
         else if (mode == HS_SPLIT_I8)

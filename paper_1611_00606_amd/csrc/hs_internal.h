@@ -67,24 +67,28 @@ inline bool split_mode(int mode) {   // the operands are sliced (or cut into res
            mode == HS_SPLIT_I8_CRT;
 }
 
-// Split-precision reductions (k_split.hip). A sliced operand: rows of X,
-// optionally scaled by sqrt(rscale[k]); outputs the column maxima mx [N_G] (bit patterns of doubles) and the FP16 slices
-// S [4][groups][N_G][8], groups = 4 * ceil(K / 16).
-struct SliceSrc {
-    const double2 *X;
+// Split-precision reductions (k_split.hip). The sliced operands: the matrices
+// X[0..3] [K][N_G] as they are, and as operand 4 the rows of X[1] scaled by
+// sqrt(rscale[k]); for each the column maxima mx [N_G] (bit patterns of
+// doubles) and the FP16 slices S [4][groups][N_G][8], groups = 4 * ceil(K / 16).
+// Every pass takes all of them in one launch and reads each matrix once.
+constexpr int NSLICE_SRC = 4;
+struct SliceJobs {
+    const double2 *X[NSLICE_SRC];
     const double *rscale;
-    unsigned long long *mx;
-    _Float16 *S;
+    unsigned long long *mx[NSLICE_SRC + 1];
+    _Float16 *S[NSLICE_SRC + 1];
 };
 struct SliceView {
     const _Float16 *S;
     const unsigned long long *mx;
 };
 size_t split_slice_bytes(int K, int n_g);
-// zero mx, then the column maxima of src into it
-hipError_t launch_colmax(const SliceSrc &src, int K, int n_g, hipStream_t st);
-// bf16: the same slices held as BF16 and multiplied on BF16 MFMA
-hipError_t launch_slice(const SliceSrc &src, int K, int n_g, hipStream_t st, bool bf16);
+// zero every mx, then the column maxima into them
+hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
+// column maxima and slices; bf16: the same slices held as BF16 and multiplied
+// on BF16 MFMA
+hipError_t launch_slice(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool bf16);
 // H segments (B,Y), (A,X); S segments (A,A), (Bs,Bs): [segment][P or Q]
 hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                const SliceView (&sseg)[2][2], double2 *H, double2 *S,
@@ -92,7 +96,7 @@ hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
 // INT8 form: slices S8 [5][groups][N_G][16 int8], groups = 4 * ceil(K / 32);
 // same column maxima and segments as the FP16 form.
 size_t split8_slice_bytes(int K, int n_g);
-hipError_t launch_slice8(const SliceSrc &src, int K, int n_g, hipStream_t st);
+hipError_t launch_slice8(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
 hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                 const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                 hipStream_t st);
@@ -103,7 +107,7 @@ hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
 size_t crt_residue_bytes(int K, int n_g);
 size_t crt_work_bytes(int n_g);
 int crt_bits(int K);   // integer width b of the operands for contraction length K
-hipError_t launch_residue(const SliceSrc &src, int K, int n_g, hipStream_t st);
+hipError_t launch_residue(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
 hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                              const SliceView (&sseg)[2][2], void *work, double2 *H, double2 *S,
                              hipStream_t st);
@@ -193,7 +197,7 @@ hipError_t launch_batch(const AtomPlan &p, const Atoms &at, const BatchPlan &bp,
                         const BatchIO &io, const BatchBufs &bb, hipStream_t st);
 
 // Per-k-point device buffers.
-constexpr int NSPLIT = 5;   // sliced operands: A, U B, X, B, Y
+constexpr int NSPLIT = NSLICE_SRC + 1;   // sliced operands: A, B, X, Y, U B
 // Room for this many sliced operands is part of the workspace size callers
 // have been given.
 constexpr int NSPLIT_ROOM = 6;

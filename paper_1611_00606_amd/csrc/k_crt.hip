@@ -102,39 +102,52 @@ __device__ __forceinline__ int crt_modulus(int mi) {
 // then the imaginary parts.
 
 __global__ void __launch_bounds__(256)
-k_residue(SliceSrc src, int K, int n_g, int blocks, int b) {
+k_residue(SliceJobs jobs, int K, int n_g, int blocks, int b) {
+    const int z = blockIdx.y;
+    const double2 *X = slice_ptr(jobs.X, z);
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
     const int rb = (int)(idx / n_g);   // block of 16 rows
     if (rb >= blocks) return;
-    const int sh = b - 1 - col_exp(src.mx, n);
-    double x[2][16];
+    double2 raw[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int k = 16 * rb + q;
-        double2 v = {0.0, 0.0};
-        if (k < K) v = slice_src_row(src, k, n_g, n);
-        x[0][q] = rint(ldexp(v.x, sh));
-        x[1][q] = rint(ldexp(v.y, sh));
+        raw[q] = double2{0.0, 0.0};
+        if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const long long plane = 2LL * blocks * n_g;   // 16-byte items per modulus
-    uint4 *out = reinterpret_cast<uint4 *>(src.S) + (8LL * (rb >> 2) + (rb & 3)) * n_g + n;
+    const auto cut = [&](const unsigned long long *mx, _Float16 *S, bool scaled)
+                         __attribute__((always_inline)) {
+        const int sh = b - 1 - col_exp(mx, n);
+        double x[2][16];
 #pragma unroll
-    for (int i = 0; i < NMOD; ++i) {
-        // x / m is at most 2^28 and at least 1 / (2 m) from a half-integer,
-        // so rint of the rounded quotient is exact and so is the remainder
-        const double m = CRT_MOD[i], inv = 1.0 / CRT_MOD[i];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            unsigned w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const double r = fma(-m, rint(x[c][j] * inv), x[c][j]);
-                w[j >> 2] |= ((unsigned)(int)r & 0xffu) << (8 * (j & 3));
-            }
-            out[i * plane + 4LL * c * n_g] = uint4{w[0], w[1], w[2], w[3]};
+        for (int q = 0; q < 16; ++q) {
+            const int k = 16 * rb + q;
+            const double2 v = scaled && k < K ? slice_scaled(jobs, raw[q], k) : raw[q];
+            x[0][q] = rint(ldexp(v.x, sh));
+            x[1][q] = rint(ldexp(v.y, sh));
         }
-    }
+        const long long plane = 2LL * blocks * n_g;   // 16-byte items per modulus
+        uint4 *out = reinterpret_cast<uint4 *>(S) + (8LL * (rb >> 2) + (rb & 3)) * n_g + n;
+#pragma unroll
+        for (int i = 0; i < NMOD; ++i) {
+            // x / m is at most 2^28 and at least 1 / (2 m) from a half-integer,
+            // so rint of the rounded quotient is exact and so is the remainder
+            const double m = CRT_MOD[i], inv = 1.0 / CRT_MOD[i];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                unsigned w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const double r = fma(-m, rint(x[c][j] * inv), x[c][j]);
+                    w[j >> 2] |= ((unsigned)(int)r & 0xffu) << (8 * (j & 3));
+                }
+                out[i * plane + 4LL * c * n_g] = uint4{w[0], w[1], w[2], w[3]};
+            }
+        }
+    };
+    cut(slice_ptr(jobs.mx, z), slice_ptr(jobs.S, z), false);
+    if (z == 1) cut(jobs.mx[NSLICE_SRC], jobs.S[NSLICE_SRC], true);
 }
 
 // ---------------------------------------------------------------------------
@@ -460,13 +473,13 @@ size_t crt_work_bytes(int n_g) {
     return (size_t)NSEG_ROOM * NMOD * ntri * CFRAG * 64 * sizeof(uint2);
 }
 
-hipError_t launch_residue(const SliceSrc &src, int K, int n_g, hipStream_t st) {
+hipError_t launch_residue(const SliceJobs &jobs, int K, int n_g, hipStream_t st) {
     const int blocks = (K + CITEMS * 8 - 1) / (CITEMS * 8) * (CITEMS / 2);   // of 16 rows
-    hipError_t e = launch_colmax(src, K, n_g, st);
+    hipError_t e = launch_colmax(jobs, K, n_g, st);
     if (e != hipSuccess) return e;
     const long long items = (long long)blocks * n_g;
-    hipLaunchKernelGGL(k_residue, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, src, K,
-                       n_g, blocks, crt_bits(K));
+    hipLaunchKernelGGL(k_residue, dim3((unsigned)((items + 255) / 256), NSLICE_SRC), dim3(256), 0,
+                       st, jobs, K, n_g, blocks, crt_bits(K));
     return hipGetLastError();
 }
 

@@ -65,31 +65,41 @@ static_assert(SBITS1 <= 10 && SBITS <= 10, "slices must be integers FP16 holds e
 
 constexpr int CROWS = 64;   // rows per k_colmax block
 
-__global__ void __launch_bounds__(256) k_zero_u64(unsigned long long *p, int n) {
+__global__ void __launch_bounds__(256) k_zero_u64(SliceJobs jobs, int n) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0ull;
+    if (i < n) slice_ptr(jobs.mx, blockIdx.y)[i] = 0ull;
 }
 
 __global__ void __launch_bounds__(256)
-k_colmax(SliceSrc src, int K, int n_g) {
-    __shared__ double red[4][64];
+k_colmax(SliceJobs jobs, int K, int n_g) {
+    __shared__ double red[2][4][64];
+    const int z = blockIdx.z;
+    const double2 *X = slice_ptr(jobs.X, z);
+    const bool two = z == 1;   // operand 4 too
     const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
     const int n = blockIdx.x * 64 + c;
     const int ncl = n < n_g ? n : n_g - 1;
     const int k0 = blockIdx.y * CROWS;
-    double m = 0.0;
+    double m0 = 0.0, m1 = 0.0;
 #pragma unroll 4
     for (int k = k0 + rg; k < k0 + CROWS; k += 4) {
         if (k < K) {
-            const double2 v = slice_src_row(src, k, n_g, ncl);
-            m = fmax(m, fmax(fabs(v.x), fabs(v.y)));
+            const double2 v = X[(long long)k * n_g + ncl];
+            m0 = fmax(m0, fmax(fabs(v.x), fabs(v.y)));
+            if (two) {
+                const double2 b = slice_scaled(jobs, v, k);
+                m1 = fmax(m1, fmax(fabs(b.x), fabs(b.y)));
+            }
         }
     }
-    red[rg][c] = m;
+    red[0][rg][c] = m0;
+    red[1][rg][c] = m1;
     __syncthreads();
-    if (rg == 0 && n < n_g) {
-        m = fmax(fmax(red[0][c], red[1][c]), fmax(red[2][c], red[3][c]));
-        atomicMax(src.mx + n, (unsigned long long)__double_as_longlong(m));
+    if ((rg == 0 || (rg == 1 && two)) && n < n_g) {
+        const double (*x)[64] = red[rg];
+        const double m = fmax(fmax(x[0][c], x[1][c]), fmax(x[2][c], x[3][c]));
+        unsigned long long *mx = rg == 0 ? slice_ptr(jobs.mx, z) : jobs.mx[NSLICE_SRC];
+        atomicMax(mx + n, (unsigned long long)__double_as_longlong(m));
     }
 }
 
@@ -103,47 +113,60 @@ k_colmax(SliceSrc src, int K, int n_g) {
 // reduction's FP32 sums of their exact products are the same numbers.
 template <bool BF>
 __global__ void __launch_bounds__(256)
-k_slice(SliceSrc src, int K, int n_g, int groups) {
+k_slice(SliceJobs jobs, int K, int n_g, int groups) {
+    const int z = blockIdx.y;
+    const double2 *X = slice_ptr(jobs.X, z);
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
     const int g = (int)(idx / n_g);
     if (g >= groups) return;
-    const double sc = ldexp(1.0, -col_exp(src.mx, n));
-    double x[8];
+    double2 raw[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int k = 4 * g + q;
-        double2 v = {0.0, 0.0};
-        if (k < K) v = slice_src_row(src, k, n_g, n);
-        x[2 * q] = v.x * sc;
-        x[2 * q + 1] = v.y * sc;
+        raw[q] = double2{0.0, 0.0};
+        if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const long long plane = (long long)groups * n_g * 8;   // halves per slice
-    _Float16 *out = src.S + ((long long)g * n_g + n) * 8;
+    const auto cut = [&](const unsigned long long *mx, _Float16 *S, bool scaled)
+                         __attribute__((always_inline)) {
+        const double sc = ldexp(1.0, -col_exp(mx, n));
+        double x[8];
 #pragma unroll
-    for (int s = 0; s < NSL; ++s) {
-        h8 h;
-        unsigned short b[8];
+        for (int q = 0; q < 4; ++q) {
+            const int k = 4 * g + q;
+            const double2 v = scaled && k < K ? slice_scaled(jobs, raw[q], k) : raw[q];
+            x[2 * q] = v.x * sc;
+            x[2 * q + 1] = v.y * sc;
+        }
+        const long long plane = (long long)groups * n_g * 8;   // halves per slice
+        _Float16 *out = S + ((long long)g * n_g + n) * 8;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const double t = x[j] * (double)(1 << (s == 0 ? SBITS1 : SBITS));
-            const double sig = rint(t);
-            x[j] = t - sig;
-            h[j] = (_Float16)sig;
-            // BF16 of an integer of at most 9 bits: the float's upper half, exactly
-            b[j] = (unsigned short)(__builtin_bit_cast(unsigned, (float)sig) >> 16);
+        for (int s = 0; s < NSL; ++s) {
+            h8 h;
+            unsigned short b[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const double t = x[j] * (double)(1 << (s == 0 ? SBITS1 : SBITS));
+                const double sig = rint(t);
+                x[j] = t - sig;
+                h[j] = (_Float16)sig;
+                // BF16 of an integer of at most 9 bits: the float's upper half, exactly
+                b[j] = (unsigned short)(__builtin_bit_cast(unsigned, (float)sig) >> 16);
+            }
+            if constexpr (BF) {
+                uint4 w;
+                w.x = b[0] | ((unsigned)b[1] << 16);
+                w.y = b[2] | ((unsigned)b[3] << 16);
+                w.z = b[4] | ((unsigned)b[5] << 16);
+                w.w = b[6] | ((unsigned)b[7] << 16);
+                *reinterpret_cast<uint4 *>(out + s * plane) = w;
+            } else {
+                *reinterpret_cast<h8 *>(out + s * plane) = h;
+            }
         }
-        if constexpr (BF) {
-            uint4 w;
-            w.x = b[0] | ((unsigned)b[1] << 16);
-            w.y = b[2] | ((unsigned)b[3] << 16);
-            w.z = b[4] | ((unsigned)b[5] << 16);
-            w.w = b[6] | ((unsigned)b[7] << 16);
-            *reinterpret_cast<uint4 *>(out + s * plane) = w;
-        } else {
-            *reinterpret_cast<h8 *>(out + s * plane) = h;
-        }
-    }
+    };
+    cut(slice_ptr(jobs.mx, z), slice_ptr(jobs.S, z), false);
+    if (z == 1) cut(jobs.mx[NSLICE_SRC], jobs.S[NSLICE_SRC], true);
 }
 
 // ---------------------------------------------------------------------------
@@ -456,36 +479,49 @@ __device__ __forceinline__ int col_exp8(const unsigned long long *mx, int n) {
 // One thread per (group of 8 complex rows, column): 16 interleaved real
 // values -> 5 slices of 16 int8, written to S8[s][g][n][0..15].
 __global__ void __launch_bounds__(256)
-k_slice8(SliceSrc src, int K, int n_g, int groups) {
+k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
+    const int z = blockIdx.y;
+    const double2 *X = slice_ptr(jobs.X, z);
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
     const int g = (int)(idx / n_g);
     if (g >= groups) return;
-    const double sc = ldexp(1.0, -col_exp8(src.mx, n));
-    double x[16];
+    double2 raw[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int k = 8 * g + q;
-        double2 v = {0.0, 0.0};
-        if (k < K) v = slice_src_row(src, k, n_g, n);
-        x[2 * q] = v.x * sc;
-        x[2 * q + 1] = v.y * sc;
+        raw[q] = double2{0.0, 0.0};
+        if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const long long plane = (long long)groups * n_g;   // 16-byte items per slice
-    uint4 *out = reinterpret_cast<uint4 *>(src.S) + (long long)g * n_g + n;
+    const auto cut = [&](const unsigned long long *mx, _Float16 *S, bool scaled)
+                         __attribute__((always_inline)) {
+        const double sc = ldexp(1.0, -col_exp8(mx, n));
+        double x[16];
 #pragma unroll
-    for (int s = 0; s < NSL8; ++s) {
-        unsigned w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const double t = x[j] * 128.0;
-            double sig = rint(t);
-            sig = fmin(fmax(sig, -127.0), 127.0);
-            x[j] = t - sig;
-            w[j >> 2] |= ((unsigned)(int)sig & 0xffu) << (8 * (j & 3));
+        for (int q = 0; q < 8; ++q) {
+            const int k = 8 * g + q;
+            const double2 v = scaled && k < K ? slice_scaled(jobs, raw[q], k) : raw[q];
+            x[2 * q] = v.x * sc;
+            x[2 * q + 1] = v.y * sc;
         }
-        out[s * plane] = uint4{w[0], w[1], w[2], w[3]};
-    }
+        const long long plane = (long long)groups * n_g;   // 16-byte items per slice
+        uint4 *out = reinterpret_cast<uint4 *>(S) + (long long)g * n_g + n;
+#pragma unroll
+        for (int s = 0; s < NSL8; ++s) {
+            unsigned w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const double t = x[j] * 128.0;
+                double sig = rint(t);
+                sig = fmin(fmax(sig, -127.0), 127.0);
+                x[j] = t - sig;
+                w[j >> 2] |= ((unsigned)(int)sig & 0xffu) << (8 * (j & 3));
+            }
+            out[s * plane] = uint4{w[0], w[1], w[2], w[3]};
+        }
+    };
+    cut(slice_ptr(jobs.mx, z), slice_ptr(jobs.S, z), false);
+    if (z == 1) cut(jobs.mx[NSLICE_SRC], jobs.S[NSLICE_SRC], true);
 }
 
 struct Split8Seg {
@@ -697,26 +733,26 @@ size_t split_slice_bytes(int K, int n_g) {
     return (size_t)NSL * groups * n_g * 16;
 }
 
-hipError_t launch_colmax(const SliceSrc &src, int K, int n_g, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_u64, dim3((n_g + 255) / 256), dim3(256), 0, st, src.mx, n_g);
+hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_u64, dim3((n_g + 255) / 256, NSLICE_SRC + 1), dim3(256), 0, st,
+                       jobs, n_g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colmax, dim3((n_g + 63) / 64, (K + CROWS - 1) / CROWS), dim3(256), 0, st,
-                       src, K, n_g);
+    hipLaunchKernelGGL(k_colmax, dim3((n_g + 63) / 64, (K + CROWS - 1) / CROWS, NSLICE_SRC),
+                       dim3(256), 0, st, jobs, K, n_g);
     return hipGetLastError();
 }
 
-hipError_t launch_slice(const SliceSrc &src, int K, int n_g, hipStream_t st, bool bf16) {
+hipError_t launch_slice(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool bf16) {
     const int groups = (K + 15) / 16 * 4;
-    hipError_t e = launch_colmax(src, K, n_g, st);
+    hipError_t e = launch_colmax(jobs, K, n_g, st);
     if (e != hipSuccess) return e;
     const long long items = (long long)groups * n_g;
+    const dim3 grid((unsigned)((items + 255) / 256), NSLICE_SRC);
     if (bf16)
-        hipLaunchKernelGGL(k_slice<true>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st,
-                           src, K, n_g, groups);
+        hipLaunchKernelGGL(k_slice<true>, grid, dim3(256), 0, st, jobs, K, n_g, groups);
     else
-        hipLaunchKernelGGL(k_slice<false>, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st,
-                           src, K, n_g, groups);
+        hipLaunchKernelGGL(k_slice<false>, grid, dim3(256), 0, st, jobs, K, n_g, groups);
     return hipGetLastError();
 }
 
@@ -745,13 +781,13 @@ size_t split8_slice_bytes(int K, int n_g) {
     return (size_t)NSL8 * groups * n_g * 16;
 }
 
-hipError_t launch_slice8(const SliceSrc &src, int K, int n_g, hipStream_t st) {
+hipError_t launch_slice8(const SliceJobs &jobs, int K, int n_g, hipStream_t st) {
     const int groups = (K + 31) / 32 * GRP8;
-    hipError_t e = launch_colmax(src, K, n_g, st);
+    hipError_t e = launch_colmax(jobs, K, n_g, st);
     if (e != hipSuccess) return e;
     const long long items = (long long)groups * n_g;
-    hipLaunchKernelGGL(k_slice8, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, src, K,
-                       n_g, groups);
+    hipLaunchKernelGGL(k_slice8, dim3((unsigned)((items + 255) / 256), NSLICE_SRC), dim3(256), 0, st,
+                       jobs, K, n_g, groups);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // Device helpers shared by the split-precision reductions (k_split.hip) and
-// the modular INT8 form (k_crt.hip): the sliced operand's rows, column
+// the modular INT8 form (k_crt.hip): the sliced operands' values, column
 // exponents, the (Re, Im) -> (Im, -Re) byte-pair form and the banded
 // lower-triangle tile order.
 #pragma once
@@ -8,15 +8,21 @@
 
 namespace hs {
 
-// Row k, column n of a sliced operand, optionally scaled by sqrt(rscale[k]).
-__device__ __forceinline__ double2 slice_src_row(const SliceSrc &src, int k, int n_g, int n) {
-    double2 v = src.X[(long long)k * n_g + n];
-    if (src.rscale) {
-        const double w = sqrt(src.rscale[k]);
-        v.x *= w;
-        v.y *= w;
-    }
-    return v;
+// v[z], formed arithmetically (a dynamic index into the argument block would
+// copy it to scratch memory).
+template <class T, int N>
+__device__ __forceinline__ T *slice_ptr(T *const (&v)[N], int z) {
+    const uintptr_t base = reinterpret_cast<uintptr_t>(v[0]);
+    uintptr_t p = base;
+#pragma unroll
+    for (int i = 1; i < N; ++i) p += z == i ? reinterpret_cast<uintptr_t>(v[i]) - base : 0;
+    return reinterpret_cast<T *>(p);
+}
+
+// Element v of row k of X[1] as operand 4.
+__device__ __forceinline__ double2 slice_scaled(const SliceJobs &jobs, double2 v, int k) {
+    const double w = sqrt(jobs.rscale[k]);
+    return double2{v.x * w, v.y * w};
 }
 
 // exponent e with column max < 2^e (0 for an all-zero column)

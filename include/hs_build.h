@@ -174,7 +174,8 @@ typedef struct {
        [0] start, [1] after the operand preparation, [2] after the per-atom
        products and the Cholesky factorizations beside them, [3] after the
        large lower-triangle reductions of H and S, [4] after the conjugate
-       mirroring (end of the build). */
+       mirroring (end of the build; the FP64 forms write both triangles at
+       once, so that [4] follows [3] directly). */
     void **phase_events;
     /* 0: the per-atom products with one tile shape for all atoms (the largest
        N_L decides). 1: batched form - one persistent launch runs every atom's

@@ -13,6 +13,23 @@
 
 namespace hs {
 
+// Consecutive blocks of a launch go to the 8 XCDs in turn. Of n items (H's
+// `first` ones, then S's) XCD x takes a contiguous run of H's and one of S's,
+// H's before S's, so that the blocks resident on one XCD share operand panels
+// through its L2 and all XCDs work on the same output; every XCD gets n / 8
+// items, up to rounding.
+__host__ __device__ inline int xcd_blocks(int n) { return (n + 7) / 8 * 8; }
+// Item of block b < xcd_blocks(n), or -1.
+__device__ __forceinline__ int xcd_item(int b, int n, int first) {
+    const long long x = b % 8;
+    const int i = b / 8;
+    const int nf = n < first ? n : first;
+    const int h0 = (int)(x * nf / 8), h1 = (int)((x + 1) * nf / 8);
+    const int c0 = (int)(x * n / 8), c1 = (int)((x + 1) * n / 8);
+    if (i >= c1 - c0) return -1;
+    return i < h1 - h0 ? h0 + i : first + (c0 - h0) + i - (h1 - h0);
+}
+
 // Device-side description of the atoms of one build.
 struct Atoms {
     const int *row_off;  // [N_A+1] first row of each atom in A, B, U, X, Y

@@ -172,13 +172,20 @@ k_slice(SliceJobs jobs, int K, int n_g, int groups) {
 // ---------------------------------------------------------------------------
 // Slice GEMM over lower-triangle tiles of H and S.
 
-constexpr int SBM = 64;                 // tile rows (g')
-constexpr int SBN = 64;                 // tile cols (g)
-constexpr int SWM = 2, SWN = 4;         // waves
-constexpr int SNT = 64 * SWM * SWN;
-constexpr int SWTM = SBM / SWM, SWTN = SBN / SWN;   // wave tile
-constexpr int STM = SWTM / 16;          // 16-row blocks per wave
-constexpr int STN = SWTN / 16;          // 16-col blocks per wave
+// Tile shapes: 64 x 64, and for the tiles of an unfilled last round (all of
+// them when they are few) 64 x 32 halves, on the same 8 waves. split_plan says
+// how many.
+constexpr int SNT = 512;
+constexpr int SBM = 64;   // tile rows
+template <int BN_, int WM_, int WN_>
+struct SplitTile {
+    static constexpr int BN = BN_, WM = WM_, WN = WN_;             // tile columns, waves
+    static constexpr int TM = SBM / WM / 16, TN = BN / WN / 16;    // 16 x 16 blocks per wave
+    static constexpr int PER = 64 / BN;                            // slices of Q per 64-lane load
+    static_assert(SBM % (16 * WM) == 0 && BN % (16 * WN) == 0 && WM * WN == 8, "wave tiling");
+};
+using SplitWhole = SplitTile<64, 2, 4>;
+using SplitHalf = SplitTile<32, 4, 2>;
 constexpr int SGRP = 4;                 // groups (of 4 complex rows) per stage = 16 rows
 constexpr int FLUSH = 4;                // stages per flush
 // exactness of the two leading levels between flushes (2 * 16 * FLUSH real
@@ -189,10 +196,15 @@ static_assert((32 * FLUSH) == (1 << ilog2(32 * FLUSH)), "FLUSH is a power of two
 static_assert(2 * SBITS1 + ilog2(32 * FLUSH) <= 24, "level 2 exact in FP32");
 static_assert(SBITS1 + SBITS - 1 + 1 + ilog2(32 * FLUSH) <= 24, "level 3 exact in FP32");
 constexpr int SBAND = 8;
-// LDS per operand per stage: NSL slices x SGRP groups x 64 columns x 16 B
-constexpr int LDS_OP = NSL * SGRP * 64;   // in units of 16 B
-static_assert(SBM == 64 && SBN == 64, "loader assumes 64-column tiles");
-static_assert(SWTM % 16 == 0 && SWTN % 16 == 0, "wave tiling");
+// LDS items (16 B) per stage: P, then Q
+constexpr int SPLIT_P = NSL * SGRP * SBM;
+template <class C>
+constexpr int SPLIT_STAGE = SPLIT_P + NSL * SGRP * C::BN;
+
+// Time of a half tile, in whole tiles (all in halves 78.9 against 107 TFLOP/s
+// FP64-equivalent at N_G = 3893, K = 4096). With the last round in halves:
+// 79.7 -> 86.7 TFLOP/s at N_G = 1501, 54 -> 62 at 1000, 24 -> 32 at 500 (K = 1024).
+constexpr double SPLIT_HALF_COST = 0.68;
 
 struct SplitSeg {
     const _Float16 *P, *Q;                  // slices [NSL][groups][n_g][8]
@@ -204,45 +216,58 @@ struct SplitArgs {
     SplitSeg s[2];
     double2 *H, *S;
     int n_g, groups;         // groups = K padded to 16, over 4
-    int nt, ntri, ntri8;
+    SplitPlan plan;
 };
 
+template <class C>
 struct Acc64 {
-    double re[STM][STN][4];
-    double im[STM][STN][4];
+    double re[C::TM][C::TN][4];
+    double im[C::TM][C::TN][4];
 };
 
 // One (P, Q) segment into the FP64 accumulators (BF: BF16 slices on BF16
 // MFMA). The segment is taken by
 // value: a reference into the by-value kernel argument would move the whole
 // argument block into scratch memory.
-template <bool BF>
+template <class C, bool BF>
 __device__ __forceinline__ void split_segment(const SplitSeg sg, int n_g, int groups, int m0,
-                                              int n0, Acc64 &acc, uint4 *lds) {
+                                              int n0, Acc64<C> &acc, uint4 *lds) {
+    constexpr int STM = C::TM, STN = C::TN, SWTM = SBM / C::WM, SWTN = C::BN / C::WN;
+    constexpr int STAGE = SPLIT_STAGE<C>;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % SWM, wn = wave / SWM;
+    const int wm = wave % C::WM, wn = wave / C::WM;
 
     const long long plane = (long long)groups * n_g;   // 16-byte items per slice
     const int nstage = groups / SGRP;
-    // direct global -> LDS loads, 64 columns each: wave w loads group w % 4
-    // of every slice of operand w / 4 (P for waves 0-3, Q for 4-7); columns
-    // past the edge read the last column (they only feed outputs past N_G)
-    static_assert(SNT == 512 && SGRP == 4, "direct loader assumes 8 waves, 4 groups");
-    const int grp_w = wave % SGRP, op_w = wave / SGRP;
-    int ldc = (op_w == 0 ? m0 : n0) + lane;
+    // direct global -> LDS loads, 64 items each: wave w loads group w % 4 of
+    // every slice of operand w / 4 (P for waves 0-3, Q for 4-7; C::PER slices
+    // of Q per load); columns past the edge read the last column (they only
+    // feed outputs past N_G)
+    static_assert(SNT == 512 && SGRP == 4 && SBM == 64 && NSL % C::PER == 0, "8 waves, 4 groups");
+    const int grp_w = wave % SGRP;
+    const bool isq = wave >= SGRP;
+    int ldc = isq ? n0 + lane % C::BN : m0 + lane;
     ldc = ldc < n_g ? ldc : n_g - 1;
     const unsigned ldvo = (unsigned)ldc * 16u;
-    const uint4 *ldrows = reinterpret_cast<const uint4 *>(op_w == 0 ? sg.P : sg.Q);
+    const uint4 *ldrows = reinterpret_cast<const uint4 *>(isq ? sg.Q : sg.P);
+    const long long second = C::PER > 1 ? (lane / C::BN) * plane : 0;   // Q's further slices
     auto issue = [&](uint4 *buf, int st) __attribute__((always_inline)) {
         const uint4 *rows = ldrows + (long long)(st * SGRP + grp_w) * n_g;
-        uint4 *dst = buf + op_w * LDS_OP + grp_w * 64;
-#pragma unroll
-        for (int s = 0; s < NSL; ++s)
+        uint4 *dst = buf + (isq ? SPLIT_P : 0) + grp_w * 64;
+        auto load = [&](const uint4 *row, int s) __attribute__((always_inline)) {
             __builtin_amdgcn_global_load_lds(
-                reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(rows + s * plane) + ldvo),
+                reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(row) + ldvo),
                 dst + s * SGRP * 64, 16, 0, 0);
+        };
+        if (C::PER == 1 || !isq) {
+#pragma unroll
+            for (int s = 0; s < NSL; ++s) load(rows + s * plane, s);
+        } else {
+#pragma unroll
+            for (int s = 0; s < NSL / C::PER; ++s) load(rows + s * C::PER * plane + second, s);
+        }
     };
 
     // column scales of this lane's accumulator rows (g') and columns (g),
@@ -304,7 +329,7 @@ __device__ __forceinline__ void split_segment(const SplitSeg sg, int n_g, int gr
 #pragma unroll
             for (int i = 0; i < STM; ++i) a[i][s] = lp[(s * SGRP + lg) * 64 + wm * SWTM + i * 16 + lc];
 #pragma unroll
-            for (int j = 0; j < STN; ++j) bre[j][s] = lq[(s * SGRP + lg) * 64 + wn * SWTN + j * 16 + lc];
+            for (int j = 0; j < STN; ++j) bre[j][s] = lq[(s / C::PER * SGRP + lg) * 64 + s % C::PER * C::BN + wn * SWTN + j * 16 + lc];
         }
 #pragma unroll
         for (int t = 0; t < NSL; ++t)
@@ -362,65 +387,66 @@ __device__ __forceinline__ void split_segment(const SplitSeg sg, int n_g, int gr
         auto stage = [&](const uint4 *__restrict__ cur, uint4 *__restrict__ nxt)
                          __attribute__((always_inline)) {
             if (st + 1 < nstage) issue(nxt, st + 1);
-            compute(cur, cur + LDS_OP);
+            compute(cur, cur + SPLIT_P);
         };
-        stage(lds + (st & 1) * 2 * LDS_OP, lds + ((st + 1) & 1) * 2 * LDS_OP);
+        stage(lds + (st & 1) * STAGE, lds + ((st + 1) & 1) * STAGE);
         if ((st + 1) % FLUSH == 0 || st + 1 == nstage) flush();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
 }
 
-template <bool BF>
-__global__ void __launch_bounds__(SNT)
-k_split_reduce(SplitArgs args) {
-    __shared__ uint4 lds[2 * 2 * LDS_OP];   // 2 buffers x (P, Q)
-
-    int b = blockIdx.x;
-    const bool isH = b < args.ntri8;
-    if (!isH) b -= args.ntri8;
-    const int per_xcd = args.ntri8 / 8;
-    const int t = (b % 8) * per_xcd + b / 8;
-    if (t >= args.ntri) return;
-    int ti, tj;
-    sband_tile(t, args.nt, ti, tj, SBAND);
-    if (ti < 0) return;
-    const int m0 = ti * SBM, n0 = tj * SBN;
+template <class C, bool BF>
+__device__ __forceinline__ void split_tile(const SplitArgs &args, bool isH, int m0, int n0,
+                                           uint4 *lds) {
     const int n_g = args.n_g;
-
-    Acc64 acc;
+    if (n0 >= n_g) return;
+    Acc64<C> acc;
 #pragma unroll
-    for (int i = 0; i < STM; ++i)
+    for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-        for (int j = 0; j < STN; ++j)
+        for (int j = 0; j < C::TN; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc.re[i][j][v] = acc.im[i][j][v] = 0.0;
 
     if (isH) {
         const SplitSeg h0 = args.h[0], h1 = args.h[1];
-        split_segment<BF>(h0, n_g, args.groups, m0, n0, acc, lds);
-        split_segment<BF>(h1, n_g, args.groups, m0, n0, acc, lds);
+        split_segment<C, BF>(h0, n_g, args.groups, m0, n0, acc, lds);
+        split_segment<C, BF>(h1, n_g, args.groups, m0, n0, acc, lds);
     } else {
         const SplitSeg s0 = args.s[0], s1 = args.s[1];
-        split_segment<BF>(s0, n_g, args.groups, m0, n0, acc, lds);
-        split_segment<BF>(s1, n_g, args.groups, m0, n0, acc, lds);
+        split_segment<C, BF>(s0, n_g, args.groups, m0, n0, acc, lds);
+        split_segment<C, BF>(s1, n_g, args.groups, m0, n0, acc, lds);
     }
 
     double2 *out = isH ? args.H : args.S;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave % SWM, wn = wave / SWM;
+    const int wm = wave % C::WM, wn = wave / C::WM;
 #pragma unroll
-    for (int j = 0; j < STN; ++j) {
-        const int g = n0 + wn * SWTN + j * 16 + (lane & 15);
+    for (int j = 0; j < C::TN; ++j) {
+        const int g = n0 + wn * (C::BN / C::WN) + j * 16 + (lane & 15);
 #pragma unroll
-        for (int i = 0; i < STM; ++i)
+        for (int i = 0; i < C::TM; ++i)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int gp = m0 + wm * SWTM + i * 16 + 4 * (lane >> 4) + v;
+                const int gp = m0 + wm * (SBM / C::WM) + i * 16 + 4 * (lane >> 4) + v;
                 if (gp < n_g && g <= gp)
                     out[(long long)gp * n_g + g] = double2{acc.re[i][j][v], acc.im[i][j][v]};
             }
     }
+}
+
+template <bool BF>
+__global__ void __launch_bounds__(SNT)
+k_split_reduce(SplitArgs args) {
+    __shared__ uint4 lds[2 * SPLIT_STAGE<SplitWhole>];   // 2 buffers
+
+    const SplitPlace p = split_place(args.plan, blockIdx.x, SBAND);
+    if (p.ti < 0) return;
+    if (p.half < 0)
+        split_tile<SplitWhole, BF>(args, p.isH, p.ti * 64, p.tj * 64, lds);
+    else
+        split_tile<SplitHalf, BF>(args, p.isH, p.ti * 64, p.tj * 64 + 32 * p.half, lds);
 }
 
 
@@ -768,11 +794,10 @@ hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
     a.S = S;
     a.n_g = n_g;
     a.groups = (K + 15) / 16 * 4;
-    a.nt = (n_g + SBM - 1) / SBM;
-    a.ntri = a.nt * (a.nt + 1) / 2;
-    a.ntri8 = (a.ntri + 7) / 8 * 8;
-    if (bf16) hipLaunchKernelGGL(k_split_reduce<true>, dim3(2 * a.ntri8), dim3(SNT), 0, st, a);
-    else hipLaunchKernelGGL(k_split_reduce<false>, dim3(2 * a.ntri8), dim3(SNT), 0, st, a);
+    a.plan = split_plan(n_g, num_cus(), SPLIT_HALF_COST);
+    const dim3 grid(split_blocks(a.plan));
+    if (bf16) hipLaunchKernelGGL(k_split_reduce<true>, grid, dim3(SNT), 0, st, a);
+    else hipLaunchKernelGGL(k_split_reduce<false>, grid, dim3(SNT), 0, st, a);
     return hipGetLastError();
 }
 

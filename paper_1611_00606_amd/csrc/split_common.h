@@ -75,4 +75,57 @@ __device__ __forceinline__ void sband_tile(int t, int nt, int &ti, int &tj, int 
     }
 }
 
+// Tiles of H and S over the lower triangle of nt x nt 64-tiles, H's first in
+// banded order, then S's: the first `whole` as 64-tiles, the others as two
+// 64 x 32 halves each.
+struct SplitPlan {
+    int nt, ntri, whole;
+};
+inline unsigned split_blocks(const SplitPlan &p) {
+    return (unsigned)(xcd_blocks(p.whole) + 2 * (2 * p.ntri - p.whole));
+}
+// The split with the earliest end when a half takes `half` of a whole tile's
+// time and the compute units take them in turn: all whole, whole rounds only,
+// or none.
+inline SplitPlan split_plan(int n_g, int cus, double half) {
+    SplitPlan p;
+    p.nt = (n_g + 63) / 64;
+    p.ntri = p.nt * (p.nt + 1) / 2;
+    const int all = 2 * p.ntri;
+    double best = -1.0;
+    for (int w : {all, all / cus * cus, 0}) {
+        const double t = (w + cus - 1) / cus + (2 * (all - w) + cus - 1) / cus * half;
+        if (best < 0.0 || t < best) {
+            best = t;
+            p.whole = w;
+        }
+    }
+    return p;
+}
+// Tile of block b: (ti, tj), half 0 or 1 of its columns or -1 for all of them;
+// ti < 0: none.
+struct SplitPlace {
+    bool isH;
+    int ti, tj, half;
+};
+__device__ __forceinline__ SplitPlace split_place(const SplitPlan &p, int b, int band) {
+    SplitPlace r;
+    int t;
+    r.half = -1;
+    if (b < xcd_blocks(p.whole)) {
+        t = xcd_item(b, p.whole, p.ntri);
+        if (t < 0) {
+            r.ti = -1;
+            return r;
+        }
+    } else {
+        b -= xcd_blocks(p.whole);
+        t = p.whole + (b >> 1);
+        r.half = b & 1;
+    }
+    r.isH = t < p.ntri;
+    sband_tile(r.isH ? t : t - p.ntri, p.nt, r.ti, r.tj, band);
+    return r;
+}
+
 }  // namespace hs

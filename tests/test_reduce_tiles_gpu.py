@@ -55,3 +55,27 @@ def test_tile_edges(n_g, mode):
 def test_stage_edges(K, mode):
     _check([K], 70, mode, seed=K)
     _check([K], 1500, mode, seed=100 + K, batch=1)
+
+
+@pytest.mark.parametrize("mode", [1, 2, 4, 5], ids=["f16", "i8", "bf16", "crt"])
+@pytest.mark.parametrize("n_g", [1, 31, 33, 64, 65, 97, 129, 500, 1501])
+def test_split_tile_edges(n_g, mode):
+    """The split forms' whole and half tiles, against their bound of 1e-9 (the
+    slices keep 2^-35 of the operand column maxima per term)."""
+    import torch
+    from paper_1611_00606_amd import DeviceBuild
+    nl = [5, 16, 2]
+    p = make_problem(len(nl), nl, n_g, seed=n_g)
+    print(f"case N_G={n_g} mode={mode}", flush=True)
+    r = DeviceBuild.from_problem(p, mode=mode)
+    nan = complex(np.nan, np.nan)
+    r.H.fill_(nan)
+    r.S.fill_(nan)
+    r.run()
+    torch.cuda.synchronize()
+    H, S, _ = r.results()
+    Hr = oracle.hamiltonian(p.A, p.B, p.T_AA, p.T_AB, p.T_BB, p.nl)
+    Sr = oracle.overlap(p.A, p.B, p.U, p.nl)
+    assert np.linalg.norm(H - Hr) <= 1e-9 * np.linalg.norm(Hr)
+    assert np.linalg.norm(S - Sr) <= 1e-9 * np.linalg.norm(Sr)
+    assert np.array_equal(H, H.conj().T) and np.array_equal(S, S.conj().T)

@@ -12,19 +12,22 @@
 //
 // Only lower-triangle tiles are computed; a tile's epilogue also writes its
 // conjugate transpose and Im(diagonal) = 0, so the outputs need no further
-// pass. Three tile sizes share one launch (one 8-wave block per CU, the same
-// LDS), because a 128 x 128 tile takes 0.45 us of a CU per contraction row
+// pass. Three tile sizes share one launch (8-wave blocks of the same LDS),
+// because a 128 x 128 tile takes 0.45 us of a CU per contraction row
 // and 16 K N_G^2 operations rarely make a whole number of rounds of them:
 //   128 x 128  the tiles strictly below the diagonal, first;
 //    64 x  64  the diagonal blocks (3 of 4 quarters), the ragged last rows,
 //              and the 128-tiles that would start an unfilled last round;
 //    32 x  32  the 64-tiles that would start an unfilled last round.
-// make_plan chooses how many of each from their measured costs. (All in
-// 128-tiles the build of 32 atoms of N_L = 49 at N_G = 2000 took 3.17 ms, two
-// rounds for 272 tiles on 256 compute units; now 1.98 ms. The smallest
-// build, 4 atoms of 16 at N_G = 256: 87 us, 30 us now. N_G = 8000: 124.7 ms,
-// 122.9 ms now, of which the mirroring pass was 0.4 ms.) All three add an output's contraction rows in the same order, so the bits of H and S
-// do not depend on the split.
+// make_plan chooses how many of each from their measured costs, and whether
+// one block has a compute unit to itself or two share it, each with half the
+// LDS and half a 128-tile (128 x 64) at a time. (All in 128-tiles the build of
+// 32 atoms of N_L = 49 at N_G = 2000 took 3.17 ms, two rounds for 272 tiles on
+// 256 compute units; 1.96 ms in blocks of one per unit, 1.82 ms in two. The
+// smallest build, 4 atoms of 16 at N_G = 256: 87 us, 30 us now. N_G = 8000, in
+// one: 124.7 ms, 119.7 ms now, of which the mirroring pass was 0.4 ms.) All add
+// an output's contraction rows in the same order, so the bits of H and S do not
+// depend on the split.
 //
 // The tiles follow a banded order, of which each XCD walks a contiguous run
 // of H's tiles and one of S's, H's first (xcd_item; one run over both outputs,
@@ -43,12 +46,28 @@ namespace hs {
 
 namespace {
 
-using Tile128 = TileCfg<128, 128, 8, 2, 4, 4>;   // 64 x 32 complex outputs per wave
-using Tile64 = TileCfg<64, 64, 16, 2, 4, 4>;     // 32 x 16
-using Tile32 = TileCfg<32, 32, 16, 2, 2, 8>;     // 16 x 16, four waves only load
-constexpr int RED_LDS = Tile128::LDS_ELEMS;
-static_assert(Tile64::LDS_ELEMS <= RED_LDS && Tile32::LDS_ELEMS <= RED_LDS, "one LDS ring");
-constexpr int RED_THREADS = Tile128::NT;
+// One block per compute unit, or two (2 x 72 KB of LDS, 128 registers a lane).
+template <bool TWO>
+struct Tiles {
+    using T128 = TileCfg<128, 128, 8, 2, 4, 4>;   // 64 x 32 complex outputs per wave
+    using T64 = TileCfg<64, 64, 16, 2, 4, 4>;     // 32 x 16
+    using T32 = TileCfg<32, 32, 16, 2, 2, 8>;     // 16 x 16, four waves only load
+    static constexpr int PARTS = 1;               // blocks per 128-tile
+};
+template <>
+struct Tiles<true> {
+    using T128 = TileCfg<128, 64, 8, 4, 2, 3>;    // 32 x 32
+    using T64 = TileCfg<64, 64, 8, 2, 4, 4>;
+    using T32 = TileCfg<32, 32, 16, 2, 2, 4>;
+    static constexpr int PARTS = 2;
+};
+template <class T>
+constexpr int red_lds() {
+    static_assert(T::T64::LDS_ELEMS <= T::T128::LDS_ELEMS && T::T32::LDS_ELEMS <= T::T128::LDS_ELEMS,
+                  "one LDS ring");
+    return T::T128::LDS_ELEMS;
+}
+constexpr int RED_THREADS = Tiles<false>::T128::NT;
 constexpr int BAND = 4;   // tile columns per band of the tile order
 
 struct RedArgs {
@@ -92,7 +111,7 @@ __device__ __forceinline__ void band_tile(int t, int nt, int &ti, int &tj) {
     }
 }
 
-// One C::BM x C::BM tile of H or S at rows m0, columns n0 (multiples of C::BM).
+// One C::BM x C::BN tile of H or S at rows m0, columns n0 (multiples of C::BN).
 template <class C, bool G3>
 __device__ __forceinline__ void reduce_tile(const RedArgs &args, bool isH, int m0, int n0,
                                             double2 *lds) {
@@ -148,19 +167,22 @@ __device__ __forceinline__ void reduce_tile(const RedArgs &args, bool isH, int m
         }
 }
 
-template <bool G3>
-__global__ void __launch_bounds__(RED_THREADS)
+template <bool G3, bool TWO>
+__global__ void __launch_bounds__(RED_THREADS) __attribute__((amdgpu_waves_per_eu(TWO ? 4 : 2)))
 k_reduce(RedArgs args) {
-    __shared__ double2 lds[RED_LDS];
+    using T = Tiles<TWO>;
+    __shared__ double2 lds[red_lds<T>()];
 
     int b = blockIdx.x;
     if (b < args.b128) {
-        const int q = xcd_item(b, args.n128, args.nlow);
+        int q = xcd_item(b, T::PARTS * args.n128, T::PARTS * args.nlow);
         if (q < 0) return;
+        const int part = q % T::PARTS;
+        q /= T::PARTS;
         const bool isH = q < args.nlow;
         int ti, tj;
         band_tile(isH ? q : q - args.nlow, args.nf, ti, tj);
-        reduce_tile<Tile128, G3>(args, isH, ti * 128, tj * 128, lds);
+        reduce_tile<typename T::T128, G3>(args, isH, ti * 128, tj * 128 + part * T::T128::BN, lds);
         return;
     }
     b -= args.b128;
@@ -204,12 +226,12 @@ k_reduce(RedArgs args) {
         }
     }
     if (whole)
-        reduce_tile<Tile64, G3>(args, isH, I * 64, J * 64, lds);
+        reduce_tile<typename T::T64, G3>(args, isH, I * 64, J * 64, lds);
     else
-        reduce_tile<Tile32, G3>(args, isH, I * 64 + (sub >> 1) * 32, J * 64 + (sub & 1) * 32, lds);
+        reduce_tile<typename T::T32, G3>(args, isH, I * 64 + (sub >> 1) * 32, J * 64 + (sub & 1) * 32, lds);
 }
 
-// When n tiles of equal cost have been handed to the compute units in turn,
+// When n tiles of equal cost have been handed to slots for a block in turn,
 // each to the first that is free; level: the busy time of groups of them.
 struct Level {
     double t;
@@ -228,41 +250,81 @@ void hand_out(std::vector<Level> &lv, long long n, double cost) {
     }
 }
 
-// How many tiles of each size: the split with the earliest end among a few of
-// each kind. The costs, in 128-tiles of a compute unit's time, are those of a
-// full device at N_G = 8000, K = 8100: all in 64-tiles (32-tiles) the
-// reductions take 1.17 (1.45) times as long as in 128-tiles, in the 3M form
-// 1.22 (1.61) times.
-void make_plan(RedArgs &a, int cus, bool g3) {
+// End of the last block. Of two blocks per compute unit, those left when half
+// the slots are empty have a unit to themselves and run 1.7 times as fast.
+double end_time(std::vector<Level> &lv, int cus, bool two) {
+    std::sort(lv.begin(), lv.end(), [](const Level &a, const Level &b) { return a.t < b.t; });
+    const double end = lv.back().t;
+    if (!two) return end;
+    double half = 0.0;
+    int n = 0;
+    for (const Level &x : lv) {
+        half = x.t;
+        n += x.n;
+        if (n >= cus) break;
+    }
+    return half + (end - half) / 1.7;
+}
+
+// Costs of the tiles, in units of a compute unit's time for a row of a
+// 128-tile in blocks of one per unit: per row the 128-tile, and the 64- and
+// 32-tiles by area, from a full device at N_G = 8000, K = 8100 (116.0 ms in
+// 128-tiles; in two blocks per unit 118.4 in halves of them, 133.0 in 64-tiles,
+// 150.6 in 32-tiles); per tile 20 rows (10 us) to fill the ring and to write.
+struct Costs {
+    double c128, c64, c32;
+};
+constexpr Costs COSTS_ONE = {1.0, 1.17, 1.45}, COSTS_TWO = {1.02, 1.14, 1.30},
+                COSTS_ONE_3M = {1.0, 1.22, 1.61};
+constexpr double TILE_ROWS = 20.0;
+
+// How many tiles of each size, and whether in one or two blocks per compute
+// unit (true): the split with the earliest end among a few of each kind. Two
+// blocks cover each other's first loads and last stores and end more evenly,
+// one block loads each operand less often: (ms, one / two) N_G = 600 0.153 /
+// 0.140, 2000 1.76 / 1.62, 2500 6.85 / 6.65, 3000 8.62 / 8.96, 8000 116.0 /
+// 118.4; the estimates are within 3% of most measured times. The 3M form's
+// third accumulator leaves no room for two.
+bool make_plan(RedArgs &a, int cus, bool g3) {
     const int n64rows = (a.n_g + 63) / 64;
     a.nf = a.n_g / 128;
     a.nlow = a.nf * (a.nf - 1) / 2;
     a.nedge = 3 * a.nf;
     for (int i = 2 * a.nf; i < n64rows; ++i) a.nedge += i + 1;
-    const double c64 = (g3 ? 1.22 : 1.17) / 4, c32 = (g3 ? 1.61 : 1.45) / 16;
     const int all = 2 * a.nlow;
+    const double rows = 2.0 * a.K;
     double best = -1.0;
-    for (int k = 0; k < 4; ++k) {   // all 128-tiles, the whole rounds of them, one fewer, none
-        const int f = k == 0 ? all : k == 3 ? 0 : std::max(0, all / cus - (k - 1)) * cus;
-        const int rest = 4 * (all - f) + 2 * a.nedge;
-        for (int l = 0; l < 6; ++l) {   // all 64-tiles, up to two rounds fewer, none
-            const int h = l == 5 ? 0 : std::max(0, rest - l * cus / 2);
-            std::vector<Level> lv{Level{(double)(f / cus), cus}};
-            hand_out(lv, f % cus, 1.0);
-            hand_out(lv, h, c64);
-            hand_out(lv, 4 * (rest - h), c32);
-            double end = 0.0;
-            for (const Level &x : lv) end = std::max(end, x.t);
-            if (best < 0.0 || end < best) {
-                best = end;
-                a.n128 = f;
-                a.n64 = h;
-                a.n32 = rest - h;
+    bool best_two = false;
+    std::vector<Level> lv;
+    for (int parts = 1; parts <= (g3 ? 1 : 2); ++parts) {
+        const bool two = parts == 2;
+        const Costs &c = g3 ? COSTS_ONE_3M : two ? COSTS_TWO : COSTS_ONE;
+        const double t128 = c.c128 * rows + TILE_ROWS;   // a slot's time
+        const double t64 = parts * c.c64 / 4 * rows + TILE_ROWS;
+        const double t32 = parts * c.c32 / 16 * rows + TILE_ROWS;
+        for (int k = 0; k < 4; ++k) {   // all 128-tiles, the whole rounds of them, one fewer, none
+            const int f = k == 0 ? all : k == 3 ? 0 : std::max(0, all / cus - (k - 1)) * cus;
+            const int rest = 4 * (all - f) + 2 * a.nedge;
+            for (int l = 0; l < 6; ++l) {   // all 64-tiles, up to two rounds fewer, none
+                const int h = l == 5 ? 0 : std::max(0, rest - l * cus / 2);
+                lv.assign(1, Level{f / cus * t128, parts * cus});
+                hand_out(lv, parts * (f % cus), t128);
+                hand_out(lv, h, t64);
+                hand_out(lv, 4LL * (rest - h), t32);
+                const double end = end_time(lv, cus, two);
+                if (best < 0.0 || end < best) {
+                    best = end;
+                    best_two = two;
+                    a.n128 = f;
+                    a.n64 = h;
+                    a.n32 = rest - h;
+                }
             }
         }
     }
-    a.b128 = xcd_blocks(a.n128);
+    a.b128 = xcd_blocks((best_two ? 2 : 1) * a.n128);
     a.b64 = xcd_blocks(a.n64);
+    return best_two;
 }
 
 // upper := conj(lower) through a 32x32 LDS transpose; Im(diag) := 0.
@@ -309,12 +371,14 @@ hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
     args.H = H;
     args.S = S;
     args.n_g = n_g;
-    make_plan(args, num_cus(), g3);
+    const bool two = make_plan(args, num_cus(), g3);
     const dim3 grid(args.b128 + args.b64 + 4 * args.n32);
     if (g3)
-        hipLaunchKernelGGL(k_reduce<true>, grid, dim3(RED_THREADS), 0, st, args);
+        hipLaunchKernelGGL((k_reduce<true, false>), grid, dim3(RED_THREADS), 0, st, args);
+    else if (two)
+        hipLaunchKernelGGL((k_reduce<false, true>), grid, dim3(RED_THREADS), 0, st, args);
     else
-        hipLaunchKernelGGL(k_reduce<false>, grid, dim3(RED_THREADS), 0, st, args);
+        hipLaunchKernelGGL((k_reduce<false, false>), grid, dim3(RED_THREADS), 0, st, args);
     return hipGetLastError();
 }
 

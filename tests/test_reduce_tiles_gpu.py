@@ -57,6 +57,14 @@ def test_stage_edges(K, mode):
     _check([K], 1500, mode, seed=100 + K, batch=1)
 
 
+@pytest.mark.parametrize("n_g", [1000, 1301, 1501, 2001])
+@pytest.mark.parametrize("K", [63, 64, 65])
+def test_two_blocks_per_unit(K, n_g):
+    """Sizes that take two blocks per compute unit: halves of 128-tiles, 64-
+    and 32-tiles in all of their mixtures."""
+    _check([K], n_g, 0, seed=K + n_g, batch=1)
+
+
 @pytest.mark.parametrize("mode", [1, 2, 4, 5], ids=["f16", "i8", "bf16", "crt"])
 @pytest.mark.parametrize("n_g", [1, 31, 33, 64, 65, 97, 129, 500, 1501])
 def test_split_tile_edges(n_g, mode):

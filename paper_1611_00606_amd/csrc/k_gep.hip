@@ -95,7 +95,9 @@ struct MmArgs {
     const double2 *P, *Q;
     const double2 *P2, *Q2;   // second term, same rectangle and contraction range
     double2 *C;
-    int N;                    // leading dimension of P, Q, C
+    double2 *T;               // or null; with one term: C's elements with one index
+    int w0;                   // below w0 and one not, also as T = C^H
+    int N;                    // leading dimension of P, Q, C, T
     int op;
     int tile;                 // 128, 64 or 32
     int njobs;
@@ -103,11 +105,21 @@ struct MmArgs {
     MmJob job[MM_JOBS];
 };
 
+// The engine's one call for each shape (clang's host pass instantiates a
+// specialization of it for one caller only).
+template <class Cfg, int NSEG, bool G3>
+__device__ __forceinline__ void mm_product(const Segs<NSEG, false> &t, int m0, int i1, int n0,
+                                           int j1, Acc<Cfg> &acc, double2 *lds) {
+    ztile_direct<Cfg, NSEG, false, G3>(t, m0, i1, n0, j1, acc, lds);
+}
+
 // C[i][j] (op)= sum_k conj(P[k][i]) Q[k][j] over each job's rectangle, in
 // absolute indices; the triangular flags trim each tile's contraction range
 // to the rows where both operands can be nonzero. G3: 3 real products per
-// complex product (the 3M form of the tile engine).
-template <class Cfg, int NSEG, bool G3>
+// complex product (the 3M form of the tile engine). TR: args.T is written too
+// (kernels of their own: in the ones that do not, the longer epilogue made
+// N = 8000 0.4% slower).
+template <class Cfg, int NSEG, bool G3, bool TR>
 __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *lds) {
     const int N = args.N;
     int jb = 0;
@@ -187,7 +199,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
     }
     t.qscale = nullptr;
     Acc<Cfg> acc;
-    ztile_direct<Cfg, NSEG, false, G3>(t, m0, i1, n0, j1, acc, lds);
+    mm_product<Cfg, NSEG, G3>(t, m0, i1, n0, j1, acc, lds);
     if (!wave_works<Cfg>()) return;
 
     const bool lower = flags & (MM_LOWER | MM_MASK);
@@ -211,6 +223,10 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
                         r.x -= re;
                         r.y -= im;
                         *o = r;
+                        if constexpr (TR) {
+                            acc.re[i][j][v] = r.x;
+                            acc.im[i][j][v] = r.y;
+                        }
                     } else if (op == OP_NEG) {
                         *o = double2{-re, -im};
                     } else {
@@ -219,15 +235,31 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
                 }
             }
         }
+    if constexpr (TR) {   // of OP_STORE or OP_SUB
+        double2 *T = args.T;
+        const int w0 = args.w0;
+#pragma unroll
+        for (int i = 0; i < Cfg::TM; ++i)
+#pragma unroll
+            for (int j = 0; j < Cfg::TN; ++j) {
+                const int g = n0 + acc_col<Cfg>(j);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int gp = m0 + acc_row<Cfg>(i, v);
+                    if (gp < i1 && g < j1 && (g < w0) != (gp < w0))
+                        T[(long long)g * N + gp] = double2{acc.re[i][j][v], -acc.im[i][j][v]};
+                }
+            }
+    }
 }
 
 // Blocks loop over the tiles (a launch may have fewer blocks than tiles when
 // it runs beside latency-critical work).
-template <class Cfg, int NSEG, bool G3>
+template <class Cfg, int NSEG, bool G3, bool TR>
 __global__ void __launch_bounds__(MM_THREADS) k_gep_mm(const MmArgs args) {
     __shared__ double2 lds[Cfg::LDS_ELEMS];
     for (int tile = blockIdx.x; tile < args.total; tile += gridDim.x) {
-        mm_tile<Cfg, NSEG, G3>(args, tile, lds);
+        mm_tile<Cfg, NSEG, G3, TR>(args, tile, lds);
         __syncthreads();   // LDS is reused by the next tile
     }
 }
@@ -236,13 +268,17 @@ template <class Cfg>
 void mm_launch(const MmArgs &a, bool g3, unsigned grid, hipStream_t st) {
     const dim3 gd(grid), bd(MM_THREADS);
     if (a.P2 && g3)
-        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, true>), gd, bd, 0, st, a);
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, true, false>), gd, bd, 0, st, a);
     else if (a.P2)
-        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, false>), gd, bd, 0, st, a);
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, false, false>), gd, bd, 0, st, a);
+    else if (a.T && g3)
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, true, true>), gd, bd, 0, st, a);
+    else if (a.T)
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, false, true>), gd, bd, 0, st, a);
     else if (g3)
-        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, true>), gd, bd, 0, st, a);
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, true, false>), gd, bd, 0, st, a);
     else
-        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, false>), gd, bd, 0, st, a);
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 1, false, false>), gd, bd, 0, st, a);
 }
 
 // Leaf: Cholesky of the diagonal block [kb, kb + nb) (nb <= LB = 128) of the
@@ -610,13 +646,15 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
 }
 
 // L := lower(S) (upper triangle zero), M := 0, MH := 0, LH := 0 below the
-// diagonal, HL := lower(H) with half its diagonal (so that H = HL + HL^H)
+// diagonal, HL := lower(H) with half its diagonal (so that H = HL + HL^H),
+// info := 0
 __global__ void __launch_bounds__(256)
 k_gep_init(const double2 *__restrict__ H, const double2 *__restrict__ S, double2 *__restrict__ L,
            double2 *__restrict__ M, double2 *__restrict__ MH, double2 *__restrict__ LH,
-           double2 *__restrict__ HL, int N) {
+           double2 *__restrict__ HL, int N, int *__restrict__ info) {
     const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
     if (e >= (long long)N * N) return;
+    if (e == 0) *info = 0;
     const int i = (int)(e / N), j = (int)(e % N);
     const double2 z = double2{0.0, 0.0};
     double2 sv = z;
@@ -632,8 +670,6 @@ k_gep_init(const double2 *__restrict__ H, const double2 *__restrict__ S, double2
         HL[e] = hv;
     }
 }
-
-__global__ void k_gep_info_clear(int *info) { *info = 0; }
 
 // D[j][i] = conj(X[i][j]) for i in [i0, i1), j in [j0, j1) of each job
 // (blockIdx.z), through 32 x 32 LDS tiles (blockIdx.y: source tile row,
@@ -888,6 +924,10 @@ void sched_mm(const Gep &g, const MmArgs &a) {
                     g_sched->add(op, a.Q2, klo, khi, n0, n1, false);
                 }
                 g_sched->add(op, a.C, m0, m1, n0, n1, true);
+                if (a.T) {
+                    g_sched->add(op, a.T, n0, std::min(n1, a.w0), std::max(m0, a.w0), m1, true);
+                    g_sched->add(op, a.T, std::max(n0, a.w0), n1, m0, std::min(m1, a.w0), true);
+                }
             }
     }
 }
@@ -941,7 +981,8 @@ int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
 // blocks take the rectangles in the order given.
 hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C, const Rect *r,
                     int n, int flags, int op, const double2 *P2 = nullptr,
-                    const double2 *Q2 = nullptr, const int *rflags = nullptr) {
+                    const double2 *Q2 = nullptr, const int *rflags = nullptr,
+                    double2 *T = nullptr, int w0 = 0) {
     for (int b = 0; b < n; b += MM_JOBS) {
         MmArgs a = {};
         a.P = P;
@@ -949,6 +990,8 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
         a.P2 = P2;
         a.Q2 = Q2;
         a.C = C;
+        a.T = T;
+        a.w0 = w0;
         a.N = g.N;
         a.op = op;
         Rect rj[MM_JOBS];
@@ -993,9 +1036,10 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
 }
 
 hipError_t mm(const Gep &g, const double2 *P, const double2 *Q, double2 *C, int i0, int i1,
-              int j0, int j1, int k0, int k1, int flags, int op) {
+              int j0, int j1, int k0, int k1, int flags, int op, double2 *T = nullptr,
+              int w0 = 0) {
     const Rect r = {i0, i1, j0, j1, k0, k1};
-    return mm_batch(g, P, Q, C, &r, 1, flags, op);
+    return mm_batch(g, P, Q, C, &r, 1, flags, op, nullptr, nullptr, nullptr, T, w0);
 }
 
 // Transposes of the rectangles r[0 .. n), up to MM_JOBS per launch.
@@ -1055,20 +1099,26 @@ hipStream_t aux_stream(int which) {
 
 // Cholesky, right-looking over panels of LB columns: factor and invert the
 // diagonal block, then the panel L21 = S21 L11^{-H} (as LH21 = M11 S21^H) and
-// the update of the trailing lower triangle S22 -= L21 L21^H.
+// the update of the trailing lower triangle S22 -= L21 L21^H, whose epilogue
+// also writes the next panel's S21^H. A panel is a chain of one workgroup and
+// two small products, so what stands between them counts: an event record
+// between two kernels of a stream takes 6 us, next to none 1 us (with S21^H
+// and L21 as transposes of their own behind events on each panel, N = 300 316
+// us and N = 2000 2.50 ms).
 // Lookahead (from 4 panels on), with three streams and panels in pairs:
 //   caller's    leaf, panel product; after the first panel of a pair the
 //               update of the next column block with it, after the second
 //               the update of the next two column blocks with both panels
 //               (contraction 2 LB);
-//   lookahead   L21 = LH21^H (an output only); after the second panel of a
-//               pair the bulk of the update with both panels (contraction
-//               2 LB), beside the next two leaves and panels;
-//   transposes  the next panel's S21^H, beside the next leaf.
+//   lookahead   after the second panel of a pair its L21 = LH21^H (an output
+//               only; it gives the caller's update a start on the bulk, which
+//               would take its compute units: N = 4000 9.15 ms, 9.4 without),
+//               the bulk of the update with both panels (contraction 2 LB),
+//               beside the next two leaves and panels, and the first's L21;
+//   transposes  the first panel's S21^H, beside the first leaf.
 // The update of the two column blocks after a pair waits for the previous
 // pair's bulk update (both write those blocks); the bulk update and L21
-// wait for the panel they use; the next S21^H waits for the update of its
-// column block.
+// wait for the panels they use.
 template <class Hook>
 hipError_t factor(const Gep &g, Hook after_panel) {
     const int N = g.N;
@@ -1088,16 +1138,17 @@ hipError_t factor(const Gep &g, Hook after_panel) {
     // e_bulk: the last bulk update, e_look: everything on the lookahead stream
     bool bulk_pending = false, look_pending = false, w_pending = false;
     hipError_t err = hipSuccess;
-    // S21^H of the first panel, beside the first leaf
-    const auto next_s21h = [&](int c0, int c1) -> hipError_t {   // columns [c0, c1)
+    // S21^H of the first panel
+    const auto first_s21h = [&]() -> hipError_t {
+        if (!ahead) return conj_t(g, g.L, g.W, LB, N, 0, LB);
         GEP_TRY(ev_record(e_next, g.st));
         GEP_TRY(ev_wait(gc.st, e_next, WT_TRANSPOSE_AFTER_BLOCK));
-        GEP_TRY(conj_t(gc, g.L, g.W, c1, N, c0, c1));
+        GEP_TRY(conj_t(gc, g.L, g.W, LB, N, 0, LB));
         GEP_TRY(ev_record(e_w, gc.st));
         w_pending = true;
         return hipSuccess;
     };
-    if (ahead) err = next_s21h(0, LB);
+    if (np > 1) err = first_s21h();
     for (int kb = 0; kb < N && err == hipSuccess; kb += LB) {
         const int nb = N - kb < LB ? N - kb : LB;
         const int t0 = kb + nb;
@@ -1113,45 +1164,52 @@ hipError_t factor(const Gep &g, Hook after_panel) {
             err = hipGetLastError();
         }
         if (err != hipSuccess || t0 >= N) break;
+        const int t1 = N - t0 < LB ? N : t0 + LB;   // the next column block
         if (!ahead) {
-            if ((err = conj_t(g, g.L, g.W, t0, N, kb, t0)) != hipSuccess) break;  // W = S21^H
-            if ((err = mm(g, g.MH, g.W, g.LH, kb, t0, t0, N, kb, t0, MM_PU, OP_STORE)) !=
+            if ((err = mm(g, g.MH, g.W, g.LH, kb, t0, t0, N, kb, t0, MM_PU, OP_STORE, g.L, t0)) !=
                 hipSuccess)
-                break;                                                             // LH21 = M11 S21^H
-            if ((err = after_panel(t0, nullptr)) != hipSuccess) break;
-            if ((err = conj_t(g, g.LH, g.L, kb, t0, t0, N)) != hipSuccess) break; // L21
-            err = mm(g, g.LH, g.LH, g.L, t0, N, t0, N, kb, t0, MM_LOWER, OP_SUB);  // S22 -= L21 L21^H
+                break;                                                // LH21 = M11 S21^H, L21
+            Rect none = {};
+            if ((err = after_panel(t0, nullptr, none)) != hipSuccess) break;
+            err = mm(g, g.LH, g.LH, g.L, t0, N, t0, N, kb, t0, MM_LOWER, OP_SUB, g.W,
+                     t1);                                             // S22 -= L21 L21^H, next S21^H
             continue;
         }
-        if ((err = ev_wait(g.st, e_w, WT_PANEL_AFTER_TRANSPOSE)) != hipSuccess) break;   // W = S21^H
-        w_pending = false;
-        if ((err = mm(g, g.MH, g.W, g.LH, kb, t0, t0, N, kb, t0, MM_PU, OP_STORE)) != hipSuccess)
-            break;                                                                 // LH21 = M11 S21^H
-        // the hook also gets the lookahead stream's latest event (or null),
-        // which orders that stream's pending work before anything it forks
-        if ((err = after_panel(t0, look_pending ? e_look : nullptr)) != hipSuccess) break;
-        const bool second = ((kb / LB) & 1) != 0;   // second panel of a pair
-        const int k0 = second ? kb - LB : kb;        // first contraction row of the update
-        const int t1 = N - t0 < LB ? N : t0 + LB;
-        const int u1 = second ? std::min(N, t0 + 2 * LB) : t1;   // columns the caller updates
-        if ((err = ev_record(e_panel, g.st)) != hipSuccess) break;
-        if (second && bulk_pending &&
-            (err = ev_wait(g.st, e_bulk, WT_BLOCK_AFTER_BULK)) != hipSuccess)
-            break;
-        if ((err = ev_wait(ga.st, e_panel, WT_AHEAD_AFTER_PANEL)) != hipSuccess) break;
-        if ((err = conj_t(ga, g.LH, g.L, kb, t0, t0, N)) != hipSuccess) break;    // L21
-        if (second) {
-            if (u1 < N && (err = mm(ga, g.LH, g.LH, g.L, u1, N, u1, N, k0, t0, MM_LOWER,
-                                    OP_SUB)) != hipSuccess)
-                break;                                                             // the rest
-            if ((err = ev_record(e_bulk, ga.st)) != hipSuccess) break;
-            bulk_pending = true;
+        if (w_pending) {
+            if ((err = ev_wait(g.st, e_w, WT_PANEL_AFTER_TRANSPOSE)) != hipSuccess) break;
+            w_pending = false;
         }
-        if ((err = ev_record(e_look, ga.st)) != hipSuccess) break;
-        look_pending = true;
-        if ((err = mm(g, g.LH, g.LH, g.L, t0, N, t0, u1, k0, t0, MM_MASK, OP_SUB)) != hipSuccess)
-            break;                                                                 // next column block(s)
-        if (t1 < N) err = next_s21h(t0, t1);
+        if ((err = mm(g, g.MH, g.W, g.LH, kb, t0, t0, N, kb, t0, MM_PU, OP_STORE)) != hipSuccess)
+            break;                                                    // LH21 = M11 S21^H
+        const bool second = ((kb / LB) & 1) != 0;    // second panel of a pair
+        const int k0 = second ? kb - LB : kb;        // first contraction row of the update
+        const int u1 = second ? std::min(N, t0 + 2 * LB) : t1;   // columns the caller updates
+        // the first panel's L21 of a pair is still to come: the hook also gets
+        // its rectangle, and empties it when it takes that on itself, and the
+        // latest L21's event (or null), which orders the lookahead stream's
+        // reads of LH before anything that the hook forks
+        Rect first = {kb - LB, second ? kb : kb - LB, kb, N, 0, 0};
+        if ((err = after_panel(t0, look_pending ? e_look : nullptr, first)) != hipSuccess) break;
+        if (second || t1 == N) {   // L21 of the pair, or of a first panel that stays alone
+            if ((err = ev_record(e_panel, g.st)) != hipSuccess) break;
+            if ((err = ev_wait(ga.st, e_panel, WT_AHEAD_AFTER_PANEL)) != hipSuccess) break;
+            if ((err = conj_t(ga, g.LH, g.L, kb, t0, t0, N)) != hipSuccess) break;
+            if (second) {
+                if (bulk_pending &&
+                    (err = ev_wait(g.st, e_bulk, WT_BLOCK_AFTER_BULK)) != hipSuccess)
+                    break;
+                if (u1 < N && (err = mm(ga, g.LH, g.LH, g.L, u1, N, u1, N, k0, t0, MM_LOWER,
+                                        OP_SUB)) != hipSuccess)
+                    break;                                            // the rest
+                if ((err = ev_record(e_bulk, ga.st)) != hipSuccess) break;
+                bulk_pending = true;
+                if ((err = conj_t_batch(ga, g.LH, g.L, &first, 1)) != hipSuccess) break;
+            }
+            if ((err = ev_record(e_look, ga.st)) != hipSuccess) break;
+            look_pending = true;
+        }
+        err = mm(g, g.LH, g.LH, g.L, t0, N, t0, u1, k0, t0, MM_MASK, OP_SUB, g.W,
+                 t1);                                  // next column block(s), next S21^H
     }
     // join the other streams, also after an error
     if (look_pending) {
@@ -1295,9 +1353,7 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
         g_sched->add(op, g.info, 0, 1, 0, 1, true);
     } else {
         hipLaunchKernelGGL(k_gep_init, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, st, H, S,
-                           L, g.M, g.MH, g.LH, two ? g.HL : nullptr, N);
-        GEP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_gep_info_clear, dim3(1), dim3(1), 0, st, g.info);
+                           L, g.M, g.MH, g.LH, two ? g.HL : nullptr, N, g.info);
         GEP_TRY(hipGetLastError());
     }
     g.cap = 0;
@@ -1307,7 +1363,7 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     const int np = (N + LB - 1) / LB;
     hipStream_t sb = np >= 8 ? aux_stream(1) : nullptr;
     if (!sb) {
-        GEP_TRY(factor(g, [](int, hipEvent_t) { return hipSuccess; }));
+        GEP_TRY(factor(g, [](int, hipEvent_t, Rect &) { return hipSuccess; }));
         GEP_TRY(invert(g, lv, all));
         if (two) {
             GEP_TRY(wh_cols(g, 0, N));
@@ -1336,15 +1392,17 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     bool forked = false;
     const auto left = [mt](const Node &n) { return n.b <= mt; };
     if (err == hipSuccess)
-        err = factor(g, [&](int t0, hipEvent_t e_ahead) -> hipError_t {
+        err = factor(g, [&](int t0, hipEvent_t e_ahead, Rect &l21) -> hipError_t {
             if (t0 != mt) return hipSuccess;
             GEP_TRY(ev_record(e_split, st));
             GEP_TRY(ev_wait(sb, e_split, WT_FORK));
-            // the previous panel's L21 = LH21^H may still read LH columns
-            // >= m - LB on the lookahead stream; V (or WH) overwrites LH's
-            // columns < m below
+            // an earlier L21 = LH21^H may still read LH's columns < m on the
+            // lookahead stream, or is still to come; V (or WH) overwrites them
+            // below
             if (e_ahead) GEP_TRY(ev_wait(sb, e_ahead, WT_FORK_AHEAD));
             forked = true;
+            GEP_TRY(conj_t_batch(gb, g.LH, L, &l21, 1));
+            l21.i1 = l21.i0;
             GEP_TRY(invert(gb, lv, left));
             GEP_TRY(node_w21(gb, {top}));   // L21 and M11 of the top split are final too
             GEP_TRY(ev_record(e_inv, sb));

@@ -10,32 +10,30 @@
 //                                       inverse M11 = L11^{-1} (one workgroup)
 //     LH21 = M11 S21^H                  (= L21^H, the panel)
 //     S22 -= L21 L21^H                  lower triangle, contraction over 128
-//   invert, recursive over the same blocks (split at m):
-//     M21 = -M22 (L21 M11)              M = L^{-1}
-//   then, with MH = M^H = L^{-H} (upper triangular), below N = 2500
-//     V  = H MH                         (= (L^{-1} H)^H for Hermitian H)
-//     Ht = V^H MH                       lower triangle, then mirrored
-//   and from N = 2500 on, with HL the lower triangle of H (half diagonal),
-//     WH = HL^H MH                      (= (M HL)^H, upper triangular)
-//     Ht = WH^H MH + M WH               two-term lower triangle, mirrored
+//   invert, recursive over the blocks of a diagonal block of L (split at m):
+//     M21 = -M22 (L21 M11)              M, its inverse
+//   step, over diagonal blocks c of some hundred columns, R the rows below:
+//     Ht_c,: = M E_c,:                  left of the block
+//     E_R,: -= L_Rc Ht_c,:
+//     W = M^H L_Rc^H, F = K_cR - K_cc W, E_Rc = F^H M^H
+//     K_RR -= F^H W + W^H K_cR          lower triangle, mirrored
+//     V = K_cc M^H, Ht_cc = M V         lower triangle
+// with K = H at first; Ht's lower triangle is mirrored at the end.
 //
-// Work: N^3/3 complex multiply-adds for the factor and its inverse; then
-// N^3/2 for V and N^3/6 for the lower triangle of Ht (triangular operands
-// skip their zero blocks), N^3 in all = 8 N^3 real flops; or, in the
-// two-term form, N^3/6 for WH and N^3/3 for Ht, 5N^3/6 in all = 20/3 N^3
-// real flops. The minimal count of the reduction (LAPACK's zpotrf + zhegst)
-// is 16/3 N^3. The explicit inverse of L is the usual choice for this
-// reduction in FLAPW eigensolvers; its error grows with cond(L) =
-// cond(S)^{1/2} like that of the substitutions.
-//
-// Once the factorization passes the top split of the inverse's recursion,
-// the leading block's inverse and the matching columns of the result run on
-// a third stream beside it.
+// Work: N^3/6 complex multiply-adds for the factor, N^3/2 for the steps in the
+// limit of small blocks: 16/3 N^3 real flops, the minimal count of the
+// reduction (LAPACK's zpotrf + zhegst); the blocks' inverses and diagonal
+// blocks add 0.3 N^3 at the sizes used. Through the inverse of all of L
+// (Ht = M H M^H) it was 20/3 N^3 (8 N^3 below N = 2500) and nearly all of it
+// waited for the end of the factorization: N = 2000 2.39 ms, now 2.23, 8000
+// 56.9 and 52.2 ms. From 8 panels on, the first steps run on a third stream
+// beside the factorization.
 //
 // Storage (all N x N row-major complex): L (output; working copy of S's
-// lower triangle during the factorization), LH (panels L21^H, then V),
-// M = L^{-1} and MH = L^{-H} (zero outside their triangles), W (S21^H,
-// L21 M11), Ht (output).
+// lower triangle during the factorization), LH (panels L21^H, then V in the
+// diagonal blocks), M and MH = M^H of the diagonal blocks (zero in their
+// other triangles), E left of M's diagonal blocks, F right of MH's, W (S21^H,
+// L21 M11 of the invert, W of the steps), K, Ht (output).
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
@@ -95,9 +93,10 @@ struct MmArgs {
     const double2 *P, *Q;
     const double2 *P2, *Q2;   // second term, same rectangle and contraction range
     double2 *C;
-    double2 *T;               // or null; with one term: C's elements with one index
-    int w0;                   // below w0 and one not, also as T = C^H
-    int N;                    // leading dimension of P, Q, C, T
+    const double2 *S;         // OP_SUB: C = S - the product
+    double2 *T;               // or null: C's elements with one index below w0 and one
+    int w0;                   // not (w0 < 0: below the diagonal) also as T = C^H
+    int N;                    // leading dimension of all
     int op;
     int tile;                 // 128, 64 or 32
     int njobs;
@@ -219,7 +218,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
                     const bool z = upper && g < gp;
                     const double re = z ? 0.0 : acc.re[i][j][v], im = z ? 0.0 : acc.im[i][j][v];
                     if (op == OP_SUB) {
-                        double2 r = *o;
+                        double2 r = args.S[(long long)gp * N + g];
                         r.x -= re;
                         r.y -= im;
                         *o = r;
@@ -246,7 +245,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int gp = m0 + acc_row<Cfg>(i, v);
-                    if (gp < i1 && g < j1 && (g < w0) != (gp < w0))
+                    if (gp < i1 && g < j1 && (w0 < 0 ? g < gp : (g < w0) != (gp < w0)))
                         T[(long long)g * N + gp] = double2{acc.re[i][j][v], -acc.im[i][j][v]};
                 }
             }
@@ -267,10 +266,10 @@ __global__ void __launch_bounds__(MM_THREADS) k_gep_mm(const MmArgs args) {
 template <class Cfg>
 void mm_launch(const MmArgs &a, bool g3, unsigned grid, hipStream_t st) {
     const dim3 gd(grid), bd(MM_THREADS);
-    if (a.P2 && g3)
-        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, true, false>), gd, bd, 0, st, a);
+    if (a.P2 && g3)   // always with a transpose
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, true, true>), gd, bd, 0, st, a);
     else if (a.P2)
-        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, false, false>), gd, bd, 0, st, a);
+        hipLaunchKernelGGL((k_gep_mm<Cfg, 2, false, true>), gd, bd, 0, st, a);
     else if (a.T && g3)
         hipLaunchKernelGGL((k_gep_mm<Cfg, 1, true, true>), gd, bd, 0, st, a);
     else if (a.T)
@@ -647,12 +646,11 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
 }
 
 // L := lower(S) (upper triangle zero), M := 0, MH := 0, LH := 0 below the
-// diagonal, HL := lower(H) with half its diagonal (so that H = HL + HL^H),
-// info := 0
+// diagonal, K := H, info := 0
 __global__ void __launch_bounds__(256)
 k_gep_init(const double2 *__restrict__ H, const double2 *__restrict__ S, double2 *__restrict__ L,
            double2 *__restrict__ M, double2 *__restrict__ MH, double2 *__restrict__ LH,
-           double2 *__restrict__ HL, int N, int *__restrict__ info) {
+           double2 *__restrict__ K, int N, int *__restrict__ info) {
     const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
     if (e >= (long long)N * N) return;
     if (e == 0) *info = 0;
@@ -664,12 +662,7 @@ k_gep_init(const double2 *__restrict__ H, const double2 *__restrict__ S, double2
     M[e] = z;
     MH[e] = z;
     if (j < i) LH[e] = z;
-    if (HL) {
-        double2 hv = z;
-        if (j <= i) hv = H[e];
-        if (j == i) hv = double2{0.5 * hv.x, 0.0};
-        HL[e] = hv;
-    }
+    if (K) K[e] = H[e];
 }
 
 // D[j][i] = conj(X[i][j]) for i in [i0, i1), j in [j0, j1) of each job
@@ -703,7 +696,7 @@ k_gep_conj_t(const double2 *__restrict__ X, double2 *__restrict__ D, int N, cons
 }
 
 struct Gep {
-    double2 *L, *LH, *M, *MH, *W, *HL;
+    double2 *L, *LH, *M, *MH, *W, *K;
     int N;
     int *info;
     hipStream_t st;
@@ -730,8 +723,8 @@ struct Rect {
 // vector-clock pass over the log: two launches on different streams that
 // touch a common 128 x 128 cell of a matrix, one of them writing, must be
 // ordered by a chain of stream order and event waits.
-enum SchedBuf { SB_H, SB_S, SB_L, SB_HT, SB_LH, SB_M, SB_MH, SB_W, SB_HL, SB_INFO, SB_COUNT };
-const char *const kSchedBufName[SB_COUNT] = {"H", "S", "L", "Ht", "LH", "M", "MH", "W", "HL", "info"};
+enum SchedBuf { SB_H, SB_S, SB_L, SB_HT, SB_LH, SB_M, SB_MH, SB_W, SB_K, SB_INFO, SB_COUNT };
+const char *const kSchedBufName[SB_COUNT] = {"H", "S", "L", "Ht", "LH", "M", "MH", "W", "K", "info"};
 
 struct SchedAcc {
     int buf, r0, r1, c0, c1;   // element rectangle [r0, r1) x [c0, c1)
@@ -925,7 +918,9 @@ void sched_mm(const Gep &g, const MmArgs &a) {
                     g_sched->add(op, a.Q2, klo, khi, n0, n1, false);
                 }
                 g_sched->add(op, a.C, m0, m1, n0, n1, true);
-                if (a.T) {
+                if (a.op == OP_SUB) g_sched->add(op, a.S, m0, m1, n0, n1, false);
+                if (a.T && a.w0 < 0) g_sched->add(op, a.T, n0, n1, m0, m1, true);
+                if (a.T && a.w0 >= 0) {
                     g_sched->add(op, a.T, n0, std::min(n1, a.w0), std::max(m0, a.w0), m1, true);
                     g_sched->add(op, a.T, std::max(n0, a.w0), n1, m0, std::min(m1, a.w0), true);
                 }
@@ -983,7 +978,7 @@ int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
 hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C, const Rect *r,
                     int n, int flags, int op, const double2 *P2 = nullptr,
                     const double2 *Q2 = nullptr, const int *rflags = nullptr,
-                    double2 *T = nullptr, int w0 = 0) {
+                    double2 *T = nullptr, int w0 = 0, const double2 *S = nullptr) {
     for (int b = 0; b < n; b += MM_JOBS) {
         MmArgs a = {};
         a.P = P;
@@ -991,6 +986,7 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
         a.P2 = P2;
         a.Q2 = Q2;
         a.C = C;
+        a.S = S ? S : C;
         a.T = T;
         a.w0 = w0;
         a.N = g.N;
@@ -1272,52 +1268,69 @@ hipError_t invert(const Gep &g, const std::vector<std::vector<Node>> &lv, Keep k
     return hipSuccess;
 }
 
+// Columns whose steps run beside the factorization: as many as it leaves time
+// for. Up to N = 2000 it is a chain of small launches that leaves the device
+// nearly empty, from 4000 on its bulk updates fill half of it. Measured best
+// (us, with half as many and with half as many again): N = 1500 1024 (1361;
+// 1580, -), 2000 1152 (2205; 2550, 2370), 4000 1280 (8660; -, 9255), 8000 2560
+// (51955; 54140, 53900), 10000 3584 (94693; 99990, 100100).
+int bg_columns(int N) {
+    const double c = std::max(std::min(0.68 * N, 1280.0), 0.32 * N);
+    return (int)(c / LB + 0.5) * LB;
+}
+// [a, b) in equal steps of at most about `most` columns, multiples of LB but
+// the last: larger ones leave the invert of the step's block and its products
+// under-filled longer, smaller ones contract over fewer rows (N = 2000 in
+// steps of 512 2.22 ms, 640 2.23, 1280 2.43; N = 10000 640 > 99.8, 896 94.7,
+// 1536 98.7).
+void split_steps(int a, int b, int most, std::vector<int> &ends) {
+    const int n = (b - a + most - 1) / most;
+    for (int k = 1; k <= n; ++k)
+        ends.push_back(k == n ? b : a + (int)((long long)(b - a) * k / n + LB / 2) / LB * LB);
+}
+
 size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
-// With H = HL + HL^H (HL: lower triangle of H, half its diagonal),
-//   Ht = M H M^H = A B^H + B A^H,  A = M HL (lower), B = M,
-// so Ht takes WH = A^H = HL^H MH (upper: WH[i][j] sums k in [i, j]) and the
-// two-term lower-triangle product Ht = WH^H MH + MH^H WH (k <= j). WH is
-// kept in LH, whose lower triangle is zero.
-
-// Below this size the two-term form's longer contractions cost more than the
-// smaller work saves, and Ht = V^H MH with V = H MH (N^3/2 + N^3/6 complex
-// multiply-adds) is faster: 3.47 against 3.57 ms at N = 2000, 6.78 against
-// 6.46 ms at N = 3000.
-constexpr int GEP_HER2K_MIN_N = 2500;
-
-// V[:, c0:c1) = H MH[:, c0:c1), kept in LH
-hipError_t v_cols(const Gep &g, const double2 *H, int c0, int c1) {
-    return mm(g, H, g.MH, g.LH, 0, g.N, c0, c1, 0, g.N, MM_QU, OP_STORE);
+// A diagonal block [a, b) of Ht = M K M^H, through V = K MH (kept in LH).
+hipError_t diag_block(const Gep &g, const double2 *K, double2 *Ht, int a, int b) {
+    GEP_TRY(mm(g, K, g.MH, g.LH, a, b, a, b, a, b, MM_QU, OP_STORE));
+    return mm(g, g.LH, g.MH, Ht, a, b, a, b, a, b, MM_QU | MM_LOWER, OP_STORE);
 }
 
-// WH[:, c0:c1) (rows i <= j): the rows above the block (longer contractions)
-// and the block's upper triangle in one launch
-hipError_t wh_cols(const Gep &g, int c0, int c1) {
+// One step of the blocked transformation: rows and columns c = [a, b) of Ht
+// left of and in the diagonal block, and what the rest R = [b, N) needs of
+// them. On entry K (in full) and E (in M, left of the diagonal blocks) hold
+// what the blocks before left. With M the inverse of L_cc:
+//   Ht[c, :a) = M E[c, :a),   E[R, :a) -= L_Rc Ht[c, :a)
+//   W = M^H L_Rc^H,   F = K_cR - K_cc W   (F in MH, right of the diagonal block)
+//   E[R, c) = F^H M^H,   K_RR -= F^H W + W^H K_cR
+//   Ht_cc = M K_cc M^H
+// which is the congruence that eliminates L_Rc from both sides.
+template <class Ready>
+hipError_t step(const Gep &g, double2 *Ht, int a, int b, Ready ready) {
     const int N = g.N;
-    const Rect r[2] = {{0, c0, c0, c1, 0, N}, {c0, c1, c0, c1, 0, N}};
-    const int f[2] = {MM_PL | MM_QU, MM_PL | MM_QU | MM_UPPER};
-    return mm_batch(g, g.HL, g.MH, g.LH, r, 2, 0, OP_STORE, nullptr, nullptr, f);
-}
-
-// lower triangle of Ht, rows [r0, r1): the triangle (contractions up to
-// r1) and then the rows' columns left of it (up to r0) in one launch
-hipError_t her2k_rows(const Gep &g, double2 *Ht, int r0, int r1) {
-    const int N = g.N;
-    const Rect r[2] = {{r0, r1, r0, r1, 0, N}, {r0, r1, 0, r0, 0, N}};
-    const int f[2] = {MM_QU | MM_LOWER, MM_QU};
-    return mm_batch(g, g.LH, g.MH, Ht, r, 2, 0, OP_STORE, g.MH, g.LH, f);
+    std::vector<std::vector<Node>> lv;
+    tree(a, b, 0, lv);
+    GEP_TRY(invert(g, lv, [](const Node &) { return true; }));
+    GEP_TRY(ready());
+    GEP_TRY(mm(g, g.MH, g.M, Ht, a, b, 0, a, a, b, MM_PU, OP_STORE));
+    GEP_TRY(mm(g, g.LH, Ht, g.M, b, N, 0, a, a, b, 0, OP_SUB));
+    GEP_TRY(mm(g, g.M, g.LH, g.W, a, b, b, N, a, b, MM_PL, OP_STORE));
+    const Rect f = {a, b, b, N, a, b}, k = {b, N, b, N, a, b};
+    GEP_TRY(mm_batch(g, g.K, g.W, g.MH, &f, 1, 0, OP_SUB, nullptr, nullptr, nullptr, nullptr, 0,
+                     g.K));
+    GEP_TRY(mm(g, g.MH, g.MH, g.M, b, N, a, b, a, b, MM_QU, OP_STORE));
+    return mm_batch(g, g.MH, g.W, g.K, &k, 1, MM_LOWER, OP_SUB, g.W, g.K, nullptr, g.K, -1);
 }
 
 }  // namespace
 
 size_t gep_workspace_bytes(int N) {
-    return 5 * padded(16 * (size_t)N * (size_t)N) + 256;   // LH, M, MH, W, HL, info slot
+    return 5 * padded(16 * (size_t)N * (size_t)N) + 256;   // LH, M, MH, W, K, info slot
 }
 
 hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, double2 *Ht,
                       int *info, char *ws, hipStream_t st, bool g3) {
-    const bool two = N >= GEP_HER2K_MIN_N;   // Ht from WH (two-term product), else from V
     const size_t m = padded(16 * (size_t)N * (size_t)N);
     Gep g;
     g.L = L;
@@ -1325,12 +1338,14 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     g.M = reinterpret_cast<double2 *>(ws + m);
     g.MH = reinterpret_cast<double2 *>(ws + 2 * m);
     g.W = reinterpret_cast<double2 *>(ws + 3 * m);
-    g.HL = reinterpret_cast<double2 *>(ws + 4 * m);
+    g.K = reinterpret_cast<double2 *>(ws + 4 * m);
     g.N = N;
     g.info = info ? info : reinterpret_cast<int *>(ws + 5 * m);
     g.st = st;
     g.g3 = g3;
     const long long nn = (long long)N * N;
+    const int np = (N + LB - 1) / LB;
+    hipStream_t sb = np >= 8 ? aux_stream(1) : nullptr;
     // Ht's upper triangle by conjugation, Im(diag) = 0
     const auto mirror = [&]() -> hipError_t {
         if (g_sched) {
@@ -1340,49 +1355,43 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
         return launch_mirror1(Ht, N, st);
     };
     if (g_sched) {
-        const void *b[SB_COUNT] = {H, S, L, Ht, g.LH, g.M, g.MH, g.W, g.HL, g.info};
+        const void *b[SB_COUNT] = {H, S, L, Ht, g.LH, g.M, g.MH, g.W, g.K, g.info};
         std::copy(b, b + SB_COUNT, g_sched->base);
         SchedOp &op = g_sched->launch(st, "k_gep_init");
         g_sched->add(op, S, 0, N, 0, N, false);
         for (const void *X : {(const void *)L, (const void *)g.M, (const void *)g.MH,
                               (const void *)g.LH})
             g_sched->add(op, X, 0, N, 0, N, true);
-        if (two) {
+        if (sb) {
             g_sched->add(op, H, 0, N, 0, N, false);
-            g_sched->add(op, g.HL, 0, N, 0, N, true);
+            g_sched->add(op, g.K, 0, N, 0, N, true);
         }
         g_sched->add(op, g.info, 0, 1, 0, 1, true);
     } else {
         hipLaunchKernelGGL(k_gep_init, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, st, H, S,
-                           L, g.M, g.MH, g.LH, two ? g.HL : nullptr, N, g.info);
+                           L, g.M, g.MH, g.LH, sb ? g.K : nullptr, N, g.info);
         GEP_TRY(hipGetLastError());
     }
     g.cap = 0;
-    std::vector<std::vector<Node>> lv;
-    tree(0, N, 0, lv);
-    const auto all = [](const Node &) { return true; };
-    const int np = (N + LB - 1) / LB;
-    hipStream_t sb = np >= 8 ? aux_stream(1) : nullptr;
-    if (!sb) {
+    if (!sb) {   // few panels: one block
+        std::vector<std::vector<Node>> lv;
+        tree(0, N, 0, lv);
         GEP_TRY(factor(g, [](int, hipEvent_t, Rect &) { return hipSuccess; }));
-        GEP_TRY(invert(g, lv, all));
-        if (two) {
-            GEP_TRY(wh_cols(g, 0, N));
-            GEP_TRY(her2k_rows(g, Ht, 0, N));
-        } else {
-            GEP_TRY(v_cols(g, H, 0, N));
-            GEP_TRY(mm(g, g.LH, g.MH, Ht, 0, N, 0, N, 0, N, MM_QU | MM_LOWER, OP_STORE));  // V^H MH
-        }
+        GEP_TRY(invert(g, lv, [](const Node &) { return true; }));
+        GEP_TRY(diag_block(g, H, Ht, 0, N));
         return mirror();
     }
-    // Once the factorization has passed the top split m (the leaf and the
-    // panel product LH21 of the panel ending at m are enqueued), the inverse of the
-    // leading block [0, m), the top split's W21 = L21 M11, WH[:, 0:m) and the
-    // rows [0, m) of Ht (or V[:, 0:m)) depend on nothing still to come: they run on a second
-    // stream, with at most HS_GEP_BG_QUARTERS / 4 of the compute units, beside
-    // the rest of the factorization (which no longer touches LH's columns < m).
-    const Node top = lv[0][0];
-    const int mt = top.m;
+    // In steps of columns. Once the factorization has passed a step's columns
+    // (the leaf and the panel product LH21 of its last panel are enqueued), the
+    // step depends on nothing still to come: those of the first `bg` columns run
+    // on a second stream, with at most HS_GEP_BG_QUARTERS / 4 of the compute
+    // units, beside the rest of the factorization, which no longer touches LH's
+    // columns < t0. The others follow it on all compute units.
+    const int bg = bg_columns(N);
+    std::vector<int> ends;
+    split_steps(0, bg, 896, ends);
+    const size_t nbg = ends.size();
+    split_steps(bg, N, 960, ends);
     Gep gb = g;
     gb.st = sb;
     gb.cap = (g_sched ? 256 : num_cus()) * HS_GEP_BG_QUARTERS / 4;
@@ -1390,42 +1399,35 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     hipError_t err = ev_create(&e_split);
     if (err == hipSuccess) err = ev_create(&e_inv);
     if (err == hipSuccess) err = ev_create(&e_v);
-    bool forked = false;
-    const auto left = [mt](const Node &n) { return n.b <= mt; };
+    size_t done = 0;   // steps enqueued
+    const auto begin = [&](size_t k) { return k ? ends[k - 1] : 0; };
     if (err == hipSuccess)
         err = factor(g, [&](int t0, hipEvent_t e_ahead, Rect &l21) -> hipError_t {
-            if (t0 != mt) return hipSuccess;
+            if (done == nbg || t0 != ends[done]) return hipSuccess;
             GEP_TRY(ev_record(e_split, st));
             GEP_TRY(ev_wait(sb, e_split, WT_FORK));
-            // an earlier L21 = LH21^H may still read LH's columns < m on the
-            // lookahead stream, or is still to come; V (or WH) overwrites them
-            // below
+            // an earlier L21 = LH21^H may still read LH's columns < t0 on the
+            // lookahead stream, or is still to come; V overwrites them below
             if (e_ahead) GEP_TRY(ev_wait(sb, e_ahead, WT_FORK_AHEAD));
-            forked = true;
+            const int a = begin(done++);
             GEP_TRY(conj_t_batch(gb, g.LH, L, &l21, 1));
             l21.i1 = l21.i0;
-            GEP_TRY(invert(gb, lv, left));
-            GEP_TRY(node_w21(gb, {top}));   // L21 and M11 of the top split are final too
+            GEP_TRY(step(gb, Ht, a, t0, [] { return hipSuccess; }));
             GEP_TRY(ev_record(e_inv, sb));
-            if (two) {
-                GEP_TRY(wh_cols(gb, 0, mt));
-                GEP_TRY(her2k_rows(gb, Ht, 0, mt));
-            } else {
-                GEP_TRY(v_cols(gb, H, 0, mt));
-            }
+            GEP_TRY(diag_block(gb, g.K, Ht, a, t0));
             return ev_record(e_v, sb);
         });
-    if (err == hipSuccess) err = invert(g, lv, [mt](const Node &n) { return n.a >= mt; });
-    if (err == hipSuccess && forked) err = ev_wait(st, e_inv, WT_END_AFTER_INVERSE);
-    if (err == hipSuccess) err = node_m21(g, {top});
-    if (err == hipSuccess) err = two ? wh_cols(g, mt, N) : v_cols(g, H, mt, N);
-    if (forked) {   // join the second stream even after an error
+    const size_t forked = done;
+    for (; err == hipSuccess && done < ends.size(); ++done) {
+        err = step(g, Ht, begin(done), ends[done], [&] {
+            return done == forked ? ev_wait(st, e_inv, WT_END_AFTER_INVERSE) : hipSuccess;
+        });
+        if (err == hipSuccess) err = diag_block(g, g.K, Ht, begin(done), ends[done]);
+    }
+    if (forked > 0) {   // join the second stream even after an error
         const hipError_t e = ev_wait(st, e_v, WT_END_AFTER_BACKGROUND);
         if (err == hipSuccess) err = e;
     }
-    if (err == hipSuccess)
-        err = two ? her2k_rows(g, Ht, mt, N)
-                  : mm(g, g.LH, g.MH, Ht, 0, N, 0, N, 0, N, MM_QU | MM_LOWER, OP_STORE);
     for (hipEvent_t e : {e_split, e_inv, e_v}) ev_destroy(e);
     GEP_TRY(err);
     return mirror();

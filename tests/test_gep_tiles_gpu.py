@@ -1,10 +1,11 @@
 """The eigenproblem reduction at the edges of its tile shapes.
 
 Each product launch takes 128, 64 or 32-wide tiles by an estimate of its time,
-so these sizes reach every shape, in both result forms (Ht through V below
-N = 2500, through the two-term product above) and both arithmetics: a last
-block of 1, 31, 33, 63, 65 and 127 rows, one block, and sizes whose panels and
-inverse levels take different shapes. Tolerance: the 1e-12 bound of the
+so these sizes reach every shape, in both result forms (Ht in one block up to
+seven panels, in steps of columns from eight on) and both arithmetics: a last
+block of 1, 31, 33, 63, 65 and 127 rows, one block, sizes whose panels and
+inverse levels take different shapes, and every pattern of one to three steps
+beside and after the factorization. Tolerance: the 1e-12 bound of the
 reduction's parity tests (cond(S) u sqrt(N) is about 1e-13 here).
 """
 
@@ -19,6 +20,15 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("mode", [0, 3], ids=["fp64", "3m"])
 @pytest.mark.parametrize("N", [31, 97, 128, 160, 191, 383, 512, 545, 895, 1281, 2499, 2531])
 def test_gep_tile_edges(N, mode):
+    _check(N, mode)
+
+
+@pytest.mark.parametrize("N", [896, 897, 1024, 1025, 1411, 1920, 2241, 3295])
+def test_gep_steps(N):
+    _check(N, 0)
+
+
+def _check(N, mode):
     import torch
     from paper_1611_00606_amd import hs_gep_reduce
     rng = np.random.default_rng(N)

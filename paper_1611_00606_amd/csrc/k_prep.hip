@@ -17,9 +17,12 @@ namespace {
 // 60 us at 512 atoms), writes its table entries and forms
 //   M1_a = T^AA_a, M2_a = T^BB_a   Hermitian, from the lower triangles
 //   d[r] = 1, d[K + r] = |u_r|^2   per contraction row of the S reduction
-// (bandwidth and launch latency; 5 us at N_A = 32, N_L = 49).
+// The blocks are spread in y over an atom's elements, FORM_ELEMS each, and in z
+// over the two matrices; bound by latency (with one block per atom 20 us at
+// N_A = 32, N_L = 49 and 69 us at N_A = 108, N_L = 121; now 10 and 28).
 constexpr int FORM_CHUNK = 1024;
 constexpr int FORM_THREADS = 256;
+constexpr int FORM_ELEMS = 4 * FORM_THREADS;   // elements of a matrix per block
 struct FormChunk {
     unsigned char nl[FORM_CHUNK];
     int a0;         // first atom of the chunk
@@ -28,12 +31,13 @@ struct FormChunk {
     int n_atoms;    // of the build
 };
 
-// Hermitian n x n block (row-major, element (i,k)) from the lower triangle of
-// the stored block t; Im of the diagonal dropped.
+// Elements [e0, e0 + FORM_ELEMS) of the Hermitian n x n block (row-major,
+// element (i,k)) from the lower triangle of the stored block t; Im of the
+// diagonal dropped.
 __device__ __forceinline__ void hermitian_from_lower(const double2 *__restrict__ t, int n,
-                                                     double2 *__restrict__ m) {
-    const int nn = n * n;
-    for (int e = threadIdx.x; e < nn; e += FORM_THREADS) {
+                                                     int e0, double2 *__restrict__ m) {
+    const int e1 = min(n * n, e0 + FORM_ELEMS);
+    for (int e = e0 + threadIdx.x; e < e1; e += FORM_THREADS) {
         const int i = e / n, k = e - (e / n) * n;
         double2 v;
         if (k < i) v = t[i * n + k];
@@ -54,7 +58,8 @@ k_forms(FormChunk c, int K, int *__restrict__ row_off, int *__restrict__ t_off,
         const double2 *__restrict__ U, double2 *__restrict__ M1, double2 *__restrict__ M2,
         double *__restrict__ d) {
     __shared__ int part[2][FORM_THREADS / 64];
-    const int i = blockIdx.x;
+    const int i = blockIdx.x, e0 = blockIdx.y * FORM_ELEMS;
+    if (e0 >= c.nl[i] * c.nl[i]) return;
     int r = 0, t = 0;
     for (int j = threadIdx.x; j < i; j += FORM_THREADS) {
         r += c.nl[j];
@@ -78,6 +83,12 @@ k_forms(FormChunk c, int K, int *__restrict__ row_off, int *__restrict__ t_off,
         t += part[1][w];
     }
     const int a = c.a0 + i, n = c.nl[i];
+    if (blockIdx.z) {
+        hermitian_from_lower(T_BB + t, n, e0, M2 + t);
+        return;
+    }
+    hermitian_from_lower(T_AA + t, n, e0, M1 + t);
+    if (e0) return;
     if (threadIdx.x == 0) {
         row_off[a] = r;
         t_off[a] = t;
@@ -86,8 +97,6 @@ k_forms(FormChunk c, int K, int *__restrict__ row_off, int *__restrict__ t_off,
             t_off[a + 1] = t + n * n;
         }
     }
-    hermitian_from_lower(T_AA + t, n, M1 + t);
-    hermitian_from_lower(T_BB + t, n, M2 + t);
     for (int l = threadIdx.x; l < n; l += FORM_THREADS) {
         const double2 u = U[r + l];
         d[r + l] = 1.0;
@@ -113,7 +122,9 @@ hipError_t launch_forms(const AtomPlan &p, const AtomBufs &ab, const double2 *T_
         c.row0 = p.row_off[a0];
         c.t0 = p.t_off[a0];
         c.n_atoms = p.n_atoms;
-        hipLaunchKernelGGL(k_forms, dim3(n), dim3(FORM_THREADS), 0, st, c, p.K, ab.tables,
+        const int nl = *std::max_element(c.nl, c.nl + n);
+        const int ny = (nl * nl + FORM_ELEMS - 1) / FORM_ELEMS;
+        hipLaunchKernelGGL(k_forms, dim3(n, ny, 2), dim3(FORM_THREADS), 0, st, c, p.K, ab.tables,
                            ab.tables + p.n_atoms + 1, T_AA, T_BB, U, ab.M1, ab.M2, ab.d);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -293,8 +293,9 @@ int hs_autotune_atoms(const int32_t *nl_values, int n_values, int N_G, int reps,
  *     S = L L^H   (Cholesky; L lower with a positive real diagonal)
  *     Ht = L^{-1} H L^{-H}
  * H c = lambda S c holds exactly when Ht y = lambda y with y = L^H c.
- * Right-looking over 128-column panels with an explicit inverse of L; the
- * O(N^3) work runs as products on the complex FP64 MFMA tiles.
+ * Right-looking over 128-column panels, then a blocked elimination with the
+ * inverses of L's diagonal blocks; the O(N^3) work runs as products on the
+ * complex FP64 MFMA tiles.
  * ---------------------------------------------------------------------- */
 
 /* Device scratch hs_gep_reduce needs for N (0 for N < 1): 5 N^2 complex. */

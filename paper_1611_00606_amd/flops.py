@@ -73,3 +73,31 @@ def atom_flops(nl, n_g):
 def executed_flops(nl, n_g):
     """Flops one build executes in the 4-product form (see module docstring)."""
     return reduction_flops(nl, n_g) + atom_flops(nl, n_g)
+
+
+def gep_steps(N, panel=128):
+    """Column ends of the steps of the eigenproblem reduction, as k_gep.hip
+    takes them (bg_columns, split_steps); one step below eight panels."""
+    if -(-N // panel) < 8:
+        return [N]
+
+    def split(a, b, most):
+        n = -(-(b - a) // most)
+        return [b if k == n else a + ((b - a) * k // n + panel // 2) // panel * panel
+                for k in range(1, n + 1)]
+
+    bg = int(max(min(0.68 * N, 1280.0), 0.32 * N) / panel + 0.5) * panel
+    return split(0, bg, 896) + split(bg, N, 960)
+
+
+def gep_executed_flops(N):
+    """Flops the eigenproblem reduction executes: the factor (N^3/6 complex
+    multiply-adds) and per step of n columns, a before and R after it, the
+    block's inverse, V and Ht (5/6 n^3), Ht left of it (n^2 a / 2), E (n a R
+    and n^2 R / 2), W (n^2 R / 2), F (n^2 R) and K (n R^2)."""
+    t, a = N ** 3 / 6.0, 0
+    for b in gep_steps(N):
+        n, R = b - a, N - b
+        t += 5.0 / 6.0 * n ** 3 + 0.5 * n * n * a + n * a * R + 2.0 * n * n * R + n * R * R
+        a = b
+    return 8.0 * t

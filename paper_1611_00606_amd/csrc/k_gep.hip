@@ -26,7 +26,7 @@
 // over one block 5.56 N^3 at N = 8000 and 6.06 N^3 at 2000. Through the inverse of all of L
 // (Ht = M H M^H) it was 20/3 N^3 (8 N^3 below N = 2500) and nearly all of it
 // waited for the end of the factorization: N = 2000 2.39 ms, now 2.23, 8000
-// 56.9 and 52.2 ms. From 8 panels on, the first steps run on a third stream
+// 56.9 and 52.2 ms. From 4 panels on, the first steps run on a third stream
 // beside the factorization.
 //
 // Storage (all N x N row-major complex): L (output; working copy of S's
@@ -1345,7 +1345,9 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     g.g3 = g3;
     const long long nn = (long long)N * N;
     const int np = (N + LB - 1) / LB;
-    hipStream_t sb = np >= 8 ? aux_stream(1) : nullptr;
+    // With up to three panels the fork costs what it saves (N = 300 305 us in
+    // one block, 309 in steps; 400 434 and 405, 600 590 and 535).
+    hipStream_t sb = np >= 4 ? aux_stream(1) : nullptr;
     // Ht's upper triangle by conjugation, Im(diag) = 0
     const auto mirror = [&]() -> hipError_t {
         if (g_sched) {

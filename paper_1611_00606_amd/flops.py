@@ -77,8 +77,8 @@ def executed_flops(nl, n_g):
 
 def gep_steps(N, panel=128):
     """Column ends of the steps of the eigenproblem reduction, as k_gep.hip
-    takes them (bg_columns, split_steps); one step below eight panels."""
-    if -(-N // panel) < 8:
+    takes them (bg_columns, split_steps); one step up to three panels."""
+    if -(-N // panel) < 4:
         return [N]
 
     def split(a, b, most):

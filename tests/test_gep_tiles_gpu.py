@@ -2,7 +2,7 @@
 
 Each product launch takes 128, 64 or 32-wide tiles by an estimate of its time,
 so these sizes reach every shape, in both result forms (Ht in one block up to
-seven panels, in steps of columns from eight on) and both arithmetics: a last
+three panels, in steps of columns from four on) and both arithmetics: a last
 block of 1, 31, 33, 63, 65 and 127 rows, one block, sizes whose panels and
 inverse levels take different shapes, and every pattern of one to three steps
 beside and after the factorization. Tolerance: the 1e-12 bound of the
@@ -23,7 +23,7 @@ def test_gep_tile_edges(N, mode):
     _check(N, mode)
 
 
-@pytest.mark.parametrize("N", [896, 897, 1024, 1025, 1411, 1920, 2241, 3295])
+@pytest.mark.parametrize("N", [384, 385, 513, 641, 896, 897, 1024, 1025, 1411, 1920, 2241, 3295])
 def test_gep_steps(N):
     _check(N, 0)
 

@@ -25,8 +25,8 @@
 // reduction (LAPACK's zpotrf + zhegst); with the products
 // over one block 5.56 N^3 at N = 8000 and 6.06 N^3 at 2000. Through the inverse of all of L
 // (Ht = M H M^H) it was 20/3 N^3 (8 N^3 below N = 2500) and nearly all of it
-// waited for the end of the factorization: N = 2000 2.39 ms, now 2.23, 8000
-// 56.9 and 52.2 ms. From 4 panels on, the first steps run on a third stream
+// waited for the end of the factorization: N = 2000 2.39 ms, now 2.12, 8000
+// 56.9 and 52.3 ms. From 4 panels on, the first steps run on a third stream
 // beside the factorization.
 //
 // Storage (all N x N row-major complex): L (output; working copy of S's
@@ -61,11 +61,12 @@ using Mm64 = TileCfg<64, 64, 16, 2, 4, 4>;
 using Mm32 = TileCfg<32, 32, 16, 2, 2, 4>;
 constexpr int MM_THREADS = 512;
 
-// Share of the compute units (in quarters) the work moved off the
-// factorization's critical path may occupy.
-#ifndef HS_GEP_BG_QUARTERS
-#define HS_GEP_BG_QUARTERS 3
-#endif
+// Compute units that the steps beside the factorization may occupy: 7/8 below
+// N = 2500, where it is a chain of small launches, 3/4 above, where its bulk
+// updates need them (us, 3/4 and 7/8: N = 1500 1370 and 1366, 2000 2232 and
+// 2118, 2300 2744 and 2667, 4000 8596 and 8877, 10000 96971 and 97750; 3M form
+// 2000 2026 and 1972, 3700 6189 and 6490; 1/2: 2000 2456, 8000 63259).
+inline int bg_cap(int N, int cus) { return N < 2500 ? cus * 7 / 8 : cus * 3 / 4; }
 
 // product flags
 constexpr int MM_PU = 1;      // P upper triangular: k <= row of C
@@ -1386,9 +1387,8 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     // In steps of columns. Once the factorization has passed a step's columns
     // (the leaf and the panel product LH21 of its last panel are enqueued), the
     // step depends on nothing still to come: those of the first `bg` columns run
-    // on a second stream, with at most HS_GEP_BG_QUARTERS / 4 of the compute
-    // units, beside the rest of the factorization, which no longer touches LH's
-    // columns < t0. The others follow it on all compute units.
+    // on a second stream, on bg_cap of the compute units, beside the rest of
+    // the factorization, which no longer touches LH's columns < t0. The others follow it on all compute units.
     const int bg = bg_columns(N);
     std::vector<int> ends;
     split_steps(0, bg, 896, ends);
@@ -1396,7 +1396,7 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     split_steps(bg, N, 960, ends);
     Gep gb = g;
     gb.st = sb;
-    gb.cap = (g_sched ? 256 : num_cus()) * HS_GEP_BG_QUARTERS / 4;
+    gb.cap = bg_cap(N, g_sched ? 256 : num_cus());
     hipEvent_t e_split = nullptr, e_inv = nullptr, e_v = nullptr;
     hipError_t err = ev_create(&e_split);
     if (err == hipSuccess) err = ev_create(&e_inv);

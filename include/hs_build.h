@@ -84,15 +84,19 @@ enum {
 /* Arithmetic of the large reductions (the per-atom Cholesky, the HPD test and
  * the per-atom products are always binary64).
  *   HS_FP64       complex binary64 MFMA.
- *   HS_SPLIT_F16  split precision: each binary64 operand column is scaled by a
- *                 power of two and cut into 4 exact integer slices of 8, 9,
+ *   HS_SPLIT_F16  split precision: each binary64 operand column is scaled by its
+ *                 maximum and cut into 4 exact integer slices of 8, 9,
  *                 9, 9 bits held in FP16; the slice products (pairs
  *                 s + t <= 5) run on FP16 MFMA with FP32 accumulation (the two
  *                 leading levels exact, flushed every 64 contraction rows)
  *                 and are recombined in binary64. Error about 2^-35 of the
  *                 operand column maxima per product term (relative Frobenius
- *                 error of H and S 2e-10 .. 4e-10 for Gaussian operands,
- *                 below 1e-9). Inputs must be finite.
+ *                 error of H and S 1e-10 .. 2e-10 for Gaussian operands,
+ *                 below 1e-9). In the split and modular forms the rows of A
+ *                 and X in A^H X are first balanced against each other by
+ *                 powers of two, so that atoms and rows of unlike magnitude
+ *                 in T_AA do not raise the error; H and S hold the row maxima
+ *                 until they are written. Inputs must be finite.
  *   HS_SPLIT_I8   split precision on INT8 MFMA: the same column scaling, 5
  *                 integer slices of 7 bits (int8; the first within +-127),
  *                 the 15 pairs s + t <= 6 on INT8 MFMA with exact INT32
@@ -117,16 +121,17 @@ enum {
  *                 bitwise those of HS_SPLIT_F16 (MI355X runs BF16 and FP16
  *                 MFMA at the same dense rate). Workspace as HS_SPLIT_F16.
  *   HS_SPLIT_I8_CRT modular form on INT8 MFMA: each operand column is scaled by
- *                 a power of two and rounded to signed integers of b bits
- *                 (b = 36 for contraction lengths up to about 5e4, one bit
- *                 less per factor of four beyond); the exact integer products
+ *                 a power of two to a Euclidean norm of at most 2^42.85 and
+ *                 rounded to integers; the exact integer products
  *                 of each contraction segment are formed modulo 11 pairwise
  *                 coprime moduli <= 255 (symmetric residues in int8, INT32
  *                 sums, one INT8 MFMA product per modulus instead of the 15
  *                 slice pairs of HS_SPLIT_I8) and rebuilt by the Chinese
  *                 remainder theorem (mixed-radix digits) before the binary64
  *                 scaling. The only error is the rounding of the operands,
- *                 2^-36 of their column maxima per element. Workspace: 22
+ *                 at most 2^-42.8 of their column's norm per element for
+ *                 columns of even rows (relative error of H and S about 1e-11
+ *                 for Gaussian operands). Workspace: 22
  *                 bytes per operand element and a residue buffer of about
  *                 55 N_G^2 bytes. Inputs must be finite. */
 typedef enum {

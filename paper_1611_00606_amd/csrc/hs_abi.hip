@@ -101,7 +101,7 @@ size_t AtomPlan::atom_bytes() const {
 size_t AtomPlan::kpoint_bytes(int n_g, int mode) const {
     size_t b = 2 * align_up(16 * (size_t)K * (size_t)n_g) + BatchBufs::bytes(n_atoms, n_g);
     if (split_mode(mode))
-        b += NSPLIT_ROOM * (align_up(slice_bytes(mode, K, n_g)) + align_up(8 * (size_t)n_g));
+        b += NSPLIT * (align_up(slice_bytes(mode, K, n_g)) + align_up(8 * (size_t)n_g));
     if (mode == HS_SPLIT_I8_CRT) b += align_up(crt_work_bytes(n_g));
     return b;
 }
@@ -167,7 +167,6 @@ void KpointBufs::carve(const AtomPlan &p, int n_g, int mode, char *base) {
         mx[i] = reinterpret_cast<unsigned long long *>(base + o);
         o += align_up(8 * (size_t)n_g);
     }
-    // the work buffer of the modular form takes the unused operand's room too
     crt = mode == HS_SPLIT_I8_CRT ? base + o : nullptr;
 }
 
@@ -192,9 +191,14 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
     if (e != hipSuccess) return e;
     if ((e = mark(2)) != hipSuccess) return e;
     if (split_mode(mode)) {
-        // operands: 0 A, 1 B, 2 X, 3 Y, 4 U B
+        // operands: 0 A, 1 B, 2 X 2^-e, 3 Y, 4 U B, 5 A 2^e
         const int K = p.K;
-        SliceJobs jobs = {{A, B, kb.X, kb.Y}, ab.d + K, {}, {}};
+        SliceJobs jobs = {{A, B, kb.X, kb.Y}, ab.d + K, {}, {}, {}, 1};
+        // The row maxima live in H and S until the reductions write those:
+        // 4 N_G^2 entries each, for more rows than that one per group of rows.
+        jobs.rmx[0] = reinterpret_cast<unsigned *>(H);
+        jobs.rmx[1] = reinterpret_cast<unsigned *>(S);
+        jobs.rgroup = (int)((K - 1) / (4LL * n_g * n_g) + 1);
         for (int i = 0; i < NSPLIT; ++i) {
             jobs.mx[i] = kb.mx[i];
             jobs.S[i] = kb.sl[i];
@@ -205,7 +209,7 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
         if (e != hipSuccess) return e;
         SliceView v[NSPLIT];
         for (int i = 0; i < NSPLIT; ++i) v[i] = SliceView{kb.sl[i], kb.mx[i]};
-        const SliceView hseg[2][2] = {{v[1], v[3]}, {v[0], v[2]}};
+        const SliceView hseg[2][2] = {{v[1], v[3]}, {v[5], v[2]}};
         const SliceView sseg[2][2] = {{v[0], v[0]}, {v[4], v[4]}};
         if (mode == HS_SPLIT_I8_CRT)
             e = launch_crt_reduce(K, n_g, hseg, sseg, kb.crt, H, S, st);

@@ -84,29 +84,37 @@ inline bool split_mode(int mode) {   // the operands are sliced (or cut into res
            mode == HS_SPLIT_I8_CRT;
 }
 
-// Split-precision reductions (k_split.hip). The sliced operands: the matrices
-// X[0..3] [K][N_G] as they are, and as operand 4 the rows of X[1] scaled by
-// sqrt(rscale[k]); for each the column maxima mx [N_G] (bit patterns of
-// doubles) and the FP16 slices S [4][groups][N_G][8], groups = 4 * ceil(K / 16).
+// Split-precision reductions (k_split.hip). The sliced operands, from the
+// matrices M[0..3] = A, B, X, Y [K][N_G]: 0 A, 1 B, 2 X 2^-e, 3 Y, 4 the rows
+// of B scaled by sqrt(rscale[k]), 5 A 2^e, with e[k] per row (slice_row_exp);
+// for each the column maxima mx [N_G] (bit patterns of doubles; block norms in
+// the modular form) and the FP16 slices S [4][groups][N_G][8], groups = 4 * ceil(K / 16).
 // Every pass takes all of them in one launch and reads each matrix once.
 constexpr int NSLICE_SRC = 4;
+constexpr int NSPLIT = 6;
 struct SliceJobs {
-    const double2 *X[NSLICE_SRC];
+    const double2 *M[NSLICE_SRC];
     const double *rscale;
-    unsigned long long *mx[NSLICE_SRC + 1];
-    _Float16 *S[NSLICE_SRC + 1];
+    unsigned long long *mx[NSPLIT];
+    _Float16 *S[NSPLIT];
+    // scratch, one entry per rgroup rows: upper halves of the largest |Re| or
+    // |Im| of A's rows and of X's
+    unsigned *rmx[2];
+    int rgroup;
 };
 struct SliceView {
     const _Float16 *S;
     const unsigned long long *mx;
 };
 size_t split_slice_bytes(int K, int n_g);
-// zero every mx, then the column maxima into them
-hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
+// zero every mx and rmx, then A's and X's row maxima and the column maxima
+// into them; norm: instead of the maxima the largest Euclidean norm of 64 rows
+// of each column
+hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool norm);
 // column maxima and slices; bf16: the same slices held as BF16 and multiplied
 // on BF16 MFMA
 hipError_t launch_slice(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool bf16);
-// H segments (B,Y), (A,X); S segments (A,A), (Bs,Bs): [segment][P or Q]
+// H segments (B,Y), (A 2^e, X 2^-e); S segments (A,A), (Bs,Bs): [segment][P or Q]
 hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                hipStream_t st, bool bf16);
@@ -118,12 +126,12 @@ hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                                 const SliceView (&sseg)[2][2], double2 *H, double2 *S,
                                 hipStream_t st);
 // Modular INT8 form (k_crt.hip): residues R [NMOD][groups][N_G][16 int8],
-// groups = 16 * ceil(K / 128), of each operand's b-bit integers; the
+// groups = 8 * ceil(K / 64) (of 64 rows four hold the real parts of 16 rows
+// each, four the imaginary parts), of each operand's integers; the
 // reduction writes each segment's residues into `work` (crt_work_bytes) and
 // rebuilds H and S from them.
 size_t crt_residue_bytes(int K, int n_g);
 size_t crt_work_bytes(int n_g);
-int crt_bits(int K);   // integer width b of the operands for contraction length K
 hipError_t launch_residue(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
 hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
                              const SliceView (&sseg)[2][2], void *work, double2 *H, double2 *S,
@@ -214,10 +222,6 @@ hipError_t launch_batch(const AtomPlan &p, const Atoms &at, const BatchPlan &bp,
                         const BatchIO &io, const BatchBufs &bb, hipStream_t st);
 
 // Per-k-point device buffers.
-constexpr int NSPLIT = NSLICE_SRC + 1;   // sliced operands: A, B, X, Y, U B
-// Room for this many sliced operands is part of the workspace size callers
-// have been given.
-constexpr int NSPLIT_ROOM = 6;
 struct KpointBufs {
     double2 *X, *Y;   // [K][N_G] each
     _Float16 *sl[NSPLIT];

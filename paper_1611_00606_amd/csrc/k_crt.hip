@@ -2,28 +2,33 @@
 // stacked products of H = A^H X + B^H Y and S = A^H A + (U B)^H (U B) (see
 // k_reduce.hip) computed exactly on integers.
 //
-// Operands. For each column n of a sliced operand X let e[n] be the exponent
-// with max_k max(|Re X[k][n]|, |Im X[k][n]|) < 2^e[n], and
-//     X'[k][n] = rint(X[k][n] 2^(b - 1 - e[n]))        (|X'| <= 2^(b-1))
+// Operands. For each column n of a sliced operand X let s[n] be the exponent
+// with which ||X[.][n]|| 2^s lies in (2^41.85, 2^42.85], ||X|| bounded by
+// sqrt(K / 64) times the largest norm of 64 rows, and
+//     X'[k][n] = rint(X[k][n] 2^s)
 // for the real and the imaginary parts. This rounding is the form's only
-// error: at most 2^-b of the column maximum per element.
+// error: up to 2^-43.85 .. 2^-42.85 of the column's norm per element, at 8100
+// rows of equal size 2^-36.4 .. 2^-35.4 of their size. (Integers of 36 bits at
+// the column's maximum, which the bound 2 K 2^70 on their products allows up
+// to K = 28000, are 2 to 3 bits coarser for Gaussian columns: H at N_G = 8000,
+// K = 8100 was 6.1e-11 off, now 8.8e-12.)
 //
 // Products. The real part p_re q_re + p_im q_im and the imaginary part
 // p_re q_im - p_im q_re of conj(P')^T Q' are each one dot product of 2K
-// integers, so |Re|, |Im| <= 2K 2^(2b - 2). Both are computed modulo NMOD
+// integers, so |Re|, |Im| <= ||P'|| ||Q'||. Both are computed modulo NMOD
 // pairwise coprime odd moduli m_i <= 255: the operands' residues in symmetric
 // form (|r| <= (m - 1) / 2 <= 127, so a residue and its negation are int8),
 // INT8 MFMA products summed exactly in INT32 and reduced to a symmetric
-// residue at the end of the segment. With M = prod m_i (about 2^86.8) and b
-// chosen so that 2K 2^(2b - 2) <= (M - 1) / 2, the residues fix each integer
-// uniquely in the symmetric range of M.
+// residue at the end of the segment. With M = prod m_i, (M - 1) / 2 = 2^85.803
+// and ||X'|| <= 2^42.85 + sqrt(2K) / 2 < 2^42.901 (the rounding; K <= 2^28),
+// the residues fix each integer uniquely in the symmetric range of M.
 //
 // Reconstruction (Chinese remainder theorem in Garner's mixed-radix form):
 //     X = v_0 + m_0 (v_1 + m_1 (v_2 + ... + m_9 v_10)),
 //     v_i = (r_i - sum_{j<i} v_j W_j) W_i^-1  mod m_i,   W_j = m_0 ... m_{j-1},
 // with symmetric digits v_i, computed exactly in FP32 (every intermediate is
-// an integer below 2^24) and evaluated by Horner's rule in FP64. Each
-// segment's integer is scaled by 2^(eP + eQ - 2 (b - 1)) and the segments of
+// an integer below 2^24) and evaluated in FP64 with one rounding. Each
+// segment's integer is scaled by 2^-(sP + sQ) and the segments of
 // H (two) and of S (two) are added in FP64.
 //
 // The scheme is the modular-integer emulation of floating-point matrix
@@ -31,6 +36,8 @@
 // the INT8 slice pairs of HS_SPLIT_I8 (15 INT8 products per complex product)
 // it needs one per modulus (11), and the INT32 sums of a modulus need no
 // per-level accumulators, so a wave holds a four times larger output tile.
+#include <cmath>
+
 #include "hs_internal.h"
 #include "split_common.h"
 
@@ -42,8 +49,7 @@ typedef int i4 __attribute__((ext_vector_type(4)));
 
 constexpr int NMOD = 11;
 constexpr int CRT_MOD[NMOD] = {255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217};
-constexpr int CRT_BMAX = 36;   // |X'| <= 2^35: exact in FP64, and b = 36 for K up to about 5e4
-constexpr int NSEG = 4;        // H: (B,Y), (A,X); S: (A,A), (Bs,Bs)
+constexpr int NSEG = 4;        // H: (B, Y), (A 2^e, X 2^-e); S: (A, A), (Bs, Bs)
 // Segments the work buffer has room for (part of the workspace size callers
 // have been given).
 constexpr int NSEG_ROOM = 5;
@@ -86,6 +92,16 @@ static_assert(NMOD * 127 * 127 < (1 << 24), "Garner sums exact in FP32");
 // three symmetric digits fold into an integer below 2^24 (exact in FP32)
 static_assert(255LL * 253 * 251 / 2 < (1 << 24), "digit groups exact in FP32");
 
+// Exponent s of a column from the largest norm of 64 of its rows; cn: crt_norm(K).
+__device__ __forceinline__ int crt_shift(const unsigned long long *mx, int n, double cn) {
+    const double m = __longlong_as_double((long long)mx[n]) * cn;
+    int e = 0;
+    if (m > 0.0) frexp(m, &e);
+    return 42 - e;
+}
+// 2^-0.85 sqrt(blocks of 64 rows), a little more for the norms' own rounding
+double crt_norm(int K) { return 0.55478473603393 * (1.0 + 1e-12) * std::sqrt((double)((K + 63) / 64)); }
+
 __device__ __forceinline__ int crt_modulus(int mi) {
     int m = CRT_MOD[0];
 #pragma unroll
@@ -96,15 +112,15 @@ __device__ __forceinline__ int crt_modulus(int mi) {
 
 // ---------------------------------------------------------------------------
 // Residues. One thread per (16 complex rows, column): the real and the
-// imaginary parts -> b-bit integers -> NMOD residues of 16 int8 each, written
+// imaginary parts -> integers -> NMOD residues of 16 int8 each, written
 // to R[i][g][n][0..15]. A stage of the products is 64 complex rows, eight
 // items g of a column: the real parts of rows 16 q .. 16 q + 15 (q = 0..3),
 // then the imaginary parts.
 
 __global__ void __launch_bounds__(256)
-k_residue(SliceJobs jobs, int K, int n_g, int blocks, int b) {
+k_residue(SliceJobs jobs, int K, int n_g, int blocks, double cn) {
     const int z = blockIdx.y;
-    const double2 *X = slice_ptr(jobs.X, z);
+    const double2 *X = slice_ptr(jobs.M, z);
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
     const int rb = (int)(idx / n_g);   // block of 16 rows
@@ -116,22 +132,22 @@ k_residue(SliceJobs jobs, int K, int n_g, int blocks, int b) {
         raw[q] = double2{0.0, 0.0};
         if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const auto cut = [&](const unsigned long long *mx, _Float16 *S, bool scaled)
+    const auto cut = [&](int op)
                          __attribute__((always_inline)) {
-        const int sh = b - 1 - col_exp(mx, n);
+        const int sh = crt_shift(slice_ptr(jobs.mx, op), n, cn);
         double x[2][16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int k = 16 * rb + q;
-            const double2 v = scaled && k < K ? slice_scaled(jobs, raw[q], k) : raw[q];
+            const double2 v = k < K ? slice_value(jobs, op, raw[q], k) : raw[q];
             x[0][q] = rint(ldexp(v.x, sh));
             x[1][q] = rint(ldexp(v.y, sh));
         }
         const long long plane = 2LL * blocks * n_g;   // 16-byte items per modulus
-        uint4 *out = reinterpret_cast<uint4 *>(S) + (8LL * (rb >> 2) + (rb & 3)) * n_g + n;
+        uint4 *out = reinterpret_cast<uint4 *>(slice_ptr(jobs.S, op)) + (8LL * (rb >> 2) + (rb & 3)) * n_g + n;
 #pragma unroll
         for (int i = 0; i < NMOD; ++i) {
-            // x / m is at most 2^28 and at least 1 / (2 m) from a half-integer,
+            // x / m is below 2^36 and at least 1 / (2 m) from a half-integer,
             // so rint of the rounded quotient is exact and so is the remainder
             const double m = CRT_MOD[i], inv = 1.0 / CRT_MOD[i];
 #pragma unroll
@@ -146,8 +162,8 @@ k_residue(SliceJobs jobs, int K, int n_g, int blocks, int b) {
             }
         }
     };
-    cut(slice_ptr(jobs.mx, z), slice_ptr(jobs.S, z), false);
-    if (z == 1) cut(jobs.mx[NSLICE_SRC], jobs.S[NSLICE_SRC], true);
+    cut(z);
+    if (slice_other(z) >= 0) cut(slice_other(z));
 }
 
 // ---------------------------------------------------------------------------
@@ -359,13 +375,14 @@ struct CrtRecArgs {
     const uint2 *res;
     const unsigned long long *mP[NSEG], *mQ[NSEG];
     double2 *H, *S;
-    int n_g, nt, ntri, b;
+    int n_g, nt, ntri;
+    double cn;
 };
 
 // The integer with residues rb[i] - 127 (rb: the stored bytes). Digit i is
 // (r_i u_i - sum_{j<i} (W_j u_i mod m_i) v_j) mod m_i, one reduction per
-// digit; digits are folded three at a time in FP32 (exact) and the four
-// groups by Horner's rule in FP64.
+// digit; digits are folded three at a time in FP32 and the four groups in
+// FP64 in pairs (below 2^40 and 2^48), all exact, then the two pairs.
 __device__ __forceinline__ double garner(const float (&rb)[NMOD]) {
     float v[NMOD];
     v[0] = rb[0] - 127.0f;
@@ -387,7 +404,7 @@ __device__ __forceinline__ double garner(const float (&rb)[NMOD]) {
     constexpr double P6 = (double)CRT_MOD[3] * CRT_MOD[4] * CRT_MOD[5];
     constexpr double P9 = (double)CRT_MOD[6] * CRT_MOD[7] * CRT_MOD[8];
     static_assert(NMOD == 11, "the digit grouping assumes 11 moduli");
-    return fma(fma(fma(g3, P9, g2), P6, g1), P3, g0);
+    return fma(fma(g3, P9, g2), P3 * P6, fma(g1, P3, g0));   // one rounding, the last
 }
 
 __global__ void __launch_bounds__(256)
@@ -416,7 +433,7 @@ k_crt_recon(CrtRecArgs a) {
 #pragma unroll
         for (int mi = 0; mi < NMOD; ++mi)
             w[mi] = a.res[(((long long)(s * NMOD + mi) * a.ntri + t) * CFRAG + f) * 64 + lane];
-        const int eq = col_exp(mQ, g);
+        const int sq = crt_shift(mQ, g, a.cn);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             float rr[NMOD], ri[NMOD];
@@ -426,7 +443,7 @@ k_crt_recon(CrtRecArgs a) {
                 ri[mi] = (float)((w[mi].y >> (8 * v)) & 0xffu);
             }
             const int gp = gp0 + v < n_g ? gp0 + v : n_g - 1;
-            const int sh = col_exp(mP, gp) + eq - 2 * (a.b - 1);
+            const int sh = -(crt_shift(mP, gp, a.cn) + sq);
             sr[v] += ldexp(garner(rr), sh);
             si[v] += ldexp(garner(ri), sh);
         }
@@ -453,15 +470,6 @@ int crt_tiles(int n_g, int *nt) {
 
 }  // namespace
 
-int crt_bits(int K) {
-    unsigned __int128 M = 1;
-    for (int i = 0; i < NMOD; ++i) M *= (unsigned)CRT_MOD[i];
-    const unsigned __int128 half = (M - 1) / 2;
-    int b = CRT_BMAX;
-    while (b > 1 && (unsigned __int128)(2 * (long long)K) << (2 * (b - 1)) > half) --b;
-    return b;
-}
-
 size_t crt_residue_bytes(int K, int n_g) {
     const long long groups = (long long)((K + CITEMS * 8 - 1) / (CITEMS * 8)) * CITEMS;
     return (size_t)NMOD * groups * n_g * 16;
@@ -475,11 +483,11 @@ size_t crt_work_bytes(int n_g) {
 
 hipError_t launch_residue(const SliceJobs &jobs, int K, int n_g, hipStream_t st) {
     const int blocks = (K + CITEMS * 8 - 1) / (CITEMS * 8) * (CITEMS / 2);   // of 16 rows
-    hipError_t e = launch_colmax(jobs, K, n_g, st);
+    hipError_t e = launch_colmax(jobs, K, n_g, st, true);
     if (e != hipSuccess) return e;
     const long long items = (long long)blocks * n_g;
     hipLaunchKernelGGL(k_residue, dim3((unsigned)((items + 255) / 256), NSLICE_SRC), dim3(256), 0,
-                       st, jobs, K, n_g, blocks, crt_bits(K));
+                       st, jobs, K, n_g, blocks, crt_norm(K));
     return hipGetLastError();
 }
 
@@ -511,7 +519,7 @@ hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
     r.n_g = n_g;
     r.nt = a.nt;
     r.ntri = a.ntri;
-    r.b = crt_bits(K);
+    r.cn = crt_norm(K);
     const long long threads = (long long)a.ntri * CFRAG * 64;
     hipLaunchKernelGGL(k_crt_recon, dim3((unsigned)((threads + 255) / 256), 2), dim3(256), 0, st, r);
     return hipGetLastError();

@@ -4,9 +4,9 @@
 // recombined in FP64. The per-atom Cholesky, the HPD test and the per-atom
 // products stay in FP64 (they produce the X, Y operands sliced here).
 //
-// Slicing (error-free): for each operand column n let e[n] be the exponent
-// with max_k max(|Re X[k][n]|, |Im X[k][n]|) < 2^e[n]. The scaled values
-// x = X 2^-e lie in (-1, 1) and are written exactly as
+// Slicing: for each operand column n let m[n] = max_k max(|Re X[k][n]|,
+// |Im X[k][n]|). The scaled values x = X / m (rounded once, at 2^-53 of their
+// size) lie in [-1, 1] and are written exactly as
 //     x = sig_1 2^-b1 + sum_{s=2..NSL} sig_s 2^-(b1 + b (s-1)) + r
 // with b1 bits in the first slice and b bits in the others:
 // sig_1 = rint(2^b1 x) in [-2^b1, 2^b1], then sig_s = rint(2^b r_{s-1}) in
@@ -25,7 +25,7 @@
 // Accumulation: the slice pairs (s, t) with s + t <= NSL + 1 are summed into
 // one FP32 accumulator per level c = s + t and, every FLUSH stages (16
 // complex rows each) and at the end of each (P, Q) segment, combined in FP64:
-//     acc += 2^(eP[m] + eQ[n] - 2 b1) (L_2 + 2^-b L_3 + 2^-2b L_4 + ...)
+//     acc += mP[m] mQ[n] 2^-2b1 (L_2 + 2^-b L_3 + 2^-2b L_4 + ...)
 // and cleared. Default scheme (b1 = 8, b = 9, NSL = 4, FLUSH = 4, i.e. 64
 // rows = 128 real products per pair between flushes):
 //   level 2: |sig_1 sig_1| <= 2^16, sum <= 2^7 * 2^16 = 2^23: exact;
@@ -60,45 +60,106 @@ static_assert(SBITS1 <= 10 && SBITS <= 10, "slices must be integers FP16 holds e
 // Column maxima. A positive double's bit pattern orders like the double, so
 // the per-column maximum of |Re|, |Im| is reduced with an integer atomicMax
 // (order-independent, hence deterministic) over blocks of 64 columns x 64
-// rows; k_zero_u64 clears the maxima first (a kernel, not a memset, so the
-// sequence stays valid inside a captured graph).
+// rows; k_zero_max clears the maxima first (a kernel, not a memset, so the
+// sequence stays valid inside a captured graph). The row maxima behind the
+// exponents e of A 2^e and X 2^-e are needed before the column maxima of those, so
+// A and X are read twice (the two passes 0.95 and 0.51 ms at N_G = 8000, K =
+// 8100 in the modular form, 78 and 46 us at N_G = 1501, K = 4096 in FP16;
+// with a sixth operand to cut the balance costs 1 to 6% of a build).
 
 constexpr int CROWS = 64;   // rows per k_colmax block
 
-__global__ void __launch_bounds__(256) k_zero_u64(SliceJobs jobs, int n) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) slice_ptr(jobs.mx, blockIdx.y)[i] = 0ull;
+__global__ void __launch_bounds__(256) k_zero_max(SliceJobs jobs, int n_g, int nr) {
+    const int i = blockIdx.x * 256 + threadIdx.x, z = blockIdx.y;
+    if (z < NSPLIT) {
+        if (i < n_g) slice_ptr(jobs.mx, z)[i] = 0ull;
+    } else if (i < nr) {
+        slice_ptr(jobs.rmx, z - NSPLIT)[i] = 0u;
+    }
 }
 
+// First pass (SCALED false, z = matrix): the row maxima of A and X, and the
+// column maxima of the operands that no row exponent enters. Second pass: those
+// of A 2^e (z = 0) and X 2^-e (z = 1). NORM: instead of a column's maximum the
+// largest Euclidean norm of its blocks of CROWS rows (the modular form's scale),
+// summed in a fixed order at the block's own exponent.
+template <bool SCALED, bool NORM>
 __global__ void __launch_bounds__(256)
 k_colmax(SliceJobs jobs, int K, int n_g) {
-    __shared__ double red[2][4][64];
-    const int z = blockIdx.z;
-    const double2 *X = slice_ptr(jobs.X, z);
-    const bool two = z == 1;   // operand 4 too
+    constexpr int NR = CROWS / 4;   // rows per thread
+    __shared__ double red[2][4][64], sum[2][4][64];
+    const int z = SCALED ? 2 * blockIdx.z : blockIdx.z;   // matrix
+    const double2 *X = slice_ptr(jobs.M, z);
+    const bool cols = SCALED || z != 2, rows = !SCALED && (z == 0 || z == 2);
+    const bool two = !SCALED && z == 1;   // operand 4 too
+    const int op = SCALED && z == 0 ? 5 : z;
     const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
     const int n = blockIdx.x * 64 + c;
     const int ncl = n < n_g ? n : n_g - 1;
     const int k0 = blockIdx.y * CROWS;
     double m0 = 0.0, m1 = 0.0;
-#pragma unroll 4
-    for (int k = k0 + rg; k < k0 + CROWS; k += 4) {
+    unsigned mine = 0;   // lane i < NR: row k0 + rg + 4 i
+    double2 v[NORM ? NR : 1];
+#pragma unroll(NORM ? NR : 4)
+    for (int i = 0; i < NR; ++i) {
+        const int k = k0 + rg + 4 * i;   // the same in all lanes of a wave
+        double2 x = {0.0, 0.0};
         if (k < K) {
-            const double2 v = X[(long long)k * n_g + ncl];
-            m0 = fmax(m0, fmax(fabs(v.x), fabs(v.y)));
+            x = X[(long long)k * n_g + ncl];
+            if constexpr (SCALED) x = slice_value(jobs, op, x, k);
+            const double m = fmax(fabs(x.x), fabs(x.y));
+            m0 = fmax(m0, m);
+            if (rows) {
+                unsigned r = (unsigned)__double2hiint(m);
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) r = max(r, (unsigned)__shfl_xor((int)r, o));
+                if (c == i) mine = r;
+            }
             if (two) {
-                const double2 b = slice_scaled(jobs, v, k);
+                const double2 b = slice_value(jobs, 4, x, k);
                 m1 = fmax(m1, fmax(fabs(b.x), fabs(b.y)));
             }
         }
+        if constexpr (NORM) v[i] = x;
     }
+    if (rows) {
+        const int k = k0 + rg + 4 * c;
+        if (c < NR && k < K)
+            atomicMax((z == 0 ? jobs.rmx[0] : jobs.rmx[1]) + (jobs.rgroup == 1 ? k : k / jobs.rgroup), mine);
+    }
+    if (!cols) return;
     red[0][rg][c] = m0;
     red[1][rg][c] = m1;
     __syncthreads();
+    const auto block_max = [&](int t) __attribute__((always_inline)) {
+        const double (*x)[64] = red[t];
+        return fmax(fmax(x[0][c], x[1][c]), fmax(x[2][c], x[3][c]));
+    };
+    int e[2] = {0, 0};
+    if constexpr (NORM) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (t == 1 && !two) break;
+            frexp(block_max(t), &e[t]);
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const int k = k0 + rg + 4 * i;
+                const double2 x = t == 1 && k < K ? slice_value(jobs, 4, v[i], k) : v[i];
+                const double a = ldexp(x.x, -e[t]), b = ldexp(x.y, -e[t]);
+                s += a * a + b * b;
+            }
+            sum[t][rg][c] = s;
+        }
+        __syncthreads();
+    }
     if ((rg == 0 || (rg == 1 && two)) && n < n_g) {
-        const double (*x)[64] = red[rg];
-        const double m = fmax(fmax(x[0][c], x[1][c]), fmax(x[2][c], x[3][c]));
-        unsigned long long *mx = rg == 0 ? slice_ptr(jobs.mx, z) : jobs.mx[NSLICE_SRC];
+        double m = block_max(rg);
+        if constexpr (NORM) {
+            const double (*x)[64] = sum[rg];
+            m = ldexp(sqrt((x[0][c] + x[1][c]) + (x[2][c] + x[3][c])), rg == 0 ? e[0] : e[1]);
+        }
+        unsigned long long *mx = rg == 0 ? slice_ptr(jobs.mx, op) : jobs.mx[4];
         atomicMax(mx + n, (unsigned long long)__double_as_longlong(m));
     }
 }
@@ -115,7 +176,7 @@ template <bool BF>
 __global__ void __launch_bounds__(256)
 k_slice(SliceJobs jobs, int K, int n_g, int groups) {
     const int z = blockIdx.y;
-    const double2 *X = slice_ptr(jobs.X, z);
+    const double2 *X = slice_ptr(jobs.M, z);
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
     const int g = (int)(idx / n_g);
@@ -127,19 +188,19 @@ k_slice(SliceJobs jobs, int K, int n_g, int groups) {
         raw[q] = double2{0.0, 0.0};
         if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const auto cut = [&](const unsigned long long *mx, _Float16 *S, bool scaled)
+    const auto cut = [&](int op)
                          __attribute__((always_inline)) {
-        const double sc = ldexp(1.0, -col_exp(mx, n));
+        const double sc = 1.0 / col_scale(slice_ptr(jobs.mx, op), n);
         double x[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int k = 4 * g + q;
-            const double2 v = scaled && k < K ? slice_scaled(jobs, raw[q], k) : raw[q];
+            const double2 v = k < K ? slice_value(jobs, op, raw[q], k) : raw[q];
             x[2 * q] = v.x * sc;
             x[2 * q + 1] = v.y * sc;
         }
         const long long plane = (long long)groups * n_g * 8;   // halves per slice
-        _Float16 *out = S + ((long long)g * n_g + n) * 8;
+        _Float16 *out = slice_ptr(jobs.S, op) + ((long long)g * n_g + n) * 8;
 #pragma unroll
         for (int s = 0; s < NSL; ++s) {
             h8 h;
@@ -165,8 +226,8 @@ k_slice(SliceJobs jobs, int K, int n_g, int groups) {
             }
         }
     };
-    cut(slice_ptr(jobs.mx, z), slice_ptr(jobs.S, z), false);
-    if (z == 1) cut(jobs.mx[NSLICE_SRC], jobs.S[NSLICE_SRC], true);
+    cut(z);
+    if (slice_other(z) >= 0) cut(slice_other(z));
 }
 
 // ---------------------------------------------------------------------------
@@ -278,12 +339,12 @@ __device__ __forceinline__ void split_segment(const SplitSeg sg, int n_g, int gr
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int m = m0 + wm * SWTM + i * 16 + 4 * (lane >> 4) + v;
-            sP[i][v] = ldexp(1.0, col_exp(sg.mP, m < n_g ? m : n_g - 1) - 2 * SBITS1);
+            sP[i][v] = col_scale(sg.mP, m < n_g ? m : n_g - 1) * (1.0 / (1 << 2 * SBITS1));
         }
 #pragma unroll
     for (int j = 0; j < STN; ++j) {
         const int n = n0 + wn * SWTN + j * 16 + (lane & 15);
-        sQ[j] = ldexp(1.0, col_exp(sg.mQ, n < n_g ? n : n_g - 1));
+        sQ[j] = col_scale(sg.mQ, n < n_g ? n : n_g - 1);
     }
 
     f4 lre[STM][STN][NLEV], lim[STM][STN][NLEV];
@@ -454,8 +515,8 @@ k_split_reduce(SplitArgs args) {
 // INT8 form (HS_SPLIT_I8). Same scaling and complex interleaving, integer
 // slices of 7 bits on V_MFMA_I32_16X16X64_I8 with exact INT32 accumulation.
 //
-// Slicing: with e[n] such that max |X[.][n]| * 128/127 < 2^e[n], x = X 2^-e
-// lies in (-127/128, 127/128) and
+// Slicing: x = X / (m 128/127), with the column maximum m, lies in
+// [-127/128, 127/128] and
 //     x = sum_{s=1..5} sig_s 128^-s + r,   sig_1 = rint(128 x) in [-127, 127],
 //     sig_s = rint(128 r_{s-1}) in [-64, 64] (s >= 2),  |r| <= 2^-36,
 // every value an int8. A pair (s, t) weighs 128^-(s + t); the 15 pairs with
@@ -463,7 +524,7 @@ k_split_reduce(SplitArgs args) {
 // at most 5 pairs of |sig sig'| <= 127 * 64 or 64 * 64 (level 2: 127^2), at
 // most 28544 < 2^15 per real product, so a level stays exact for 2^16 real
 // products: the accumulators are combined in FP64 (Horner, scaled by
-// 2^(eP + eQ - 14)) only at the end of each (P, Q) segment and every 32768
+// mP mQ (128/127)^2 2^-14) only at the end of each (P, Q) segment and every 32768
 // complex rows, into FP64 accumulators held in registers across the
 // segments of the output tile (a fixed order: deterministic); each output
 // element is stored to memory once, after its last segment. No FP64 work
@@ -494,12 +555,8 @@ constexpr int FLUSH8 = 1024;                  // stages (32768 complex rows) per
 constexpr int BAND8 = 8;
 static_assert((long long)FLUSH8 * 64 * 28544 < (1LL << 31), "levels exact in INT32");
 
-// exponent e with column max * 128/127 < 2^e (0 for an all-zero column)
-__device__ __forceinline__ int col_exp8(const unsigned long long *mx, int n) {
-    const double m = __longlong_as_double((long long)mx[n]);
-    int e = 0;
-    if (m > 0.0) frexp(m * (128.0 / 127.0), &e);
-    return e;
+__device__ __forceinline__ double col_scale8(const unsigned long long *mx, int n) {
+    return col_scale(mx, n) * (128.0 / 127.0);
 }
 
 // One thread per (group of 8 complex rows, column): 16 interleaved real
@@ -507,7 +564,7 @@ __device__ __forceinline__ int col_exp8(const unsigned long long *mx, int n) {
 __global__ void __launch_bounds__(256)
 k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
     const int z = blockIdx.y;
-    const double2 *X = slice_ptr(jobs.X, z);
+    const double2 *X = slice_ptr(jobs.M, z);
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     const int n = (int)(idx % n_g);
     const int g = (int)(idx / n_g);
@@ -519,19 +576,19 @@ k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
         raw[q] = double2{0.0, 0.0};
         if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const auto cut = [&](const unsigned long long *mx, _Float16 *S, bool scaled)
+    const auto cut = [&](int op)
                          __attribute__((always_inline)) {
-        const double sc = ldexp(1.0, -col_exp8(mx, n));
+        const double sc = 1.0 / col_scale8(slice_ptr(jobs.mx, op), n);
         double x[16];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int k = 8 * g + q;
-            const double2 v = scaled && k < K ? slice_scaled(jobs, raw[q], k) : raw[q];
+            const double2 v = k < K ? slice_value(jobs, op, raw[q], k) : raw[q];
             x[2 * q] = v.x * sc;
             x[2 * q + 1] = v.y * sc;
         }
         const long long plane = (long long)groups * n_g;   // 16-byte items per slice
-        uint4 *out = reinterpret_cast<uint4 *>(S) + (long long)g * n_g + n;
+        uint4 *out = reinterpret_cast<uint4 *>(slice_ptr(jobs.S, op)) + (long long)g * n_g + n;
 #pragma unroll
         for (int s = 0; s < NSL8; ++s) {
             unsigned w[4] = {0u, 0u, 0u, 0u};
@@ -546,8 +603,8 @@ k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
             out[s * plane] = uint4{w[0], w[1], w[2], w[3]};
         }
     };
-    cut(slice_ptr(jobs.mx, z), slice_ptr(jobs.S, z), false);
-    if (z == 1) cut(jobs.mx[NSLICE_SRC], jobs.S[NSLICE_SRC], true);
+    cut(z);
+    if (slice_other(z) >= 0) cut(slice_other(z));
 }
 
 struct Split8Seg {
@@ -655,14 +712,14 @@ __device__ __forceinline__ void split8_segment(const Split8Seg sg, int n_g, int 
         for (int j = 0; j < T8N; ++j) {
             const int c = wn * (B8 / W8N) + j * 16 + lc;
             const int g = n0 + c;
-            const int eq = col_exp8(sg.mQ, g < n_g ? g : n_g - 1);
+            const double sq = col_scale8(sg.mQ, g < n_g ? g : n_g - 1) * (1.0 / (1 << 14));
 #pragma unroll
             for (int i = 0; i < T8M; ++i)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int r = wm * (B8 / W8M) + i * 16 + 4 * lg + v;
                     const int gp = m0 + r;
-                    const double w = ldexp(1.0, col_exp8(sg.mP, gp < n_g ? gp : n_g - 1) + eq - 14);
+                    const double w = col_scale8(sg.mP, gp < n_g ? gp : n_g - 1) * sq;
                     double tr = (double)lre[i][j][NLEV8 - 1][v];
                     double ti = (double)lim[i][j][NLEV8 - 1][v];
 #pragma unroll
@@ -759,19 +816,26 @@ size_t split_slice_bytes(int K, int n_g) {
     return (size_t)NSL * groups * n_g * 16;
 }
 
-hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_u64, dim3((n_g + 255) / 256, NSLICE_SRC + 1), dim3(256), 0, st,
-                       jobs, n_g);
+hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool norm) {
+    const int nr = (K - 1) / jobs.rgroup + 1;
+    hipLaunchKernelGGL(k_zero_max, dim3((std::max(n_g, nr) + 255) / 256, NSPLIT + 2), dim3(256), 0,
+                       st, jobs, n_g, nr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colmax, dim3((n_g + 63) / 64, (K + CROWS - 1) / CROWS, NSLICE_SRC),
-                       dim3(256), 0, st, jobs, K, n_g);
+    const unsigned gx = (n_g + 63) / 64, gy = (K + CROWS - 1) / CROWS;
+    const dim3 first(gx, gy, NSLICE_SRC), second(gx, gy, 2);
+    if (norm) hipLaunchKernelGGL((k_colmax<false, true>), first, dim3(256), 0, st, jobs, K, n_g);
+    else hipLaunchKernelGGL((k_colmax<false, false>), first, dim3(256), 0, st, jobs, K, n_g);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (norm) hipLaunchKernelGGL((k_colmax<true, true>), second, dim3(256), 0, st, jobs, K, n_g);
+    else hipLaunchKernelGGL((k_colmax<true, false>), second, dim3(256), 0, st, jobs, K, n_g);
     return hipGetLastError();
 }
 
 hipError_t launch_slice(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool bf16) {
     const int groups = (K + 15) / 16 * 4;
-    hipError_t e = launch_colmax(jobs, K, n_g, st);
+    hipError_t e = launch_colmax(jobs, K, n_g, st, false);
     if (e != hipSuccess) return e;
     const long long items = (long long)groups * n_g;
     const dim3 grid((unsigned)((items + 255) / 256), NSLICE_SRC);
@@ -808,7 +872,7 @@ size_t split8_slice_bytes(int K, int n_g) {
 
 hipError_t launch_slice8(const SliceJobs &jobs, int K, int n_g, hipStream_t st) {
     const int groups = (K + 31) / 32 * GRP8;
-    hipError_t e = launch_colmax(jobs, K, n_g, st);
+    hipError_t e = launch_colmax(jobs, K, n_g, st, false);
     if (e != hipSuccess) return e;
     const long long items = (long long)groups * n_g;
     hipLaunchKernelGGL(k_slice8, dim3((unsigned)((items + 255) / 256), NSLICE_SRC), dim3(256), 0, st,

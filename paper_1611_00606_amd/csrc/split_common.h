@@ -19,18 +19,40 @@ __device__ __forceinline__ T *slice_ptr(T *const (&v)[N], int z) {
     return reinterpret_cast<T *>(p);
 }
 
-// Element v of row k of X[1] as operand 4.
-__device__ __forceinline__ double2 slice_scaled(const SliceJobs &jobs, double2 v, int k) {
-    const double w = sqrt(jobs.rscale[k]);
-    return double2{v.x * w, v.y * w};
+// Exponent e of row k: A's row times 2^e and X's times 2^-e have about equal
+// maxima. Every operand is cut relative to its column's maximum over all rows,
+// so an error of A^H X is that of the largest rows of A and of X against all
+// rows of the other, and X carries the whole of T_AA: with T_AA = D T D, A =
+// D^-1 A' (row magnitudes over a factor 1e4) the FP16 form's H was 2e-7 off
+// unscaled, 3e-10 in Alg. 1's grouping, whose Cholesky factors share T_AA
+// evenly between both operands, and 4e-10 with e. The upper half of a double is its
+// logarithm in units of 2^-20, to 0.09; a zero row counts as 2^-1023.
+__device__ __forceinline__ int slice_row_exp(const SliceJobs &jobs, int k) {
+    const int g = jobs.rgroup == 1 ? k : k / jobs.rgroup;
+    return ((int)jobs.rmx[1][g] - (int)jobs.rmx[0][g] + (1 << 20)) >> 21;
 }
 
-// exponent e with column max < 2^e (0 for an all-zero column)
-__device__ __forceinline__ int col_exp(const unsigned long long *mx, int n) {
-    const double m = __longlong_as_double((long long)mx[n]);
-    int e = 0;
-    if (m > 0.0) frexp(m, &e);
-    return e;
+// Element v of row k as operand z, of the matrix that operand is made from.
+__device__ __forceinline__ double2 slice_value(const SliceJobs &jobs, int z, double2 v, int k) {
+    if (z == 4) {
+        const double w = sqrt(jobs.rscale[k]);
+        return double2{v.x * w, v.y * w};
+    }
+    if (z == 2 || z == 5) {
+        const int e = slice_row_exp(jobs, k);
+        return double2{ldexp(v.x, z == 5 ? e : -e), ldexp(v.y, z == 5 ? e : -e)};
+    }
+    return v;
+}
+// The other operand made from matrix z (A: 5, B: 4), or -1.
+__device__ __forceinline__ int slice_other(int z) { return z == 0 ? 5 : z == 1 ? 4 : -1; }
+
+// Column scale of the sliced forms: the maximum itself, so that the first
+// slice's range is used in full (with the next power of two the dropped pairs
+// of slices weigh 1.4 times as much per operand, in the mean). At least
+// 2^-1021, so that it has a reciprocal; an all-zero column takes any.
+__device__ __forceinline__ double col_scale(const unsigned long long *mx, int n) {
+    return fmax(__longlong_as_double((long long)mx[n]), 0x1p-1021);
 }
 
 // (Re, Im) int8 byte pairs -> (Im, -Re): conj(p) q's imaginary part as a dot

@@ -21,6 +21,10 @@ namespace hs {
 
 namespace {
 
+// Blocks in a row of the grid: a dimension of it holds fewer than 2^32 threads,
+// and millions of light atoms, or tens of thousands at a large N_G, make more.
+constexpr int GRID_ROW = 1 << 22;
+
 template <class C>
 __global__ void __launch_bounds__(C::NT)
 k_atom(Atoms at, int n_g, int mtiles, int ctiles, int n_chol, const double2 *__restrict__ A,
@@ -31,7 +35,7 @@ k_atom(Atoms at, int n_g, int mtiles, int ctiles, int n_chol, const double2 *__r
     static_assert(C::NT == CHOL_THREADS && C::LDS_ELEMS * 16 >= CHOL_LDS_BYTES, "shared block");
     __shared__ double2 lds[C::LDS_ELEMS];
 
-    int b = blockIdx.x;
+    int b = blockIdx.y * GRID_ROW + blockIdx.x;
     if (b < n_chol) {
         chol_info(at, b, T_AA, info, reinterpret_cast<char *>(lds));
         return;
@@ -43,6 +47,7 @@ k_atom(Atoms at, int n_g, int mtiles, int ctiles, int n_chol, const double2 *__r
     b /= ctiles;
     const int a = b / mtiles;
     const int mt = b % mtiles;
+    if (a >= at.n_atoms) return;   // the last row of the grid
     const int r0 = at.row_off[a];
     const int n = at.row_off[a + 1] - r0;
     const int m0 = mt * C::BM;
@@ -63,8 +68,10 @@ hipError_t launch_atom_cfg(const Atoms &at, int n_g, const double2 *A, const dou
     const int n_chol = info ? at.n_atoms : 0;
     const long long blocks = n_chol + 2LL * ctiles * mtiles * at.n_atoms;
     if (blocks > (1LL << 30)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_atom<C>, dim3((unsigned)blocks), dim3(C::NT), 0, st, at, n_g, mtiles,
-                       ctiles, n_chol, A, B, T_AA, T_AB, M1, M2, info, X, Y);
+    const dim3 grid((unsigned)std::min<long long>(blocks, GRID_ROW),
+                    (unsigned)((blocks + GRID_ROW - 1) / GRID_ROW));
+    hipLaunchKernelGGL(k_atom<C>, grid, dim3(C::NT), 0, st, at, n_g, mtiles, ctiles, n_chol, A, B,
+                       T_AA, T_AB, M1, M2, info, X, Y);
     return hipGetLastError();
 }
 

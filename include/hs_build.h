@@ -367,6 +367,17 @@ int hs_gep_reduce_ex(const hs_complex *H, const hs_complex *S, int N,
  */
 int hs_gep_check_schedule(int N, int mode, int drop_wait, char *report, size_t report_len);
 
+/*
+ * hs_gep_check_failure - hs_gep_check_schedule with the 3 call-th launch or
+ * event call (from 1) reporting an error; other arguments as there. Returns
+ * the number of unordered pairs plus the number of launches issued that the
+ * caller's stream is not ordered after when the reduction returns (0: after an
+ * error too, work enqueued later on that stream starts when everything that
+ * was enqueued before has ended), -1 for N < 1, -2 for another mode, -3 if
+ * there is no such call.
+ */
+int hs_gep_check_failure(int N, int mode, int call, char *report, size_t report_len);
+
 /* ------------------------------------------------------------------------
  * Resident context: one atom set, many k-points.
  *

@@ -162,6 +162,8 @@ def load_library() -> ctypes.CDLL:
     lib.hs_gep_reduce_ex.restype = i32
     lib.hs_gep_check_schedule.argtypes = [i32, i32, i32, ctypes.c_char_p, sz]
     lib.hs_gep_check_schedule.restype = i32
+    lib.hs_gep_check_failure.argtypes = [i32, i32, i32, ctypes.c_char_p, sz]
+    lib.hs_gep_check_failure.restype = i32
     _lib = lib
     return lib
 
@@ -453,6 +455,15 @@ def hs_gep_check_schedule(N: int, mode: int = HS_FP64, drop_wait: int = 0):
     drop_wait leaves out one wait site (a test hook)."""
     buf = ctypes.create_string_buffer(4096)
     n = load_library().hs_gep_check_schedule(int(N), int(mode), int(drop_wait), buf, len(buf))
+    return int(n), buf.value.decode()
+
+
+def hs_gep_check_failure(N: int, call: int, mode: int = HS_FP64):
+    """(count, report): hs_gep_check_schedule's pairs, and the launches the
+    caller's stream is not ordered after, when the call-th launch or event call
+    of the reduction fails (host only); -3 if there is no such call."""
+    buf = ctypes.create_string_buffer(4096)
+    n = load_library().hs_gep_check_failure(int(N), int(mode), int(call), buf, len(buf))
     return int(n), buf.value.decode()
 
 

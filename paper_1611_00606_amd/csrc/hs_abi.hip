@@ -250,6 +250,14 @@ const double2 *c2(const hs_complex *x) { return reinterpret_cast<const double2 *
 double2 *c2(hs_complex *x) { return reinterpret_cast<double2 *>(x); }
 }  // namespace
 
+// `rep` into a caller's buffer of `len` bytes (or NULL), NUL-terminated.
+static void copy_report(const std::string &rep, char *out, size_t len) {
+    if (!out || !len) return;
+    const size_t k = std::min(rep.size(), len - 1);
+    std::memcpy(out, rep.data(), k);
+    out[k] = '\0';
+}
+
 // One-shot build: atom part then k-point part of one workspace.
 int run_build(const AtomPlan &p, int n_g, int mode, const hs_complex *A, const hs_complex *B,
               const hs_complex *T_AA, const hs_complex *T_AB, const hs_complex *T_BB,
@@ -385,12 +393,17 @@ int hs_gep_check_schedule(int N, int mode, int drop_wait, char *report, size_t r
     if (mode != HS_FP64 && mode != HS_FP64_3M) return -2;
     std::string rep;
     const int n = hs::gep_check_schedule(N, mode == HS_FP64_3M, drop_wait, rep);
-    if (report && report_len) {
-        const size_t k = std::min(rep.size(), report_len - 1);
-        std::memcpy(report, rep.data(), k);
-        report[k] = '\0';
-    }
+    hs::copy_report(rep, report, report_len);
     return n < 0 ? -6 : n;
+}
+
+int hs_gep_check_failure(int N, int mode, int call, char *report, size_t report_len) {
+    if (N < 1) return -1;
+    if (mode != HS_FP64 && mode != HS_FP64_3M) return -2;
+    std::string rep;
+    const int n = call < 1 ? -1 : hs::gep_check_failure(N, mode == HS_FP64_3M, call, rep);
+    hs::copy_report(rep, report, report_len);
+    return n < 0 ? -3 : n;
 }
 
 const char *hs_status_string(int status) {

@@ -155,6 +155,10 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
 // cell of a matrix (one writing) is ordered; returns the number of pairs
 // that are not (-1 if the orchestration failed), describing a few in report.
 int gep_check_schedule(int N, bool g3, int drop_tag, std::string &report);
+// The same with the call-th launch or event call (from 1) failing: the pairs,
+// and the launches that the caller's stream is not ordered after when
+// launch_gep returns; -1 if there is no such call.
+int gep_check_failure(int N, bool g3, int call, std::string &report);
 
 // ---------------------------------------------------------------------------
 // Host-side plan of one atom set and the enqueue steps shared by the one-shot

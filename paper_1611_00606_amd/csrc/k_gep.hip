@@ -742,7 +742,11 @@ struct Sched {
     std::vector<SchedOp> ops;
     const void *base[SB_COUNT] = {};
     int drop_tag = 0;            // waits with this tag are left out (a test hook)
+    int fail_call = 0;           // the call that fails: launches and event calls, from 1
+    int calls = 0;
     uintptr_t next_event = 1;
+    // Whether the call at hand fails.
+    bool fails() { return ++calls == fail_call; }
     int buf(const void *p) const {
         for (int i = 0; i < SB_COUNT; ++i)
             if (base[i] == p) return i;
@@ -761,6 +765,7 @@ thread_local Sched *g_sched = nullptr;
 
 hipError_t ev_create(hipEvent_t *e) {
     if (g_sched) {
+        if (g_sched->fails()) return hipErrorUnknown;
         *e = reinterpret_cast<hipEvent_t>(g_sched->next_event++);
         return hipSuccess;
     }
@@ -771,6 +776,7 @@ void ev_destroy(hipEvent_t e) {
 }
 hipError_t ev_record(hipEvent_t e, hipStream_t st) {
     if (g_sched) {
+        if (g_sched->fails()) return hipErrorUnknown;
         g_sched->ops.push_back(SchedOp{1, st, e, "record", {}});
         return hipSuccess;
     }
@@ -787,10 +793,12 @@ enum WaitTag {
     WT_FORK,                        // background stream after the top split's panel
     WT_FORK_AHEAD,                  // background stream after the pending lookahead work
     WT_END_AFTER_INVERSE,           // top split's M21 after the leading block's inverse
-    WT_END_AFTER_BACKGROUND         // Ht's last rows after the background's products
+    WT_END_AFTER_BACKGROUND,        // Ht's last rows after the background's products
+    WT_JOIN_AFTER_ERROR
 };
 hipError_t ev_wait(hipStream_t st, hipEvent_t e, int tag) {
     if (g_sched) {
+        if (g_sched->fails()) return hipErrorUnknown;
         if (tag != g_sched->drop_tag) g_sched->ops.push_back(SchedOp{2, st, e, "wait", {}});
         return hipSuccess;
     }
@@ -799,7 +807,10 @@ hipError_t ev_wait(hipStream_t st, hipEvent_t e, int tag) {
 
 // The vector-clock pass. Returns the number of unordered conflicting pairs
 // of launches and describes the first few in `report`.
-int sched_check(const Sched &sc, int N, std::string &report) {
+// `unjoined`: launches that the work after the call on stream `st` would not
+// be ordered after.
+int sched_check(const Sched &sc, int N, std::string &report, hipStream_t st = nullptr,
+                int *unjoined = nullptr) {
     constexpr int CB = 128;
     const int nc = (N + CB - 1) / CB;
     std::vector<hipStream_t> streams;
@@ -825,6 +836,7 @@ int sched_check(const Sched &sc, int N, std::string &report) {
     std::vector<signed char> mark(ncell, -1);   // per launch: 0 read, 1 write
     std::vector<size_t> touched;
     std::set<std::pair<int, int>> races;
+    std::vector<std::pair<int, int>> at;   // stream and clock of each launch
     for (int i = 0; i < (int)sc.ops.size(); ++i) {
         const SchedOp &op = sc.ops[i];
         const int s = sid(op.st);
@@ -846,6 +858,7 @@ int sched_check(const Sched &sc, int N, std::string &report) {
         }
         ++vc[s][s];
         const std::vector<int> &me = vc[s];
+        at.push_back({s, me[s]});
         touched.clear();
         for (const SchedAcc &a : op.acc) {
             const int cr0 = a.buf == SB_INFO ? 0 : a.r0 / CB, cr1 = a.buf == SB_INFO ? 0 : (a.r1 - 1) / CB;
@@ -889,6 +902,11 @@ int sched_check(const Sched &sc, int N, std::string &report) {
                 if (!had) cs.r.push_back(Last{i, s, me[s]});
             }
         }
+    }
+    if (unjoined) {
+        const std::vector<int> &end = vc[sid(st)];
+        *unjoined = 0;
+        for (const auto &l : at) *unjoined += end[l.first] < l.second;
     }
     return (int)races.size();
 }
@@ -1021,6 +1039,7 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
         }
         a.total = (int)nblk;
         if (g_sched) {
+            if (g_sched->fails()) return hipErrorUnknown;
             sched_mm(g, a);
             continue;
         }
@@ -1057,6 +1076,7 @@ hipError_t conj_t_batch(const Gep &g, const double2 *X, double2 *D, const Rect *
         }
         if (nj == 0) continue;
         if (g_sched) {
+            if (g_sched->fails()) return hipErrorUnknown;
             SchedOp &op = g_sched->launch(g.st, "k_gep_conj_t");
             for (int t = 0; t < nj; ++t) {
                 g_sched->add(op, X, j.r[t][0], j.r[t][1], j.r[t][2], j.r[t][3], false);
@@ -1080,10 +1100,11 @@ hipError_t conj_t(const Gep &g, const double2 *X, double2 *D, int i0, int i1, in
 // stream that is one hardware queue each at the default of four per
 // process); default priority,
 // created once and kept for the life of the process.
+constexpr int AUX_STREAMS = 3;
 hipStream_t aux_stream(int which) {
     if (g_sched) return reinterpret_cast<hipStream_t>((uintptr_t)(0x100 + which));
     static std::mutex mu;
-    static hipStream_t cached[64][3] = {};
+    static hipStream_t cached[64][AUX_STREAMS] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
     std::lock_guard<std::mutex> lk(mu);
@@ -1093,6 +1114,23 @@ hipStream_t aux_stream(int which) {
         cached[dev][which] = s;
     }
     return cached[dev][which];
+}
+
+// After a failed call: everything enqueued so far on the auxiliary streams
+// before later work on st (a call that failed between a launch there and its
+// event leaves it unordered). A stream that cannot be joined with an event is
+// waited for.
+void join_after_error(hipStream_t st) {
+    for (int which = 0; which < AUX_STREAMS; ++which) {
+        const hipStream_t s = aux_stream(which);
+        hipEvent_t e = nullptr;
+        if (!s) continue;
+        if (ev_create(&e) != hipSuccess || ev_record(e, s) != hipSuccess ||
+            ev_wait(st, e, WT_JOIN_AFTER_ERROR) != hipSuccess) {
+            if (!g_sched) (void)hipStreamSynchronize(s);
+        }
+        ev_destroy(e);
+    }
 }
 
 // Cholesky, right-looking over panels of LB columns: factor and invert the
@@ -1150,7 +1188,9 @@ hipError_t factor(const Gep &g, Hook after_panel) {
     for (int kb = 0; kb < N && err == hipSuccess; kb += LB) {
         const int nb = N - kb < LB ? N - kb : LB;
         const int t0 = kb + nb;
-        if (g_sched) {
+        if (g_sched && g_sched->fails()) {
+            err = hipErrorUnknown;
+        } else if (g_sched) {
             SchedOp &op = g_sched->launch(g.st, "k_gep_leaf");
             for (const double2 *X : {(const double2 *)g.L, (const double2 *)g.M,
                                      (const double2 *)g.MH})
@@ -1209,15 +1249,9 @@ hipError_t factor(const Gep &g, Hook after_panel) {
         err = mm(g, g.LH, g.LH, g.L, t0, N, t0, u1, k0, t0, MM_MASK, OP_SUB, g.W,
                  t1);                                  // next column block(s), next S21^H
     }
-    // join the other streams, also after an error
-    if (look_pending) {
-        const hipError_t e = ev_wait(g.st, e_look, WT_JOIN_AHEAD);
-        if (err == hipSuccess) err = e;
-    }
-    if (w_pending) {
-        const hipError_t e = ev_wait(g.st, e_w, WT_JOIN_TRANSPOSE);
-        if (err == hipSuccess) err = e;
-    }
+    // join the other streams
+    if (err == hipSuccess && look_pending) err = ev_wait(g.st, e_look, WT_JOIN_AHEAD);
+    if (err == hipSuccess && w_pending) err = ev_wait(g.st, e_w, WT_JOIN_TRANSPOSE);
     for (hipEvent_t e : {e_panel, e_bulk, e_look, e_next, e_w}) ev_destroy(e);
     return err;
 }
@@ -1324,14 +1358,8 @@ hipError_t step(const Gep &g, double2 *Ht, int a, int b, Ready ready) {
     return mm_batch(g, g.MH, g.W, g.K, &k, 1, MM_LOWER, OP_SUB, g.W, g.K, nullptr, g.K, -1);
 }
 
-}  // namespace
-
-size_t gep_workspace_bytes(int N) {
-    return 5 * padded(16 * (size_t)N * (size_t)N) + 256;   // LH, M, MH, W, K, info slot
-}
-
-hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, double2 *Ht,
-                      int *info, char *ws, hipStream_t st, bool g3) {
+hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, double2 *Ht,
+                       int *info, char *ws, hipStream_t st, bool g3) {
     const size_t m = padded(16 * (size_t)N * (size_t)N);
     Gep g;
     g.L = L;
@@ -1352,6 +1380,7 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     // Ht's upper triangle by conjugation, Im(diag) = 0
     const auto mirror = [&]() -> hipError_t {
         if (g_sched) {
+            if (g_sched->fails()) return hipErrorUnknown;
             g_sched->add(g_sched->launch(st, "k_mirror"), Ht, 0, N, 0, N, true);
             return hipSuccess;
         }
@@ -1360,6 +1389,7 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
     if (g_sched) {
         const void *b[SB_COUNT] = {H, S, L, Ht, g.LH, g.M, g.MH, g.W, g.K, g.info};
         std::copy(b, b + SB_COUNT, g_sched->base);
+        if (g_sched->fails()) return hipErrorUnknown;
         SchedOp &op = g_sched->launch(st, "k_gep_init");
         g_sched->add(op, S, 0, N, 0, N, false);
         for (const void *X : {(const void *)L, (const void *)g.M, (const void *)g.MH,
@@ -1426,31 +1456,58 @@ hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, dou
         });
         if (err == hipSuccess) err = diag_block(g, g.K, Ht, begin(done), ends[done]);
     }
-    if (forked > 0) {   // join the second stream even after an error
-        const hipError_t e = ev_wait(st, e_v, WT_END_AFTER_BACKGROUND);
-        if (err == hipSuccess) err = e;
-    }
+    if (err == hipSuccess && forked > 0) err = ev_wait(st, e_v, WT_END_AFTER_BACKGROUND);
     for (hipEvent_t e : {e_split, e_inv, e_v}) ev_destroy(e);
     GEP_TRY(err);
     return mirror();
 }
 
+}  // namespace
+
+size_t gep_workspace_bytes(int N) {
+    return 5 * padded(16 * (size_t)N * (size_t)N) + 256;   // LH, M, MH, W, K, info slot
+}
+
+hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, double2 *Ht,
+                      int *info, char *ws, hipStream_t st, bool g3) {
+    const hipError_t e = enqueue_gep(H, S, N, L, Ht, info, ws, st, g3);
+    if (e != hipSuccess && N > 3 * LB) join_after_error(st);   // only those use other streams
+    return e;
+}
+
+namespace {
+// launch_gep with the recorder installed: distinct stand-in addresses, nothing
+// is dereferenced or launched.
+hipStream_t sched_stream() { return reinterpret_cast<hipStream_t>((uintptr_t)0x10); }
+hipError_t sched_run(Sched &sc, int N, bool g3) {
+    auto fake = [](uintptr_t a) { return reinterpret_cast<double2 *>(a << 40); };
+    g_sched = &sc;
+    const hipError_t e = launch_gep(fake(1), fake(2), N, fake(3), fake(4), nullptr,
+                                    reinterpret_cast<char *>((uintptr_t)1 << 44), sched_stream(), g3);
+    g_sched = nullptr;
+    return e;
+}
+}  // namespace
+
 int gep_check_schedule(int N, bool g3, int drop_tag, std::string &report) {
     Sched sc;
     sc.drop_tag = drop_tag;
-    // distinct stand-in addresses; nothing is dereferenced or launched
-    auto fake = [](uintptr_t a) { return reinterpret_cast<double2 *>(a); };
-    char *ws = reinterpret_cast<char *>((uintptr_t)1 << 44);
-    g_sched = &sc;
-    const hipError_t e = launch_gep(fake((uintptr_t)1 << 40), fake((uintptr_t)2 << 40), N,
-                                    fake((uintptr_t)3 << 40), fake((uintptr_t)4 << 40), nullptr, ws,
-                                    reinterpret_cast<hipStream_t>((uintptr_t)0x10), g3);
-    g_sched = nullptr;
-    if (e != hipSuccess) {
+    if (sched_run(sc, N, g3) != hipSuccess) {
         report = "orchestration returned an error";
         return -1;
     }
     return sched_check(sc, N, report);
+}
+
+int gep_check_failure(int N, bool g3, int call, std::string &report) {
+    Sched sc;
+    sc.fail_call = call;
+    sched_run(sc, N, g3);
+    if (sc.calls < call) return -1;
+    int unjoined = 0;
+    const int races = sched_check(sc, N, report, sched_stream(), &unjoined);
+    if (unjoined) report += std::to_string(unjoined) + " launches are not joined into the caller's stream";
+    return races + unjoined;
 }
 
 }  // namespace hs

@@ -290,6 +290,18 @@ int hs_tile_config(int id, int *bm, int *bn);
 int hs_autotune_atoms(const int32_t *nl_values, int n_values, int N_G, int reps,
                       void *stream, hs_tuning *out, float *ms);
 
+/*
+ * hs_check_reduce_plan - which tiles the large reductions of 1 K = sum of N_L
+ * and 2 N_G take in 3 mode (HS_FP64, HS_FP64_3M, HS_SPLIT_F16 or _BF16) on a
+ * device of 4 cus compute units (256 on an MI355X), host only. Returns the
+ * number of cells of the lower triangles of H and S that the launch's blocks do
+ * not compute exactly once (0), or -i for an invalid argument i. 5 plan (host
+ * int32 [4] or NULL): FP64 forms blocks per compute unit (1 or 2), 128-tiles,
+ * 64-tiles, 64-tiles computed as four 32-tiles; FP16/BF16 slices 1, 64-tiles,
+ * 64 x 32 halves, 0.
+ */
+int hs_check_reduce_plan(int K, int N_G, int mode, int cus, int32_t plan[4]);
+
 /* ------------------------------------------------------------------------
  * Reduction of the generalized eigenproblem to standard form, the step that
  * follows the build: per k-point the expansion coefficients c solve

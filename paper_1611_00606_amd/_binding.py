@@ -160,6 +160,8 @@ def load_library() -> ctypes.CDLL:
     lib.hs_gep_reduce.restype = i32
     lib.hs_gep_reduce_ex.argtypes = [vp, vp, i32, vp, vp, vp, vp, sz, vp, i32]
     lib.hs_gep_reduce_ex.restype = i32
+    lib.hs_check_reduce_plan.argtypes = [i32, i32, i32, i32, ctypes.POINTER(i32)]
+    lib.hs_check_reduce_plan.restype = i32
     lib.hs_gep_check_schedule.argtypes = [i32, i32, i32, ctypes.c_char_p, sz]
     lib.hs_gep_check_schedule.restype = i32
     lib.hs_gep_check_failure.argtypes = [i32, i32, i32, ctypes.c_char_p, sz]
@@ -445,6 +447,16 @@ def hs_autotune_atoms(nl_values, N_G, reps=3, stream=None):
 
 def hs_gep_workspace_bytes(N) -> int:
     return int(load_library().hs_gep_workspace_bytes(int(N)))
+
+
+def hs_check_reduce_plan(K: int, N_G: int, mode: int = HS_FP64, cus: int = 256):
+    """(wrong, plan): cells of H's and S's lower triangles that the reductions'
+    blocks do not compute exactly once, and the tiles taken (host only):
+    [blocks per compute unit, 128-tiles, 64-tiles, 64-tiles in 32-tiles] or
+    [1, 64-tiles, halves, 0]; wrong is negative for invalid arguments."""
+    plan = (ctypes.c_int32 * 4)()
+    n = load_library().hs_check_reduce_plan(int(K), int(N_G), int(mode), int(cus), plan)
+    return int(n), list(plan)
 
 
 def hs_gep_check_schedule(N: int, mode: int = HS_FP64, drop_wait: int = 0):

@@ -357,6 +357,22 @@ int hs_build(const hs_complex *A, const hs_complex *B, const hs_complex *T_AA,
 
 int hs_tile_config(int id, int *bm, int *bn) { return hs::tile_shape(id, bm, bn); }
 
+int hs_check_reduce_plan(int K, int N_G, int mode, int cus, int32_t plan[4]) {
+    if (K < 1) return -1;
+    if (N_G < 1) return -2;
+    if (cus < 1) return -4;
+    int32_t p[4];
+    int n;
+    if (mode == HS_FP64 || mode == HS_FP64_3M)
+        n = hs::reduce_check_plan(K, N_G, mode == HS_FP64_3M, cus, p);
+    else if (mode == HS_SPLIT_F16 || mode == HS_SPLIT_BF16)
+        n = hs::split_check_plan(N_G, cus, p);
+    else
+        return -3;
+    if (plan) std::copy(p, p + 4, plan);
+    return n;
+}
+
 size_t hs_gep_workspace_bytes(int N) { return N < 1 ? 0 : hs::gep_workspace_bytes(N); }
 
 int hs_gep_reduce(const hs_complex *H, const hs_complex *S, int N, hs_complex *L, hs_complex *Ht,

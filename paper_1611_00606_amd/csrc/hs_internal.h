@@ -19,14 +19,17 @@ namespace hs {
 // through its L2 and all XCDs work on the same output; every XCD gets n / 8
 // items, up to rounding.
 __host__ __device__ inline int xcd_blocks(int n) { return (n + 7) / 8 * 8; }
-// Item of block b < xcd_blocks(n), or -1.
-__device__ __forceinline__ int xcd_item(int b, int n, int first) {
+// Item of block b < xcd_blocks(n), or -1. XCD x takes the blocks' range [c0, c1)
+// of n; of every prefix c of it H's share is floor(c nf / n), which grows by at
+// most one per block, so that the ranges of H and of S fit into the blocks for
+// any n and `first`.
+__host__ __device__ __forceinline__ int xcd_item(int b, int n, int first) {
     const long long x = b % 8;
     const int i = b / 8;
-    const int nf = n < first ? n : first;
-    const int h0 = (int)(x * nf / 8), h1 = (int)((x + 1) * nf / 8);
     const int c0 = (int)(x * n / 8), c1 = (int)((x + 1) * n / 8);
     if (i >= c1 - c0) return -1;
+    if (n <= first) return c0 + i;
+    const int h0 = (int)((long long)c0 * first / n), h1 = (int)((long long)c1 * first / n);
     return i < h1 - h0 ? h0 + i : first + (c0 - h0) + i - (h1 - h0);
 }
 
@@ -62,12 +65,40 @@ hipError_t launch_atom(const Atoms &at, int n_g, const double2 *A, const double2
                        const double2 *T_AA, const double2 *T_AB, const double2 *M1,
                        const double2 *M2, int *info, double2 *X, double2 *Y, hipStream_t st);
 
-// Large reductions H = A^H X + B^H Y, S = A^H A + B^H |U|^2 B into the lower
-// triangles of H and S (complex FP64 MFMA; g3: 3 real products per complex
-// product instead of 4).
+// Large reductions H = A^H X + B^H Y, S = A^H A + B^H |U|^2 B, both triangles
+// (complex FP64 MFMA; g3: 3 real products per complex product instead of 4).
 hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
                          const double2 *X, const double2 *Y, const double *d,
                          double2 *H, double2 *S, hipStream_t st, bool g3);
+
+// Host-only checks of the tiles that a reduction's blocks compute on a device
+// of `cus` compute units: the number of cells of the lower triangles of H and S
+// that are not computed exactly once. plan: blocks per compute unit, 128-tiles,
+// 64-tiles, 64-tiles computed as 32-tiles; 1, whole tiles, half tiles, 0.
+int reduce_check_plan(int K, int n_g, bool g3, int cus, int plan[4]);
+int split_check_plan(int n_g, int cus, int plan[4]);
+// How often each h x w cell on or below the diagonal of H and of S is computed.
+struct CellCount {
+    int n, h, w, nr, nc;
+    std::vector<unsigned char> count;   // saturates at 2
+    CellCount(int n_g, int h_, int w_)
+        : n(n_g), h(h_), w(w_), nr((n_g + h_ - 1) / h_), nc((n_g + w_ - 1) / w_),
+          count(2 * (size_t)nr * nc, 0) {}
+    void add(bool isH, int m0, int n0, int rows, int cols) {
+        for (int r = m0 / h; r < (m0 + rows) / h && r < nr; ++r)
+            for (int c = n0 / w; c < (n0 + cols) / w && c < nc; ++c) {
+                unsigned char &x = count[((isH ? 0 : (size_t)nr) + r) * nc + c];
+                if (x < 2) ++x;
+            }
+    }
+    int wrong() const {
+        int bad = 0;
+        for (int r = 0; r < 2 * nr; ++r)
+            for (int c = 0; c < nc && c * w < std::min(n, (r % nr + 1) * h); ++c)
+                bad += count[(size_t)r * nc + c] != 1;
+        return bad;
+    }
+};
 
 // Error bookkeeping shared by the C entry points (thread-local message).
 void set_error(int status, const std::string &msg);

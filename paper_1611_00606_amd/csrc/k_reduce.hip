@@ -88,7 +88,7 @@ struct RedArgs {
 
 // Tile (i, j), j < i, of the t-th position in the banded order: bands of
 // BAND tile columns, each band walked row by row from its diagonal down.
-__device__ __forceinline__ void band_tile(int t, int nt, int &ti, int &tj) {
+__host__ __device__ __forceinline__ void band_tile(int t, int nt, int &ti, int &tj) {
     for (int c0 = 0;; c0 += BAND) {
         const int m = nt - c0;   // rows of the band, its first one empty
         const int w = m < BAND ? m : BAND;
@@ -109,6 +109,73 @@ __device__ __forceinline__ void band_tile(int t, int nt, int &ti, int &tj) {
         }
         t -= cnt;
     }
+}
+
+// What a block computes: a 128-tile (a 128 / PARTS columns wide part of it), 64-
+// or 32-tile at rows m0, columns n0. size 0: nothing.
+struct RedPlace {
+    bool isH;
+    int size, m0, n0;
+};
+template <int PARTS>
+__host__ __device__ __forceinline__ RedPlace red_place(const RedArgs &args, int b) {
+    RedPlace r = {false, 0, 0, 0};
+    if (b < args.b128) {
+        int q = xcd_item(b, PARTS * args.n128, PARTS * args.nlow);
+        if (q < 0) return r;
+        const int part = q % PARTS;
+        q /= PARTS;
+        r.isH = q < args.nlow;
+        int ti, tj;
+        band_tile(r.isH ? q : q - args.nlow, args.nf, ti, tj);
+        r.size = 128;
+        r.m0 = ti * 128;
+        r.n0 = tj * 128 + part * (128 / PARTS);
+        return r;
+    }
+    b -= args.b128;
+    const bool whole = b < args.b64;
+    int sub = 0, u;
+    if (whole) {
+        u = xcd_item(b, args.n64, args.n64);
+        if (u < 0) return r;
+    } else {
+        b -= args.b64;
+        sub = b & 3;
+        u = args.n64 + (b >> 2);
+    }
+    // 64-tile u: quarters of the 128-tiles after the first n128, then the
+    // diagonal quarters and last rows of H, then of S
+    int I, J;   // in 64-tiles
+    const int nq = 4 * (2 * args.nlow - args.n128);
+    if (u < nq) {
+        const int q = args.n128 + u / 4;
+        r.isH = q < args.nlow;
+        band_tile(r.isH ? q : q - args.nlow, args.nf, I, J);
+        I = 2 * I + (u >> 1 & 1);
+        J = 2 * J + (u & 1);
+    } else {
+        u -= nq;
+        r.isH = u < args.nedge;
+        if (!r.isH) u -= args.nedge;
+        if (u < 3 * args.nf) {
+            const int q = u % 3;   // (0,0), (1,0), (1,1) of the diagonal block
+            I = 2 * (u / 3) + (q + 1) / 2;
+            J = 2 * (u / 3) + q / 2;
+        } else {
+            u -= 3 * args.nf;
+            I = 2 * args.nf;
+            if (u > I) {
+                u -= I + 1;
+                ++I;
+            }
+            J = u;
+        }
+    }
+    r.size = whole ? 64 : 32;
+    r.m0 = I * 64 + (whole ? 0 : (sub >> 1) * 32);
+    r.n0 = J * 64 + (whole ? 0 : (sub & 1) * 32);
+    return r;
 }
 
 // One C::BM x C::BN tile of H or S at rows m0, columns n0 (multiples of C::BN).
@@ -173,62 +240,10 @@ k_reduce(RedArgs args) {
     using T = Tiles<TWO>;
     __shared__ double2 lds[red_lds<T>()];
 
-    int b = blockIdx.x;
-    if (b < args.b128) {
-        int q = xcd_item(b, T::PARTS * args.n128, T::PARTS * args.nlow);
-        if (q < 0) return;
-        const int part = q % T::PARTS;
-        q /= T::PARTS;
-        const bool isH = q < args.nlow;
-        int ti, tj;
-        band_tile(isH ? q : q - args.nlow, args.nf, ti, tj);
-        reduce_tile<typename T::T128, G3>(args, isH, ti * 128, tj * 128 + part * T::T128::BN, lds);
-        return;
-    }
-    b -= args.b128;
-    const bool whole = b < args.b64;
-    int sub = 0, u;
-    if (whole) {
-        u = xcd_item(b, args.n64, args.n64);
-        if (u < 0) return;
-    } else {
-        b -= args.b64;
-        sub = b & 3;
-        u = args.n64 + (b >> 2);
-    }
-    // 64-tile u: quarters of the 128-tiles after the first n128, then the
-    // diagonal quarters and last rows of H, then of S
-    bool isH;
-    int I, J;   // in 64-tiles
-    const int nq = 4 * (2 * args.nlow - args.n128);
-    if (u < nq) {
-        const int q = args.n128 + u / 4;
-        isH = q < args.nlow;
-        band_tile(isH ? q : q - args.nlow, args.nf, I, J);
-        I = 2 * I + (u >> 1 & 1);
-        J = 2 * J + (u & 1);
-    } else {
-        u -= nq;
-        isH = u < args.nedge;
-        if (!isH) u -= args.nedge;
-        if (u < 3 * args.nf) {
-            const int q = u % 3;   // (0,0), (1,0), (1,1) of the diagonal block
-            I = 2 * (u / 3) + (q + 1) / 2;
-            J = 2 * (u / 3) + q / 2;
-        } else {
-            u -= 3 * args.nf;
-            I = 2 * args.nf;
-            if (u > I) {
-                u -= I + 1;
-                ++I;
-            }
-            J = u;
-        }
-    }
-    if (whole)
-        reduce_tile<typename T::T64, G3>(args, isH, I * 64, J * 64, lds);
-    else
-        reduce_tile<typename T::T32, G3>(args, isH, I * 64 + (sub >> 1) * 32, J * 64 + (sub & 1) * 32, lds);
+    const RedPlace p = red_place<T::PARTS>(args, blockIdx.x);
+    if (p.size == 128) reduce_tile<typename T::T128, G3>(args, p.isH, p.m0, p.n0, lds);
+    else if (p.size == 64) reduce_tile<typename T::T64, G3>(args, p.isH, p.m0, p.n0, lds);
+    else if (p.size == 32) reduce_tile<typename T::T32, G3>(args, p.isH, p.m0, p.n0, lds);
 }
 
 // When n tiles of equal cost have been handed to slots for a block in turn,
@@ -380,6 +395,24 @@ hipError_t launch_reduce(int K, int n_g, const double2 *A, const double2 *B,
     else
         hipLaunchKernelGGL((k_reduce<false, false>), grid, dim3(RED_THREADS), 0, st, args);
     return hipGetLastError();
+}
+
+int reduce_check_plan(int K, int n_g, bool g3, int cus, int plan[4]) {
+    RedArgs a = {};
+    a.K = K;
+    a.n_g = n_g;
+    const bool two = make_plan(a, cus, g3);
+    plan[0] = two ? 2 : 1;
+    plan[1] = a.n128;
+    plan[2] = a.n64;
+    plan[3] = a.n32;
+    constexpr int CELL = 32;
+    CellCount cells(n_g, CELL, CELL);
+    for (int b = 0; b < a.b128 + a.b64 + 4 * a.n32; ++b) {
+        const RedPlace p = two ? red_place<2>(a, b) : red_place<1>(a, b);
+        if (p.size) cells.add(p.isH, p.m0, p.n0, p.size, p.size == 128 ? 128 / plan[0] : p.size);
+    }
+    return cells.wrong();
 }
 
 hipError_t launch_mirror(double2 *H, double2 *S, int n_g, hipStream_t st) {

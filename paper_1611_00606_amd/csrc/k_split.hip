@@ -865,6 +865,22 @@ hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
     return hipGetLastError();
 }
 
+int split_check_plan(int n_g, int cus, int plan[4]) {
+    const SplitPlan p = split_plan(n_g, cus, SPLIT_HALF_COST);
+    plan[0] = 1;
+    plan[1] = p.whole;
+    plan[2] = 2 * (2 * p.ntri - p.whole);
+    plan[3] = 0;
+    CellCount cells(n_g, SBM, 32);
+    for (int b = 0; b < (int)split_blocks(p); ++b) {
+        const SplitPlace q = split_place(p, b, SBAND);
+        if (q.ti < 0) continue;
+        if (q.half < 0) cells.add(q.isH, q.ti * 64, q.tj * 64, 64, 64);
+        else cells.add(q.isH, q.ti * 64, q.tj * 64 + 32 * q.half, 64, 32);
+    }
+    return cells.wrong();
+}
+
 size_t split8_slice_bytes(int K, int n_g) {
     const long long groups = (long long)((K + 31) / 32) * GRP8;
     return (size_t)NSL8 * groups * n_g * 16;

@@ -68,7 +68,7 @@ __device__ __forceinline__ unsigned im_pairs(unsigned d) {
 // Tile (i, j), j <= i, at position t of the banded order over an nt x nt
 // lower triangle of tiles: bands of `band` tile columns, each band walked
 // from its diagonal triangle down; (-1, -1) past the end.
-__device__ __forceinline__ void sband_tile(int t, int nt, int &ti, int &tj, int band) {
+__host__ __device__ __forceinline__ void sband_tile(int t, int nt, int &ti, int &tj, int band) {
     int c0 = 0;
     for (;;) {
         const int m = nt - c0;
@@ -130,7 +130,7 @@ struct SplitPlace {
     bool isH;
     int ti, tj, half;
 };
-__device__ __forceinline__ SplitPlace split_place(const SplitPlan &p, int b, int band) {
+__host__ __device__ __forceinline__ SplitPlace split_place(const SplitPlan &p, int b, int band) {
     SplitPlace r;
     int t;
     r.half = -1;

@@ -92,11 +92,12 @@ enum {
  *                 and are recombined in binary64. Error about 2^-35 of the
  *                 operand column maxima per product term (relative Frobenius
  *                 error of H and S 1e-10 .. 2e-10 for Gaussian operands,
- *                 below 1e-9). In the split and modular forms the rows of A
- *                 and X in A^H X are first balanced against each other by
- *                 powers of two, so that atoms and rows of unlike magnitude
- *                 in T_AA do not raise the error; H and S hold the row maxima
- *                 until they are written. Inputs must be finite.
+ *                 below 1e-9). In the split and modular forms rows of A and X
+ *                 of unlike magnitude in A^H X are first balanced against each
+ *                 other by powers of two, so that unlike atoms or rows in T_AA
+ *                 do not raise the error (for K > 4 N_G^2 in groups of rows);
+ *                 H and S hold the row maxima until they are written. Inputs
+ *                 must be finite.
  *   HS_SPLIT_I8   split precision on INT8 MFMA: the same column scaling, 5
  *                 integer slices of 7 bits (int8; the first within +-127),
  *                 the 15 pairs s + t <= 6 on INT8 MFMA with exact INT32

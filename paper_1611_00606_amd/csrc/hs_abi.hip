@@ -113,7 +113,7 @@ long long BatchBufs::max_tiles(int n_atoms, int n_g) {
 
 size_t BatchBufs::bytes(int n_atoms, int n_g) {
     return align_up(sizeof(int) * (size_t)n_atoms) + align_up(sizeof(int) * (size_t)(n_atoms + 1)) +
-           align_up(sizeof(int)) +
+           align_up(2 * sizeof(int)) +
            align_up(2 * sizeof(int) * (size_t)max_tiles(n_atoms, n_g));
 }
 
@@ -124,7 +124,7 @@ void BatchBufs::carve(int n_atoms, char *base) {
     zoff = reinterpret_cast<int *>(base + o);
     o += align_up(sizeof(int) * (size_t)(n_atoms + 1));
     ctrl = reinterpret_cast<int *>(base + o);
-    o += align_up(sizeof(int));
+    o += align_up(2 * sizeof(int));
     tiles = reinterpret_cast<int *>(base + o);
 }
 
@@ -193,7 +193,7 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
     if (split_mode(mode)) {
         // operands: 0 A, 1 B, 2 X 2^-e, 3 Y, 4 U B, 5 A 2^e
         const int K = p.K;
-        SliceJobs jobs = {{A, B, kb.X, kb.Y}, ab.d + K, {}, {}, {}, 1};
+        SliceJobs jobs = {{A, B, kb.X, kb.Y}, ab.d + K, {}, {}, {}, 1, kb.batch.ctrl + 1};
         // The row maxima live in H and S until the reductions write those:
         // 4 N_G^2 entries each, for more rows than that one per group of rows.
         jobs.rmx[0] = reinterpret_cast<unsigned *>(H);
@@ -212,11 +212,12 @@ hipError_t enqueue_kpoint(const AtomPlan &p, const AtomBufs &ab, int n_g, int mo
         const SliceView hseg[2][2] = {{v[1], v[3]}, {v[5], v[2]}};
         const SliceView sseg[2][2] = {{v[0], v[0]}, {v[4], v[4]}};
         if (mode == HS_SPLIT_I8_CRT)
-            e = launch_crt_reduce(K, n_g, hseg, sseg, kb.crt, H, S, st);
+            e = launch_crt_reduce(K, n_g, hseg, sseg, jobs.scaled, kb.crt, H, S, st);
         else if (mode == HS_SPLIT_I8)
-            e = launch_split8_reduce(K, n_g, hseg, sseg, H, S, st);
+            e = launch_split8_reduce(K, n_g, hseg, sseg, jobs.scaled, H, S, st);
         else
-            e = launch_split_reduce(K, n_g, hseg, sseg, H, S, st, mode == HS_SPLIT_BF16);
+            e = launch_split_reduce(K, n_g, hseg, sseg, jobs.scaled, H, S, st,
+                                    mode == HS_SPLIT_BF16);
     } else {
         e = launch_reduce(p.K, n_g, A, B, kb.X, kb.Y, ab.d, H, S, st, mode == HS_FP64_3M);
     }

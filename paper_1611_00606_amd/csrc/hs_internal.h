@@ -117,8 +117,9 @@ inline bool split_mode(int mode) {   // the operands are sliced (or cut into res
 
 // Split-precision reductions (k_split.hip). The sliced operands, from the
 // matrices M[0..3] = A, B, X, Y [K][N_G]: 0 A, 1 B, 2 X 2^-e, 3 Y, 4 the rows
-// of B scaled by sqrt(rscale[k]), 5 A 2^e, with e[k] per row (slice_row_exp);
-// for each the column maxima mx [N_G] (bit patterns of doubles; block norms in
+// of B scaled by sqrt(rscale[k]), 5 A 2^e, with e[k] per row (slice_row_exp;
+// where A and X need no balance e = 0 and operand 0 stands for 5, which is not
+// written); for each the column maxima mx [N_G] (bit patterns of doubles; block norms in
 // the modular form) and the FP16 slices S [4][groups][N_G][8], groups = 4 * ceil(K / 16).
 // Every pass takes all of them in one launch and reads each matrix once.
 constexpr int NSLICE_SRC = 4;
@@ -132,11 +133,13 @@ struct SliceJobs {
     // |Im| of A's rows and of X's
     unsigned *rmx[2];
     int rgroup;
+    int *scaled;   // whether rows are scaled (written by launch_colmax)
 };
 struct SliceView {
     const _Float16 *S;
     const unsigned long long *mx;
 };
+// The reductions' (A 2^e, X 2^-e) takes hseg[1][0] if *scaled, else sseg[0][0] = A.
 size_t split_slice_bytes(int K, int n_g);
 // zero every mx and rmx, then A's and X's row maxima and the column maxima
 // into them; norm: instead of the maxima the largest Euclidean norm of 64 rows
@@ -147,15 +150,15 @@ hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st, 
 hipError_t launch_slice(const SliceJobs &jobs, int K, int n_g, hipStream_t st, bool bf16);
 // H segments (B,Y), (A 2^e, X 2^-e); S segments (A,A), (Bs,Bs): [segment][P or Q]
 hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
-                               const SliceView (&sseg)[2][2], double2 *H, double2 *S,
-                               hipStream_t st, bool bf16);
+                               const SliceView (&sseg)[2][2], const int *scaled, double2 *H,
+                               double2 *S, hipStream_t st, bool bf16);
 // INT8 form: slices S8 [5][groups][N_G][16 int8], groups = 4 * ceil(K / 32);
 // same column maxima and segments as the FP16 form.
 size_t split8_slice_bytes(int K, int n_g);
 hipError_t launch_slice8(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
 hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
-                                const SliceView (&sseg)[2][2], double2 *H, double2 *S,
-                                hipStream_t st);
+                                const SliceView (&sseg)[2][2], const int *scaled, double2 *H,
+                                double2 *S, hipStream_t st);
 // Modular INT8 form (k_crt.hip): residues R [NMOD][groups][N_G][16 int8],
 // groups = 8 * ceil(K / 64) (of 64 rows four hold the real parts of 16 rows
 // each, four the imaginary parts), of each operand's integers; the
@@ -165,8 +168,8 @@ size_t crt_residue_bytes(int K, int n_g);
 size_t crt_work_bytes(int n_g);
 hipError_t launch_residue(const SliceJobs &jobs, int K, int n_g, hipStream_t st);
 hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
-                             const SliceView (&sseg)[2][2], void *work, double2 *H, double2 *S,
-                             hipStream_t st);
+                             const SliceView (&sseg)[2][2], const int *scaled, void *work,
+                             double2 *H, double2 *S, hipStream_t st);
 inline size_t slice_bytes(int mode, int K, int n_g) {
     if (mode == HS_SPLIT_I8_CRT) return crt_residue_bytes(K, n_g);
     return mode == HS_SPLIT_I8 ? split8_slice_bytes(K, n_g) : split_slice_bytes(K, n_g);
@@ -228,7 +231,7 @@ constexpr int ATOM_TILE_MIN_BM = 32, ATOM_TILE_MIN_BN = 128;
 struct BatchBufs {
     int *perm;    // [N_A]
     int *zoff;    // [N_A + 1]
-    int *ctrl;    // [1] item counter
+    int *ctrl;    // [2] item counter; after the stage: SliceJobs.scaled
     int *tiles;   // [2 max_tiles(N_A, N_G)] atom, tile within the atom of each product tile
     static long long max_tiles(int n_atoms, int n_g);
     static size_t bytes(int n_atoms, int n_g);

@@ -163,7 +163,7 @@ k_residue(SliceJobs jobs, int K, int n_g, int blocks, double cn) {
         }
     };
     cut(z);
-    if (slice_other(z) >= 0) cut(slice_other(z));
+    if (slice_other(jobs, z) >= 0) cut(slice_other(jobs, z));
 }
 
 // ---------------------------------------------------------------------------
@@ -208,6 +208,7 @@ static_assert(CFRAG == 64, "the residue layout assumes 64 blocks per tile");
 
 struct CrtArgs {
     const uint4 *P[NSEG], *Q[NSEG];   // residue planes of modulus 0 per segment
+    const int *scaled;                 // 0: segment 1's P is segment 2's, A
     uint2 *out;                        // [NSEG * NMOD][ntri][CFRAG][64 lanes]
     long long plane;                   // items per modulus plane
     int n_g, groups, nt, ntri, ntri8;
@@ -244,6 +245,7 @@ k_crt_reduce(CrtArgs args) {
             P = args.P[s];
             Q = args.Q[s];
         }
+    if (seg == 1 && !*args.scaled) P = args.P[2];
     P += mi * args.plane;
     Q += mi * args.plane;
     const double m = crt_modulus(mi);
@@ -374,6 +376,7 @@ k_crt_reduce(CrtArgs args) {
 struct CrtRecArgs {
     const uint2 *res;
     const unsigned long long *mP[NSEG], *mQ[NSEG];
+    const int *scaled;
     double2 *H, *S;
     int n_g, nt, ntri;
     double cn;
@@ -450,7 +453,7 @@ k_crt_recon(CrtRecArgs a) {
     };
     if (isH) {
         segment(0, a.mP[0], a.mQ[0]);
-        segment(1, a.mP[1], a.mQ[1]);
+        segment(1, *a.scaled ? a.mP[1] : a.mP[2], a.mQ[1]);
     } else {
         segment(2, a.mP[2], a.mQ[2]);
         segment(3, a.mP[3], a.mQ[3]);
@@ -492,8 +495,8 @@ hipError_t launch_residue(const SliceJobs &jobs, int K, int n_g, hipStream_t st)
 }
 
 hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
-                             const SliceView (&sseg)[2][2], void *work, double2 *H, double2 *S,
-                             hipStream_t st) {
+                             const SliceView (&sseg)[2][2], const int *scaled, void *work,
+                             double2 *H, double2 *S, hipStream_t st) {
     auto u4 = [](const _Float16 *p) { return reinterpret_cast<const uint4 *>(p); };
     const SliceView *segs[NSEG] = {hseg[0], hseg[1], sseg[0], sseg[1]};
     CrtArgs a;
@@ -504,6 +507,7 @@ hipError_t launch_crt_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
         r.mP[s] = segs[s][0].mx;
         r.mQ[s] = segs[s][1].mx;
     }
+    a.scaled = r.scaled = scaled;
     a.out = reinterpret_cast<uint2 *>(work);
     a.n_g = n_g;
     a.groups = (K + CITEMS * 8 - 1) / (CITEMS * 8) * CITEMS;

@@ -63,9 +63,11 @@ static_assert(SBITS1 <= 10 && SBITS <= 10, "slices must be integers FP16 holds e
 // rows; k_zero_max clears the maxima first (a kernel, not a memset, so the
 // sequence stays valid inside a captured graph). The row maxima behind the
 // exponents e of A 2^e and X 2^-e are needed before the column maxima of those, so
-// A and X are read twice (the two passes 0.95 and 0.51 ms at N_G = 8000, K =
-// 8100 in the modular form, 78 and 46 us at N_G = 1501, K = 4096 in FP16;
-// with a sixth operand to cut the balance costs 1 to 6% of a build).
+// where rows are scaled A and X are read twice (the two passes 0.95 and 0.51 ms at
+// N_G = 8000, K = 8100 in the modular form, 78 and 46 us at N_G = 1501, K = 4096
+// in FP16) and a sixth operand is cut, 1 to 6% of a build. Where that would gain
+// nothing k_balance leaves both out, and itself with the second launch takes
+// 10 to 26 us.
 
 constexpr int CROWS = 64;   // rows per k_colmax block
 
@@ -79,7 +81,7 @@ __global__ void __launch_bounds__(256) k_zero_max(SliceJobs jobs, int n_g, int n
 }
 
 // First pass (SCALED false, z = matrix): the row maxima of A and X, and the
-// column maxima of the operands that no row exponent enters. Second pass: those
+// column maxima of all operands for e = 0. Second pass, if rows are scaled: those
 // of A 2^e (z = 0) and X 2^-e (z = 1). NORM: instead of a column's maximum the
 // largest Euclidean norm of its blocks of CROWS rows (the modular form's scale),
 // summed in a fixed order at the block's own exponent.
@@ -88,9 +90,10 @@ __global__ void __launch_bounds__(256)
 k_colmax(SliceJobs jobs, int K, int n_g) {
     constexpr int NR = CROWS / 4;   // rows per thread
     __shared__ double red[2][4][64], sum[2][4][64];
+    if (SCALED && !*jobs.scaled) return;
     const int z = SCALED ? 2 * blockIdx.z : blockIdx.z;   // matrix
     const double2 *X = slice_ptr(jobs.M, z);
-    const bool cols = SCALED || z != 2, rows = !SCALED && (z == 0 || z == 2);
+    const bool rows = !SCALED && (z == 0 || z == 2);
     const bool two = !SCALED && z == 1;   // operand 4 too
     const int op = SCALED && z == 0 ? 5 : z;
     const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
@@ -127,7 +130,6 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
         if (c < NR && k < K)
             atomicMax((z == 0 ? jobs.rmx[0] : jobs.rmx[1]) + (jobs.rgroup == 1 ? k : k / jobs.rgroup), mine);
     }
-    if (!cols) return;
     red[0][rg][c] = m0;
     red[1][rg][c] = m1;
     __syncthreads();
@@ -162,6 +164,36 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
         unsigned long long *mx = rg == 0 ? slice_ptr(jobs.mx, op) : jobs.mx[4];
         atomicMax(mx + n, (unsigned long long)__double_as_longlong(m));
     }
+}
+
+// Rows are scaled if max A max X > 2 max_k (A_k X_k) over the row maxima, i.e. if
+// the operands as they are lie more above balance than powers of two leave them
+// (2^(1/2) each). If so X's column maxima are cleared for the second pass.
+__global__ void __launch_bounds__(1024) k_balance(SliceJobs jobs, int nr, int n_g) {
+    __shared__ unsigned red[3][16];
+    unsigned m[3] = {0u, 0u, 0u};
+    for (int i = threadIdx.x; i < nr; i += 1024) {
+        const unsigned a = jobs.rmx[0][i], x = jobs.rmx[1][i];
+        m[0] = max(m[0], a);
+        m[1] = max(m[1], x);
+        m[2] = max(m[2], a + x);   // below 2^32: both are below 2^31
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m[t] = max(m[t], (unsigned)__shfl_xor((int)m[t], o));
+        if ((threadIdx.x & 63) == 0) red[t][threadIdx.x >> 6] = m[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        m[t] = red[t][0];
+        for (int w = 1; w < 16; ++w) m[t] = max(m[t], red[t][w]);
+    }
+    const bool scaled = m[0] + m[1] > m[2] + (1u << 20);
+    if (threadIdx.x == 0) *jobs.scaled = scaled ? 1 : 0;
+    if (!scaled) return;
+    for (int i = threadIdx.x; i < n_g; i += 1024) jobs.mx[2][i] = 0ull;
 }
 
 // ---------------------------------------------------------------------------
@@ -227,7 +259,7 @@ k_slice(SliceJobs jobs, int K, int n_g, int groups) {
         }
     };
     cut(z);
-    if (slice_other(z) >= 0) cut(slice_other(z));
+    if (slice_other(jobs, z) >= 0) cut(slice_other(jobs, z));
 }
 
 // ---------------------------------------------------------------------------
@@ -275,6 +307,7 @@ struct SplitSeg {
 struct SplitArgs {
     SplitSeg h[2];
     SplitSeg s[2];
+    const int *scaled;
     double2 *H, *S;
     int n_g, groups;         // groups = K padded to 16, over 4
     SplitPlan plan;
@@ -471,7 +504,12 @@ __device__ __forceinline__ void split_tile(const SplitArgs &args, bool isH, int 
             for (int v = 0; v < 4; ++v) acc.re[i][j][v] = acc.im[i][j][v] = 0.0;
 
     if (isH) {
-        const SplitSeg h0 = args.h[0], h1 = args.h[1];
+        const SplitSeg h0 = args.h[0];
+        SplitSeg h1 = args.h[1];
+        if (!*args.scaled) {
+            h1.P = args.s[0].P;
+            h1.mP = args.s[0].mP;
+        }
         split_segment<C, BF>(h0, n_g, args.groups, m0, n0, acc, lds);
         split_segment<C, BF>(h1, n_g, args.groups, m0, n0, acc, lds);
     } else {
@@ -604,7 +642,7 @@ k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
         }
     };
     cut(z);
-    if (slice_other(z) >= 0) cut(slice_other(z));
+    if (slice_other(jobs, z) >= 0) cut(slice_other(jobs, z));
 }
 
 struct Split8Seg {
@@ -615,6 +653,7 @@ struct Split8Seg {
 struct Split8Args {
     Split8Seg h[2];
     Split8Seg s[2];
+    const int *scaled;
     double2 *H, *S;
     int n_g, groups;          // groups of 8 complex rows, a multiple of GRP8
     int nt, ntri, ntri8;
@@ -783,7 +822,12 @@ k_split8_reduce(Split8Args args) {
 
     Acc8 acc;
     if (isH) {
-        const Split8Seg h0 = args.h[0], h1 = args.h[1];
+        const Split8Seg h0 = args.h[0];
+        Split8Seg h1 = args.h[1];
+        if (!*args.scaled) {
+            h1.P = args.s[0].P;
+            h1.mP = args.s[0].mP;
+        }
         split8_segment(h0, n_g, args.groups, m0, n0, true, acc, bufA, bufB);
         split8_segment(h1, n_g, args.groups, m0, n0, false, acc, bufA, bufB);
     } else {
@@ -828,6 +872,9 @@ hipError_t launch_colmax(const SliceJobs &jobs, int K, int n_g, hipStream_t st, 
     else hipLaunchKernelGGL((k_colmax<false, false>), first, dim3(256), 0, st, jobs, K, n_g);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_balance, dim3(1), dim3(1024), 0, st, jobs, nr, n_g);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     if (norm) hipLaunchKernelGGL((k_colmax<true, true>), second, dim3(256), 0, st, jobs, K, n_g);
     else hipLaunchKernelGGL((k_colmax<true, false>), second, dim3(256), 0, st, jobs, K, n_g);
     return hipGetLastError();
@@ -847,9 +894,10 @@ hipError_t launch_slice(const SliceJobs &jobs, int K, int n_g, hipStream_t st, b
 }
 
 hipError_t launch_split_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
-                               const SliceView (&sseg)[2][2], double2 *H, double2 *S,
-                               hipStream_t st, bool bf16) {
+                               const SliceView (&sseg)[2][2], const int *scaled, double2 *H,
+                               double2 *S, hipStream_t st, bool bf16) {
     SplitArgs a;
+    a.scaled = scaled;
     for (int i = 0; i < 2; ++i)
         a.h[i] = SplitSeg{hseg[i][0].S, hseg[i][1].S, hseg[i][0].mx, hseg[i][1].mx};
     for (int i = 0; i < 2; ++i)
@@ -897,10 +945,11 @@ hipError_t launch_slice8(const SliceJobs &jobs, int K, int n_g, hipStream_t st) 
 }
 
 hipError_t launch_split8_reduce(int K, int n_g, const SliceView (&hseg)[2][2],
-                                const SliceView (&sseg)[2][2], double2 *H, double2 *S,
-                                hipStream_t st) {
+                                const SliceView (&sseg)[2][2], const int *scaled, double2 *H,
+                                double2 *S, hipStream_t st) {
     auto u4 = [](const _Float16 *p) { return reinterpret_cast<const uint4 *>(p); };
     Split8Args a;
+    a.scaled = scaled;
     for (int i = 0; i < 2; ++i)
         a.h[i] = Split8Seg{u4(hseg[i][0].S), u4(hseg[i][1].S), hseg[i][0].mx, hseg[i][1].mx};
     for (int i = 0; i < 2; ++i)

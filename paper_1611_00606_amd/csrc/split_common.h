@@ -28,6 +28,7 @@ __device__ __forceinline__ T *slice_ptr(T *const (&v)[N], int z) {
 // evenly between both operands, and 4e-10 with e. The upper half of a double is its
 // logarithm in units of 2^-20, to 0.09; a zero row counts as 2^-1023.
 __device__ __forceinline__ int slice_row_exp(const SliceJobs &jobs, int k) {
+    if (!*jobs.scaled) return 0;
     const int g = jobs.rgroup == 1 ? k : k / jobs.rgroup;
     return ((int)jobs.rmx[1][g] - (int)jobs.rmx[0][g] + (1 << 20)) >> 21;
 }
@@ -44,8 +45,10 @@ __device__ __forceinline__ double2 slice_value(const SliceJobs &jobs, int z, dou
     }
     return v;
 }
-// The other operand made from matrix z (A: 5, B: 4), or -1.
-__device__ __forceinline__ int slice_other(int z) { return z == 0 ? 5 : z == 1 ? 4 : -1; }
+// The other operand made from matrix z (A: 5 if rows are scaled, B: 4), or -1.
+__device__ __forceinline__ int slice_other(const SliceJobs &jobs, int z) {
+    return z == 1 ? 4 : z == 0 && *jobs.scaled ? 5 : -1;
+}
 
 // Column scale of the sliced forms: the maximum itself, so that the first
 // slice's range is used in full (with the next power of two the dropped pairs

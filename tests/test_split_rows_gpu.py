@@ -21,9 +21,9 @@ pytestmark = pytest.mark.gpu
 BALANCE = 2.0
 
 
-def _atom_x1000(seed):
+def _atom_x1000(seed, n_g=100):
     """One atom's T_AA a thousand times the others'."""
-    p = make_problem(64, 20, 100, seed=seed)
+    p = make_problem(64, 20, n_g, seed=seed)
     p.set_t_block("T_AA", 5, 1e3 * p.t_block("T_AA", 5))
     return p
 
@@ -57,6 +57,8 @@ def _zero_rows(seed):
 
 
 CASES = {"atom_x1000": lambda: _atom_x1000(3), "unlike_rows": lambda: _unlike_rows(4),
+         # 4 N_G^2 < K: one row maximum for six rows
+         "grouped_rows": lambda: _atom_x1000(7, 8),
          "unlike_rows_failing": lambda: _unlike_rows(5, [1, 40]), "zero_rows": lambda: _zero_rows(6)}
 
 

@@ -75,7 +75,6 @@ constexpr int MM_QU = 4;      // Q upper triangular: k <= column of C
 constexpr int MM_LOWER = 8;   // only C's lower triangle (square region)
 constexpr int MM_MASK = 16;   // only elements on or below the diagonal (any region)
 constexpr int MM_PL = 32;     // P lower triangular: k >= row of C
-constexpr int MM_UPPER = 64;  // only C's upper triangle (square region); zeros below it
 // epilogue
 constexpr int OP_STORE = 0, OP_NEG = 1, OP_SUB = 2;
 
@@ -86,9 +85,11 @@ struct MmJob {
     int k0, k1;               // contraction rows of P and Q
     int ntr, ntc;             // tile rows / columns of the rectangle
     int start;                // first block of this job
-    int flags;                // MM_* of this job
 };
-constexpr int MM_JOBS = 32;
+// Nodes of one depth of a step's recursion: steps end at multiples of LB = 128 and
+// hold at most 1024 columns (split_steps), 8 blocks, so 4. (The fall-back
+// without auxiliary streams takes several launches for more.)
+constexpr int MM_JOBS = 4;
 
 struct MmArgs {
     const double2 *P, *Q;
@@ -99,6 +100,7 @@ struct MmArgs {
     int w0;                   // not (w0 < 0: below the diagonal) also as T = C^H
     int N;                    // leading dimension of all
     int op;
+    int flags;                // MM_*
     int tile;                 // 128, 64 or 32
     int njobs;
     int total;                // tiles over all jobs (blocks loop over them)
@@ -126,7 +128,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
 #pragma unroll
     for (int t = 1; t < MM_JOBS; ++t)
         if (t < args.njobs && tile >= args.job[t].start) jb = t;
-    const int flags = args.job[jb].flags;
+    const int flags = args.flags;
     const int bid = tile - args.job[jb].start;
     const int ntr = args.job[jb].ntr, ntc = args.job[jb].ntc;
     const int i0 = args.job[jb].i0, i1 = args.job[jb].i1;
@@ -134,13 +136,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
     // Tiles whose contraction is longest go first (the triangular flags
     // make it depend on the tile row or column).
     int ti, tj;
-    if (flags & MM_UPPER) {   // upper triangle, tj >= ti, by diagonals from the far corner
-        int r = (int)((sqrt(8.0 * bid + 1.0) - 1.0) * 0.5);
-        while ((r + 1) * (r + 2) / 2 <= bid) ++r;
-        while (r * (r + 1) / 2 > bid) --r;
-        ti = bid - r * (r + 1) / 2;
-        tj = ti + ntr - 1 - r;
-    } else if (flags & MM_LOWER) {   // lower triangle, tj <= ti
+    if (flags & MM_LOWER) {   // lower triangle, tj <= ti
         const bool byc = flags & MM_QU;   // contraction grows with tj: last columns first
         const int t = byc ? bid : ntr * (ntr + 1) / 2 - 1 - bid;
         int r = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
@@ -153,26 +149,13 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
             ti = r;
             tj = t - r * (r + 1) / 2;
         }
-    } else if ((flags & MM_PL) && (flags & MM_QU)) {   // longest: largest tj - ti first
-        int rem = bid, c = ntc - 1;
-        for (;; --c) {   // diagonals tj - ti = c, from the far corner
-            const int lo = c < 0 ? -c : 0;
-            const int hi = ntr < ntc - c ? ntr : ntc - c;
-            const int cnt = hi > lo ? hi - lo : 0;
-            if (rem < cnt || c <= -ntr) {
-                ti = lo + rem;
-                break;
-            }
-            rem -= cnt;
-        }
-        tj = ti + c;
     } else if (flags & MM_PU) {   // longest: last tile rows
         ti = ntr - 1 - bid / ntc;
         tj = bid % ntc;
     } else if (flags & MM_QU) {   // longest: last tile columns
         tj = ntc - 1 - bid / ntr;
         ti = bid % ntr;
-    } else {                      // MM_QL: first tile columns
+    } else {                      // MM_QL: first tile columns; MM_PL: first rows of each
         tj = bid / ntr;
         ti = bid % ntr;
     }
@@ -203,7 +186,6 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
     if (!wave_works<Cfg>()) return;
 
     const bool lower = flags & (MM_LOWER | MM_MASK);
-    const bool upper = flags & MM_UPPER;
     const int op = args.op;
     double2 *C = args.C;
 #pragma unroll
@@ -216,8 +198,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs &args, int tile, double2 *l
                 const int gp = m0 + acc_row<Cfg>(i, v);
                 if (gp < i1 && g < j1 && (!lower || g <= gp)) {
                     double2 *o = C + (long long)gp * N + g;
-                    const bool z = upper && g < gp;
-                    const double re = z ? 0.0 : acc.re[i][j][v], im = z ? 0.0 : acc.im[i][j][v];
+                    const double re = acc.re[i][j][v], im = acc.im[i][j][v];
                     if (op == OP_SUB) {
                         double2 r = args.S[(long long)gp * N + g];
                         r.x -= re;
@@ -646,12 +627,10 @@ k_gep_leaf(double2 *__restrict__ L, double2 *__restrict__ M, double2 *__restrict
     }
 }
 
-// L := lower(S) (upper triangle zero), M := 0, MH := 0, LH := 0 below the
-// diagonal, K := H, info := 0
+// L := lower(S) (upper triangle zero), M := 0, MH := 0, K := H, info := 0
 __global__ void __launch_bounds__(256)
 k_gep_init(const double2 *__restrict__ H, const double2 *__restrict__ S, double2 *__restrict__ L,
-           double2 *__restrict__ M, double2 *__restrict__ MH, double2 *__restrict__ LH,
-           double2 *__restrict__ K, int N, int *__restrict__ info) {
+           double2 *__restrict__ M, double2 *__restrict__ MH, double2 *__restrict__ K, int N, int *__restrict__ info) {
     const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
     if (e >= (long long)N * N) return;
     if (e == 0) *info = 0;
@@ -662,7 +641,6 @@ k_gep_init(const double2 *__restrict__ H, const double2 *__restrict__ S, double2
     L[e] = sv;
     M[e] = z;
     MH[e] = z;
-    if (j < i) LH[e] = z;
     if (K) K[e] = H[e];
 }
 
@@ -917,10 +895,9 @@ void sched_mm(const Gep &g, const MmArgs &a) {
     SchedOp &op = g_sched->launch(g.st, a.P2 ? "k_gep_mm<2>" : "k_gep_mm<1>");
     for (int jb = 0; jb < a.njobs; ++jb) {
         const MmJob &j = a.job[jb];
-        const int flags = j.flags;
+        const int flags = a.flags;
         for (int ti = 0; ti < j.ntr; ++ti)
             for (int tj = 0; tj < j.ntc; ++tj) {
-                if ((flags & MM_UPPER) && tj < ti) continue;
                 if ((flags & MM_LOWER) && tj > ti) continue;
                 const int m0 = j.i0 + ti * bt, n0 = j.j0 + tj * bt;
                 if (m0 >= j.i1 || n0 >= j.j1) continue;
@@ -950,7 +927,7 @@ void sched_mm(const Gep &g, const MmArgs &a) {
 // Tiles of one rectangle.
 long long mm_tiles(const Rect &r, int flags, int tile) {
     const long long ntr = (r.i1 - r.i0 + tile - 1) / tile, ntc = (r.j1 - r.j0 + tile - 1) / tile;
-    return flags & (MM_LOWER | MM_UPPER) ? ntr * (ntr + 1) / 2 : ntr * ntc;
+    return flags & MM_LOWER ? ntr * (ntr + 1) / 2 : ntr * ntc;
 }
 
 // The tile shape of a launch over n rectangles on cus compute units, by an
@@ -961,7 +938,7 @@ long long mm_tiles(const Rect &r, int flags, int tile) {
 // (measured on a full device; a 128-tile alone 70 us for 128 rows); two
 // blocks of 32-tiles on one compute unit take turns and hide each other's
 // 8 us.
-int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
+int mm_shape(const Rect *r, int flags, int n, int nseg, int cus) {
     constexpr int SHAPES[3] = {128, 64, 32};
     constexpr double PER_ROW[3] = {0.44, 0.13, 0.041};
     int best = 128;
@@ -970,11 +947,11 @@ int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
         double longest = 0.0, rows = 0.0;
         long long tiles = 0;
         for (int t = 0; t < n; ++t) {
-            const long long nt = mm_tiles(r[t], flags[t], SHAPES[s]);
+            const long long nt = mm_tiles(r[t], flags, SHAPES[s]);
             const double k = (double)(r[t].k1 - r[t].k0) * nseg;
             double avg = k;
             for (int f : {MM_PU | MM_PL, MM_QU | MM_QL})
-                if (flags[t] & f) avg *= 0.5;
+                if (flags & f) avg *= 0.5;
             longest = std::max(longest, 8.0 + k * PER_ROW[s]);
             rows += nt * avg;
             tiles += nt;
@@ -991,13 +968,12 @@ int mm_shape(const Rect *r, const int *flags, int n, int nseg, int cus) {
     return best;
 }
 
-// Products over the rectangles r[0 .. n), up to MM_JOBS per launch, with
-// the flags rflags[t] of each (or flags for all when rflags is null); the
-// blocks take the rectangles in the order given.
+// Products over the rectangles r[0 .. n), up to MM_JOBS per launch; the blocks
+// take the rectangles in the order given.
 hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C, const Rect *r,
                     int n, int flags, int op, const double2 *P2 = nullptr,
-                    const double2 *Q2 = nullptr, const int *rflags = nullptr,
-                    double2 *T = nullptr, int w0 = 0, const double2 *S = nullptr) {
+                    const double2 *Q2 = nullptr, double2 *T = nullptr, int w0 = 0,
+                    const double2 *S = nullptr) {
     for (int b = 0; b < n; b += MM_JOBS) {
         MmArgs a = {};
         a.P = P;
@@ -1010,16 +986,15 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
         a.w0 = w0;
         a.N = g.N;
         a.op = op;
+        a.flags = flags;
         Rect rj[MM_JOBS];
-        int fj[MM_JOBS];
         for (int t = b; t < n && t < b + MM_JOBS; ++t) {
             if (r[t].i1 <= r[t].i0 || r[t].j1 <= r[t].j0) continue;
-            rj[a.njobs] = r[t];
-            fj[a.njobs++] = rflags ? rflags[t] : flags;
+            rj[a.njobs++] = r[t];
         }
         if (a.njobs == 0) continue;
         const int cus = g.cap > 0 ? g.cap : g_sched ? 256 : num_cus();
-        a.tile = mm_shape(rj, fj, a.njobs, P2 ? 2 : 1, cus);
+        a.tile = mm_shape(rj, flags, a.njobs, P2 ? 2 : 1, cus);
         long long nblk = 0;
         for (int t = 0; t < a.njobs; ++t) {
             MmJob &j = a.job[t];
@@ -1032,10 +1007,8 @@ hipError_t mm_batch(const Gep &g, const double2 *P, const double2 *Q, double2 *C
             j.ntr = (j.i1 - j.i0 + a.tile - 1) / a.tile;
             j.ntc = (j.j1 - j.j0 + a.tile - 1) / a.tile;
             j.start = (int)nblk;
-            j.flags = fj[t];
-            if ((j.flags & (MM_LOWER | MM_UPPER)) && (j.i0 != j.j0 || j.i1 != j.j1))
-                return hipErrorInvalidValue;
-            nblk += mm_tiles(rj[t], fj[t], a.tile);
+            if ((flags & MM_LOWER) && (j.i0 != j.j0 || j.i1 != j.j1)) return hipErrorInvalidValue;
+            nblk += mm_tiles(rj[t], flags, a.tile);
         }
         a.total = (int)nblk;
         if (g_sched) {
@@ -1056,7 +1029,7 @@ hipError_t mm(const Gep &g, const double2 *P, const double2 *Q, double2 *C, int 
               int j0, int j1, int k0, int k1, int flags, int op, double2 *T = nullptr,
               int w0 = 0) {
     const Rect r = {i0, i1, j0, j1, k0, k1};
-    return mm_batch(g, P, Q, C, &r, 1, flags, op, nullptr, nullptr, nullptr, T, w0);
+    return mm_batch(g, P, Q, C, &r, 1, flags, op, nullptr, nullptr, T, w0);
 }
 
 // Transposes of the rectangles r[0 .. n), up to MM_JOBS per launch.
@@ -1289,16 +1262,10 @@ hipError_t node_m21(const Gep &g, const std::vector<Node> &nodes) {   // M21 = -
     return conj_t_batch(g, g.M, g.MH, r.data(), (int)r.size());
 }
 
-template <class Keep>
-hipError_t invert(const Gep &g, const std::vector<std::vector<Node>> &lv, Keep keep) {
-    std::vector<Node> nodes;
+hipError_t invert(const Gep &g, const std::vector<std::vector<Node>> &lv) {
     for (int d = (int)lv.size() - 1; d >= 0; --d) {
-        nodes.clear();
-        for (const Node &n : lv[d])
-            if (keep(n)) nodes.push_back(n);
-        if (nodes.empty()) continue;
-        GEP_TRY(node_w21(g, nodes));
-        GEP_TRY(node_m21(g, nodes));
+        GEP_TRY(node_w21(g, lv[d]));
+        GEP_TRY(node_m21(g, lv[d]));
     }
     return hipSuccess;
 }
@@ -1346,16 +1313,15 @@ hipError_t step(const Gep &g, double2 *Ht, int a, int b, Ready ready) {
     const int N = g.N;
     std::vector<std::vector<Node>> lv;
     tree(a, b, 0, lv);
-    GEP_TRY(invert(g, lv, [](const Node &) { return true; }));
+    GEP_TRY(invert(g, lv));
     GEP_TRY(ready());
     GEP_TRY(mm(g, g.MH, g.M, Ht, a, b, 0, a, a, b, MM_PU, OP_STORE));
     GEP_TRY(mm(g, g.LH, Ht, g.M, b, N, 0, a, a, b, 0, OP_SUB));
     GEP_TRY(mm(g, g.M, g.LH, g.W, a, b, b, N, a, b, MM_PL, OP_STORE));
     const Rect f = {a, b, b, N, a, b}, k = {b, N, b, N, a, b};
-    GEP_TRY(mm_batch(g, g.K, g.W, g.MH, &f, 1, 0, OP_SUB, nullptr, nullptr, nullptr, nullptr, 0,
-                     g.K));
+    GEP_TRY(mm_batch(g, g.K, g.W, g.MH, &f, 1, 0, OP_SUB, nullptr, nullptr, nullptr, 0, g.K));
     GEP_TRY(mm(g, g.MH, g.MH, g.M, b, N, a, b, a, b, MM_QU, OP_STORE));
-    return mm_batch(g, g.MH, g.W, g.K, &k, 1, MM_LOWER, OP_SUB, g.W, g.K, nullptr, g.K, -1);
+    return mm_batch(g, g.MH, g.W, g.K, &k, 1, MM_LOWER, OP_SUB, g.W, g.K, g.K, -1);
 }
 
 hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, double2 *Ht,
@@ -1392,8 +1358,7 @@ hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, do
         if (g_sched->fails()) return hipErrorUnknown;
         SchedOp &op = g_sched->launch(st, "k_gep_init");
         g_sched->add(op, S, 0, N, 0, N, false);
-        for (const void *X : {(const void *)L, (const void *)g.M, (const void *)g.MH,
-                              (const void *)g.LH})
+        for (const void *X : {(const void *)L, (const void *)g.M, (const void *)g.MH})
             g_sched->add(op, X, 0, N, 0, N, true);
         if (sb) {
             g_sched->add(op, H, 0, N, 0, N, false);
@@ -1402,7 +1367,7 @@ hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, do
         g_sched->add(op, g.info, 0, 1, 0, 1, true);
     } else {
         hipLaunchKernelGGL(k_gep_init, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, st, H, S,
-                           L, g.M, g.MH, g.LH, sb ? g.K : nullptr, N, g.info);
+                           L, g.M, g.MH, sb ? g.K : nullptr, N, g.info);
         GEP_TRY(hipGetLastError());
     }
     g.cap = 0;
@@ -1410,7 +1375,7 @@ hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, do
         std::vector<std::vector<Node>> lv;
         tree(0, N, 0, lv);
         GEP_TRY(factor(g, [](int, hipEvent_t, Rect &) { return hipSuccess; }));
-        GEP_TRY(invert(g, lv, [](const Node &) { return true; }));
+        GEP_TRY(invert(g, lv));
         GEP_TRY(diag_block(g, H, Ht, 0, N));
         return mirror();
     }

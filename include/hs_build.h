@@ -320,6 +320,14 @@ int hs_check_reduce_plan(int K, int N_G, int mode, int cus, int32_t plan[4]);
 size_t hs_gep_workspace_bytes(int N);
 
 /*
+ * hs_gep_steps - column ends of the steps in which hs_gep_reduce transforms H
+ * (one step up to three panels of 128 columns): the first 3 n of them into 2
+ * ends (host or NULL). Returns their number, or -1 for N < 1. Host only; for
+ * counts of the operations that the reduction executes.
+ */
+int hs_gep_steps(int N, int32_t *ends, int n);
+
+/*
  * hs_gep_reduce - enqueue the reduction on `stream` (NULL: default stream)
  * and return (asynchronous, like hs_build_ex).
  *   1 H   device [N][N], Hermitian, read in full (an hs_build output)

@@ -56,6 +56,7 @@ from ._binding import (  # noqa: F401,E402
     hs_autotune_atoms,
     hs_gep_workspace_bytes,
     hs_gep_reduce,
+    hs_gep_steps,
     hs_check_reduce_plan,
     hs_gep_check_failure,
     hs_gep_check_schedule,

@@ -160,6 +160,8 @@ def load_library() -> ctypes.CDLL:
     lib.hs_gep_reduce.restype = i32
     lib.hs_gep_reduce_ex.argtypes = [vp, vp, i32, vp, vp, vp, vp, sz, vp, i32]
     lib.hs_gep_reduce_ex.restype = i32
+    lib.hs_gep_steps.argtypes = [i32, ctypes.POINTER(i32), i32]
+    lib.hs_gep_steps.restype = i32
     lib.hs_check_reduce_plan.argtypes = [i32, i32, i32, i32, ctypes.POINTER(i32)]
     lib.hs_check_reduce_plan.restype = i32
     lib.hs_gep_check_schedule.argtypes = [i32, i32, i32, ctypes.c_char_p, sz]
@@ -447,6 +449,17 @@ def hs_autotune_atoms(nl_values, N_G, reps=3, stream=None):
 
 def hs_gep_workspace_bytes(N) -> int:
     return int(load_library().hs_gep_workspace_bytes(int(N)))
+
+
+def hs_gep_steps(N: int):
+    """Column ends of the eigenproblem reduction's steps (host only)."""
+    lib = load_library()
+    n = lib.hs_gep_steps(int(N), None, 0)
+    if n < 0:
+        raise ValueError("N < 1")
+    ends = (ctypes.c_int32 * n)()
+    lib.hs_gep_steps(int(N), ends, n)
+    return list(ends)
 
 
 def hs_check_reduce_plan(K: int, N_G: int, mode: int = HS_FP64, cus: int = 256):

@@ -376,6 +376,14 @@ int hs_check_reduce_plan(int K, int N_G, int mode, int cus, int32_t plan[4]) {
 
 size_t hs_gep_workspace_bytes(int N) { return N < 1 ? 0 : hs::gep_workspace_bytes(N); }
 
+int hs_gep_steps(int N, int32_t *ends, int n) {
+    if (N < 1) return -1;
+    const std::vector<int> e = hs::gep_steps(N);
+    if (ends)
+        for (int i = 0; i < n && i < (int)e.size(); ++i) ends[i] = e[i];
+    return (int)e.size();
+}
+
 int hs_gep_reduce(const hs_complex *H, const hs_complex *S, int N, hs_complex *L, hs_complex *Ht,
                   int32_t *info, void *workspace, size_t workspace_bytes, void *stream) {
     return hs_gep_reduce_ex(H, S, N, L, Ht, info, workspace, workspace_bytes, stream, HS_FP64);

@@ -182,6 +182,7 @@ hipError_t launch_mirror1(double2 *M, int n, hipStream_t st);
 // info: device int or NULL (a workspace slot is used then); g3: the large
 // products in the 3M form.
 size_t gep_workspace_bytes(int N);
+std::vector<int> gep_steps(int N);   // column ends of the steps
 hipError_t launch_gep(const double2 *H, const double2 *S, int N, double2 *L, double2 *Ht,
                       int *info, char *ws, hipStream_t st, bool g3);
 // Runs launch_gep's orchestration without issuing anything and checks that

@@ -1291,6 +1291,19 @@ void split_steps(int a, int b, int most, std::vector<int> &ends) {
         ends.push_back(k == n ? b : a + (int)((long long)(b - a) * k / n + LB / 2) / LB * LB);
 }
 
+// Column ends of all steps; nbg: how many run beside the factorization (0: one
+// block, which needs no steps).
+std::vector<int> step_ends(int N, size_t *nbg) {
+    std::vector<int> ends;
+    *nbg = 0;
+    if (N <= 3 * LB) return {N};
+    const int bg = bg_columns(N);
+    split_steps(0, bg, 896, ends);
+    *nbg = ends.size();
+    split_steps(bg, N, 960, ends);
+    return ends;
+}
+
 size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
 // A diagonal block [a, b) of Ht = M K M^H, through V = K MH (kept in LH).
@@ -1384,11 +1397,8 @@ hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, do
     // step depends on nothing still to come: those of the first `bg` columns run
     // on a second stream, on bg_cap of the compute units, beside the rest of
     // the factorization, which no longer touches LH's columns < t0. The others follow it on all compute units.
-    const int bg = bg_columns(N);
-    std::vector<int> ends;
-    split_steps(0, bg, 896, ends);
-    const size_t nbg = ends.size();
-    split_steps(bg, N, 960, ends);
+    size_t nbg;
+    const std::vector<int> ends = step_ends(N, &nbg);
     Gep gb = g;
     gb.st = sb;
     gb.cap = bg_cap(N, g_sched ? 256 : num_cus());
@@ -1428,6 +1438,11 @@ hipError_t enqueue_gep(const double2 *H, const double2 *S, int N, double2 *L, do
 }
 
 }  // namespace
+
+std::vector<int> gep_steps(int N) {
+    size_t nbg;
+    return step_ends(N, &nbg);
+}
 
 size_t gep_workspace_bytes(int N) {
     return 5 * padded(16 * (size_t)N * (size_t)N) + 256;   // LH, M, MH, W, K, info slot

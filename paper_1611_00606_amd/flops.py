@@ -26,6 +26,8 @@ from __future__ import annotations
 
 import numpy as np
 
+from ._binding import hs_gep_steps
+
 
 def paper_step_flops(nl, n_g, info):
     """Dict of Alg. 1 step -> flops, from the per-step formulas of Alg. 1."""
@@ -75,19 +77,9 @@ def executed_flops(nl, n_g):
     return reduction_flops(nl, n_g) + atom_flops(nl, n_g)
 
 
-def gep_steps(N, panel=128):
-    """Column ends of the steps of the eigenproblem reduction, as k_gep.hip
-    takes them (bg_columns, split_steps); one step up to three panels."""
-    if -(-N // panel) < 4:
-        return [N]
-
-    def split(a, b, most):
-        n = -(-(b - a) // most)
-        return [b if k == n else a + ((b - a) * k // n + panel // 2) // panel * panel
-                for k in range(1, n + 1)]
-
-    bg = int(max(min(0.68 * N, 1280.0), 0.32 * N) / panel + 0.5) * panel
-    return split(0, bg, 896) + split(bg, N, 960)
+def gep_steps(N):
+    """Column ends of the steps of the eigenproblem reduction."""
+    return hs_gep_steps(N)
 
 
 def gep_executed_flops(N):

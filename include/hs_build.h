@@ -377,7 +377,7 @@ int hs_gep_reduce_ex(const hs_complex *H, const hs_complex *S, int N,
  * event record and stream wait; then checks with vector clocks that every
  * two launches on different streams that touch a common 128 x 128 cell of a
  * matrix, one of them writing, are ordered by stream order and event waits.
- *   3 drop_wait  0, or a wait site (1..10, in the order the library's
+ *   3 drop_wait  0, or a wait site (1..10 but 6, in the order the library's
  *         schedule defines them) whose waits are left out: a test hook that
  *         shows the check finds the race a missing wait opens
  *   4 report, 5 report_len  host buffer (or NULL) for a NUL-terminated

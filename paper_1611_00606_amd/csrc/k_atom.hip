@@ -4,7 +4,13 @@
 // with M1, M2 the Hermitian T^AA_a, T^BB_a prepared by k_forms, so that
 // H = A^H X + B^H Y. (Alg. 1's Z_a, Y_a and X_a take 20 N_L^2 N_G real
 // operations per atom against 32 here, but its H contracts over 3K rows
-// instead of 2K: 4 K N_G^2 operations saved for 12 K N_L N_G.)
+// instead of 2K: 4 K N_G^2 operations saved for 12 K N_L N_G. That is fewer from
+// N_G = 3 N_L on, in FP64; below, and to several times that where the reductions
+// run on INT8, it is more. One form serves all sizes nevertheless: it needs no
+// factor before the products, and against the 3K form with its separate
+// Cholesky no build was slower (us, before and now: 100 atoms of 121, N_G = 128
+// FP64 17317 and 1494, modular 868 and 643, N_G = 363 17666 and 1769, 1180 and
+// 1016; the least gain, INT8 at N_G = 1000, 3592 and 3557).)
 //
 // Each block computes a BM x BN tile of one atom's N_L x N_G output (one
 // tile covers all of an atom's rows, BM >= N_L); the contraction runs over

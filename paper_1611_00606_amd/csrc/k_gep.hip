@@ -25,8 +25,8 @@
 // reduction (LAPACK's zpotrf + zhegst); with the products
 // over one block 5.56 N^3 at N = 8000 and 6.06 N^3 at 2000. Through the inverse of all of L
 // (Ht = M H M^H) it was 20/3 N^3 (8 N^3 below N = 2500) and nearly all of it
-// waited for the end of the factorization: N = 2000 2.39 ms, now 2.12, 8000
-// 56.9 and 52.3 ms. From 4 panels on, the first steps run on a third stream
+// waited for the end of the factorization: N = 2000 2.39 ms, now 2.05, 8000
+// 56.9 and 51.5 ms. From 4 panels on, the first steps run on a third stream
 // beside the factorization.
 //
 // Storage (all N x N row-major complex): L (output; working copy of S's
@@ -762,17 +762,16 @@ hipError_t ev_record(hipEvent_t e, hipStream_t st) {
 }
 // Wait sites, by tag (hs_gep_check_schedule's drop argument).
 enum WaitTag {
-    WT_TRANSPOSE_AFTER_BLOCK = 1,   // next S21^H after the next column block's update
-    WT_PANEL_AFTER_TRANSPOSE,       // panel product after S21^H
-    WT_BLOCK_AFTER_BULK,            // next column block after the previous bulk update
-    WT_AHEAD_AFTER_PANEL,           // L21 and bulk update after the panel product
-    WT_JOIN_AHEAD,                  // end of the factorization: lookahead stream
-    WT_JOIN_TRANSPOSE,              // end of the factorization: transposes stream
-    WT_FORK,                        // background stream after the top split's panel
-    WT_FORK_AHEAD,                  // background stream after the pending lookahead work
-    WT_END_AFTER_INVERSE,           // top split's M21 after the leading block's inverse
-    WT_END_AFTER_BACKGROUND,        // Ht's last rows after the background's products
-    WT_JOIN_AFTER_ERROR
+    WT_TRANSPOSE_AFTER_BLOCK = 1,   // first panel's S21^H after the preparation of L
+    WT_PANEL_AFTER_TRANSPOSE = 2,   // first panel product after S21^H
+    WT_BLOCK_AFTER_BULK = 3,        // next column blocks after the previous bulk update
+    WT_AHEAD_AFTER_PANEL = 4,       // L21 and bulk update after the panel product
+    WT_JOIN_AHEAD = 5,              // end of the factorization: lookahead stream
+    WT_FORK = 7,                    // a step on the background stream after its last panel
+    WT_FORK_AHEAD = 8,              // the same after the lookahead stream's reads of LH
+    WT_END_AFTER_INVERSE = 9,       // first step after the factorization after the one before it
+    WT_END_AFTER_BACKGROUND = 10,   // mirror after the background stream's products
+    WT_JOIN_AFTER_ERROR = 11
 };
 hipError_t ev_wait(hipStream_t st, hipEvent_t e, int tag) {
     if (g_sched) {
@@ -1224,7 +1223,6 @@ hipError_t factor(const Gep &g, Hook after_panel) {
     }
     // join the other streams
     if (err == hipSuccess && look_pending) err = ev_wait(g.st, e_look, WT_JOIN_AHEAD);
-    if (err == hipSuccess && w_pending) err = ev_wait(g.st, e_w, WT_JOIN_TRANSPOSE);
     for (hipEvent_t e : {e_panel, e_bulk, e_look, e_next, e_w}) ev_destroy(e);
     return err;
 }

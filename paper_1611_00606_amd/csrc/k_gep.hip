@@ -277,7 +277,7 @@ void mm_launch(const MmArgs &a, bool g3, unsigned grid, hipStream_t st) {
 //              is stored (over L's row, which nothing reads any more).
 // Outputs go to global memory from the registers that form them: the block of
 // L, of M = X (lower) and of MH = X^H (upper). Bound: the chain of diagonal
-// tiles (3 us each) and the matrix products of one compute unit (24 us). A
+// tiles (3.5 us each) and the matrix products of one compute unit (24 us). A
 // pivot that is not > 0 (NaN included) records kb + j + 1 in *info unless an
 // earlier block failed (the outputs are undefined then).
 constexpr int LB = 128;
@@ -341,7 +341,10 @@ __device__ __forceinline__ void mma_ab(Cacc &c, const double2 *A, const double2 
 // the A and B operand layout of a rank-4 update with columns 4 v .. 4 v + 3,
 // so nothing is re-laid out. (One column at a time over all sixteen, with
 // the inverse by substitution afterwards: 6 + 5 us instead of 3.5; the leaf
-// 103 us, 58 now.)
+// 103 us, 60 now.) Every update is formed by itself and subtracted once:
+// accumulated onto S and E its eight roundings per four columns at their size
+// made the error of L for random pairs of N = 16 1.67e-16 instead of 0.99e-16
+// (one column at a time 1.18e-16), and the leaf 58 us.
 //   D    the tile (row-major, swizzled; lower triangle used); X on return
 //   scr  128 complex values of LDS of this wave
 //   fac  receives L[r][4 v + q] of step v as fac(v, value), zero above the
@@ -390,8 +393,8 @@ __device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fa
                 lkx[p][k] = lx;
                 lky[p][k] = ly;
                 // s_rk -= l_rj conj(l_kj)
-                s[k].x = fma(-ly, l[p].y, fma(-lx, l[p].x, s[k].x));
-                s[k].y = fma(ly, l[p].x, fma(-lx, l[p].y, s[k].y));
+                s[k].x -= fma(ly, l[p].y, lx * l[p].x);
+                s[k].y -= fma(-ly, l[p].x, lx * l[p].y);
             }
         }
         // this lane's element of four values (selected by component: a select
@@ -405,10 +408,17 @@ __device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fa
         const double lim = own(l[0].y, l[1].y, l[2].y, l[3].y);
         const double2 lq = {low ? lre : 0.0, low ? lim : 0.0};
         if (v < 3) {   // G[i][j] -= conj(L[i][p]) L[j][p]
-            g.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, lq.x, g.re, 0, 0, 0);
-            g.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, lq.y, g.im, 0, 0, 0);
-            g.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, lq.y, g.re, 0, 0, 0);
-            g.im = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, lq.x, g.im, 0, 0, 0);
+            Cacc t;
+            acc_zero(t);
+            t.re = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.x, lq.x, t.re, 0, 0, 0);
+            t.im = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.x, lq.y, t.im, 0, 0, 0);
+            t.re = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, lq.y, t.re, 0, 0, 0);
+            t.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, lq.x, t.im, 0, 0, 0);
+#pragma unroll
+            for (int u = v + 1; u < 4; ++u) {
+                g.re[u] -= t.re[u];
+                g.im[u] -= t.im[u];
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         // the rows of the identity beside that update
@@ -422,17 +432,24 @@ __device__ __forceinline__ int diag16(double2 *D, double2 *scr, int lane, Fac fa
             x[p].y *= rc[p];
 #pragma unroll
             for (int k = p + 1; k < 4; ++k) {   // row k of E -= l_kj (row j of X)
-                x[k].x = fma(lky[p][k], x[p].y, fma(-lkx[p][k], x[p].x, x[k].x));
-                x[k].y = fma(-lky[p][k], x[p].x, fma(-lkx[p][k], x[p].y, x[k].y));
+                x[k].x -= fma(-lky[p][k], x[p].y, lkx[p][k] * x[p].x);
+                x[k].y -= fma(lky[p][k], x[p].x, lkx[p][k] * x[p].y);
             }
         }
         const double2 xq = {own(x[0].x, x[1].x, x[2].x, x[3].x), own(x[0].y, x[1].y, x[2].y, x[3].y)};
         D[lsw(4 * v + q, r)] = xq;
         if (v < 3) {   // E[i][c] -= L[i][p] X[p][c]
-            e.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, xq.x, e.re, 0, 0, 0);
-            e.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.x, xq.y, e.im, 0, 0, 0);
-            e.re = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, xq.y, e.re, 0, 0, 0);
-            e.im = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, xq.x, e.im, 0, 0, 0);
+            Cacc t;
+            acc_zero(t);
+            t.re = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.x, xq.x, t.re, 0, 0, 0);
+            t.im = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.x, xq.y, t.im, 0, 0, 0);
+            t.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-lq.y, xq.y, t.re, 0, 0, 0);
+            t.im = __builtin_amdgcn_mfma_f64_16x16x4f64(lq.y, xq.x, t.im, 0, 0, 0);
+#pragma unroll
+            for (int u = v + 1; u < 4; ++u) {
+                e.re[u] -= t.re[u];
+                e.im[u] -= t.im[u];
+            }
         }
     }
     return inf;

@@ -58,7 +58,7 @@ hipError_t launch_forms(const AtomPlan &p, const AtomBufs &ab, const double2 *T_
 hipError_t launch_chol(const Atoms &at, const double2 *T_AA, int *info, hipStream_t st);
 
 // Per-atom products:
-//   X_a = T^AA_a A_a + T^AB_a B_a = M1_a^H A_a + T_AB,a B_a
+//   X_a = T^AB_a B_a + T^AA_a A_a = T_AB,a B_a + M1_a^H A_a
 //   Y_a = T^BA_a A_a + T^BB_a B_a = T_AB,a^H A_a + M2_a^H B_a
 // and, when info is not NULL, the Cholesky of T_AA,a into info[a].
 hipError_t launch_atom(const Atoms &at, int n_g, const double2 *A, const double2 *B,

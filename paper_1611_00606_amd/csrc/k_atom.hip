@@ -1,5 +1,5 @@
 // Per-atom products, as complex MFMA tiles:
-//   X_a = T^AA_a A_a + T^AB_a B_a = M1_a^H A_a + T_AB,a B_a
+//   X_a = T^AB_a B_a + T^AA_a A_a = T_AB,a B_a + M1_a^H A_a
 //   Y_a = T^BA_a A_a + T^BB_a B_a = T_AB,a^H A_a + M2_a^H B_a
 // with M1, M2 the Hermitian T^AA_a, T^BB_a prepared by k_forms, so that
 // H = A^H X + B^H Y. (Alg. 1's Z_a, Y_a and X_a take 20 N_L^2 N_G real

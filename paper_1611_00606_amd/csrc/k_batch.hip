@@ -1,7 +1,7 @@
 // Batched form of the per-atom stage for atoms of mixed N_L: one persistent
 // launch runs every atom's Cholesky (info[a], prep_atom.h) and every atom's
 // products
-//   X_a = M1_a^H A_a + T_AB,a B_a,   Y_a = T_AB,a^H A_a + M2_a^H B_a
+//   X_a = T_AB,a B_a + M1_a^H A_a,   Y_a = T_AB,a^H A_a + M2_a^H B_a
 // with the tile shape of each atom's products chosen per N_L (a table filled
 // by the autotuner in hs_tune.hip, or the built-in choice below), on the
 // per-atom tile engine of zmfma_atom.h.

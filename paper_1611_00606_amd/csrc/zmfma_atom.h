@@ -10,7 +10,7 @@
 // * the P rows (the atom's N_L x N_L blocks) are N_L entries long: a P row is
 //   loaded as 64-column pieces with the columns past N_L clamped to the last
 //   one (they only feed output rows past N_L, which are not stored);
-// * a P of the second segment given transposed (X_a's T^AB_a, whose rows are
+// * a P of the first segment given transposed (X_a's T^AB_a, whose rows are
 //   X_a's rows): lane m of a load reads element (m, k) at its own stride and
 //   the fragment's imaginary part changes sign in registers, so no
 //   conjugate-transposed copy of T^AB_a is made. Its 16-byte loads gather one
@@ -56,8 +56,8 @@ __device__ __forceinline__ int atom_col(int j) {
     return (wave % C::WN) * C::WTN + j * 16 + (threadIdx.x & 15);
 }
 
-// tr: segment 1's contribution is sum_k P_1[m][k] Q_1[k][n] (P_1 row-major
-// with row stride ldp, not conjugated) instead of P_1^H Q_1.
+// tr: segment 0's contribution is sum_k P_0[m][k] Q_0[k][n] (P_0 row-major
+// with row stride ldp, not conjugated) instead of P_0^H Q_0.
 template <class C>
 __device__ __forceinline__ void ztile_atom(const Segs<2, false> &t, int m0, int mlim, int n0,
                                            int nlim, bool tr, Acc<C> &acc, double2 *lds) {
@@ -79,7 +79,7 @@ __device__ __forceinline__ void ztile_atom(const Segs<2, false> &t, int m0, int 
     const int ktot = t.nseg * t.len;
     const int nst = (ktot + C::BK - 1) / C::BK;
     if (nst == 0) return;
-    const int nrow0 = tr ? t.len : ktot;   // rows of P in the ordinary form
+    const int ntr = tr ? t.len : 0;   // transposed rows of P
 
     // per-lane byte offsets of the loaded columns (clamped at the edge);
     // pvt: of the loaded rows of a transposed P
@@ -109,7 +109,7 @@ __device__ __forceinline__ void ztile_atom(const Segs<2, false> &t, int m0, int 
             if (kk < ktot) {
                 const int s = kk >= t.len ? 1 : 0;
                 const long long row = kk - s * t.len;
-                const bool gather = kk >= nrow0;
+                const bool gather = kk < ntr;
                 const double2 *prow = pick<2>(t.P, s) + (gather ? row : row * t.ldp);
                 const double2 *qrow = pick<2>(t.Q, s) + row * t.ldq;
 #pragma unroll
@@ -134,7 +134,7 @@ __device__ __forceinline__ void ztile_atom(const Segs<2, false> &t, int m0, int 
                       double2 (&b)[C::TN]) __attribute__((always_inline)) {
         const int kr = k4 * 4 + lr;
         // sign flip of the rows of a transposed P (its conjugate is stored)
-        const long long flip = st * C::BK + kr >= nrow0 ? (long long)(1ull << 63) : 0ll;
+        const long long flip = st * C::BK + kr < ntr ? (long long)(1ull << 63) : 0ll;
 #pragma unroll
         for (int i = 0; i < C::TM; ++i) {
             a[i] = lp[kr * C::BMS + wm * C::WTM + i * 16 + lc];
@@ -220,8 +220,10 @@ __device__ __forceinline__ void ztile_atom(const Segs<2, false> &t, int m0, int 
 }
 
 // Operands of atom a's X (which = 0) or Y (which = 1) product: r0, n, t0 its
-// first row, N_L and first T element. X: M1^H A + T_AB B, the second segment
-// transposed (ztile_atom's tr); Y: T_AB^H A + M2^H B.
+// first row, N_L and first T element. X: T_AB B + M1^H A, the first segment
+// transposed (ztile_atom's tr), T_AA A, the larger term, last: in the other
+// order the smaller one's N_L roundings are at the size of the whole (mean error
+// of H over small builds 1% to 8% larger). Y: T_AB^H A + M2^H B.
 __device__ __forceinline__ Segs<2, false> atom_segs(int which, int n, int n_g, long long t0, int r0,
                                                     const double2 *A, const double2 *B,
                                                     const double2 *T_AB, const double2 *M1,
@@ -231,10 +233,10 @@ __device__ __forceinline__ Segs<2, false> atom_segs(int which, int n, int n_g, l
     t.len = n;
     t.ldp = n;
     t.ldq = n_g;
-    t.P[0] = (which == 0 ? M1 : T_AB) + t0;
-    t.P[1] = (which == 0 ? T_AB : M2) + t0;
-    t.Q[0] = A + (long long)r0 * n_g;
-    t.Q[1] = B + (long long)r0 * n_g;
+    t.P[0] = T_AB + t0;
+    t.P[1] = (which == 0 ? M1 : M2) + t0;
+    t.Q[0] = (which == 0 ? B : A) + (long long)r0 * n_g;
+    t.Q[1] = (which == 0 ? A : B) + (long long)r0 * n_g;
     t.qscale = nullptr;
     return t;
 }

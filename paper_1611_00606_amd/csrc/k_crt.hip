@@ -132,14 +132,12 @@ k_residue(SliceJobs jobs, int K, int n_g, int blocks, double cn) {
         raw[q] = double2{0.0, 0.0};
         if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const auto cut = [&](int op)
-                         __attribute__((always_inline)) {
+    const auto cut = [&](int op) __attribute__((always_inline)) {
         const int sh = crt_shift(slice_ptr(jobs.mx, op), n, cn);
         double x[2][16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const int k = 16 * rb + q;
-            const double2 v = k < K ? slice_value(jobs, op, raw[q], k) : raw[q];
+            const double2 v = raw[q];
             x[0][q] = rint(ldexp(v.x, sh));
             x[1][q] = rint(ldexp(v.y, sh));
         }
@@ -162,8 +160,11 @@ k_residue(SliceJobs jobs, int K, int n_g, int blocks, double cn) {
             }
         }
     };
-    cut(z);
-    if (slice_other(jobs, z) >= 0) cut(slice_other(jobs, z));
+    slice_operands(jobs, z, [&](SliceForm form) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (16 * rb + q < K) raw[q] = slice_value(jobs, form, raw[q], 16 * rb + q);
+    }, cut);
 }
 
 // ---------------------------------------------------------------------------

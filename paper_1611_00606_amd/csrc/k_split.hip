@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) k_zero_max(SliceJobs jobs, int n_g, int n
 // column maxima of all operands for e = 0. Second pass, if rows are scaled: those
 // of A 2^e (z = 0) and X 2^-e (z = 1). NORM: instead of a column's maximum the
 // largest Euclidean norm of its blocks of CROWS rows (the modular form's scale),
-// summed in a fixed order at the block's own exponent.
+// summed in a fixed order.
 template <bool SCALED, bool NORM>
 __global__ void __launch_bounds__(256)
 k_colmax(SliceJobs jobs, int K, int n_g) {
@@ -96,22 +96,21 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
     const bool rows = !SCALED && (z == 0 || z == 2);
     const bool two = !SCALED && z == 1;   // operand 4 too
     const int op = SCALED && z == 0 ? 5 : z;
+    const SliceForm form = slice_form(op, SCALED);
     const int c = threadIdx.x & 63, rg = threadIdx.x >> 6;
     const int n = blockIdx.x * 64 + c;
     const int ncl = n < n_g ? n : n_g - 1;
     const int k0 = blockIdx.y * CROWS;
-    double m0 = 0.0, m1 = 0.0;
+    double m0 = 0.0, m1 = 0.0, s0 = 0.0, s1 = 0.0;
     unsigned mine = 0;   // lane i < NR: row k0 + rg + 4 i
-    double2 v[NORM ? NR : 1];
-#pragma unroll(NORM ? NR : 4)
+#pragma unroll 4
     for (int i = 0; i < NR; ++i) {
         const int k = k0 + rg + 4 * i;   // the same in all lanes of a wave
-        double2 x = {0.0, 0.0};
         if (k < K) {
-            x = X[(long long)k * n_g + ncl];
-            if constexpr (SCALED) x = slice_value(jobs, op, x, k);
-            const double m = fmax(fabs(x.x), fabs(x.y));
+            const double2 v = slice_value(jobs, form, X[(long long)k * n_g + ncl], k);
+            const double m = fmax(fabs(v.x), fabs(v.y));
             m0 = fmax(m0, m);
+            if constexpr (NORM) s0 = fma(v.x, v.x, fma(v.y, v.y, s0));
             if (rows) {
                 unsigned r = (unsigned)__double2hiint(m);
 #pragma unroll
@@ -119,11 +118,11 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
                 if (c == i) mine = r;
             }
             if (two) {
-                const double2 b = slice_value(jobs, 4, x, k);
+                const double2 b = slice_value(jobs, SLICE_U, v, k);
                 m1 = fmax(m1, fmax(fabs(b.x), fabs(b.y)));
+                if constexpr (NORM) s1 = fma(b.x, b.x, fma(b.y, b.y, s1));
             }
         }
-        if constexpr (NORM) v[i] = x;
     }
     if (rows) {
         const int k = k0 + rg + 4 * c;
@@ -132,34 +131,30 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
     }
     red[0][rg][c] = m0;
     red[1][rg][c] = m1;
-    __syncthreads();
-    const auto block_max = [&](int t) __attribute__((always_inline)) {
-        const double (*x)[64] = red[t];
-        return fmax(fmax(x[0][c], x[1][c]), fmax(x[2][c], x[3][c]));
-    };
-    int e[2] = {0, 0};
     if constexpr (NORM) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            if (t == 1 && !two) break;
-            frexp(block_max(t), &e[t]);
-            double s = 0.0;
-#pragma unroll
-            for (int i = 0; i < NR; ++i) {
-                const int k = k0 + rg + 4 * i;
-                const double2 x = t == 1 && k < K ? slice_value(jobs, 4, v[i], k) : v[i];
-                const double a = ldexp(x.x, -e[t]), b = ldexp(x.y, -e[t]);
-                s += a * a + b * b;
-            }
-            sum[t][rg][c] = s;
-        }
-        __syncthreads();
+        sum[0][rg][c] = s0;
+        sum[1][rg][c] = s1;
     }
+    __syncthreads();
     if ((rg == 0 || (rg == 1 && two)) && n < n_g) {
-        double m = block_max(rg);
+        const double (*x)[64] = red[rg];
+        double m = fmax(fmax(x[0][c], x[1][c]), fmax(x[2][c], x[3][c]));
         if constexpr (NORM) {
-            const double (*x)[64] = sum[rg];
-            m = ldexp(sqrt((x[0][c] + x[1][c]) + (x[2][c] + x[3][c])), rg == 0 ? e[0] : e[1]);
+            const double (*y)[64] = sum[rg];
+            if (m < 0x1p500 && m > 0x1p-500) {
+                m = sqrt((y[0][c] + y[1][c]) + (y[2][c] + y[3][c]));
+            } else if (m > 0.0) {   // the squares may leave the range: scaled
+                int e;
+                frexp(m, &e);
+                double s = 0.0;
+                for (int k = k0; k < k0 + CROWS && k < K; ++k) {
+                    double2 v = slice_value(jobs, form, X[(long long)k * n_g + n], k);
+                    if (rg == 1) v = slice_value(jobs, SLICE_U, v, k);
+                    const double a = ldexp(v.x, -e), b = ldexp(v.y, -e);
+                    s = fma(a, a, fma(b, b, s));
+                }
+                m = ldexp(sqrt(s), e);
+            }
         }
         unsigned long long *mx = rg == 0 ? slice_ptr(jobs.mx, op) : jobs.mx[4];
         atomicMax(mx + n, (unsigned long long)__double_as_longlong(m));
@@ -220,14 +215,12 @@ k_slice(SliceJobs jobs, int K, int n_g, int groups) {
         raw[q] = double2{0.0, 0.0};
         if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const auto cut = [&](int op)
-                         __attribute__((always_inline)) {
+    const auto cut = [&](int op) __attribute__((always_inline)) {
         const double sc = 1.0 / col_scale(slice_ptr(jobs.mx, op), n);
         double x[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int k = 4 * g + q;
-            const double2 v = k < K ? slice_value(jobs, op, raw[q], k) : raw[q];
+            const double2 v = raw[q];
             x[2 * q] = v.x * sc;
             x[2 * q + 1] = v.y * sc;
         }
@@ -258,8 +251,11 @@ k_slice(SliceJobs jobs, int K, int n_g, int groups) {
             }
         }
     };
-    cut(z);
-    if (slice_other(jobs, z) >= 0) cut(slice_other(jobs, z));
+    slice_operands(jobs, z, [&](SliceForm form) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (4 * g + q < K) raw[q] = slice_value(jobs, form, raw[q], 4 * g + q);
+    }, cut);
 }
 
 // ---------------------------------------------------------------------------
@@ -614,14 +610,12 @@ k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
         raw[q] = double2{0.0, 0.0};
         if (k < K) raw[q] = X[(long long)k * n_g + n];
     }
-    const auto cut = [&](int op)
-                         __attribute__((always_inline)) {
+    const auto cut = [&](int op) __attribute__((always_inline)) {
         const double sc = 1.0 / col_scale8(slice_ptr(jobs.mx, op), n);
         double x[16];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int k = 8 * g + q;
-            const double2 v = k < K ? slice_value(jobs, op, raw[q], k) : raw[q];
+            const double2 v = raw[q];
             x[2 * q] = v.x * sc;
             x[2 * q + 1] = v.y * sc;
         }
@@ -641,8 +635,11 @@ k_slice8(SliceJobs jobs, int K, int n_g, int groups) {
             out[s * plane] = uint4{w[0], w[1], w[2], w[3]};
         }
     };
-    cut(z);
-    if (slice_other(jobs, z) >= 0) cut(slice_other(jobs, z));
+    slice_operands(jobs, z, [&](SliceForm form) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (8 * g + q < K) raw[q] = slice_value(jobs, form, raw[q], 8 * g + q);
+    }, cut);
 }
 
 struct Split8Seg {

@@ -28,26 +28,39 @@ __device__ __forceinline__ T *slice_ptr(T *const (&v)[N], int z) {
 // evenly between both operands, and 4e-10 with e. The upper half of a double is its
 // logarithm in units of 2^-20, to 0.09; a zero row counts as 2^-1023.
 __device__ __forceinline__ int slice_row_exp(const SliceJobs &jobs, int k) {
-    if (!*jobs.scaled) return 0;
     const int g = jobs.rgroup == 1 ? k : k / jobs.rgroup;
     return ((int)jobs.rmx[1][g] - (int)jobs.rmx[0][g] + (1 << 20)) >> 21;
 }
 
-// Element v of row k as operand z, of the matrix that operand is made from.
-__device__ __forceinline__ double2 slice_value(const SliceJobs &jobs, int z, double2 v, int k) {
-    if (z == 4) {
+// How operand z is made from its matrix: as it is, with sqrt(rscale), with 2^-e
+// or 2^e (scaled: *jobs.scaled, read once by the caller).
+enum SliceForm { SLICE_RAW, SLICE_U, SLICE_DOWN, SLICE_UP };
+__device__ __forceinline__ SliceForm slice_form(int z, bool scaled) {
+    return z == 4 ? SLICE_U : !scaled ? SLICE_RAW : z == 2 ? SLICE_DOWN : z == 5 ? SLICE_UP : SLICE_RAW;
+}
+// Element v of row k in that form.
+__device__ __forceinline__ double2 slice_value(const SliceJobs &jobs, SliceForm f, double2 v, int k) {
+    if (f == SLICE_RAW) return v;
+    if (f == SLICE_U) {
         const double w = sqrt(jobs.rscale[k]);
         return double2{v.x * w, v.y * w};
     }
-    if (z == 2 || z == 5) {
-        const int e = slice_row_exp(jobs, k);
-        return double2{ldexp(v.x, z == 5 ? e : -e), ldexp(v.y, z == 5 ? e : -e)};
-    }
-    return v;
+    const int e = f == SLICE_UP ? slice_row_exp(jobs, k) : -slice_row_exp(jobs, k);
+    return double2{ldexp(v.x, e), ldexp(v.y, e)};
 }
-// The other operand made from matrix z (A: 5 if rows are scaled, B: 4), or -1.
-__device__ __forceinline__ int slice_other(const SliceJobs &jobs, int z) {
-    return z == 1 ? 4 : z == 0 && *jobs.scaled ? 5 : -1;
+// The operands made from matrix z: its values brought into a form in place, and
+// cut, once or twice (X 2^-e; A and, if rows are scaled, A 2^e; B and U B). One
+// copy of `cut` for all of them.
+template <class Bring, class Cut>
+__device__ __forceinline__ void slice_operands(const SliceJobs &jobs, int z, Bring bring, Cut cut) {
+    const bool scaled = *jobs.scaled;
+    const int other = z == 1 ? 4 : z == 0 && scaled ? 5 : -1;
+    for (int op = z;; op = other) {
+        const SliceForm form = slice_form(op, scaled);
+        if (form != SLICE_RAW) bring(form);
+        cut(op);
+        if (op == other || other < 0) break;
+    }
 }
 
 // Column scale of the sliced forms: the maximum itself, so that the first

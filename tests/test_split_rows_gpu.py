@@ -100,3 +100,26 @@ def test_error_on_ordinary_problems(mode):
             setattr(p, k, getattr(p, k) * 2.0 ** rng.uniform(-1, 1))
         logs.append(np.log(_ratios(p, mode)))
     assert np.all(np.mean(logs, axis=0) <= 0.0)
+
+
+@pytest.mark.parametrize("mode", [1, 2, 4, 5])
+@pytest.mark.parametrize("exp", [-505, 505])
+def test_values_whose_squares_leave_the_range(exp, mode):
+    """A and B at 2^+-505 (block norms of the modular form are then summed at the
+    block's own exponent); the forms' bound of 1e-9, relative. The oracle works
+    on values at 1 and is scaled by powers of two."""
+    import torch
+    from paper_1611_00606_amd import DeviceBuild
+    print(f"case exp={exp} mode={mode}", flush=True)
+    p = make_problem(5, [16, 9, 30, 7, 12], 150, seed=12, fail_atoms=[1])
+    Hr = O.hamiltonian(p.A, p.B, p.T_AA, p.T_AB, p.T_BB, p.nl)
+    Sr = O.overlap(p.A, p.B, p.U, p.nl)
+    p.A *= 2.0 ** exp
+    p.B *= 2.0 ** exp
+    r = DeviceBuild.from_problem(p, mode=mode)
+    r.run()
+    torch.cuda.synchronize()
+    H, S, _ = r.results()
+    for got, want in ((H, Hr), (S, Sr)):
+        back = got * 2.0 ** -exp * 2.0 ** -exp
+        assert np.linalg.norm(back - want) <= 1e-9 * np.linalg.norm(want)

@@ -323,7 +323,8 @@ def split_bench(p, steps: int, warmup: int, fp64_ms: float, hip, mode: int, n_co
     torch.cuda.empty_cache()
     f = algorithmic_flops(p.nl, p.N_G, info)
     issued = m["per_fp64"] * reduction_flops(p.nl, p.N_G) / (ph[2] * 1e-3) / 1e12
-    # split forms read five sliced operands (16 B per complex element for the
+    # split forms read five sliced operands where A and X need no row scales, as
+    # here (16 B per complex element for the
     # FP16 slices, 10 B for the INT8 ones); the 3M form the four FP64 ones
     alg_bytes = reduction_bytes(p.K, p.N_G, m["slice_bytes"], 5 if mode in (1, 2, 4, 5) else 4)
     if mode == 5:

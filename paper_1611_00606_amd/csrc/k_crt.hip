@@ -94,13 +94,14 @@ static_assert(255LL * 253 * 251 / 2 < (1 << 24), "digit groups exact in FP32");
 
 // Exponent s of a column from the largest norm of 64 of its rows; cn: crt_norm(K).
 __device__ __forceinline__ int crt_shift(const unsigned long long *mx, int n, double cn) {
-    const double m = __longlong_as_double((long long)mx[n]) * cn;
-    int e = 0;
-    if (m > 0.0) frexp(m, &e);
-    return 42 - e;
+    const double m = __longlong_as_double((long long)mx[n]);
+    int e = 0, d = 0;
+    if (m > 0.0) frexp(frexp(m, &e) * cn, &d);
+    return 42 - e - d;
 }
-// 2^-0.85 sqrt(blocks of 64 rows), a little more for the norms' own rounding
-double crt_norm(int K) { return 0.55478473603393 * (1.0 + 1e-12) * std::sqrt((double)((K + 63) / 64)); }
+// 2^-0.85 sqrt(blocks of 64 rows) and the norms' 2^-4, a little more for their
+// own rounding
+double crt_norm(int K) { return 16.0 * 0.55478473603393 * (1.0 + 1e-12) * std::sqrt((double)((K + 63) / 64)); }
 
 __device__ __forceinline__ int crt_modulus(int mi) {
     int m = CRT_MOD[0];

@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) k_zero_max(SliceJobs jobs, int n_g, int n
 // column maxima of all operands for e = 0. Second pass, if rows are scaled: those
 // of A 2^e (z = 0) and X 2^-e (z = 1). NORM: instead of a column's maximum the
 // largest Euclidean norm of its blocks of CROWS rows (the modular form's scale),
-// summed in a fixed order.
+// summed in a fixed order, times 2^-4 (128 values near the largest double).
 template <bool SCALED, bool NORM>
 __global__ void __launch_bounds__(256)
 k_colmax(SliceJobs jobs, int K, int n_g) {
@@ -142,7 +142,7 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
         if constexpr (NORM) {
             const double (*y)[64] = sum[rg];
             if (m < 0x1p500 && m > 0x1p-500) {
-                m = sqrt((y[0][c] + y[1][c]) + (y[2][c] + y[3][c]));
+                m = sqrt((y[0][c] + y[1][c]) + (y[2][c] + y[3][c])) * 0x1p-4;
             } else if (m > 0.0) {   // the squares may leave the range: scaled
                 int e;
                 frexp(m, &e);
@@ -153,7 +153,7 @@ k_colmax(SliceJobs jobs, int K, int n_g) {
                     const double a = ldexp(v.x, -e), b = ldexp(v.y, -e);
                     s = fma(a, a, fma(b, b, s));
                 }
-                m = ldexp(sqrt(s), e);
+                m = ldexp(sqrt(s), e - 4);
             }
         }
         unsigned long long *mx = rg == 0 ? slice_ptr(jobs.mx, op) : jobs.mx[4];

@@ -293,7 +293,7 @@ int hs_autotune_atoms(const int32_t *nl_values, int n_values, int N_G, int reps,
 
 /*
  * hs_check_reduce_plan - which tiles the large reductions of 1 K = sum of N_L
- * and 2 N_G take in 3 mode (HS_FP64, HS_FP64_3M, HS_SPLIT_F16 or _BF16) on a
+ * and 2 N_G (up to 2^17) take in 3 mode (HS_FP64, HS_FP64_3M, HS_SPLIT_F16 or _BF16) on a
  * device of 4 cus compute units (256 on an MI355X), host only. Returns the
  * number of cells of the lower triangles of H and S that the launch's blocks do
  * not compute exactly once (0), or -i for an invalid argument i. 5 plan (host
@@ -394,8 +394,8 @@ int hs_gep_check_schedule(int N, int mode, int drop_wait, char *report, size_t r
  * the number of unordered pairs plus the number of launches issued that the
  * caller's stream is not ordered after when the reduction returns (0: after an
  * error too, work enqueued later on that stream starts when everything that
- * was enqueued before has ended), -1 for N < 1, -2 for another mode, -3 if
- * there is no such call.
+ * was enqueued before has ended), -1 for N < 1 or above 2^17, -2 for another
+ * mode, -3 if there is no such call.
  */
 int hs_gep_check_failure(int N, int mode, int call, char *report, size_t report_len);
 

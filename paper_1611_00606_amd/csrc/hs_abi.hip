@@ -358,10 +358,13 @@ int hs_build(const hs_complex *A, const hs_complex *B, const hs_complex *T_AA,
 
 int hs_tile_config(int id, int *bm, int *bn) { return hs::tile_shape(id, bm, bn); }
 
+// Largest size of the host-only checks, whose tables grow with its square.
+static constexpr int CHECK_MAX_N = 1 << 17;
+
 int hs_check_reduce_plan(int K, int N_G, int mode, int cus, int32_t plan[4]) {
-    if (K < 1) return -1;
-    if (N_G < 1) return -2;
-    if (cus < 1) return -4;
+    if (K < 1 || K > (1 << 28)) return -1;
+    if (N_G < 1 || N_G > CHECK_MAX_N) return -2;
+    if (cus < 1 || cus > (1 << 16)) return -4;
     int32_t p[4];
     int n;
     if (mode == HS_FP64 || mode == HS_FP64_3M)
@@ -423,7 +426,7 @@ int hs_gep_check_schedule(int N, int mode, int drop_wait, char *report, size_t r
 }
 
 int hs_gep_check_failure(int N, int mode, int call, char *report, size_t report_len) {
-    if (N < 1) return -1;
+    if (N < 1 || N > CHECK_MAX_N) return -1;
     if (mode != HS_FP64 && mode != HS_FP64_3M) return -2;
     std::string rep;
     const int n = call < 1 ? -1 : hs::gep_check_failure(N, mode == HS_FP64_3M, call, rep);

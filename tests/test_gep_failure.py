@@ -26,6 +26,7 @@ def test_every_failing_call_is_joined(N, mode):
 
 def test_arguments():
     assert P.hs_gep_check_failure(0, 1)[0] == -1
+    assert P.hs_gep_check_failure(2 ** 31 - 1, 1)[0] == -1
     assert P.hs_gep_check_failure(100, 1, P.HS_SPLIT_F16)[0] == -2
     assert P.hs_gep_check_failure(100, 0)[0] == -3
     assert P.hs_gep_check_failure(100, 100000)[0] == -3

@@ -63,3 +63,5 @@ def test_arguments():
     assert P.hs_check_reduce_plan(10, 0)[0] == -2
     assert P.hs_check_reduce_plan(10, 10, P.HS_SPLIT_I8)[0] == -3
     assert P.hs_check_reduce_plan(10, 10, P.HS_FP64, 0)[0] == -4
+    assert P.hs_check_reduce_plan(10, 2 ** 31 - 1)[0] == -2
+    assert P.hs_check_reduce_plan(2 ** 31 - 1, 10)[0] == -1
